@@ -45,16 +45,29 @@ template <> struct io_traits<bf16_t> {
   }
 };
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+// Reductions over lanes that stay in registers (DPP within 16 lanes, permlane swaps across): every lane gets the result.
+template <int CTRL>
+__device__ __forceinline__ float dpp_get(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
+template <typename F> __device__ __forceinline__ float row16_reduce(float x, F f) {
+  x = f(x, dpp_get<0xB1>(x));     // quad_perm [1,0,3,2]
+  x = f(x, dpp_get<0x4E>(x));     // quad_perm [2,3,0,1]
+  x = f(x, dpp_get<0x141>(x));    // row_half_mirror
+  return f(x, dpp_get<0x140>(x)); // row_mirror
 }
+// across the four 16-lane rows of a wave (lanes l, l^16, l^32, l^48)
+template <typename F> __device__ __forceinline__ float rows_reduce(float x, F f) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float rows_sum(float x) { return rows_reduce(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float rows_max(float x) { return rows_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float sum16(float x) { return row16_reduce(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_sum(float x) { return rows_sum(sum16(x)); }
+__device__ __forceinline__ float wave_max(float x) { return rows_max(row16_reduce(x, [](float a, float b) { return fmaxf(a, b); })); }
 // value held by lane `l` (wave-uniform l) broadcast to the whole wave through an SGPR
 __device__ __forceinline__ float bcast(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));

@@ -191,19 +191,6 @@ __device__ __forceinline__ void dq_subtile(const unsigned char* kt, const unsign
 }
 
 // grid (ntile * Hq * B), 256 threads: 128 queries of one head, wave w owns 32.
-// sum over the 16 lanes of a DPP row (quad butterflies, then the two mirror steps)
-template <int CTRL>
-__device__ __forceinline__ float dpp_get(float x) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float sum16(float x) {
-  x += dpp_get<0xB1>(x);   // quad_perm [1,0,3,2]
-  x += dpp_get<0x4E>(x);   // quad_perm [2,3,0,1]
-  x += dpp_get<0x141>(x);  // row_half_mirror
-  x += dpp_get<0x140>(x);  // row_mirror
-  return x;
-}
-
 // Backward of the two RMS norms (Sec. 3.2) for 32 consecutive query rows of one head, by one wave: 16 lanes per row,
 // 8 features each, four rows per pass (row-contiguous 16-byte accesses).  With y = g * x * r, r = rsqrt(mean x^2 +
 // eps):  dx = r g dy - x r^3 mean(g dy x),  dg += dy x r.  Stores d xs, d xr (bf16) and delta = rowsum(d xs * xs)

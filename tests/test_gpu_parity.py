@@ -218,6 +218,18 @@ def test_decode_bf16_long_rings(W):
     _decode_vs_oracle(cfg, pos, TOL["bf16"])
 
 
+@pytest.mark.parametrize("dtype,N,Hq,Hkv,D,W", [
+    ("bf16", 1, 5, 1, 128, 5), ("bf16", 2, 16, 1, 128, 33), ("bf16", 1, 17, 1, 128, 95), ("bf16", 3, 3, 3, 64, 2049),
+    ("bf16", 70, 16, 8, 64, 40), ("bf16", 130, 8, 8, 128, 31), ("f32", 1, 8, 1, 128, 15), ("f32", 2, 40, 2, 64, 17),
+    ("f32", 66, 24, 8, 128, 48), ("f32", 128, 8, 8, 64, 16), ("f32", 1, 20, 1, 128, 300)])
+def test_decode_group_sizes_rings_and_wave_counts(dtype, N, Hq, Hkv, D, W):
+    """Rings around one set of keys (32 bf16, 16 fp32) and beyond one set per wave, head groups up to and past the 16
+    columns of a matrix-core tile, batches on either side of the wave-count rule, every fill level of the ring."""
+    cfg = synth.DecodeConfig("edges", N, Hq, Hkv, D, W, dtype, 17, 0, 4 * W, 1.0 / math.sqrt(D))
+    levels = [0, 1, W - 1, W, W + 1, W // 2, 3 * W + 7]
+    _decode_vs_oracle(cfg, [levels[(i + N) % 7] for i in range(N)] if N > 2 else [W - 1, 2 * W + 3][-N:], TOL[dtype])
+
+
 def test_decode_full_config_all_sequences():
     """The decode workload the benchmark times (128 sequences, 32 query / 8 kv heads, W = 512), every output."""
     cfg = synth.DECODE_CONFIGS["decode_b128_w512"]
