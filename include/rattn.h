@@ -77,7 +77,7 @@ typedef struct {
                             independent implementation used by tests).  It changes what `saved` holds:
                             rattn_fwd and rattn_bwd of one step must be given the same value           */
   int32_t state_policy;  /* rattn_state_policy: what rattn_fwd keeps of the linear-branch chunk states for
-                            rattn_bwd (matrix-core kernels; ignored by the general kernels, which always rebuild).
+                            rattn_bwd (bf16 matrix-core kernels; the general kernels always keep their fp32 states).
                             Same value in both calls: it changes what `saved` holds                           */
 } rattn_params;
 

@@ -70,8 +70,7 @@ struct Layout {
   int state_stride;   // chunk states kept in `saved`: 0 = none, 1 = all, m = every m-th
   // generic forward / backward workspace
   size_t gf_states, gen_fwd_bytes;
-  size_t gb_states, gb_rstates, gb_dxs, gb_dxr, gb_delta, gb_dgpart, gen_bwd_bytes;
-  int RB;
+  size_t gb_rstates, gb_dxs, gb_dxr, gb_delta, gb_dgpart, gen_bwd_bytes;
   // MFMA forward workspace
   bool fast_fwd;
   size_t ff_u, ff_states, fast_fwd_bytes;
@@ -147,27 +146,26 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   L->sv_rs = off; off += align_up(nrow_f * 4);
   L->sv_rr = off; off += align_up(nrow_f * 4);
   L->sv_states = off;
-  L->state_stride = !L->fast_fwd || p->state_policy == RATTN_STATES_REBUILD ? 0
-                    : p->state_policy == RATTN_STATES_KEEP ? 1 : p->state_policy;
-  if (L->state_stride > 0) {
+  const size_t nstate = (size_t)dm.B * dm.Hkv * dm.nst * dm.D * dm.D;   // general kernels
+  L->state_stride = !L->fast_fwd || p->state_policy == RATTN_STATES_KEEP ? 1
+                    : p->state_policy == RATTN_STATES_REBUILD ? 0 : p->state_policy;
+  if (!L->fast_fwd) {
+    off += align_up(nstate * 4);
+  } else if (L->state_stride > 0) {
     const int nstf = rattn::fast_fwd_plan(dmf).nstf;
     off += align_up((size_t)dmf.B * dmf.Hkv * ((nstf + L->state_stride - 1) / L->state_stride) * 128 * 128 * 2);
   }
   L->saved_bytes = off;
 
-  const size_t nstate = (size_t)dm.B * dm.Hkv * dm.nst * dm.D * dm.D;
   L->gf_states = 0;
   L->gen_fwd_bytes = align_up(nstate * 4);
 
-  const long long rows = (long long)dm.B * dm.T;
-  L->RB = (int)(rows / 4 < 1 ? 1 : (rows / 4 > 256 ? 256 : rows / 4));
   off = 0;
-  L->gb_states = off; off += align_up(nstate * 4);
   L->gb_rstates = off; off += align_up(nstate * 4);
   L->gb_dxs = off; off += align_up(nq * 4);
   L->gb_dxr = off; off += align_up(nq * 4);
   L->gb_delta = off; off += align_up(nrow * 4);
-  L->gb_dgpart = off; off += align_up((size_t)2 * L->RB * dm.Hq * dm.D * 4);
+  L->gb_dgpart = off; off += align_up((size_t)2 * dm.B * ((dm.T + 15) / 16) * dm.Hq * dm.D * 4);
   L->gen_bwd_bytes = off;
 
   L->ff_u = L->ff_states = L->fast_fwd_bytes = 0;
@@ -261,9 +259,11 @@ rattn_status make_chunk_layout(const rattn_params* p, int32_t pos0, ChunkLayout*
   size_t off = 0;
   C->kc = off; off += align_up(nkv);
   C->vc = off; off += align_up(nkv);
-  C->qc = off; off += align_up(nq);
-  C->oc = off; off += align_up(nq);
-  C->saved = off; off += align_up(C->L2.saved_bytes);
+  if (C->L2.fast_fwd) {
+    C->qc = off; off += align_up(nq);
+    C->oc = off; off += align_up(nq);
+    C->saved = off; off += align_up(C->L2.saved_bytes);
+  }
   C->fwdws = off; off += align_up(C->L2.fwd_bytes);
   C->partial = off; off += align_up(rattn::export_plan(dm).partial_bytes);
   C->bytes = off;
@@ -390,7 +390,8 @@ rattn_status rattn_fwd(const rattn_params* p, const void* q, const void* k, cons
                     sv.states && sv.state_stride <= 1 ? sv.states : (void*)(w + L.ff_states), st);
     if (L.pad) rattn::unpad_rows(of, o, L.dm.B, L.dm.T, L.dmf.T, L.dm.Hq, hb, hbp, st);
   } else
-    rattn::generic_fwd(L.dm, p->dtype, q, k, v, gamma_swa, gamma_rla, o, sv, (float*)((char*)workspace + L.gf_states), st);
+    rattn::generic_fwd(L.dm, p->dtype, q, k, v, gamma_swa, gamma_rla, o, sv,
+                       sv.states ? (float*)sv.states : (float*)((char*)workspace + L.gf_states), st);
   return check_launch("rattn_fwd");
 }
 
@@ -491,10 +492,9 @@ rattn_status rattn_bwd(const rattn_params* p, const void* q, const void* k, cons
     return check_launch("rattn_bwd");
   }
   rattn::GenericBwdWs ws;
-  ws.states = (float*)(w + L.gb_states); ws.rstates = (float*)(w + L.gb_rstates);
+  ws.rstates = (float*)(w + L.gb_rstates);
   ws.dxs = (float*)(w + L.gb_dxs); ws.dxr = (float*)(w + L.gb_dxr);
   ws.delta = (float*)(w + L.gb_delta); ws.dgpart = (float*)(w + L.gb_dgpart);
-  ws.RB = L.RB;
   rattn::generic_bwd(L.dm, p->dtype, q, k, v, gamma_swa, gamma_rla, sv, dO, dq, dk, dv, dgamma_swa, dgamma_rla, ws, st);
   return check_launch("rattn_bwd");
 }
@@ -590,6 +590,16 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
     rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, 0};
     rattn::fast_fwd(dm, q, w + C.kc, w + C.vc, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.ff_u),
                     w + C.fwdws + C.L2.ff_states, st, C.R / 128, carried ? state : nullptr);
+    rattn::prefill_export(dm, p->dtype, w + C.kc, w + C.vc, k_ring, v_ring, state, (float*)(w + C.partial), st,
+                          pos0 - C.R, carried);
+    return check_launch("rattn_prefill_chunk");
+  }
+  // General kernels: the same with 16-row tiles, which may start at any row
+  if (!C.L2.fast_fwd) {
+    rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, nullptr, k, v, k_ring, v_ring, nullptr, w + C.kc, w + C.vc, st);
+    rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true, 0};
+    rattn::generic_fwd(dm, p->dtype, q, w + C.kc, w + C.vc, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.gf_states),
+                       st, C.R, carried ? state : nullptr);
     rattn::prefill_export(dm, p->dtype, w + C.kc, w + C.vc, k_ring, v_ring, state, (float*)(w + C.partial), st,
                           pos0 - C.R, carried);
     return check_launch("rattn_prefill_chunk");

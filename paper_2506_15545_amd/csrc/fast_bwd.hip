@@ -897,6 +897,11 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
 
 }  // namespace
 
+void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st) {
+  ProfScope ps("dgamma_reduce_kernel", st);
+  dgamma_reduce_kernel<<<dim3(HD / 32, 2), 256, 0, st>>>(dgpart, dgs, dgr, RB, HD);
+}
+
 void fast_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr,
               const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs, float* dgr,
               const FastBwdWs& ws, hipStream_t st, const RaggedTails* tails) {
@@ -948,9 +953,7 @@ void fast_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, 
 #undef RATTN_DQ_LAUNCH
   }
   if (dgs || dgr) {
-    const int HD = dm.Hq * 128;
-    ProfScope ps("dgamma_reduce_kernel", st);
-    dgamma_reduce_kernel<<<dim3(HD / 32, 2), 256, 0, st>>>(ws.dgpart, dgs, dgr, pl.RB, HD);
+    dgamma_reduce(ws.dgpart, dgs, dgr, pl.RB, dm.Hq * 128, st);
   }
   rla_reverse_states(dm, pl, q, ws.dxr, ws.U, ws.rstates, st, tails);
   // the dk/dv kernel needs more LDS than a launch gets by default: raised once per instantiation

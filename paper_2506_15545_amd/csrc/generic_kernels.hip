@@ -1,259 +1,452 @@
-// General-shape kernels of librattn: any T, any window W >= 1, D in {64,128}, fp32 or bf16 I/O,
-// fp32 arithmetic on the vector ALUs.  One wavefront owns one query (or one key) row; the other
-// operand's rows are spread over the 64 lanes.  These kernels serve fp32 tensors and every shape
-// the MFMA kernels do not cover; they follow the same decomposition:
+// General-shape kernels of librattn: any T, any window W >= 1, D in {64,128}, fp32 or bf16 tensors, fp32 arithmetic
+// throughout.  They serve fp32 tensors and every shape the bf16 matrix-core kernels do not cover, by the same
+// decomposition:
 //   softmax branch  : Sec. 2.1 (windowed softmax, online normalisation)
-//   linear branch   : Eqs. 2-4 (chunk states S_[j], inter-chunk product + intra-chunk masked product,
-//                     read at lag W), phi (row softmax, or the ablation's ReLU / identity of Sec. 4.5)
-//                     computed in-kernel, never stored
+//   linear branch   : Eqs. 2-4 (chunk states S_[j], inter-chunk product + intra-chunk masked product, read at lag W),
+//                     phi (row softmax, or the ablation's ReLU / identity of Sec. 4.5) computed in-kernel, never stored
 //   combination     : Sec. 3.2 (two RMS norms with per-head gains)
-// Element d of a row lives in lane d % 64, register d / 64.
+//
+// All contractions run on v_mfma_f32_16x16x4_f32 (exact fp32 products, fp32 sums).  A work-group of four waves owns 16
+// query rows (forward, dq) or 16 key rows (dk/dv); the waves share the rows of the other side between them, 16 at a
+// time, and add up their partial results in LDS at the end.  Inside a wave everything is transposed, as in the bf16
+// kernels: the owned rows are the columns of the tiles (lane = 16*q4 + r16 holds column r16, register i row 4*q4 + i).
+// The order of a contraction is free as long as both operands follow it, which lets every operand be loaded from global
+// memory (L1/L2: neighbouring waves share the rows) as 16-byte pieces in one of two forms, without LDS:
+//   row form     x[j][e]     = row r16,      feature 16j + 4*q4 + e        (contraction over features)
+//   column form  x[i][hf][e] = row 4*q4 + i, feature 64hf + 4*r16 + e      (contraction over rows)
+// A column-form product leaves feature 64hf + 4*(4*q4 + i) + e of column r16 in acc[4*hf + e][i].
+//
+// Bound: launch latency and the dependent chain of a wave on small tensors, the fp32 matrix rate (157 TFLOP/s; a tile
+// takes 32 cycles, so operands out of L1 keep up) on large ones.  Measured, fp32, one sequence of T = 256, 2 heads,
+// D = 64, W = 32, forward + backward: 51 us in the kernels (forward 6 + 3 + 9, dq 10, reverse states 6 + 3, dk/dv 14),
+// 427 us with one wave per row and vector arithmetic, states walked in token order and built twice.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma.hpp"
 
 namespace rattn {
 
-template <typename IO, int D> struct Row {
-  static constexpr int EPL = D / 64;
-  float x[EPL];
-  __device__ __forceinline__ void load(const IO* p) {
+namespace {
+
+constexpr int GW = 4;  // waves per work-group
+
+__device__ __forceinline__ f32x4_t mm4(float a, float b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ f32x4_t load4(const float* p) { return *reinterpret_cast<const f32x4_t*>(p); }
+__device__ __forceinline__ f32x4_t load4(const bf16_t* p) {
+  const uint2 r = *reinterpret_cast<const uint2*>(p);
+  return f32x4_t{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u)};
+}
+__device__ __forceinline__ void store4(float* p, f32x4_t v) { *reinterpret_cast<f32x4_t*>(p) = v; }
+__device__ __forceinline__ void store4(bf16_t* p, f32x4_t v) {
+  *reinterpret_cast<uint2*>(p) = make_uint2(f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                                            f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16));
+}
+
+// 16 rows in row form; `row` points to feature 0 of this lane's row
+template <int D> struct RowForm {
+  f32x4_t x[D / 16];
+  template <typename IO> __device__ __forceinline__ void load(const IO* row, int q4) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) x[e] = io_traits<IO>::ld(p + lane_id() + 64 * e);
+    for (int j = 0; j < D / 16; ++j) x[j] = load4(row + 16 * j + 4 * q4);
   }
-  __device__ __forceinline__ void store(IO* p) const {
+  template <typename F> __device__ __forceinline__ float fold(float init, F f) const {  // over this lane's features
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) io_traits<IO>::st(p + lane_id() + 64 * e, x[e]);
+    for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) init = f(init, x[j][e]);
+    return init;
   }
-  __device__ __forceinline__ float get(int d) const { return bcast(x[d / 64], d % 64); }  // d compile-time after unrolling
-  __device__ __forceinline__ float sumsq() const {
+  __device__ __forceinline__ float dot(const RowForm& o) const {  // of the whole rows
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) s += x[e] * x[e];
-    return wave_sum(s);
-  }
-  __device__ __forceinline__ float dot(const Row& o) const {
-    float s = 0.f;
+    for (int j = 0; j < D / 16; ++j)
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) s += x[e] * o.x[e];
-    return wave_sum(s);
+      for (int e = 0; e < 4; ++e) s += x[j][e] * o.x[j][e];
+    return rows_sum(s);
   }
-  // in place feature map over the D features
-  __device__ __forceinline__ void feature(int phi) { feature_row<EPL>(x, x, phi); }
+  __device__ __forceinline__ void feature(int phi) {  // feature map, in place
+    float m = 0.f;
+    if (phi == PHI_SOFTMAX) m = rows_max(fold(-INFINITY, [](float a, float b) { return fmaxf(a, b); }));
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[j][e] = feat(x[j][e], m, phi);
+    if (phi == PHI_SOFTMAX) {
+      const float inv = 1.f / rows_sum(fold(0.f, [](float a, float b) { return a + b; }));
+#pragma unroll
+      for (int j = 0; j < D / 16; ++j) x[j] *= inv;
+    }
+  }
 };
 
-// <row held across the wave, row read privately by this lane>
-template <typename RT, int D, typename IO2>
-__device__ __forceinline__ float lane_dot(const Row<RT, D>& r, const IO2* own) {
-  float a = 0.f;
+// 16 rows in column form; row(i) points to feature 0 of row 4*q4 + i
+template <int D> struct ColForm {
+  static constexpr int NH = D / 64;
+  f32x4_t x[4][NH];
+  template <typename R> __device__ __forceinline__ void load(R row, int r16) {
 #pragma unroll
-  for (int c = 0; c < D / 8; ++c) {
-    float t[8];
-    io_traits<IO2>::ld8(own + c * 8, t);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a += r.get(c * 8 + i) * t[i];
+      for (int hf = 0; hf < NH; ++hf) x[i][hf] = load4(row(i) + 64 * hf + 4 * r16);
   }
-  return a;
+  __device__ __forceinline__ void feature(int phi) {  // feature map, in place
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float m = 0.f;
+      if (phi == PHI_SOFTMAX) {
+        m = x[i][0][0];
+#pragma unroll
+        for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m = fmaxf(m, x[i][hf][e]);
+        m = row16_reduce(m, [](float a, float b) { return fmaxf(a, b); });
+      }
+      float z = 0.f;
+#pragma unroll
+      for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[i][hf][e] = feat(x[i][hf][e], m, phi); z += x[i][hf][e]; }
+      if (phi == PHI_SOFTMAX) {
+        const float inv = 1.f / sum16(z);
+#pragma unroll
+        for (int hf = 0; hf < NH; ++hf) x[i][hf] *= inv;
+      }
+    }
+  }
+};
+
+// <rows of a, columns b> over the features: element i = row 4*q4 + i of a against column r16
+template <int D> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
+  f32x4_t t[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e & 1] = mm4(a.x[j][e], b.x[j][e], t[e & 1]);
+  return t[0] + t[1];
+}
+// acc += sum over the 16 rows of row^T (x) p,  p[i] = coefficient of row 4*q4 + i for column r16
+template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a, f32x4_t p, f32x4_t (&acc)[D / 16]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[4 * hf + e] = mm4(a.x[i][hf][e], p[i], acc[4 * hf + e]);
+}
+// acc[d] += sum over the features f of slice j of  M[f][d] b[f],  M row-major [D][D] fp32
+template <int D> __device__ __forceinline__ void state_product(const float* M, int j, f32x4_t b, int r16, int q4, f32x4_t (&acc)[D / 16]) {
+  ColForm<D> a;
+  a.load([&](int e) { return M + (size_t)(16 * j + 4 * q4 + e) * D; }, r16);
+  col_product<D>(a, b, acc);
+}
+// acc[f] += sum over the values d of slice j of  M[f][d] b[d]
+template <int D> __device__ __forceinline__ void state_product_t(const float* M, int j, f32x4_t b, int r16, int q4, f32x4_t (&acc)[D / 16]) {
+#pragma unroll
+  for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x4_t m = load4(M + (size_t)(64 * hf + 4 * r16 + e) * D + 16 * j + 4 * q4);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[4 * hf + e] = mm4(m[s], b[s], acc[4 * hf + e]);
+    }
 }
 
-// row statistics (m, z) of the row this lane reads privately: max and sum(exp(x - max)) for softmax, (0, 1) otherwise
+template <int D> __device__ __forceinline__ void zero(f32x4_t (&acc)[D / 16]) {
+#pragma unroll
+  for (int e = 0; e < D / 16; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+}
+
+// A wave's accumulators into its [16 columns][D + 4] plane of LDS
+template <int D> __device__ __forceinline__ void put_partial(float* plane, const f32x4_t (&acc)[D / 16], int r16, int q4) {
+#pragma unroll
+  for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4_t*>(plane + r16 * (D + 4) + 64 * hf + 4 * (4 * q4 + i)) =
+          f32x4_t{acc[4 * hf][i], acc[4 * hf + 1][i], acc[4 * hf + 2][i], acc[4 * hf + 3][i]};
+}
+template <int D> constexpr int plane_floats() { return 16 * (D + 4); }
+
+// Jacobian of phi for a gradient df of phi(x), both in accumulator layout (x is re-read there): df <- J^T df.
+// Linear in df, so every wave applies it to its own partial sum.
 template <int D, typename IO>
-__device__ __forceinline__ void lane_feature_stats(const IO* own, float& m, float& z, int phi) {
-  if (phi != PHI_SOFTMAX) { m = 0.f; z = 1.f; return; }
-  m = -INFINITY;
+__device__ __forceinline__ void feature_backward(const IO* row, f32x4_t (&df)[D / 16], int q4, int phi) {
+  constexpr int NH = D / 64;
+  f32x4_t x[NH][4];  // [hf][i]: features 64hf + 4*(4*q4 + i) ..
 #pragma unroll
-  for (int c = 0; c < D / 8; ++c) {
-    float t[8];
-    io_traits<IO>::ld8(own + c * 8, t);
+  for (int hf = 0; hf < NH; ++hf)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(m, t[i]);
+    for (int i = 0; i < 4; ++i) x[hf][i] = load4(row + 64 * hf + 4 * (4 * q4 + i));
+  float m = 0.f, inv = 1.f, inner = 0.f;
+  if (phi == PHI_SOFTMAX) {
+    m = -INFINITY;
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = fmaxf(m, x[hf][i][e]);
+    m = rows_max(m);
+    float z = 0.f;
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[hf][i][e] = expf(x[hf][i][e] - m);
+          z += x[hf][i][e];
+          inner += x[hf][i][e] * df[4 * hf + e][i];
+        }
+    inv = 1.f / rows_sum(z);
+    inner = rows_sum(inner) * inv;
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) df[4 * hf + e][i] = x[hf][i][e] * inv * (df[4 * hf + e][i] - inner);
+  } else if (phi == PHI_RELU) {
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) df[4 * hf + e][i] = x[hf][i][e] > 0.f ? df[4 * hf + e][i] : 0.f;
   }
-  z = 0.f;
-#pragma unroll
-  for (int c = 0; c < D / 8; ++c) {
-    float t[8];
-    io_traits<IO>::ld8(own + c * 8, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) z += expf(t[i] - m);
-  }
-}
-
-// sum_f r[f] * feat(own[f], m)   (r spread over the wave, own row private)
-template <typename RT, int D, typename IO>
-__device__ __forceinline__ float lane_dot_feat(const Row<RT, D>& r, const IO* own, float m, int phi) {
-  float a = 0.f;
-#pragma unroll
-  for (int c = 0; c < D / 8; ++c) {
-    float t[8];
-    io_traits<IO>::ld8(own + c * 8, t);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a += r.get(c * 8 + i) * feat(t[i], m, phi);
-  }
-  return a;
 }
 
 // ------------------------------------------------------------------------------------------------
-// Chunk-boundary states of the linear branch (Eq. 2): exclusive prefix (REV=false) or suffix
-// (REV=true) sums over chunks of  sum_t phi(a_t)^T b_t,  t' in [0,Tp), token index t' + off,
-// summed over the GA heads g*GA .. g*GA+GA-1 of a tensor with H heads.
-// out[(b*Hkv+g)*nst + j] is the D x D state seen by chunk j.  grid (D/16, Hkv, B), 256 threads:
-// the block owns a 16-column slice of the state and walks the tokens in order.
-template <typename AT, typename BT, int D, bool REV>
-__global__ __launch_bounds__(256) void gen_scan_kernel(const AT* __restrict__ a, const BT* __restrict__ bsrc,
-                                                       float* __restrict__ out, int T, int H, int GA, int off,
-                                                       int Tp, int C, int nst, int phi) {
-  constexpr int TB = 16;
-  constexpr int CPT = D / 16;    // state columns per thread
-  constexpr int TPR = 16 / CPT;  // threads per state row
-  __shared__ float af[TB][D];
-  __shared__ float bs[TB][16];
-  const int slice = blockIdx.x, g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
-  const int tid = threadIdx.x, f = tid / TPR, c0 = (tid % TPR) * CPT;
-  const int w = wave_id();
-  float S[CPT];
+// Chunk-local products of the linear branch (Eq. 2): U_c[f][d] = sum over the tokens t' in [cC, (c+1)C) below Tp, and
+// over the GA heads g*GA .. of tensors with H heads, of phi(a)[f] b[d]; token index t' + off.  grid (n, Hkv, B), block x
+// forms product first + x into out[(b*Hkv + g)*nst + first + x].  Steps of 64 tokens: every wave maps 16 of them into LDS
+// (the map is most of the step's latency), then each wave forms the products of its D/4 features with all 64.
+template <typename AT, typename BT, int D>
+__global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict__ a, const BT* __restrict__ bsrc,
+                                                           float* __restrict__ out, int T, int H, int GA, int off, int Tp,
+                                                           int C, int nst, int first, int phi) {
+  constexpr int NH = D / 64, PS = D + 4;
+  __shared__ __align__(16) float pf[64 * PS];
+  const int c = first + blockIdx.x, g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
+  const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
+  const int lo = c * C, hi = min(lo + C, Tp);
+  f32x4_t acc[NH][4 * NH];  // [feature tile GW*ft + w][value 4*hd + e]
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) S[c] = 0.f;
-  float* obase = out + (size_t)(b * Hkv + g) * nst * D * D;
-  for (int jj = 0; jj < nst; ++jj) {
-    const int j = REV ? nst - 1 - jj : jj;
-    float* dst = obase + (size_t)j * D * D + (size_t)f * D + slice * 16 + c0;
+  for (int ft = 0; ft < NH; ++ft) zero<D>(acc[ft]);
+  const int nt = (hi - lo + 63) / 64, nstep = GA * nt;
+  auto row = [&](int u, int k) {  // token k of step u (heads outermost)
+    return ((size_t)(b * T + min(lo + 64 * (u % nt) + k, hi - 1) + off) * H + g * GA + u / nt) * D;
+  };
+  ColForm<D> fa;
+  fa.load([&](int i) { return a + row(0, 16 * w + 4 * q4 + i); }, r16);
+  for (int u = 0; u < nstep; ++u) {
+    f32x4_t fb[8][NH];  // the first 32 tokens' b rows, requested ahead of the map
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) dst[c] = S[c];
-    if (jj == nst - 1) break;
-    const int lo = j * C, hi = min(lo + C, Tp);
-    for (int ga = 0; ga < GA; ++ga) {
-      const int head = g * GA + ga;
-      for (int t0 = lo; t0 < hi; t0 += TB) {
-        const int n = min(TB, hi - t0);
-        __syncthreads();
-        for (int tt = w; tt < n; tt += 4) {
-          Row<AT, D> r;
-          r.load(a + ((size_t)(b * T + t0 + tt + off) * H + head) * D);
-          r.feature(phi);
+    for (int tg = 0; tg < 8; ++tg)
 #pragma unroll
-          for (int e = 0; e < D / 64; ++e) af[tt][lane_id() + 64 * e] = r.x[e];
-        }
-        if (tid < n * 16) {
-          const int tt = tid / 16, c = tid % 16;
-          bs[tt][c] = io_traits<BT>::ld(bsrc + ((size_t)(b * T + t0 + tt + off) * H + head) * D + slice * 16 + c);
-        }
-        __syncthreads();
-        for (int tt = 0; tt < n; ++tt) {
-          const float av = af[tt][f];
+      for (int hd = 0; hd < NH; ++hd) fb[tg][hd] = load4(bsrc + row(u, 4 * tg + q4) + 64 * hd + 4 * r16);
+    fa.feature(phi);
+    if (u) __syncthreads();
 #pragma unroll
-          for (int c = 0; c < CPT; ++c) S[c] += av * bs[tt][c0 + c];
-        }
+    for (int i = 0; i < 4; ++i) {
+      const bool live = lo + 64 * (u % nt) + 16 * w + 4 * q4 + i < hi;
+#pragma unroll
+      for (int hf = 0; hf < NH; ++hf)
+        *reinterpret_cast<f32x4_t*>(pf + (16 * w + 4 * q4 + i) * PS + 64 * hf + 4 * r16) = live ? fa.x[i][hf] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    if (u + 1 < nstep) fa.load([&](int i) { return a + row(u + 1, 16 * w + 4 * q4 + i); }, r16);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half) {
+#pragma unroll
+        for (int tg = 0; tg < 8; ++tg)
+#pragma unroll
+          for (int hd = 0; hd < NH; ++hd) fb[tg][hd] = load4(bsrc + row(u, 32 + 4 * tg + q4) + 64 * hd + 4 * r16);
       }
+#pragma unroll
+      for (int tg = 0; tg < 8; ++tg)
+#pragma unroll
+        for (int ft = 0; ft < NH; ++ft) {
+          const float av = pf[(32 * half + 4 * tg + q4) * PS + 16 * (GW * ft + w) + r16];
+#pragma unroll
+          for (int hd = 0; hd < NH; ++hd)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[ft][4 * hd + e] = mm4(av, fb[tg][hd][e], acc[ft][4 * hd + e]);
+        }
     }
   }
+  float* U = out + ((size_t)(b * Hkv + g) * nst + c) * D * D;
+#pragma unroll
+  for (int ft = 0; ft < NH; ++ft)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int hd = 0; hd < NH; ++hd)
+        store4(U + (size_t)(16 * (GW * ft + w) + 4 * q4 + i) * D + 64 * hd + 4 * r16,
+               f32x4_t{acc[ft][4 * hd][i], acc[ft][4 * hd + 1][i], acc[ft][4 * hd + 2][i], acc[ft][4 * hd + 3][i]});
+}
+
+// Products -> states, in place: exclusive prefix (REV = false; state 0 = `init` or zero) or suffix (REV = true) sums over
+// the nst chunks of every (b, kv head), in order.  One thread per four elements; the products of eight chunks are
+// requested together.  (The product of the last / first chunk is never read.)
+template <bool REV>
+__global__ __launch_bounds__(64) void gen_scan_kernel(float* __restrict__ U, const float* __restrict__ init, int nst, int vecs) {
+  const int v = blockIdx.x * 64 + threadIdx.x;
+  if (v >= vecs) return;
+  f32x4_t* p = reinterpret_cast<f32x4_t*>(U) + (size_t)blockIdx.y * nst * vecs + v;
+  f32x4_t acc = init ? reinterpret_cast<const f32x4_t*>(init)[(size_t)blockIdx.y * vecs + v] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto at = [&](int k) -> f32x4_t& { return p[(size_t)(REV ? nst - 1 - k : k) * vecs]; };
+  constexpr int GRP = 8;
+  for (int k0 = 0; k0 < nst; k0 += GRP) {
+    f32x4_t u[GRP];
+#pragma unroll
+    for (int k = 0; k < GRP; ++k)
+      if (k0 + k < nst - 1) u[k] = at(k0 + k);
+#pragma unroll
+    for (int k = 0; k < GRP; ++k)
+      if (k0 + k < nst) {
+        at(k0 + k) = acc;
+        if (k0 + k < nst - 1) acc += u[k];
+      }
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
-// Forward: one wave per query row, QPW rows per wave.  grid (ceil(T/(4*QPW)), Hq, B), 256 threads.
-constexpr int GEN_QPW = 4;
-
-template <typename IO, typename ST, int D>
-__global__ __launch_bounds__(256) void gen_fwd_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
-                                                      const IO* __restrict__ v, const float* __restrict__ gs,
-                                                      const float* __restrict__ gr,
-                                                      const float* __restrict__ states, IO* __restrict__ o,
-                                                      ST* __restrict__ xs_out, ST* __restrict__ xr_out,
-                                                      float* __restrict__ lse_out, float* __restrict__ rs_out,
-                                                      float* __restrict__ rr_out, LayerDims dm) {
-  constexpr int EPL = D / 64;
+// Forward.  grid (ceil((T - q0) / 16), Hq, B): 16 query rows of one head.  Only rows q0 .. T-1 have queries; q, o and the
+// saved tensors hold just those Tq = T - q0 rows per sequence.
+template <typename IO, int D>
+__global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+                                                         const IO* __restrict__ v, const float* __restrict__ gs,
+                                                         const float* __restrict__ gr, const float* __restrict__ states,
+                                                         IO* __restrict__ o, float* __restrict__ xs_out,
+                                                         float* __restrict__ xr_out, float* __restrict__ lse_out,
+                                                         float* __restrict__ rs_out, float* __restrict__ rr_out,
+                                                         LayerDims dm, int q0) {
+  constexpr int PL = plane_floats<D>();
+  __shared__ __align__(16) float part[GW * PL];  // partial x_s, then partial x_r
+  __shared__ float ml[GW][16][2];
   const int h = blockIdx.y, b = blockIdx.z, g = h / dm.G;
-  const int lane = lane_id();
-  const int T = dm.T, W = dm.W, C = dm.C, Hq = dm.Hq, Hkv = dm.Hkv;
-  for (int qi = 0; qi < GEN_QPW; ++qi) {
-    const int t = (blockIdx.x * 4 + wave_id()) * GEN_QPW + qi;
-    if (t >= T) break;
-    const size_t qoff = ((size_t)(b * T + t) * Hq + h) * D;
-    Row<IO, D> qv;
-    qv.load(q + qoff);
-    // ---- softmax branch over keys max(0,t-W+1)..t
-    float m = -INFINITY, l = 0.f, acc[EPL];
+  const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
+  const int T = dm.T, W = dm.W, C = dm.C, Hq = dm.Hq, Hkv = dm.Hkv, Tq = T - q0;
+  const int t0 = q0 + 16 * blockIdx.x, t_hi = min(t0 + 15, T - 1), t = min(t0 + r16, t_hi);
+  auto krow = [&](int s) { return k + ((size_t)(b * T + min(s, t_hi)) * Hkv + g) * D; };
+  auto vrow = [&](int s) { return v + ((size_t)(b * T + min(s, t_hi)) * Hkv + g) * D; };
+  RowForm<D> qv;
+  qv.load(q + ((size_t)(b * Tq + t - q0) * Hq + h) * D, q4);
+  // ---- softmax branch over keys max(0,t-W+1)..t; key tile n is wave n % 4's
+  {
+    const int lo = max(0, t0 - W + 1), nt = (t_hi - lo) / 16 + 1;
+    f32x4_t acc[D / 16];
+    zero<D>(acc);
+    float m = -1.0e30f, l = 0.f;
+    RowForm<D> kf;
+    ColForm<D> vf;
+    if (w < nt) {
+      kf.load(krow(lo + 16 * w + r16), q4);
+      vf.load([&](int i) { return vrow(lo + 16 * w + 4 * q4 + i); }, r16);
+    }
+    for (int n = w; n < nt; n += GW) {
+      const int s0 = lo + 16 * n, next = s0 + 16 * GW;
+      f32x4_t s = row_product<D>(kf, qv);
+      if (n + GW < nt) kf.load(krow(next + r16), q4);
+      float mx = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    const int s_lo = max(0, t - W + 1);
-    for (int base = s_lo; base <= t; base += 64) {
-      const int s = base + lane;
-      const bool valid = s <= t;
-      const int sc = valid ? s : t;
-      float a = dm.scale * lane_dot(qv, k + ((size_t)(b * T + sc) * Hkv + g) * D);
-      a = valid ? a : -INFINITY;
-      const float m_new = fmaxf(m, wave_max(a));
-      const float alpha = expf(m - m_new);
-      const float p = valid ? expf(a - m_new) : 0.f;
-      l = l * alpha + wave_sum(p);
+      for (int i = 0; i < 4; ++i) {
+        const unsigned dist = (unsigned)(t - (s0 + 4 * q4 + i));  // in the window <=> 0 <= query - key < W
+        s[i] = dist < (unsigned)W ? s[i] * dm.scale : -INFINITY;
+        mx = fmaxf(mx, s[i]);
+      }
+      const float m_new = fmaxf(m, rows_max(mx)), alpha = expf(m - m_new);
       m = m_new;
-      const int n = min(64, t - base + 1);
+      l *= alpha;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] *= alpha;
-      for (int j = 0; j < n; ++j) {
-        const float pj = bcast(p, j);
-        const IO* vr = v + ((size_t)(b * T + base + j) * Hkv + g) * D;
+      for (int i = 0; i < 4; ++i) { s[i] = expf(s[i] - m); l += s[i]; }
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += pj * io_traits<IO>::ld(vr + lane + 64 * e);
+      for (int e = 0; e < D / 16; ++e) acc[e] *= alpha;
+      col_product<D>(vf, s, acc);
+      if (n + GW < nt) vf.load([&](int i) { return vrow(next + 4 * q4 + i); }, r16);
+    }
+    l = rows_sum(l);
+    if (q4 == 0) { ml[w][r16][0] = m; ml[w][r16][1] = l; }
+    put_partial<D>(part + w * PL, acc, r16, q4);
+  }
+  // ---- linear branch: phi(q) S_[j] + intra-chunk part over keys jC..t-W, with the chunk j of the tile's first query
+  const bool has_lin = t_hi >= W;
+  f32x4_t acc[D / 16];
+  zero<D>(acc);
+  if (has_lin) {
+    qv.feature(dm.phi);
+    const int j = max(0, t0 - W) / C;
+    const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
+#pragma unroll
+    for (int jj = 0; jj < D / 16; ++jj)
+      if (jj % GW == w) state_product<D>(S, jj, qv.x[jj], r16, q4, acc);
+    const int lo = j * C, nt = (t_hi - W - lo) / 16 + 1;
+    for (int n = w; n < nt; n += GW) {
+      const int s0 = lo + 16 * n;
+      RowForm<D> kf;
+      ColForm<D> vf;
+      kf.load(krow(s0 + r16), q4);
+      vf.load([&](int i) { return vrow(s0 + 4 * q4 + i); }, r16);
+      kf.feature(dm.phi);
+      f32x4_t c = row_product<D>(kf, qv);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = s0 + 4 * q4 + i <= t - W ? c[i] : 0.f;
+      col_product<D>(vf, c, acc);
+    }
+  }
+  __syncthreads();
+  // ---- the waves' partial results and the combination: 16 threads per query row, features 64hf + 4c ..
+  {
+    const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
+    float M = ml[0][row][0];
+#pragma unroll
+    for (int r = 1; r < GW; ++r) M = fmaxf(M, ml[r][row][0]);
+    float l = 0.f, sw[GW];
+#pragma unroll
+    for (int r = 0; r < GW; ++r) { sw[r] = expf(ml[r][row][0] - M); l += sw[r] * ml[r][row][1]; }
+    f32x4_t xs[D / 64], xr[D / 64];
+    float ss = 0.f, sr = 0.f;
+    auto partial = [&](int r, int hf) { return *reinterpret_cast<const f32x4_t*>(part + r * PL + row * (D + 4) + 64 * hf + 4 * c); };
+#pragma unroll
+    for (int hf = 0; hf < D / 64; ++hf) {
+      xs[hf] = xr[hf] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < GW; ++r) xs[hf] += sw[r] * partial(r, hf);
+      xs[hf] *= 1.f / l;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss += xs[hf][e] * xs[hf][e];
+    }
+    if (has_lin) {
+      __syncthreads();
+      put_partial<D>(part + w * PL, acc, r16, q4);
+      __syncthreads();
+#pragma unroll
+      for (int hf = 0; hf < D / 64; ++hf) {
+#pragma unroll
+        for (int r = 0; r < GW; ++r) xr[hf] += partial(r, hf);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sr += xr[hf][e] * xr[hf][e];
       }
     }
-    Row<float, D> xs;
-    const float inv_l = 1.f / l;
+    const float r_s = rsqrtf(sum16(ss) / D + dm.eps), r_r = rsqrtf(sum16(sr) / D + dm.eps);
+    const int tq = 16 * blockIdx.x + row;
+    if (tq < Tq) {
+      const size_t off = ((size_t)(b * Tq + tq) * Hq + h) * D;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) xs.x[e] = acc[e] * inv_l;
-    // ---- linear branch: phi(q) S_[j] + intra-chunk part over keys jC..t-W
-    Row<float, D> xr;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) xr.x[e] = 0.f;
-    const int pidx = t - W;
-    if (pidx >= 0) {
-      Row<IO, D> qf = qv;
-      qf.feature(dm.phi);
-      const int j = pidx / C;
-      const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-#pragma unroll 8
-      for (int f = 0; f < D; ++f) {
-        const float qff = bcast(qf.x[f / 64], f % 64);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) xr.x[e] += qff * S[(size_t)f * D + lane + 64 * e];
+      for (int hf = 0; hf < D / 64; ++hf) {
+        const int d = 64 * hf + 4 * c;
+        f32x4_t y1 = xs[hf] * r_s, y2 = xr[hf] * r_r;
+        if (gs) y1 *= load4(gs + h * D + d);
+        if (gr) y2 *= load4(gr + h * D + d);
+        store4(o + off + d, y1 + y2);
+        if (xs_out) { store4(xs_out + off + d, xs[hf]); store4(xr_out + off + d, xr[hf]); }
       }
-      for (int base = j * C; base <= pidx; base += 64) {
-        const int s = base + lane;
-        const bool valid = s <= pidx;
-        const int sc = valid ? s : pidx;
-        const IO* kr = k + ((size_t)(b * T + sc) * Hkv + g) * D;
-        float mk, zk;
-        lane_feature_stats<D>(kr, mk, zk, dm.phi);
-        float c = lane_dot_feat(qf, kr, mk, dm.phi) / zk;
-        c = valid ? c : 0.f;
-        const int n = min(64, pidx - base + 1);
-        for (int jj = 0; jj < n; ++jj) {
-          const float cj = bcast(c, jj);
-          const IO* vr = v + ((size_t)(b * T + base + jj) * Hkv + g) * D;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) xr.x[e] += cj * io_traits<IO>::ld(vr + lane + 64 * e);
-        }
-      }
-    }
-    // ---- combination
-    const float r_s = rsqrtf(xs.sumsq() / D + dm.eps);
-    const float r_r = rsqrtf(xr.sumsq() / D + dm.eps);
-    Row<float, D> out;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const int d = lane + 64 * e;
-      const float g1 = gs ? gs[h * D + d] : 1.f, g2 = gr ? gr[h * D + d] : 1.f;
-      out.x[e] = g1 * xs.x[e] * r_s + g2 * xr.x[e] * r_r;
-    }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) io_traits<IO>::st(o + qoff + lane + 64 * e, out.x[e]);
-    if (xs_out) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        io_traits<ST>::st(xs_out + qoff + lane + 64 * e, xs.x[e]);
-        io_traits<ST>::st(xr_out + qoff + lane + 64 * e, xr.x[e]);
-      }
-      if (lane == 0) {
-        const size_t so = (size_t)(b * Hq + h) * T + t;
-        lse_out[so] = m + logf(l);
+      if (xs_out && c == 0) {
+        const size_t so = (size_t)(b * Hq + h) * Tq + tq;
+        lse_out[so] = M + logf(l);
         rs_out[so] = r_s;
         rr_out[so] = r_r;
       }
@@ -262,338 +455,308 @@ __global__ __launch_bounds__(256) void gen_fwd_kernel(const IO* __restrict__ q, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Backward, step 1: through the two RMS norms (Sec. 3.2).  For y = g*x*r, r = (mean x^2+eps)^-1/2:
-//   dx = r*(g*dy) - x*r^3*mean(g*dy*x),   dgamma += dy*x*r,   delta = <dx_s, x_s>.
-// grid (RB, Hq): block rb walks rows rb, rb+RB, ... of the B*T rows of head h; each wave keeps
-// per-feature dgamma partials, combined across the 4 waves at the end -> dgpart[2][RB][Hq][D].
-template <typename IO, typename ST, int D>
-__global__ __launch_bounds__(256) void gen_bwd_prep_kernel(const IO* __restrict__ dO, const ST* __restrict__ xs_in,
-                                                           const ST* __restrict__ xr_in,
-                                                           const float* __restrict__ rs_in,
-                                                           const float* __restrict__ rr_in,
-                                                           const float* __restrict__ gs, const float* __restrict__ gr,
-                                                           float* __restrict__ dxs, float* __restrict__ dxr,
-                                                           float* __restrict__ delta, float* __restrict__ dgpart,
-                                                           LayerDims dm) {
-  constexpr int EPL = D / 64;
-  __shared__ float red[2][4][D];
-  const int h = blockIdx.y, RB = gridDim.x, lane = lane_id(), w = wave_id();
-  const int rows = dm.B * dm.T;
-  float dg1[EPL], dg2[EPL], g1[EPL], g2[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) {
-    dg1[e] = dg2[e] = 0.f;
-    g1[e] = gs ? gs[h * D + lane + 64 * e] : 1.f;
-    g2[e] = gr ? gr[h * D + lane + 64 * e] : 1.f;
-  }
-  for (int r = blockIdx.x * 4 + w; r < rows; r += RB * 4) {
-    const int b = r / dm.T, t = r % dm.T;
-    const size_t off = ((size_t)r * dm.Hq + h) * D;
-    const size_t so = (size_t)(b * dm.Hq + h) * dm.T + t;
-    Row<IO, D> dy;
-    Row<ST, D> xs, xr;
-    dy.load(dO + off); xs.load(xs_in + off); xr.load(xr_in + off);
-    const float r_s = rs_in[so], r_r = rr_in[so];
-    float m1 = 0.f, m2 = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) { m1 += g1[e] * dy.x[e] * xs.x[e]; m2 += g2[e] * dy.x[e] * xr.x[e]; }
-    m1 = wave_sum(m1) / D; m2 = wave_sum(m2) / D;
-    float dl = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const float a = r_s * g1[e] * dy.x[e] - xs.x[e] * r_s * r_s * r_s * m1;
-      const float c = r_r * g2[e] * dy.x[e] - xr.x[e] * r_r * r_r * r_r * m2;
-      dxs[off + lane + 64 * e] = a;
-      dxr[off + lane + 64 * e] = c;
-      dl += a * xs.x[e];
-      dg1[e] += dy.x[e] * xs.x[e] * r_s;
-      dg2[e] += dy.x[e] * xr.x[e] * r_r;
-    }
-    dl = wave_sum(dl);
-    if (lane == 0) delta[so] = dl;
-  }
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) { red[0][w][lane + 64 * e] = dg1[e]; red[1][w][lane + 64 * e] = dg2[e]; }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 2 * D; i += 256) {
-    const int which = i / D, d = i % D;
-    const float s = red[which][0][d] + red[which][1][d] + red[which][2][d] + red[which][3][d];
-    dgpart[((size_t)(which * RB + blockIdx.x) * dm.Hq + h) * D + d] = s;
-  }
-}
-
-// dgamma[h][d] = sum over the RB partials, in a fixed order.  grid (ceil(Hq*D/256)), 256 threads.
-__global__ void gen_dgamma_reduce_kernel(const float* __restrict__ dgpart, float* __restrict__ dgs,
-                                         float* __restrict__ dgr, int RB, int HD) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= HD) return;
-  float s1 = 0.f, s2 = 0.f;
-  for (int r = 0; r < RB; ++r) { s1 += dgpart[(size_t)r * HD + i]; s2 += dgpart[(size_t)(RB + r) * HD + i]; }
-  if (dgs) dgs[i] = s1;
-  if (dgr) dgr[i] = s2;
-}
-
-// ------------------------------------------------------------------------------------------------
-// Backward, dq: one wave per query row (layout as the forward).
+// Backward, dq.  grid (ceil(T / 16), Hq, B): 16 query rows of one head.
+//   RMS norms (Sec. 3.2): for y = g*x*r, r = (mean x^2+eps)^-1/2:  dx = r*(g*dy) - x*r^3*mean(g*dy*x),
+//                   dgamma += dy*x*r,  delta = <dx_s, x_s>;  dx_s, dx_r, delta are stored for the dk/dv kernel, the sums
+//                   over the 16 rows of the gain gradients go to dgpart[2][RB][Hq][D] (NULL: not wanted)
 //   softmax branch: p = exp(scale q.k - lse), dp = <dx_s, v_s>, da = p(dp - delta), dq += scale*da*k_s
-//                   (delta recomputed from p and dp, and written back, when the window fits one pass: W <= 64)
 //   linear branch : dphi(q) = S_[j] dx_r + sum_{intra} <dx_r, v_s> phi(k_s);  dq += phi(q)*(dphi - <dphi,phi(q)>)
 //                   (softmax map; ReLU passes dphi where q > 0, identity passes it unchanged)
 template <typename IO, int D>
-__global__ __launch_bounds__(256) void gen_bwd_dq_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
-                                                         const IO* __restrict__ v, const float* __restrict__ dxs,
-                                                         const float* __restrict__ dxr, float* delta,
-                                                         const float* __restrict__ lse,
-                                                         const float* __restrict__ states, IO* __restrict__ dq,
-                                                         LayerDims dm) {
-  constexpr int EPL = D / 64;
+__global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+                                                            const IO* __restrict__ v, const IO* __restrict__ dO,
+                                                            const float* __restrict__ gs, const float* __restrict__ gr,
+                                                            SavedPtrs sv, const float* __restrict__ states,
+                                                            IO* __restrict__ dq, float* __restrict__ dxs_out,
+                                                            float* __restrict__ dxr_out, float* __restrict__ delta_out,
+                                                            float* __restrict__ dgpart, LayerDims dm) {
+  constexpr int PL = plane_floats<D>();
+  __shared__ __align__(16) float part[GW * PL];
   const int h = blockIdx.y, b = blockIdx.z, g = h / dm.G;
-  const int lane = lane_id();
+  const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
   const int T = dm.T, W = dm.W, C = dm.C, Hq = dm.Hq, Hkv = dm.Hkv;
-  for (int qi = 0; qi < GEN_QPW; ++qi) {
-    const int t = (blockIdx.x * 4 + wave_id()) * GEN_QPW + qi;
-    if (t >= T) break;
-    const size_t qoff = ((size_t)(b * T + t) * Hq + h) * D;
-    const size_t so = (size_t)(b * Hq + h) * T + t;
-    Row<IO, D> qv;
-    qv.load(q + qoff);
-    Row<float, D> gxs, gxr;
-    gxs.load(dxs + qoff); gxr.load(dxr + qoff);
-    float dl = delta[so];
-    const float ls = lse[so];
-    float acc[EPL];
+  const int t0 = 16 * blockIdx.x, t_hi = min(t0 + 15, T - 1), t = min(t0 + r16, t_hi);
+  const bool live = t0 + r16 <= t_hi;
+  auto krow = [&](int s) { return k + ((size_t)(b * T + min(s, t_hi)) * Hkv + g) * D; };
+  auto vrow = [&](int s) { return v + ((size_t)(b * T + min(s, t_hi)) * Hkv + g) * D; };
+  const size_t qoff = ((size_t)(b * T + t) * Hq + h) * D, so = (size_t)(b * Hq + h) * T + t;
+  // ---- RMS norms; every wave forms the gradients of the 16 rows for itself
+  RowForm<D> dxs, dxr;
+  float delta;
+  {
+    RowForm<D> dy, x;
+    dy.load(dO + qoff, q4);
+    const float r_s = sv.rs[so], r_r = sv.rr[so];
+    float* dg = dgpart && w == 0 ? dgpart + ((size_t)(b * gridDim.x + blockIdx.x) * Hq + h) * D : nullptr;
+    const size_t dg_which = (size_t)gridDim.x * gridDim.z * Hq * D;
+    auto branch = [&](const float* xp, const float* gain, float r, RowForm<D>& dx, float* dgp) {
+      x.load(xp + qoff, q4);
+      float mean = 0.f;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    const int s_lo = max(0, t - W + 1);
-    for (int base = s_lo; base <= t; base += 64) {
-      const int s = base + lane;
-      const bool valid = s <= t;
-      const int sc = valid ? s : t;
-      const size_t ko = ((size_t)(b * T + sc) * Hkv + g) * D;
-      const float a = dm.scale * lane_dot(qv, k + ko);
-      const float p = valid ? expf(a - ls) : 0.f;
-      const float dp = lane_dot(gxs, v + ko);
-      if (W <= 64) {
-        // The window fits one pass of the wave: delta = sum_j p_j dp_j from the very p and dp that form da, instead
-        // of <dx_s, x_s> with the stored x_s.  For windows of a few keys p is nearly one-hot and p (dp - delta)
-        // cancels; the rounding of a bf16-stored x_s would be what is left.  The dk/dv kernel reads it back.
-        dl = wave_sum(p * dp);
-        if (lane == 0) delta[so] = dl;
-      }
-      const float da = p * (dp - dl);
-      const int n = min(64, t - base + 1);
-      for (int j = 0; j < n; ++j) {
-        const float daj = bcast(da, j);
-        const IO* kr = k + ((size_t)(b * T + base + j) * Hkv + g) * D;
+      for (int j = 0; j < D / 16; ++j) {
+        const f32x4_t gj = gain ? load4(gain + h * D + 16 * j + 4 * q4) : f32x4_t{1.f, 1.f, 1.f, 1.f};
+        dx.x[j] = gj * dy.x[j];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += daj * io_traits<IO>::ld(kr + lane + 64 * e);
-      }
-    }
+        for (int e = 0; e < 4; ++e) mean += dx.x[j][e] * x.x[j][e];
+        if (dgp) {
+          f32x4_t s = dy.x[j] * x.x[j] * (live ? r : 0.f);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] *= dm.scale;
-    const int pidx = t - W;
-    if (pidx >= 0) {
-      Row<IO, D> qf = qv;
-      qf.feature(dm.phi);
-      const int j = pidx / C;
-      const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-      Row<float, D> dqf;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) dqf.x[e] = lane_dot(gxr, S + (size_t)(lane + 64 * e) * D);
-      for (int base = j * C; base <= pidx; base += 64) {
-        const int s = base + lane;
-        const bool valid = s <= pidx;
-        const int sc = valid ? s : pidx;
-        const size_t ko = ((size_t)(b * T + sc) * Hkv + g) * D;
-        float mk, zk;
-        lane_feature_stats<D>(k + ko, mk, zk, dm.phi);
-        float coef = lane_dot(gxr, v + ko) / zk;
-        coef = valid ? coef : 0.f;
-        const int n = min(64, pidx - base + 1);
-        for (int jj = 0; jj < n; ++jj) {
-          const float cf = bcast(coef, jj), mj = bcast(mk, jj);
-          const IO* kr = k + ((size_t)(b * T + base + jj) * Hkv + g) * D;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) dqf.x[e] += cf * feat(io_traits<IO>::ld(kr + lane + 64 * e), mj, dm.phi);
+          for (int e = 0; e < 4; ++e) s[e] = sum16(s[e]);
+          if (r16 == 0) store4(dgp + 16 * j + 4 * q4, s);
         }
       }
-      float inner = 0.f;
+      mean = rows_sum(mean) / D;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) inner += dqf.x[e] * qf.x[e];
-      inner = wave_sum(inner);
+      for (int j = 0; j < D / 16; ++j) dx.x[j] = r * dx.x[j] - x.x[j] * (r * r * r * mean);
+    };
+    branch((const float*)sv.xr, gr, r_r, dxr, dg ? dg + dg_which : nullptr);
+    branch((const float*)sv.xs, gs, r_s, dxs, dg);
+    delta = dxs.dot(x);
+    if (w == GW - 1 && live) {
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] += feat_bwd(qv.x[e], qf.x[e], dqf.x[e], inner, dm.phi);
+      for (int j = 0; j < D / 16; ++j) {
+        store4(dxs_out + qoff + 16 * j + 4 * q4, dxs.x[j]);
+        store4(dxr_out + qoff + 16 * j + 4 * q4, dxr.x[j]);
+      }
+      if (q4 == 0) delta_out[so] = delta;
     }
+  }
+  f32x4_t acc[D / 16];
+  zero<D>(acc);
+  // ---- linear branch
+  if (t_hi >= W) {
+    const int j = max(0, t0 - W) / C;
+    const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) io_traits<IO>::st(dq + qoff + lane + 64 * e, acc[e]);
+    for (int jj = 0; jj < D / 16; ++jj)
+      if (jj % GW == w) state_product_t<D>(S, jj, dxr.x[jj], r16, q4, acc);
+    const int lo = j * C, nt = (t_hi - W - lo) / 16 + 1;
+    for (int n = w; n < nt; n += GW) {
+      const int s0 = lo + 16 * n;
+      RowForm<D> vf;
+      ColForm<D> kf;
+      vf.load(vrow(s0 + r16), q4);
+      kf.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
+      kf.feature(dm.phi);
+      f32x4_t c = row_product<D>(vf, dxr);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = s0 + 4 * q4 + i <= t - W ? c[i] : 0.f;
+      col_product<D>(kf, c, acc);
+    }
+    feature_backward<D>(q + qoff, acc, q4, dm.phi);
+  }
+  // ---- softmax branch
+  {
+    RowForm<D> qv;
+    qv.load(q + qoff, q4);
+    const float lse = sv.lse[so];
+    const int lo = max(0, t0 - W + 1), nt = (t_hi - lo) / 16 + 1;
+    for (int n = w; n < nt; n += GW) {
+      const int s0 = lo + 16 * n;
+      RowForm<D> kf, vf;
+      ColForm<D> kc;
+      kf.load(krow(s0 + r16), q4);
+      vf.load(vrow(s0 + r16), q4);
+      kc.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
+      const f32x4_t s = row_product<D>(kf, qv), dp = row_product<D>(vf, dxs);
+      f32x4_t da;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned dist = (unsigned)(t - (s0 + 4 * q4 + i));
+        const float p = dist < (unsigned)W ? expf(s[i] * dm.scale - lse) : 0.f;
+        da[i] = p * (dp[i] - delta) * dm.scale;
+      }
+      col_product<D>(kc, da, acc);
+    }
+  }
+  put_partial<D>(part + w * PL, acc, r16, q4);
+  __syncthreads();
+  const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
+  if (t0 + row < T) {
+#pragma unroll
+    for (int hf = 0; hf < D / 64; ++hf) {
+      f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < GW; ++r) s += *reinterpret_cast<const f32x4_t*>(part + r * PL + row * (D + 4) + 64 * hf + 4 * c);
+      store4(dq + ((size_t)(b * T + t0 + row) * Hq + h) * D + 64 * hf + 4 * c, s);
+    }
   }
 }
 
 // ------------------------------------------------------------------------------------------------
-// Backward, dk and dv: one wave per key row of a KV head; the G query heads of the group are
-// visited in turn, so no atomics are needed.  `rstates` are the reverse-time chunk states
-// R_[j] = sum over query chunks after j of phi(q)^T dx_r (summed over the group's heads).
+// Backward, dk and dv.  grid (ceil(T / 16), Hkv, B): 16 key rows of one KV head; the G query heads of the group are
+// visited in turn, so no atomics are needed.  `rstates` are the reverse-time chunk states R_[j] = sum over query chunks
+// after j of phi(q)^T dx_r (summed over the group's heads); j is the chunk of the tile's last key.
 template <typename IO, int D>
-__global__ __launch_bounds__(256) void gen_bwd_dkv_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
-                                                          const IO* __restrict__ v, const float* __restrict__ dxs,
-                                                          const float* __restrict__ dxr,
-                                                          const float* __restrict__ delta,
-                                                          const float* __restrict__ lse,
-                                                          const float* __restrict__ rstates, IO* __restrict__ dk,
-                                                          IO* __restrict__ dv, LayerDims dm) {
-  constexpr int EPL = D / 64;
+__global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+                                                             const IO* __restrict__ v, const float* __restrict__ dxs,
+                                                             const float* __restrict__ dxr, const float* __restrict__ delta,
+                                                             const float* __restrict__ lse, const float* __restrict__ rstates,
+                                                             IO* __restrict__ dk, IO* __restrict__ dv, LayerDims dm) {
+  constexpr int PL = plane_floats<D>();
+  __shared__ __align__(16) float part[GW * PL];
   const int g = blockIdx.y, b = blockIdx.z;
-  const int lane = lane_id();
+  const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
   const int T = dm.T, W = dm.W, C = dm.C, Hq = dm.Hq, Hkv = dm.Hkv, G = dm.G;
   const int Tp = max(T - W, 0);
-  for (int ki = 0; ki < GEN_QPW; ++ki) {
-    const int s = (blockIdx.x * 4 + wave_id()) * GEN_QPW + ki;
-    if (s >= T) break;
-    const size_t koff = ((size_t)(b * T + s) * Hkv + g) * D;
-    Row<IO, D> kv, vv;
-    kv.load(k + koff); vv.load(v + koff);
-    Row<IO, D> kf = kv;
-    kf.feature(dm.phi);
-    float dka[EPL], dva[EPL];
-    Row<float, D> dkf;
+  const int s0 = 16 * blockIdx.x, s_hi = min(s0 + 15, T - 1), s = min(s0 + r16, s_hi);
+  const size_t koff = ((size_t)(b * T + s) * Hkv + g) * D;
+  RowForm<D> kv, vv;
+  vv.load(v + koff, q4);
+  kv.load(k + koff, q4);
+  f32x4_t dka[D / 16], dva[D / 16];
+  zero<D>(dka);
+  zero<D>(dva);
+  // ---- linear branch: queries t = t' + W, t' >= s
+  if (s0 < Tp) {
+    kv.feature(dm.phi);
+    const int j = min(s_hi, Tp - 1) / C;
+    const float* R = rstates + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) dka[e] = dva[e] = dkf.x[e] = 0.f;
-    const int tmax = min(s + W - 1, T - 1);
-    const bool in_lin = s < Tp;
-    const int j = s / C;
-    const int tpmax = min((j + 1) * C, Tp) - 1;
-    for (int hh = 0; hh < G; ++hh) {
-      const int h = g * G + hh;
+    for (int jj = 0; jj < D / 16; ++jj)
+      if (jj % GW == w) {
+        state_product<D>(R, jj, kv.x[jj], r16, q4, dva);
+        state_product_t<D>(R, jj, vv.x[jj], r16, q4, dka);
+      }
+    const int hi = min((j + 1) * C, Tp) - 1, nt = (hi - s0) / 16 + 1;
+    for (int u = w; u < G * nt; u += GW) {
+      const int h = g * G + u / nt, tp0 = s0 + 16 * (u % nt);
+      auto off = [&](int tp) { return ((size_t)(b * T + min(tp, hi) + W) * Hq + h) * D; };
+      {
+        RowForm<D> qf;
+        qf.load(q + off(tp0 + r16), q4);
+        ColForm<D> dc;
+        dc.load([&](int i) { return dxr + off(tp0 + 4 * q4 + i); }, r16);
+        qf.feature(dm.phi);
+        f32x4_t c = row_product<D>(qf, kv);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { const int tp = tp0 + 4 * q4 + i; c[i] = tp >= s && tp <= hi ? c[i] : 0.f; }
+        col_product<D>(dc, c, dva);
+      }
+      {
+        RowForm<D> dr;
+        dr.load(dxr + off(tp0 + r16), q4);
+        ColForm<D> qc;
+        qc.load([&](int i) { return q + off(tp0 + 4 * q4 + i); }, r16);
+        qc.feature(dm.phi);
+        f32x4_t c = row_product<D>(dr, vv);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { const int tp = tp0 + 4 * q4 + i; c[i] = tp >= s && tp <= hi ? c[i] : 0.f; }
+        col_product<D>(qc, c, dka);
+      }
+    }
+    feature_backward<D>(k + koff, dka, q4, dm.phi);
+    if (s >= Tp) {  // (a key without residual queries in a tile that has some: its column is zero up to here)
+#pragma unroll
+      for (int e = 0; e < D / 16; ++e) dka[e] = dva[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    kv.load(k + koff, q4);
+  }
+  // ---- softmax branch: queries s .. s + W - 1
+  {
+    const int hi = min(s_hi + W - 1, T - 1), nt = (hi - s0) / 16 + 1;
+    for (int u = w; u < G * nt; u += GW) {
+      const int h = g * G + u / nt, q0 = s0 + 16 * (u % nt);
+      auto off = [&](int t) { return ((size_t)(b * T + min(t, hi)) * Hq + h) * D; };
       const size_t sbase = (size_t)(b * Hq + h) * T;
-      for (int base = s; base <= tmax; base += 64) {
-        const int t = base + lane;
-        const bool valid = t <= tmax;
-        const int tc = valid ? t : tmax;
-        const size_t qo = ((size_t)(b * T + tc) * Hq + h) * D;
-        const float a = dm.scale * lane_dot(kv, q + qo);
-        const float p = valid ? expf(a - lse[sbase + tc]) : 0.f;
-        const float dp = lane_dot(vv, dxs + qo);
-        const float da = p * (dp - delta[sbase + tc]);
-        const int n = min(64, tmax - base + 1);
-        for (int jj = 0; jj < n; ++jj) {
-          const float pj = bcast(p, jj), daj = bcast(da, jj);
-          const size_t ro = ((size_t)(b * T + base + jj) * Hq + h) * D;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            dva[e] += pj * dxs[ro + lane + 64 * e];
-            dka[e] += daj * io_traits<IO>::ld(q + ro + lane + 64 * e);
-          }
-        }
+      f32x4_t p, da;
+      {
+        RowForm<D> qf;
+        qf.load(q + off(q0 + r16), q4);
+        p = row_product<D>(qf, kv);
       }
-      if (in_lin) {
-        for (int base = s; base <= tpmax; base += 64) {
-          const int tp = base + lane;
-          const bool valid = tp <= tpmax;
-          const int t = (valid ? tp : tpmax) + W;
-          const size_t qo = ((size_t)(b * T + t) * Hq + h) * D;
-          float mq, zq;
-          lane_feature_stats<D>(q + qo, mq, zq, dm.phi);
-          float c = lane_dot_feat(kf, q + qo, mq, dm.phi) / zq;
-          float coef = lane_dot(vv, dxr + qo) / zq;
-          c = valid ? c : 0.f;
-          coef = valid ? coef : 0.f;
-          const int n = min(64, tpmax - base + 1);
-          for (int jj = 0; jj < n; ++jj) {
-            const float cj = bcast(c, jj), cf = bcast(coef, jj), mj = bcast(mq, jj);
-            const size_t ro = ((size_t)(b * T + base + jj + W) * Hq + h) * D;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) {
-              dva[e] += cj * dxr[ro + lane + 64 * e];
-              dkf.x[e] += cf * feat(io_traits<IO>::ld(q + ro + lane + 64 * e), mj, dm.phi);
-            }
-          }
-        }
+      {
+        RowForm<D> dx;
+        dx.load(dxs + off(q0 + r16), q4);
+        da = row_product<D>(dx, vv);
       }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = q0 + 4 * q4 + i;
+        const unsigned dist = (unsigned)(t - s);
+        const size_t st = sbase + min(t, hi);
+        p[i] = dist < (unsigned)W && t <= hi ? expf(p[i] * dm.scale - lse[st]) : 0.f;
+        da[i] = p[i] * (da[i] - delta[st]) * dm.scale;
+      }
+      ColForm<D> c;
+      c.load([&](int i) { return dxs + off(q0 + 4 * q4 + i); }, r16);
+      col_product<D>(c, p, dva);
+      c.load([&](int i) { return q + off(q0 + 4 * q4 + i); }, r16);
+      col_product<D>(c, da, dka);
     }
-    if (in_lin) {
-      const float* R = rstates + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-#pragma unroll 8
-      for (int f = 0; f < D; ++f) {
-        const float kff = bcast(kf.x[f / 64], f % 64);
+  }
+  const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) dva[e] += kff * R[(size_t)f * D + lane + 64 * e];
+  for (int which = 0; which < 2; ++which) {
+    if (which) __syncthreads();
+    put_partial<D>(part + w * PL, which ? dva : dka, r16, q4);
+    __syncthreads();
+    IO* dst = which ? dv : dk;
+    if (s0 + row < T) {
+#pragma unroll
+      for (int hf = 0; hf < D / 64; ++hf) {
+        f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < GW; ++r) x += *reinterpret_cast<const f32x4_t*>(part + r * PL + row * (D + 4) + 64 * hf + 4 * c);
+        store4(dst + ((size_t)(b * T + s0 + row) * Hkv + g) * D + 64 * hf + 4 * c, x);
       }
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) dkf.x[e] += lane_dot(vv, R + (size_t)(lane + 64 * e) * D);
-    }
-    float inner = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) inner += dkf.x[e] * kf.x[e];
-    inner = wave_sum(inner);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      io_traits<IO>::st(dk + koff + lane + 64 * e,
-                        dm.scale * dka[e] + feat_bwd(kv.x[e], kf.x[e], dkf.x[e], inner, dm.phi));
-      io_traits<IO>::st(dv + koff + lane + 64 * e, dva[e]);
     }
   }
 }
 
 // ------------------------------------------------------------------------------------------------
 // host launchers
-template <typename IO, typename ST, int D>
-static void launch_fwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs,
-                       const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st) {
-  if (dm.nst > 0) {
-    ProfScope ps("gen_scan_kernel", st);
-    gen_scan_kernel<IO, IO, D, false><<<dim3(D / 16, dm.Hkv, dm.B), 256, 0, st>>>(
-        (const IO*)k, (const IO*)v, states, dm.T, dm.Hkv, 1, 0, dm.T - dm.W, dm.C, dm.nst, dm.phi);
+template <typename AT, typename BT, int D, bool REV>
+void build_states(const LayerDims& dm, const void* a, const void* bsrc, float* states, int H, int GA, int off,
+                  const float* init, hipStream_t st) {
+  if (dm.nst <= 0) return;
+  const int first = REV ? 1 : 0;
+  if (dm.nst > 1) {
+    ProfScope ps(REV ? "gen_chunk_kernel(rev)" : "gen_chunk_kernel", st);
+    gen_chunk_kernel<AT, BT, D><<<dim3(dm.nst - 1, dm.Hkv, dm.B), 256, 0, st>>>(
+        (const AT*)a, (const BT*)bsrc, states, dm.T, H, GA, off, dm.T - dm.W, dm.C, dm.nst, first, dm.phi);
   }
-  dim3 grid((dm.T + 4 * GEN_QPW - 1) / (4 * GEN_QPW), dm.Hq, dm.B);
-  ProfScope ps("gen_fwd_kernel", st);
-  gen_fwd_kernel<IO, ST, D><<<grid, 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, gs, gr, states, (IO*)o,
-                                                  (ST*)sv.xs, (ST*)sv.xr, sv.lse, sv.rs, sv.rr, dm);
+  ProfScope ps(REV ? "gen_scan_kernel(rev)" : "gen_scan_kernel", st);
+  gen_scan_kernel<REV><<<dim3(D * D / 256, dm.B * dm.Hkv), 64, 0, st>>>(states, init, dm.nst, D * D / 4);
 }
 
-template <typename IO, typename ST, int D>
-static void launch_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs,
-                       const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv,
-                       float* dgs, float* dgr, const GenericBwdWs& ws, hipStream_t st) {
-  {
-    ProfScope ps("gen_bwd_prep_kernel", st);
-    gen_bwd_prep_kernel<IO, ST, D><<<dim3(ws.RB, dm.Hq), 256, 0, st>>>((const IO*)dO, (const ST*)sv.xs,
-                                                                       (const ST*)sv.xr, sv.rs, sv.rr, gs, gr, ws.dxs,
-                                                                       ws.dxr, ws.delta, ws.dgpart, dm);
-  }
-  if (dgs || dgr) {
-    const int HD = dm.Hq * D;
-    gen_dgamma_reduce_kernel<<<(HD + 255) / 256, 256, 0, st>>>(ws.dgpart, dgs, dgr, ws.RB, HD);
-  }
-  if (dm.nst > 0) {
-    ProfScope ps("gen_scan_kernel(x2)", st);
-    gen_scan_kernel<IO, IO, D, false><<<dim3(D / 16, dm.Hkv, dm.B), 256, 0, st>>>(
-        (const IO*)k, (const IO*)v, ws.states, dm.T, dm.Hkv, 1, 0, dm.T - dm.W, dm.C, dm.nst, dm.phi);
-    gen_scan_kernel<IO, float, D, true><<<dim3(D / 16, dm.Hkv, dm.B), 256, 0, st>>>(
-        (const IO*)q, ws.dxr, ws.rstates, dm.T, dm.Hq, dm.G, dm.W, dm.T - dm.W, dm.C, dm.nst, dm.phi);
-  }
-  dim3 gq((dm.T + 4 * GEN_QPW - 1) / (4 * GEN_QPW), dm.Hq, dm.B);
+template <typename IO, int D>
+void launch_fwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr, void* o,
+                const SavedPtrs& sv, float* states, hipStream_t st, int q0, const float* state0) {
+  build_states<IO, IO, D, false>(dm, k, v, states, dm.Hkv, 1, 0, state0, st);
+  ProfScope ps("gen_fwd_kernel", st);
+  gen_fwd_kernel<IO, D><<<dim3((dm.T - q0 + 15) / 16, dm.Hq, dm.B), 256, 0, st>>>(
+      (const IO*)q, (const IO*)k, (const IO*)v, gs, gr, states, (IO*)o, (float*)sv.xs, (float*)sv.xr, sv.lse, sv.rs, sv.rr, dm, q0);
+}
+
+template <typename IO, int D>
+void launch_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr,
+                const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs, float* dgr,
+                const GenericBwdWs& ws, hipStream_t st) {
+  const int tiles = (dm.T + 15) / 16;
   {
     ProfScope ps("gen_bwd_dq_kernel", st);
-    gen_bwd_dq_kernel<IO, D><<<gq, 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr, ws.delta,
-                                                 sv.lse, ws.states, (IO*)dq, dm);
+    gen_bwd_dq_kernel<IO, D><<<dim3(tiles, dm.Hq, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, (const IO*)dO, gs, gr,
+                                                                       sv, (const float*)sv.states, (IO*)dq, ws.dxs, ws.dxr,
+                                                                       ws.delta, dgs || dgr ? ws.dgpart : nullptr, dm);
   }
-  dim3 gk((dm.T + 4 * GEN_QPW - 1) / (4 * GEN_QPW), dm.Hkv, dm.B);
+  if (dgs || dgr) dgamma_reduce(ws.dgpart, dgs, dgr, tiles * dm.B, dm.Hq * D, st);
+  build_states<IO, float, D, true>(dm, q, ws.dxr, ws.rstates, dm.Hq, dm.G, dm.W, nullptr, st);
   ProfScope ps("gen_bwd_dkv_kernel", st);
-  gen_bwd_dkv_kernel<IO, D><<<gk, 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr, ws.delta,
-                                                sv.lse, ws.rstates, (IO*)dk, (IO*)dv, dm);
+  gen_bwd_dkv_kernel<IO, D><<<dim3(tiles, dm.Hkv, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr,
+                                                                       ws.delta, sv.lse, ws.rstates, (IO*)dk, (IO*)dv, dm);
 }
 
+}  // namespace
+
 void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
-                 const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st) {
+                 const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st, int q0, const float* state0) {
   if (dtype == 0) {
-    if (dm.D == 64) launch_fwd<float, float, 64>(dm, q, k, v, gs, gr, o, sv, states, st);
-    else launch_fwd<float, float, 128>(dm, q, k, v, gs, gr, o, sv, states, st);
-  } else if (sv.f32) {
-    if (dm.D == 64) launch_fwd<bf16_t, float, 64>(dm, q, k, v, gs, gr, o, sv, states, st);
-    else launch_fwd<bf16_t, float, 128>(dm, q, k, v, gs, gr, o, sv, states, st);
+    if (dm.D == 64) launch_fwd<float, 64>(dm, q, k, v, gs, gr, o, sv, states, st, q0, state0);
+    else launch_fwd<float, 128>(dm, q, k, v, gs, gr, o, sv, states, st, q0, state0);
   } else {
-    if (dm.D == 64) launch_fwd<bf16_t, bf16_t, 64>(dm, q, k, v, gs, gr, o, sv, states, st);
-    else launch_fwd<bf16_t, bf16_t, 128>(dm, q, k, v, gs, gr, o, sv, states, st);
+    if (dm.D == 64) launch_fwd<bf16_t, 64>(dm, q, k, v, gs, gr, o, sv, states, st, q0, state0);
+    else launch_fwd<bf16_t, 128>(dm, q, k, v, gs, gr, o, sv, states, st, q0, state0);
   }
 }
 
@@ -601,14 +764,11 @@ void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st) {
   if (dtype == 0) {
-    if (dm.D == 64) launch_bwd<float, float, 64>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
-    else launch_bwd<float, float, 128>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
-  } else if (sv.f32) {
-    if (dm.D == 64) launch_bwd<bf16_t, float, 64>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
-    else launch_bwd<bf16_t, float, 128>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
+    if (dm.D == 64) launch_bwd<float, 64>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
+    else launch_bwd<float, 128>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
   } else {
-    if (dm.D == 64) launch_bwd<bf16_t, bf16_t, 64>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
-    else launch_bwd<bf16_t, bf16_t, 128>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
+    if (dm.D == 64) launch_bwd<bf16_t, 64>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
+    else launch_bwd<bf16_t, 128>(dm, q, k, v, gs, gr, sv, dO, dq, dk, dv, dgs, dgr, ws, st);
   }
 }
 

@@ -32,15 +32,15 @@ struct LayerDims {
 // on the general path: the backward through the second RMS norm projects the upstream gradient off x^r, and where
 // the state has very low rank - the first rows past the window - rounding x^r to bf16 leaves an error that the
 // state multiplies back up) and the
-// row statistics (fp32, [B,Hq,T]): log-sum-exp of the softmax branch and the two RMS reciprocals; on the MFMA
-// path also the linear-branch chunk states (bf16, transposed), so that backward does not rebuild them
+// row statistics (fp32, [B,Hq,T]): log-sum-exp of the softmax branch and the two RMS reciprocals, and the
+// linear-branch chunk states (MFMA path: bf16, transposed; general path: fp32), so that backward does not rebuild them
 struct SavedPtrs {
   void* xs;
   void* xr;
   float* lse;
   float* rs;
   float* rr;
-  void* states;  // null on the general path
+  void* states;
   bool f32;      // x^s, x^r are stored as fp32 whatever the tensor dtype
   int state_stride;  // `states` holds every chunk state (0 or 1) or states 0, m, 2m, ... only (m = 2, 4): the
                      // forward then works on the full set in its workspace and backward rebuilds the states in
@@ -48,20 +48,26 @@ struct SavedPtrs {
 };
 
 struct GenericBwdWs {
-  float* states;   // [B,Hkv,nst,D,D]
   float* rstates;  // [B,Hkv,nst,D,D]
   float* dxs;      // [B,T,Hq,D]
   float* dxr;      // [B,T,Hq,D]
   float* delta;    // [B,Hq,T]
-  float* dgpart;   // [2,RB,Hq,D]
-  int RB;
+  float* dgpart;   // [2,RB,Hq,D], one gain-gradient partial per 16-row tile (RB = B ceil(T/16))
 };
 
+// Only rows q0 .. T-1 have queries (q, o and the saved tensors hold just those); `states` receives the chunk states
+// (B*Hkv*nst*D*D floats); state0 (fp32 [B,Hkv,D,D], may be NULL): a linear-branch state that precedes key 0.
 void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
-                 const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st);
+                 const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st, int q0 = 0,
+                 const float* state0 = nullptr);
+// sv.states: the chunk states as the forward left them
 void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st);
+
+// gain gradients [Hq*D] from RB partials each, summed in a fixed order: dgpart[2][RB][HD], HD a multiple of 32; either
+// output may be NULL
+void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st);
 
 // compile-time feature-map variant (FM_* in mfma.hpp) the matrix-core kernels use for these dimensions
 inline int feature_map_variant(const LayerDims& dm) {

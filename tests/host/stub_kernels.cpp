@@ -9,7 +9,7 @@ namespace rattn {
 int g_stub_launches = 0;
 
 void generic_fwd(const LayerDims&, int, const void*, const void*, const void*, const float*, const float*, void*,
-                 const SavedPtrs&, float*, hipStream_t) { ++g_stub_launches; }
+                 const SavedPtrs&, float*, hipStream_t, int, const float*) { ++g_stub_launches; }
 void generic_bwd(const LayerDims&, int, const void*, const void*, const void*, const float*, const float*,
                  const SavedPtrs&, const void*, void*, void*, void*, float*, float*, const GenericBwdWs&, hipStream_t) {
   ++g_stub_launches;

@@ -135,6 +135,16 @@ def test_bwd_f32_shapes(B, T, Hq, Hkv, D, W, chunk):
     run_bwd_case(B, T, Hq, Hkv, D, W, "f32", seed=300 + T, chunk=chunk)
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W,chunk", [
+    (1, 15, 2, 1, 64, 4, 3), (2, 16, 2, 2, 128, 16, 5), (1, 17, 5, 1, 64, 1, 16), (1, 33, 3, 1, 128, 17, 1),
+    (2, 129, 4, 2, 64, 16, 64), (1, 200, 2, 1, 128, 9, 80)])
+def test_general_kernels_tile_edges(B, T, Hq, Hkv, D, W, chunk):
+    """Lengths, windows and chunks around the 16-row tiles, the four-tile share of a work-group and the 64-token steps of
+    the chunk products."""
+    run_fwd_case(B, T, Hq, Hkv, D, W, "f32", seed=600 + T, chunk=chunk, gains=True)
+    run_bwd_case(B, T, Hq, Hkv, D, W, "f32", seed=610 + T, chunk=chunk)
+
+
 def test_bwd_config1_tiny_f32():
     cfg = synth.CONFIGS["tiny_f32"]
     q, k, v, dO = synth.make_layer_inputs(cfg, with_dO=True)
