@@ -760,6 +760,20 @@ void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
   }
 }
 
+void generic_chunk_products(const LayerDims& dm, int dtype, const void* k, const void* v, float* out, int Tp, int nseg,
+                            int seg_len, hipStream_t st) {
+  ProfScope ps("gen_chunk_kernel", st);
+  const dim3 grid(nseg, dm.Hkv, dm.B);
+#define RATTN_PRODUCTS(IO, DD)                                                                                        \
+  gen_chunk_kernel<IO, IO, DD><<<grid, 256, 0, st>>>((const IO*)k, (const IO*)v, out, dm.T, dm.Hkv, 1, 0, Tp, seg_len, nseg, 0, dm.phi)
+  if (dtype == 0) {
+    if (dm.D == 64) RATTN_PRODUCTS(float, 64); else RATTN_PRODUCTS(float, 128);
+  } else {
+    if (dm.D == 64) RATTN_PRODUCTS(bf16_t, 64); else RATTN_PRODUCTS(bf16_t, 128);
+  }
+#undef RATTN_PRODUCTS
+}
+
 void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st) {

@@ -65,6 +65,11 @@ void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st);
 
+// partial linear-branch states of key segments, out[b][kv head][segment][feature][value] (fp32): segment c covers keys
+// [c seg_len, (c+1) seg_len) below Tp
+void generic_chunk_products(const LayerDims& dm, int dtype, const void* k, const void* v, float* out, int Tp, int nseg,
+                            int seg_len, hipStream_t st);
+
 // gain gradients [Hq*D] from RB partials each, summed in a fixed order: dgpart[2][RB][HD], HD a multiple of 32; either
 // output may be NULL
 void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st);
@@ -145,7 +150,7 @@ void fast_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, 
 struct ExportPlan {
   int Tp;        // keys folded into the state (T - W, or 0)
   int nseg;      // key segments with their own partial state
-  int seg_len;   // keys per segment (multiple of the staging batch)
+  int seg_len;   // keys per segment (a multiple of 64)
   size_t partial_bytes;
 };
 ExportPlan export_plan(const LayerDims& dm);

@@ -51,12 +51,13 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
 ExportPlan export_plan(const LayerDims& dm) {
   ExportPlan pl;
   pl.Tp = dm.T > dm.W ? dm.T - dm.W : 0;
-  const int kb = 256 / (dm.D / 8);
-  int nseg = (pl.Tp + 4 * kb - 1) / (4 * kb);  // at least four key batches per segment
-  if (nseg > 64) nseg = 64;
-  pl.nseg = nseg;
-  pl.seg_len = nseg > 0 ? ((pl.Tp + nseg - 1) / nseg + kb - 1) / kb * kb : 0;
-  pl.partial_bytes = (size_t)dm.B * dm.Hkv * nseg * dm.D * dm.D * sizeof(float);
+  // Segments of 64-key tiles, enough of them for two work-groups on every CU: more only add partial states to write
+  // and read back (each as large as 128 keys and values of a bf16 head)
+  const int tiles = (pl.Tp + 63) / 64, most = 512 / (dm.B * dm.Hkv) > 1 ? 512 / (dm.B * dm.Hkv) : 1;
+  const int per = (tiles + most - 1) / most;
+  pl.seg_len = 64 * per;
+  pl.nseg = per > 0 ? (tiles + per - 1) / per : 0;
+  pl.partial_bytes = (size_t)dm.B * dm.Hkv * pl.nseg * dm.D * dm.D * sizeof(float);
   return pl;
 }
 
