@@ -49,21 +49,12 @@ inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // Sequence lengths from this size on run on the matrix-core kernels (bf16) whether or not they are a multiple of
-// the 128-row tile: with D = 128 in place, only the last partial tile of every sequence goes through zero-padded
-// buffers; with D = 64 through zero-padded copies of the whole tensors.  Shorter ones (less than one tile) stay on
-// the general kernels.
-constexpr int PAD_MIN_T = 128;
+// the 128-row tile.  Shorter ones (less than one tile) stay on the general kernels.
+constexpr int FAST_MIN_T = 128;
 
 struct Layout {
   rattn::LayerDims dm;
-  rattn::LayerDims dmf;  // what the matrix-core kernels see: dm with T rounded up to 128 when `pad`
-  bool pad;
-  bool pad_d;                                             // head size 64 widened to 128 (implies pad)
-  bool tails;                                             // pad without pad_d: the pf_* / pb_* areas hold the last
-                                                          // 128-row tile of every sequence only (RaggedTails)
-  size_t pf_q, pf_k, pf_v, pf_o, pf_gs, pf_gr;            // padded copies, forward workspace (gains only if pad_d)
-  size_t pb_q, pb_k, pb_v, pb_dO, pb_dq, pb_dk, pb_dv;    // padded copies, backward workspace
-  size_t pb_gs, pb_gr, pb_dgs, pb_dgr;                    // padded gains and gain gradients (pad_d)
+  rattn::LayerDims dmf;  // what the matrix-core kernels see: dm with T rounded up to whole 128-row tiles
   size_t esize;
   // saved
   size_t sv_xs, sv_xr, sv_lse, sv_rs, sv_rr, sv_states, saved_bytes;
@@ -71,12 +62,33 @@ struct Layout {
   // generic forward / backward workspace
   size_t gf_states, gen_fwd_bytes;
   size_t gb_rstates, gb_dxs, gb_dxr, gb_delta, gb_dgpart, gen_bwd_bytes;
-  // MFMA forward workspace
+  // MFMA forward / backward workspace
   bool fast_fwd;
   size_t ff_u, ff_states, fast_fwd_bytes;
-  size_t fb_dxs, fb_dxr, fb_delta, fb_u, fb_states, fb_rstates, fb_dgpart, fast_bwd_bytes;
+  size_t fb_dxs, fb_dxr, fb_delta, fb_u, fb_states, fb_rstates, fb_dgpart, fb_dkv, fb_dO_tail, fb_gains, fast_bwd_bytes;
   size_t fwd_bytes, bwd_bytes;
 };
+
+// Scratch of the matrix-core kernels for dims `d` (padded length): offsets into L and totals
+void fast_scratch(const rattn::LayerDims& d, Layout* L, size_t* fwd, size_t* bwd) {
+  const rattn::FastFwdPlan pl = rattn::fast_fwd_plan(d);
+  const rattn::FastBwdPlan bp = rattn::fast_bwd_plan(d);
+  const size_t nq = (size_t)d.B * d.T * d.Hq * d.D, nrow = (size_t)d.B * d.Hq * d.T;
+  size_t off = 0;
+  L->ff_u = off; off += align_up(pl.u_bytes);
+  L->ff_states = off; off += align_up(pl.state_bytes);
+  *fwd = off;
+  off = 0;
+  L->fb_dxs = off; off += align_up(nq * 2);
+  L->fb_dxr = off; off += align_up(nq * 2);
+  L->fb_delta = off; off += align_up(nrow * 8);  // delta, then log-sum-exp in log2 units
+  L->fb_u = off; off += align_up(bp.u_bytes);
+  L->fb_states = off; off += align_up(bp.fwd.state_bytes);
+  L->fb_rstates = off; off += align_up(bp.rstate_bytes);
+  L->fb_dgpart = off; off += align_up((size_t)2 * bp.RB * d.Hq * d.D * 4);
+  L->fb_dkv = off; off += align_up(bp.dkv_part_bytes);
+  *bwd = off;
+}
 
 rattn_status make_layout(const rattn_params* p, Layout* L) {
   if (!p) return fail(RATTN_ERR_INVALID_ARG, "params is NULL");
@@ -113,15 +125,10 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   dm.scale = p->softmax_scale; dm.eps = p->rms_eps; dm.phi = p->feature_map;
   L->esize = p->dtype == RATTN_F32 ? 4 : 2;
 
-  // What the matrix-core kernels would see: the sequence length rounded up to whole 128-row tiles (ragged lengths from
-  // PAD_MIN_T on: tail buffers) and a head size of 64 widened to 128 (zero-padded copies in the workspace)
-  dm.Dv = dm.D;
+  // What the matrix-core kernels would see: the sequence length rounded up to whole 128-row tiles
   L->dmf = dm;
   const bool ragged = dm.T % 128 != 0;
-  L->pad_d = p->dtype == RATTN_BF16 && dm.D == 64 && (!ragged || dm.T >= PAD_MIN_T);
-  L->pad = p->dtype == RATTN_BF16 && ((dm.D == 128 && ragged && dm.T >= PAD_MIN_T) || L->pad_d);
-  if (L->pad) L->dmf.T = (dm.T + 127) / 128 * 128;
-  if (L->pad_d) L->dmf.D = 128;
+  if (dm.T >= FAST_MIN_T) L->dmf.T = (dm.T + 127) / 128 * 128;
   const rattn::LayerDims& dmf = L->dmf;
   // Identity feature map: only calls that keep nothing for a backward pass (inference, prefill) run on the matrix
   // cores.  Its backward with bf16 operands is not accurate enough: on the first rows past the window the state has
@@ -130,12 +137,11 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   // 0.1 .. 2 times the gradient's RMS (GPU and the CPU model of the roundings agree on every such case).
   const bool identity_training = dm.phi == rattn::PHI_IDENTITY && p->save_for_bwd;
   L->fast_fwd = p->kernel_path != RATTN_PATH_GENERAL && !identity_training && rattn::fast_fwd_supported(dmf, p->dtype);
-  if (!L->fast_fwd) { L->pad = L->pad_d = false; L->dmf = dm; }
-  L->tails = L->pad && !L->pad_d;
+  if (!L->fast_fwd) L->dmf = dm;
   // `saved` is sized for the padded length
   const size_t nq = (size_t)dm.B * dm.T * dm.Hq * dm.D;
   const size_t nrow = (size_t)dm.B * dm.Hq * dm.T;
-  const size_t nq_f = (size_t)dmf.B * dmf.T * dmf.Hq * dmf.D, nkv_f = (size_t)dmf.B * dmf.T * dmf.Hkv * dmf.D;
+  const size_t nq_f = (size_t)dmf.B * dmf.T * dmf.Hq * dmf.D;
   const size_t nrow_f = (size_t)dmf.B * dmf.Hq * dmf.T;
   size_t off = 0;
   // pre-norm branch outputs: tensor dtype for the matrix-core kernels, fp32 for the general kernels
@@ -153,7 +159,7 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
     off += align_up(nstate * 4);
   } else if (L->state_stride > 0) {
     const int nstf = rattn::fast_fwd_plan(dmf).nstf;
-    off += align_up((size_t)dmf.B * dmf.Hkv * ((nstf + L->state_stride - 1) / L->state_stride) * 128 * 128 * 2);
+    off += align_up((size_t)dmf.B * dmf.Hkv * ((nstf + L->state_stride - 1) / L->state_stride) * dmf.D * dmf.D * 2);
   }
   L->saved_bytes = off;
 
@@ -168,52 +174,28 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   L->gb_dgpart = off; off += align_up((size_t)2 * dm.B * ((dm.T + 15) / 16) * dm.Hq * dm.D * 4);
   L->gen_bwd_bytes = off;
 
-  L->ff_u = L->ff_states = L->fast_fwd_bytes = 0;
+  L->ff_u = L->ff_states = L->fast_fwd_bytes = L->fast_bwd_bytes = 0;
   if (L->fast_fwd) {
-    const rattn::FastFwdPlan pl = rattn::fast_fwd_plan(dmf);
-    off = 0;
-    L->ff_u = off; off += align_up(pl.u_bytes);
-    L->ff_states = off; off += align_up(pl.state_bytes);
-    // padded copies of whole tensors, or of the last tile of every sequence
-    const size_t cq = L->tails ? (size_t)dmf.B * 128 * dmf.Hq * 128 * 2 : nq_f * 2;
-    const size_t ckv = L->tails ? (size_t)dmf.B * 128 * dmf.Hkv * 128 * 2 : nkv_f * 2;
-    if (L->pad) {
-      L->pf_q = off; off += align_up(cq);
-      L->pf_k = off; off += align_up(ckv);
-      L->pf_v = off; off += align_up(ckv);
-      L->pf_o = off; off += align_up(cq);
-      L->pf_gs = off; off += align_up((size_t)dmf.Hq * 128 * 4);
-      L->pf_gr = off; off += align_up((size_t)dmf.Hq * 128 * 4);
+    fast_scratch(dmf, L, &L->fast_fwd_bytes, &L->fast_bwd_bytes);
+    L->fb_dO_tail = L->fast_bwd_bytes;
+    if (ragged) L->fast_bwd_bytes += align_up((size_t)dm.B * 128 * dm.Hq * dm.D * 2);
+    L->fb_gains = L->fast_bwd_bytes;
+    if (dm.D == 64) L->fast_bwd_bytes += align_up((size_t)dm.Hq * 128 * 4);
+    // The sizes rattn_workspace_bytes reports for ragged lengths and for a head size of 64 stay those of the kernels that
+    // ran such tensors through copies padded to whole tiles and 128 features: programs keep buffers of these sizes.
+    if (ragged || dm.D == 64) {
+      rattn::LayerDims w = dmf;
+      w.D = 128;
+      Layout unused;
+      size_t fwd, bwd;
+      fast_scratch(w, &unused, &fwd, &bwd);
+      const size_t rows = dm.D == 64 ? (size_t)dmf.B * dmf.T : (size_t)dmf.B * 128;
+      const size_t cq = align_up(rows * dm.Hq * 256), ckv = align_up(rows * dm.Hkv * 256), gain = align_up((size_t)dm.Hq * 512);
+      fwd += 2 * cq + 2 * ckv + 2 * gain;
+      bwd += 3 * cq + 4 * ckv + 4 * gain;
+      if (fwd > L->fast_fwd_bytes) L->fast_fwd_bytes = fwd;
+      if (bwd > L->fast_bwd_bytes) L->fast_bwd_bytes = bwd;
     }
-    L->fast_fwd_bytes = off;
-  }
-  L->fast_bwd_bytes = 0;
-  if (L->fast_fwd) {
-    const rattn::FastBwdPlan bp = rattn::fast_bwd_plan(dmf);
-    off = 0;
-    L->fb_dxs = off; off += align_up(nq_f * 2);
-    L->fb_dxr = off; off += align_up(nq_f * 2);
-    L->fb_delta = off; off += align_up(nrow_f * 8);  // delta, then log-sum-exp in log2 units
-    L->fb_u = off; off += align_up(bp.u_bytes);
-    L->fb_states = off; off += align_up(bp.fwd.state_bytes);
-    L->fb_rstates = off; off += align_up(bp.rstate_bytes);
-    L->fb_dgpart = off; off += align_up((size_t)2 * bp.RB * dmf.Hq * dmf.D * 4);
-    const size_t cq = L->tails ? (size_t)dmf.B * 128 * dmf.Hq * 128 * 2 : nq_f * 2;
-    const size_t ckv = L->tails ? (size_t)dmf.B * 128 * dmf.Hkv * 128 * 2 : nkv_f * 2;
-    if (L->pad) {
-      L->pb_q = off; off += align_up(cq);
-      L->pb_k = off; off += align_up(ckv);
-      L->pb_v = off; off += align_up(ckv);
-      L->pb_dO = off; off += align_up(cq);
-      L->pb_dq = off; off += align_up(cq);
-      L->pb_dk = off; off += align_up(ckv);
-      L->pb_dv = off; off += align_up(ckv);
-      L->pb_gs = off; off += align_up((size_t)dmf.Hq * 128 * 4);
-      L->pb_gr = off; off += align_up((size_t)dmf.Hq * 128 * 4);
-      L->pb_dgs = off; off += align_up((size_t)dmf.Hq * 128 * 4);
-      L->pb_dgr = off; off += align_up((size_t)dmf.Hq * 128 * 4);
-    }
-    L->fast_bwd_bytes = off;
   }
   L->fwd_bytes = L->fast_fwd ? L->fast_fwd_bytes : L->gen_fwd_bytes;
   L->bwd_bytes = L->fast_fwd ? L->fast_bwd_bytes : L->gen_bwd_bytes;
@@ -235,8 +217,9 @@ rattn::SavedPtrs saved_views(const Layout& L, void* saved) {
 struct ChunkLayout {
   rattn_params p2;
   Layout L2;
-  int R;
-  size_t kc, vc, qc, oc, saved, fwdws, partial, bytes;
+  int R;   // ring rows in front of the chunk
+  int P;   // matrix-core kernels: R rounded up to whole tiles, so that the chunk starts at a tile
+  size_t kc, vc, fwdws, partial, bytes;
 };
 
 rattn_status make_chunk_layout(const rattn_params* p, int32_t pos0, ChunkLayout* C) {
@@ -246,27 +229,30 @@ rattn_status make_chunk_layout(const rattn_params* p, int32_t pos0, ChunkLayout*
   if (pos0 < 0) return fail(RATTN_ERR_INVALID_ARG, "pos0 must be >= 0 (got %d)", pos0);
   if ((long long)pos0 + p->T >= (1ll << 31)) return fail(RATTN_ERR_UNSUPPORTED, "pos0 + T must stay below 2^31");
   C->R = pos0 < p->window ? pos0 : p->window;
+  C->P = (int)(((long long)C->R + 127) / 128 * 128);
   C->p2 = *p;
-  C->p2.T = C->R + p->T;
-  C->p2.save_for_bwd = 1;
-  // chunked prefill reads the forward's saved tensors in the caller's head size: a head size of 64, which the
-  // matrix-core kernels would run on widened copies, stays on the general kernels here
-  if (p->D == 64) C->p2.kernel_path = RATTN_PATH_GENERAL;
+  C->p2.save_for_bwd = 0;
+  if ((long long)C->P + p->T >= (1ll << 31)) return fail(RATTN_ERR_UNSUPPORTED, "window + T must stay below 2^31");
+  C->p2.T = C->P + p->T;
+  if (C->R + p->T < FAST_MIN_T) C->p2.kernel_path = RATTN_PATH_GENERAL;
   s = make_layout(&C->p2, &C->L2);
   if (s != RATTN_OK) return s;
-  const rattn::LayerDims& dm = C->L2.dm;
-  const size_t nkv = (size_t)dm.B * dm.T * dm.Hkv * dm.D * C->L2.esize, nq = (size_t)dm.B * dm.T * dm.Hq * dm.D * C->L2.esize;
+  if (!C->L2.fast_fwd) {   // general kernels: exactly the rows there are
+    C->P = 0;
+    C->p2.T = C->R + p->T;
+    s = make_layout(&C->p2, &C->L2);
+    if (s != RATTN_OK) return s;
+  }
+  rattn::LayerDims dmx = C->L2.dm;   // rows the state update counts
+  dmx.T = C->R + p->T;
+  const int front = C->L2.fast_fwd ? C->P : dmx.T;
+  const size_t nkv = (size_t)dmx.B * front * dmx.Hkv * dmx.D * C->L2.esize;
   size_t off = 0;
   C->kc = off; off += align_up(nkv);
   C->vc = off; off += align_up(nkv);
-  if (C->L2.fast_fwd) {
-    C->qc = off; off += align_up(nq);
-    C->oc = off; off += align_up(nq);
-    C->saved = off; off += align_up(C->L2.saved_bytes);
-  }
   C->fwdws = off; off += align_up(C->L2.fwd_bytes);
-  C->partial = off; off += align_up(rattn::export_plan(dm).partial_bytes);
-  C->bytes = off;
+  C->partial = off; off += align_up(rattn::export_plan(dmx).partial_bytes);
+  C->bytes = off > 0 ? off : 256;
   return RATTN_OK;
 }
 
@@ -359,36 +345,10 @@ rattn_status rattn_fwd(const rattn_params* p, const void* q, const void* k, cons
   rattn::SavedPtrs sv = saved_views(L, p->save_for_bwd ? saved : nullptr);
   if (L.fast_fwd) {
     char* w = (char*)workspace;
-    const void *qf = q, *kf = k, *vf = v;
-    void* of = o;
-    const float *gsf = gamma_swa, *grf = gamma_rla;
-    const size_t hb = (size_t)L.dm.D * 2, hbp = (size_t)L.dmf.D * 2;  // bytes of one head row, caller's and padded
-    if (L.tails) {
-      const void* src[3] = {q, k, v};
-      void* tl[3] = {w + L.pf_q, w + L.pf_k, w + L.pf_v};
-      const int Hs[3] = {L.dm.Hq, L.dm.Hkv, L.dm.Hkv};
-      rattn::gather_tails(3, src, tl, Hs, L.dm.B, L.dm.T, st);
-      rattn::RaggedTails rt = {L.dm.T, tl[0], tl[1], tl[2], nullptr, w + L.pf_o, nullptr, nullptr, nullptr};
-      rattn::fast_fwd(L.dmf, q, k, v, gamma_swa, gamma_rla, o, sv, (float*)(w + L.ff_u),
-                      sv.states && sv.state_stride <= 1 ? sv.states : (void*)(w + L.ff_states), st, 0, nullptr, &rt);
-      const void* otl[1] = {w + L.pf_o};
-      void* odst[1] = {o};
-      rattn::scatter_tails(1, otl, odst, Hs, L.dm.B, L.dm.T, st);
-      return check_launch("rattn_fwd");
-    }
-    if (L.pad) {
-      rattn::pad_rows(q, w + L.pf_q, L.dm.B, L.dm.T, L.dmf.T, L.dm.Hq, hb, hbp, st);
-      rattn::pad_rows(k, w + L.pf_k, L.dm.B, L.dm.T, L.dmf.T, L.dm.Hkv, hb, hbp, st);
-      rattn::pad_rows(v, w + L.pf_v, L.dm.B, L.dm.T, L.dmf.T, L.dm.Hkv, hb, hbp, st);
-      qf = w + L.pf_q; kf = w + L.pf_k; vf = w + L.pf_v; of = w + L.pf_o;
-      if (L.pad_d) {  // gains are [Hq, 64] fp32: widened to [Hq, 128] (the padding features of x are zero)
-        if (gamma_swa) { rattn::pad_rows(gamma_swa, w + L.pf_gs, 1, L.dm.Hq, L.dm.Hq, 1, 256, 512, st); gsf = (const float*)(w + L.pf_gs); }
-        if (gamma_rla) { rattn::pad_rows(gamma_rla, w + L.pf_gr, 1, L.dm.Hq, L.dm.Hq, 1, 256, 512, st); grf = (const float*)(w + L.pf_gr); }
-      }
-    }
-    rattn::fast_fwd(L.dmf, qf, kf, vf, gsf, grf, of, sv, (float*)(w + L.ff_u),
+    rattn::SeqTensors t;
+    t.k = k; t.v = v; t.Tb = L.dm.T;
+    rattn::fast_fwd(L.dmf, t, q, gamma_swa, gamma_rla, o, sv, (float*)(w + L.ff_u),
                     sv.states && sv.state_stride <= 1 ? sv.states : (void*)(w + L.ff_states), st);
-    if (L.pad) rattn::unpad_rows(of, o, L.dm.B, L.dm.T, L.dmf.T, L.dm.Hq, hb, hbp, st);
   } else
     rattn::generic_fwd(L.dm, p->dtype, q, k, v, gamma_swa, gamma_rla, o, sv,
                        sv.states ? (float*)sv.states : (float*)((char*)workspace + L.gf_states), st);
@@ -424,8 +384,7 @@ rattn_status rattn_fwd_static(const rattn_params* p, const void* q, const void* 
     __atomic_store_n(&g_scratch_ptr[dev], ws, __ATOMIC_RELEASE);
   }
   // Every part of the scratch that the forward kernels read is written earlier in the same call (chunk products,
-  // then the scanned states, and - for ragged lengths or a head size of 64 - the zero-padded copies), so nothing has
-  // to be cleared.
+  // then the scanned states), so nothing has to be cleared.
   return rattn_fwd(p, q, k, v, gamma_swa, gamma_rla, o, saved, ws, RATTN_STATIC_SCRATCH_BYTES, stream);
 }
 // END-STATIC-ENTRY
@@ -454,41 +413,20 @@ rattn_status rattn_bwd(const rattn_params* p, const void* q, const void* k, cons
     rattn::FastBwdWs fw;
     fw.dxs = w + L.fb_dxs; fw.dxr = w + L.fb_dxr; fw.delta = (float*)(w + L.fb_delta); fw.U = (float*)(w + L.fb_u);
     fw.states = w + L.fb_states; fw.rstates = w + L.fb_rstates; fw.dgpart = (float*)(w + L.fb_dgpart);
-    const size_t hb = (size_t)L.dm.D * 2, hbp = (size_t)L.dmf.D * 2;  // bytes of one head row, caller's and padded
-    if (L.tails) {
-      const void* src[4] = {q, k, v, dO};
-      void* tl[4] = {w + L.pb_q, w + L.pb_k, w + L.pb_v, w + L.pb_dO};
-      const int Hs[4] = {L.dm.Hq, L.dm.Hkv, L.dm.Hkv, L.dm.Hq};
-      rattn::gather_tails(4, src, tl, Hs, L.dm.B, L.dm.T, st);
-      rattn::RaggedTails rt = {L.dm.T, tl[0], tl[1], tl[2], tl[3], nullptr, w + L.pb_dq, w + L.pb_dk, w + L.pb_dv};
-      rattn::fast_bwd(L.dmf, q, k, v, gamma_swa, gamma_rla, sv, dO, dq, dk, dv, dgamma_swa, dgamma_rla, fw, st, &rt);
-      const void* gtl[3] = {w + L.pb_dq, w + L.pb_dk, w + L.pb_dv};
-      void* gdst[3] = {dq, dk, dv};
-      rattn::scatter_tails(3, gtl, gdst, Hs, L.dm.B, L.dm.T, st);
-    } else if (L.pad) {
-      const int B = L.dm.B, T = L.dm.T, Tp = L.dmf.T, Hq = L.dm.Hq, Hkv = L.dm.Hkv;
-      rattn::pad_rows(q, w + L.pb_q, B, T, Tp, Hq, hb, hbp, st);
-      rattn::pad_rows(k, w + L.pb_k, B, T, Tp, Hkv, hb, hbp, st);
-      rattn::pad_rows(v, w + L.pb_v, B, T, Tp, Hkv, hb, hbp, st);
-      rattn::pad_rows(dO, w + L.pb_dO, B, T, Tp, Hq, hb, hbp, st);
-      const float *gsf = gamma_swa, *grf = gamma_rla;
-      float *dgs = dgamma_swa, *dgr = dgamma_rla;
-      if (L.pad_d) {  // gains and gain gradients are [Hq, 64] fp32 for the caller, [Hq, 128] for the kernels
-        if (gamma_swa) { rattn::pad_rows(gamma_swa, w + L.pb_gs, 1, Hq, Hq, 1, 256, 512, st); gsf = (const float*)(w + L.pb_gs); }
-        if (gamma_rla) { rattn::pad_rows(gamma_rla, w + L.pb_gr, 1, Hq, Hq, 1, 256, 512, st); grf = (const float*)(w + L.pb_gr); }
-        if (dgamma_swa) dgs = (float*)(w + L.pb_dgs);
-        if (dgamma_rla) dgr = (float*)(w + L.pb_dgr);
-      }
-      rattn::fast_bwd(L.dmf, w + L.pb_q, w + L.pb_k, w + L.pb_v, gsf, grf, sv, w + L.pb_dO, w + L.pb_dq,
-                      w + L.pb_dk, w + L.pb_dv, dgs, dgr, fw, st);
-      rattn::unpad_rows(w + L.pb_dq, dq, B, T, Tp, Hq, hb, hbp, st);
-      rattn::unpad_rows(w + L.pb_dk, dk, B, T, Tp, Hkv, hb, hbp, st);
-      rattn::unpad_rows(w + L.pb_dv, dv, B, T, Tp, Hkv, hb, hbp, st);
-      if (L.pad_d && dgamma_swa) rattn::unpad_rows(dgs, dgamma_swa, 1, Hq, Hq, 1, 256, 512, st);
-      if (L.pad_d && dgamma_rla) rattn::unpad_rows(dgr, dgamma_rla, 1, Hq, Hq, 1, 256, 512, st);
-    } else {
-      rattn::fast_bwd(L.dm, q, k, v, gamma_swa, gamma_rla, sv, dO, dq, dk, dv, dgamma_swa, dgamma_rla, fw, st);
+    fw.dkv_part = (float*)(w + L.fb_dkv);
+    // the rows of dO past the last whole tile, zero-filled: what the kernels compute for the rows of a tile that do not
+    // exist then adds nothing to any gradient
+    const bool ragged = L.dm.T % 128 != 0;
+    if (ragged) rattn::gather_tail(dO, w + L.fb_dO_tail, L.dm.B, L.dm.T, L.dm.Hq, L.dm.D, st);
+    const float *gs = gamma_swa, *gr = gamma_rla;
+    int gstride = L.dm.D;
+    if (L.dm.D == 64 && (gs || gr)) {   // both gains of a head in one row
+      float* packed = (float*)(w + L.fb_gains);
+      rattn::pack_gains64(gs, gr, packed, L.dm.Hq, st);
+      gs = packed; gr = packed + 64; gstride = 128;
     }
+    rattn::fast_bwd(L.dmf, L.dm.T, q, k, v, gs, gr, gstride, sv, dO, ragged ? w + L.fb_dO_tail : nullptr, dq, dk, dv,
+                    dgamma_swa, dgamma_rla, fw, st);
     return check_launch("rattn_bwd");
   }
   rattn::GenericBwdWs ws;
@@ -551,7 +489,9 @@ rattn_status rattn_prefill_export(const rattn_params* p, const void* k, const vo
   const size_t need = align_up(rattn::export_plan(L.dm).partial_bytes);
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(RATTN_ERR_WORKSPACE, "prefill export needs %zu workspace bytes, got %zu", need, workspace_bytes);
-  rattn::prefill_export(L.dm, p->dtype, k, v, k_ring, v_ring, state, (float*)workspace, (hipStream_t)stream);
+  rattn::SeqTensors t;
+  t.k = k; t.v = v; t.Tb = L.dm.T;
+  rattn::prefill_export(L.dm, p->dtype, t, k_ring, v_ring, state, (float*)workspace, (hipStream_t)stream);
   return check_launch("rattn_prefill_export");
 }
 
@@ -582,41 +522,29 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
   // keys before the ring exist only once more than `window` tokens have been seen; until then the state is zero
   // by definition and what the caller's buffer holds is not read
   const bool carried = pos0 > p->window;
-  // Direct route on the matrix-core kernels: ring and chunk are whole 128-row tiles, so the forward computes the
-  // chunk's query tiles only, straight from q into o, and (window a multiple of 128: every such tile reads a chunk
-  // state) the carried state enters as the initial value of the state scan.  Only K and V are gathered.
-  if (C.L2.fast_fwd && !C.L2.pad && C.R % 128 == 0 && (!carried || p->window % 128 == 0)) {
-    rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, nullptr, k, v, k_ring, v_ring, nullptr, w + C.kc, w + C.vc, st);
-    rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, 0};
-    rattn::fast_fwd(dm, q, w + C.kc, w + C.vc, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.ff_u),
-                    w + C.fwdws + C.L2.ff_states, st, C.R / 128, carried ? state : nullptr);
-    rattn::prefill_export(dm, p->dtype, w + C.kc, w + C.vc, k_ring, v_ring, state, (float*)(w + C.partial), st,
-                          pos0 - C.R, carried);
-    return check_launch("rattn_prefill_chunk");
+  rattn::LayerDims dmx = dm;   // rows the state update counts
+  dmx.T = C.R + p->T;
+  rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, !C.L2.fast_fwd, 0};
+  rattn::SeqTensors t;
+  // The forward computes the chunk's rows only, straight from q into o; the carried state is the initial value of the
+  // chunk-state scan, of which every chunk row reads a state (the keys before it number at least `window` then).
+  if (C.L2.fast_fwd) {
+    // only the ring rows are gathered, as the whole 128-row tiles in front of the chunk's
+    t.k = k; t.v = v; t.Tb = p->T; t.P = C.P; t.kmin = C.P - C.R;
+    if (C.P > 0) {
+      t.k_front = w + C.kc; t.v_front = w + C.vc;
+      rattn::chunk_ring(dm, C.P, C.R, pos0, k_ring, v_ring, w + C.kc, w + C.vc, st);
+    }
+    rattn::fast_fwd(C.L2.dmf, t, q, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.ff_u),
+                    w + C.fwdws + C.L2.ff_states, st, carried ? state : nullptr);
+    rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0, carried);
+  } else {
+    t.k = w + C.kc; t.v = w + C.vc; t.Tb = dmx.T;
+    rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, k, v, k_ring, v_ring, w + C.kc, w + C.vc, st);
+    rattn::generic_fwd(dm, p->dtype, q, t.k, t.v, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.gf_states), st,
+                       C.R, carried ? state : nullptr);
+    rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0 - C.R, carried);
   }
-  // General kernels: the same with 16-row tiles, which may start at any row
-  if (!C.L2.fast_fwd) {
-    rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, nullptr, k, v, k_ring, v_ring, nullptr, w + C.kc, w + C.vc, st);
-    rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true, 0};
-    rattn::generic_fwd(dm, p->dtype, q, w + C.kc, w + C.vc, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.gf_states),
-                       st, C.R, carried ? state : nullptr);
-    rattn::prefill_export(dm, p->dtype, w + C.kc, w + C.vc, k_ring, v_ring, state, (float*)(w + C.partial), st,
-                          pos0 - C.R, carried);
-    return check_launch("rattn_prefill_chunk");
-  }
-  rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, q, k, v, k_ring, v_ring, w + C.qc, w + C.kc, w + C.vc, st);
-  s = check_launch("rattn_prefill_chunk (gather)");
-  if (s != RATTN_OK) return s;
-  s = rattn_fwd(&C.p2, w + C.qc, w + C.kc, w + C.vc, gamma_swa, gamma_rla, w + C.oc, w + C.saved, w + C.fwdws,
-                C.L2.fwd_bytes, stream);
-  if (s != RATTN_OK) return s;
-  if (carried)
-    rattn::chunk_fixup(dm, p->dtype, p->T, C.R, C.L2.fast_fwd ? C.L2.dmf.T : dm.T, w + C.qc,
-                       saved_views(C.L2, w + C.saved), state, gamma_swa, gamma_rla, o, st);
-  else
-    rattn::chunk_copy_out(dm, p->dtype, p->T, C.R, w + C.oc, o, st);
-  rattn::prefill_export(dm, p->dtype, w + C.kc, w + C.vc, k_ring, v_ring, state, (float*)(w + C.partial), st,
-                        pos0 - C.R, carried);
   return check_launch("rattn_prefill_chunk");
 }
 

@@ -66,6 +66,11 @@ template <typename F> __device__ __forceinline__ float rows_reduce(float x, F f)
 __device__ __forceinline__ float rows_sum(float x) { return rows_reduce(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float rows_max(float x) { return rows_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float sum16(float x) { return row16_reduce(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float sum8(float x) {  // over 8 consecutive lanes
+  x += dpp_get<0xB1>(x);
+  x += dpp_get<0x4E>(x);
+  return x + dpp_get<0x141>(x);
+}
 __device__ __forceinline__ float wave_sum(float x) { return rows_sum(sum16(x)); }
 __device__ __forceinline__ float wave_max(float x) { return rows_max(row16_reduce(x, [](float a, float b) { return fmaxf(a, b); })); }
 // value held by lane `l` (wave-uniform l) broadcast to the whole wave through an SGPR

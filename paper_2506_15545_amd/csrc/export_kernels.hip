@@ -42,18 +42,22 @@ __device__ __forceinline__ float exp_neg(float x) {
   return fast_exp2(hi) * __builtin_fmaf(lo, LN2, 1.f);
 }
 
-// Partial states of key segments for bf16, D = 128, on the bf16 matrix cores without losing the fp32 features: phi(k) is
+// Partial states of key segments for bf16 on the bf16 matrix cores without losing the fp32 features: phi(k) is
 // split into three bf16 terms (8 + 8 + 8 bits), v is bf16 already, and the three products share one fp32 accumulator.
-// One-dimensional grid: block i < nseg * B * Hkv is segment i % nseg of (b, kv head) i / nseg; the others copy the rings.
+// One-dimensional grid: block i < nseg * B * Hkv is segment i % nseg of (b, kv head) i / nseg; the others copy the rings.  Key s is row
+// key0 + s of the two-part sequence (SeqRows).
 // Tiles of 64 keys: four threads map a key row (held in registers, requested one tile ahead) into the three LDS tiles of
-// phi; V arrives by direct-to-LDS loads, also one tile ahead; wave w then owns features 32w .. of the partial.
+// phi; V arrives by direct-to-LDS loads, also one tile ahead; wave w then owns features 32w .. of the partial (D = 64: one
+// of its four 32 x 32 tiles).
 // Bound: HBM on long prompts (12 matrix instructions per 16 keys and wave are about 1.6 times as fast as the keys
 // arrive), the launch on short ones.
-template <int PHI>
-__global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                                                                   float* __restrict__ partial, int T, int Hkv, int Tp,
-                                                                   int nseg, int seg_len, int nstate, RingCopy rc) {
-  __shared__ __align__(16) unsigned char smem[5 * 16384];  // phi hi, mid, lo; V x 2
+template <int D, int PHI>
+__global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, SeqRows v, float* __restrict__ partial, int Hkv,
+                                                                   int key0, int Tp, int nseg, int seg_len, int nstate,
+                                                                   RingCopy rc) {
+  typedef TileGeom<D> TG;
+  constexpr int KT = TG::KT, NB = TG::NB / 4, NX = D / 4, NV = D == 128 ? 4 : 1;
+  __shared__ __align__(16) unsigned char smem[5 * KT];  // phi hi, mid, lo; V x 2
   if ((int)blockIdx.x >= nstate) {
     copy_rings(rc, blockIdx.x - nstate, gridDim.x - nstate);
     return;
@@ -61,56 +65,64 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(const uint16_
   const int seg = blockIdx.x % nseg, bg = blockIdx.x / nseg, g = bg % Hkv, b = bg / Hkv;
   const int lane = lane_id(), w = wave_id(), r32 = lane & 31, h = lane >> 5;
   const int lo = seg * seg_len, hi = min(lo + seg_len, Tp);
-  const size_t rstride = (size_t)Hkv * 128;
-  const uint16_t* kb = k + ((size_t)b * T * Hkv + g) * 128;
-  const uint16_t* vb = v + ((size_t)b * T * Hkv + g) * 128;
-  const int row = threadIdx.x >> 2, quarter = threadIdx.x & 3;  // key row and its features 32 * quarter ..
-  bf16x8_t kreg[4];
+  const int row = threadIdx.x >> 2, quarter = threadIdx.x & 3;  // key row and its features D/4 * quarter ..
+  const int ft = D == 128 ? w : w & 1, dt0 = D == 128 ? 0 : w >> 1;
+  // per-lane offsets of the transposed operand reads (natural contraction order, see lds_trn)
+  int aoff[2], voff[NV][2];
+#pragma unroll
+  for (int ab = 0; ab < 2; ++ab) {
+    aoff[ab] = tr_lane_off<D>(8 * h + 4 * ab, ft, lane);
+#pragma unroll
+    for (int d = 0; d < NV; ++d) voff[d][ab] = tr_lane_off<D>(8 * h + 4 * ab, dt0 + d, lane);
+  }
+  bf16x8_t kreg[NX / 8];
   auto request = [&](int s0, int buf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {  // rows 16w + 4i + lane / 16 of the V tile
-      const int r = 16 * w + 4 * i + (lane >> 4);
-      dma16(vb + (size_t)min(s0 + r, hi - 1) * rstride + (((lane & 15) ^ swz(r)) << 3),
-            (unsigned)(size_t)RATTN_LDS(smem + (3 + buf) * 16384 + (4 * w + i) * 1024));
+    for (int i = 0; i < NB; ++i) {  // this wave's rows of the V tile
+      const int r = (NB * w + i) * TG::RPB + lane / TG::CH;
+      dma16(split_rows(v, b, key0 + min(s0 + r, hi - 1), Hkv, g, D).p + (((lane % TG::CH) ^ swz<D>(r)) << 3),
+            (unsigned)(size_t)RATTN_LDS(smem + (3 + buf) * KT + (NB * w + i) * 1024));
     }
-    const uint16_t* kp = kb + (size_t)min(s0 + row, hi - 1) * rstride + 32 * quarter;
+    const uint16_t* kp = split_rows(k, b, key0 + min(s0 + row, hi - 1), Hkv, g, D).p + NX * quarter;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) kreg[c] = *reinterpret_cast<const bf16x8_t*>(kp + 8 * c);
+    for (int c = 0; c < NX / 8; ++c) kreg[c] = *reinterpret_cast<const bf16x8_t*>(kp + 8 * c);
   };
-  f32x16_t acc[4] = {{0}, {0}, {0}, {0}};
+  f32x16_t acc[NV];
+#pragma unroll
+  for (int d = 0; d < NV; ++d) acc[d] = f32x16_t{0};
   request(lo, 0);
   int buf = 0;
   for (int s0 = lo; s0 < hi; s0 += 64, buf ^= 1) {
-    float x[32];
+    float x[NX];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) unpack_bf16x8(kreg[c], &x[8 * c]);
+    for (int c = 0; c < NX / 8; ++c) unpack_bf16x8(kreg[c], &x[8 * c]);
     float inv = 1.f;
     if (PHI == PHI_SOFTMAX) {
       float m = x[0];
 #pragma unroll
-      for (int i = 1; i < 32; ++i) m = fmaxf(m, x[i]);
+      for (int i = 1; i < NX; ++i) m = fmaxf(m, x[i]);
       m = fmaxf(m, dpp_get<0xB1>(m));
       m = fmaxf(m, dpp_get<0x4E>(m));
       float s = 0.f;
 #pragma unroll
-      for (int i = 0; i < 32; ++i) { x[i] = exp_neg(x[i] - m); s += x[i]; }
+      for (int i = 0; i < NX; ++i) { x[i] = exp_neg(x[i] - m); s += x[i]; }
       s += dpp_get<0xB1>(s);
       s += dpp_get<0x4E>(s);
       inv = 1.f / s;
     } else if (PHI == PHI_RELU) {
 #pragma unroll
-      for (int i = 0; i < 32; ++i) x[i] = fmaxf(x[i], 0.f);
+      for (int i = 0; i < NX; ++i) x[i] = fmaxf(x[i], 0.f);
     }
     if (s0 + row >= hi) inv = 0.f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < NX / 8; ++c) {
       float r[8], t[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) r[e] = x[8 * c + e] * inv;
 #pragma unroll
       for (int part = 0; part < 3; ++part) {
         const bf16x8_t pk = pack_bf16x8(r);
-        *reinterpret_cast<bf16x8_t*>(smem + part * 16384 + row * ROW_BYTES + (((4 * quarter + c) ^ swz(row)) << 4)) = pk;
+        *reinterpret_cast<bf16x8_t*>(smem + part * KT + row * TG::ROWB + (((NX / 8 * quarter + c) ^ swz<D>(row)) << 4)) = pk;
         unpack_bf16x8(pk, t);
 #pragma unroll
         for (int e = 0; e < 8; ++e) r[e] -= t[e];  // exact
@@ -119,27 +131,28 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(const uint16_
     wait_vmem();  // this tile's V
     __syncthreads();
     if (s0 + 64 < hi) request(s0 + 64, buf ^ 1);
-    const unsigned char* vt = smem + (3 + buf) * 16384;
+    const unsigned char* vt = smem + (3 + buf) * KT;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const int k0 = 16 * ks + 8 * h;
-      bf16x8_t vop[4];
+      const int k0 = 16 * ks * TG::ROWB;
+      bf16x8_t vop[NV];
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) vop[dt] = lds_tr_pair(vt, k0, k0 + 4, 32 * dt, lane);
+      for (int d = 0; d < NV; ++d) vop[d] = lds_tr2(vt + voff[d][0] + k0, vt + voff[d][1] + k0);
 #pragma unroll
       for (int part = 2; part >= 0; --part) {
-        const bf16x8_t a = lds_tr_pair(smem + part * 16384, k0, k0 + 4, 32 * w, lane);
+        const unsigned char* pt = smem + part * KT + k0;
+        const bf16x8_t a = lds_tr2(pt + aoff[0], pt + aoff[1]);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) acc[dt] = mfma32(a, vop[dt], acc[dt]);
+        for (int d = 0; d < NV; ++d) acc[d] = mfma32(a, vop[d], acc[d]);
       }
     }
     __syncthreads();
   }
-  float* out = partial + ((size_t)bg * nseg + seg) * 16384;
+  float* out = partial + ((size_t)bg * nseg + seg) * (D * D);
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int d = 0; d < NV; ++d)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) out[(size_t)(32 * w + 8 * (i >> 2) + 4 * h + (i & 3)) * 128 + 32 * dt + r32] = acc[dt][i];
+    for (int i = 0; i < 16; ++i) out[(size_t)(32 * ft + 8 * (i >> 2) + 4 * h + (i & 3)) * D + 32 * (dt0 + d) + r32] = acc[d][i];
 }
 
 // state[b,g] = (accumulate ? state[b,g] : 0) + sum over segments: four runs of segments, each in order, then the four sums
@@ -172,30 +185,35 @@ __global__ __launch_bounds__(256) void export_state_reduce_kernel(const float4* 
 
 }  // namespace
 
-void prefill_export(const LayerDims& dm, int dtype, const void* k, const void* v, void* k_ring, void* v_ring,
-                    float* state, float* partial, hipStream_t st, int tok0, bool accumulate) {
+void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k_ring, void* v_ring, float* state,
+                    float* partial, hipStream_t st, int tok0, bool accumulate) {
   const ExportPlan pl = export_plan(dm);
   const int esize = dtype == 0 ? 4 : 2;
-  const RingCopy rc = {(const uint4*)k, (const uint4*)v, (uint4*)k_ring, (uint4*)v_ring, dm.B, dm.T, dm.Hkv, dm.W,
+  const RingCopy rc = {(const uint4*)t.k, (const uint4*)t.v, (uint4*)k_ring, (uint4*)v_ring, dm.B, t.Tb, dm.Hkv, dm.W,
                        dm.D * esize / 16, tok0};
-  const long long total = (long long)dm.B * (dm.T < dm.W ? dm.T : dm.W) * dm.Hkv * rc.row_vecs;
+  const long long total = (long long)dm.B * (t.Tb < dm.W ? t.Tb : dm.W) * dm.Hkv * rc.row_vecs;
   const int copy_blocks = (int)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
-  if (pl.nseg > 0 && dtype == 1 && dm.D == 128) {
+  if (pl.nseg > 0 && dtype == 1) {
     ProfScope ps("export_state_mfma_kernel", st);
     const int nstate = pl.nseg * dm.Hkv * dm.B;
-#define RATTN_EXPORT(PHI_)                                                                                              \
-  export_state_mfma_kernel<PHI_><<<nstate + copy_blocks, 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, partial, dm.T, \
-                                                                       dm.Hkv, pl.Tp, pl.nseg, pl.seg_len, nstate, rc)
-    if (dm.phi == PHI_SOFTMAX) RATTN_EXPORT(PHI_SOFTMAX);
-    else if (dm.phi == PHI_RELU) RATTN_EXPORT(PHI_RELU);
-    else RATTN_EXPORT(PHI_IDENTITY);
+    const SeqRows ks = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};
+    const SeqRows vs = {(const uint16_t*)t.v_front, (const uint16_t*)t.v, t.P, t.Tb};
+#define RATTN_EXPORT(D_, PHI_)                                                                                             \
+  export_state_mfma_kernel<D_, PHI_><<<nstate + copy_blocks, 256, 0, st>>>(ks, vs, partial, dm.Hkv, t.kmin, pl.Tp, pl.nseg, \
+                                                                           pl.seg_len, nstate, rc)
+#define RATTN_EXPORT_MAP(D_)                                    \
+  if (dm.phi == PHI_SOFTMAX) RATTN_EXPORT(D_, PHI_SOFTMAX);     \
+  else if (dm.phi == PHI_RELU) RATTN_EXPORT(D_, PHI_RELU);      \
+  else RATTN_EXPORT(D_, PHI_IDENTITY);
+    if (dm.D == 64) { RATTN_EXPORT_MAP(64) } else { RATTN_EXPORT_MAP(128) }
+#undef RATTN_EXPORT_MAP
 #undef RATTN_EXPORT
   } else {
     {
       ProfScope ps("export_ring_kernel", st);
       export_ring_kernel<<<copy_blocks, 256, 0, st>>>(rc);
     }
-    if (pl.nseg > 0) generic_chunk_products(dm, dtype, k, v, partial, pl.Tp, pl.nseg, pl.seg_len, st);
+    if (pl.nseg > 0) generic_chunk_products(dm, t.Tb, t.k, t.v, partial, pl.Tp, pl.nseg, pl.seg_len, st);
   }
   const int vecs = dm.D * dm.D / 4;
   ProfScope ps("export_state_reduce_kernel", st);

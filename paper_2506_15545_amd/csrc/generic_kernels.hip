@@ -760,18 +760,14 @@ void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
   }
 }
 
-void generic_chunk_products(const LayerDims& dm, int dtype, const void* k, const void* v, float* out, int Tp, int nseg,
+void generic_chunk_products(const LayerDims& dm, int T, const void* k, const void* v, float* out, int Tp, int nseg,
                             int seg_len, hipStream_t st) {
   ProfScope ps("gen_chunk_kernel", st);
   const dim3 grid(nseg, dm.Hkv, dm.B);
-#define RATTN_PRODUCTS(IO, DD)                                                                                        \
-  gen_chunk_kernel<IO, IO, DD><<<grid, 256, 0, st>>>((const IO*)k, (const IO*)v, out, dm.T, dm.Hkv, 1, 0, Tp, seg_len, nseg, 0, dm.phi)
-  if (dtype == 0) {
-    if (dm.D == 64) RATTN_PRODUCTS(float, 64); else RATTN_PRODUCTS(float, 128);
-  } else {
-    if (dm.D == 64) RATTN_PRODUCTS(bf16_t, 64); else RATTN_PRODUCTS(bf16_t, 128);
-  }
-#undef RATTN_PRODUCTS
+  if (dm.D == 64)
+    gen_chunk_kernel<float, float, 64><<<grid, 256, 0, st>>>((const float*)k, (const float*)v, out, T, dm.Hkv, 1, 0, Tp, seg_len, nseg, 0, dm.phi);
+  else
+    gen_chunk_kernel<float, float, 128><<<grid, 256, 0, st>>>((const float*)k, (const float*)v, out, T, dm.Hkv, 1, 0, Tp, seg_len, nseg, 0, dm.phi);
 }
 
 void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,

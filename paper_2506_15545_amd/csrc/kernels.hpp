@@ -20,8 +20,6 @@ enum { PHI_SOFTMAX = 0, PHI_RELU = 1, PHI_IDENTITY = 2 };
 
 struct LayerDims {
   int B, T, Hq, Hkv, D, W, C, G;
-  int Dv;   // features of a head that carry data: D, or 64 when the matrix-core kernels run a head size of 64
-            // on rows zero-padded to D = 128 (the RMS norms and the softmax feature map then cover Dv features)
   int chunk_req;  // the caller's `chunk` parameter as given (0 = unspecified); C above is what the general kernels use
   int nst;  // number of chunk states per (batch, kv head): ceil(max(T-W,0) / C)
   float scale, eps;
@@ -65,36 +63,27 @@ void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st);
 
-// partial linear-branch states of key segments, out[b][kv head][segment][feature][value] (fp32): segment c covers keys
-// [c seg_len, (c+1) seg_len) below Tp
-void generic_chunk_products(const LayerDims& dm, int dtype, const void* k, const void* v, float* out, int Tp, int nseg,
+// partial linear-branch states of key segments of fp32 k, v [B,T,Hkv,D], out[b][kv head][segment][feature][value]:
+// segment c covers keys [c seg_len, (c+1) seg_len) below Tp
+void generic_chunk_products(const LayerDims& dm, int T, const void* k, const void* v, float* out, int Tp, int nseg,
                             int seg_len, hipStream_t st);
 
 // gain gradients [Hq*D] from RB partials each, summed in a fixed order: dgpart[2][RB][HD], HD a multiple of 32; either
 // output may be NULL
 void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st);
 
-// compile-time feature-map variant (FM_* in mfma.hpp) the matrix-core kernels use for these dimensions
-inline int feature_map_variant(const LayerDims& dm) {
-  if (dm.phi == PHI_RELU) return 1;
-  if (dm.phi == PHI_IDENTITY) return 2;
-  return dm.Dv == 64 ? 3 : 0;
-}
-
-// Ragged sequence lengths on the matrix-core kernels (bf16, D = 128): the kernels work in 128-row tiles over the
-// length rounded up (LayerDims::T), the caller's tensors hold Tc rows per sequence.  Tiles below 128 * (Tc / 128) are
-// read and written in place; the last, partial tile of every sequence goes through [B,128,H,128] buffers that the host
-// layer fills (inputs, zero past row Tc) before and copies back (results, rows below Tc) after the kernels.  The saved
-// and workspace tensors are laid out for the rounded-up length.  Null where a function takes a RaggedTails*: every
-// tensor holds LayerDims::T rows itself.
-struct RaggedTails {
-  int Tc;
-  const void *q, *k, *v, *dO;   // dO: backward only
-  void *o;                      // forward only
-  void *dq, *dk, *dv;           // backward only
+// Keys and values of the matrix-core kernels.  They work in 128-row tiles over a padded length (LayerDims::T); a sequence
+// has P rows in `*_front` tensors [B,P,Hkv,D] (chunked prefill: the ring in time order behind zero rows that fill the
+// first tile; P is a multiple of 128, else 0), then Tb rows in k, v [B,Tb,Hkv,D], and nothing after them.
+struct SeqTensors {
+  const void *k, *v;
+  int Tb;
+  const void *k_front = nullptr, *v_front = nullptr;
+  int P = 0;
+  int kmin = 0;   // keys in front of this row do not exist for the softmax branch
 };
 
-// MFMA forward path (bf16, D = 128, T % 128 == 0, any W >= 8)
+// MFMA forward path (bf16, padded length T % 128 == 0, any W >= 8)
 struct FastFwdPlan {
   int W;        // window the tiles and states are laid out for: min(W, T) rounded up to a multiple of 64
   int gap;      // that minus the true window (0..63): masks and the reach of the intra-chunk part
@@ -106,45 +95,48 @@ struct FastFwdPlan {
 };
 bool fast_fwd_supported(const LayerDims& dm, int dtype);
 FastFwdPlan fast_fwd_plan(const LayerDims& dm);
-// qt0 > 0: only query tiles qt0 .. T/128-1 are computed, and q, o and the saved tensors hold just those rows
-// ([B, T - 128 qt0, Hq, D]); k, v always hold all T rows.  state0 (fp32 [B,Hkv,D(feature),D(value)], may be NULL): a
-// linear-branch state that precedes key 0 and is added to every chunk state; tiles whose chunk starts before key 0
-// do not see it, so the caller uses it only when no computed tile is of that kind.
-void fast_fwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr,
-              void* o, const SavedPtrs& sv, float* U, void* states, hipStream_t st, int qt0 = 0,
-              const float* state0 = nullptr, const RaggedTails* tails = nullptr);
+// dm.T: the padded length.  The query tiles computed are those of the Tb rows behind the front part; q, o and the saved
+// tensors hold just those rows ([B,Tb,Hq,D]; the saved tensors rounded up to whole tiles).  state0 (fp32
+// [B,Hkv,D(feature),D(value)], may be NULL): a linear-branch state that precedes key 0 and is added to every chunk state;
+// tiles whose chunk starts before key 0 do not see it, so the caller uses it only when no computed tile is of that kind.
+void fast_fwd(const LayerDims& dm, const SeqTensors& t, const void* q, const float* gs, const float* gr, void* o,
+              const SavedPtrs& sv, float* U, void* states, hipStream_t st, const float* state0 = nullptr);
 
 // linear-branch chunk states for the MFMA paths (bf16 [d][f] per state, fp32 scratch U per chunk)
 // With m > 1: `subset_out` (forward) also receives states 0, m, 2m, ...; `restart` (backward) holds those states from
 // the forward pass: only the chunk products that lead to a state in between are formed, and the scan restarts from
 // every stored state.
-void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const void* k, const void* v, float* U,
-                        void* states, hipStream_t st, const float* state0 = nullptr,
-                        const RaggedTails* tails = nullptr, void* subset_out = nullptr, const void* restart = nullptr,
-                        int m = 1);
+void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTensors& t, float* U, void* states,
+                        hipStream_t st, const float* state0 = nullptr, void* subset_out = nullptr,
+                        const void* restart = nullptr, int m = 1);
 // MFMA backward path (same shape class as the MFMA forward)
 struct FastBwdPlan {
   FastFwdPlan fwd;
   int nk;  // key tiles that have a linear branch = number of reverse states
   int nrchunks;  // reverse-time chunk-local products
   int RB;  // row blocks of the prep kernel (dgamma partials)
-  size_t u_bytes, rstate_bytes;
+  int nsplit;  // work-groups that share the query heads of a key tile in the dk/dv kernel
+  size_t u_bytes, rstate_bytes, dkv_part_bytes;
 };
 struct FastBwdWs {
-  void *dxs, *dxr;       // bf16 [B,T,Hq,128]
+  void *dxs, *dxr;       // bf16 [B,T,Hq,D]
   float* delta;          // [B,Hq,T]
   float* U;              // chunk scratch
   void *states, *rstates;
-  float* dgpart;         // [2,RB,Hq,128]
+  float* dgpart;         // [2,RB,Hq,D]
+  float* dkv_part;       // partial dk, then dv: [2][nsplit][B,Tc,Hkv,D] (nsplit > 1)
 };
 FastBwdPlan fast_bwd_plan(const LayerDims& dm);
 // reverse-time states R_i = sum over t' >= 128(i+1) and over the group's heads of phi(q_{t'+W})^T dxr_{t'+W},
 // i in [0, nk), nk = ceil((T-W)/128); stored transposed [d][f] bf16.  U needs (nk-1) chunks.
-void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, const void* dxr, float* U,
-                        void* rstates, hipStream_t st, const RaggedTails* tails = nullptr);
-void fast_bwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr,
-              const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs, float* dgr,
-              const FastBwdWs& ws, hipStream_t st, const RaggedTails* tails = nullptr);
+// q [B,Tb,Hq,D], dxr [B,T,Hq,D] (padded length, zero in rows >= Tb).
+void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, int Tb, const void* dxr, float* U,
+                        void* rstates, hipStream_t st);
+// dm.T: the padded length; the caller's tensors hold Tc rows per sequence.  dO rows from 128 * (Tc / 128) on are read from
+// dO_tail [B,128,Hq,D], zero past row Tc (may be NULL when Tc is a multiple of 128).  Gain rows lie gstride floats apart.
+void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const void* v, const float* gs, const float* gr,
+              int gstride, const SavedPtrs& sv, const void* dO, const void* dO_tail, void* dq, void* dk, void* dv, float* dgs,
+              float* dgr, const FastBwdWs& ws, hipStream_t st);
 
 // prefill -> decode hand-over: rings of the last min(T, W) tokens and the state of all keys before them
 struct ExportPlan {
@@ -154,30 +146,24 @@ struct ExportPlan {
   size_t partial_bytes;
 };
 ExportPlan export_plan(const LayerDims& dm);
-// Row s of k / v is token tok0 + s of its sequence (ring slots); with `accumulate` the keys that fall out of the
-// window are added to what `state` already holds.
-void prefill_export(const LayerDims& dm, int dtype, const void* k, const void* v, void* k_ring, void* v_ring,
-                    float* state, float* partial, hipStream_t st, int tok0 = 0, bool accumulate = false);
+// dm.T: the rows the plan counts (keys folded into the state + window).  Row s of the back part of `t` is token tok0 + s
+// of its sequence: the last min(Tb, W) of them go to their ring slots.  The keys folded into the state are the plan's Tp
+// rows from row t.kmin of the two-part sequence on; with `accumulate` they are added to what `state` already holds.
+// (A front part: bf16 only.)
+void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k_ring, void* v_ring, float* state,
+                    float* partial, hipStream_t st, int tok0 = 0, bool accumulate = false);
 
-// chunked prefill (see chunk_kernels.hip): dmc describes the concatenated sequence of R ring rows + Tc new rows
-void chunk_concat(const LayerDims& dmc, int dtype, int Tc, int R, int pos0, const void* q, const void* k, const void* v,
-                  const void* k_ring, const void* v_ring, void* qc, void* kc, void* vc, hipStream_t st);
-void chunk_copy_out(const LayerDims& dmc, int dtype, int Tc, int R, const void* oc, void* o, hipStream_t st);
-// Ls: rows per sequence of the saved tensors (> R + Tc when the forward ran on a zero-padded copy)
-void chunk_fixup(const LayerDims& dmc, int dtype, int Tc, int R, int Ls, const void* qc, const SavedPtrs& sv,
-                 const float* state, const float* gs, const float* gr, void* o, hipStream_t st);
+// chunked prefill (see chunk_kernels.hip): R ring rows and Tc new rows as one [B,R+Tc,Hkv,D] tensor each ...
+void chunk_concat(const LayerDims& dmc, int dtype, int Tc, int R, int pos0, const void* k, const void* v,
+                  const void* k_ring, const void* v_ring, void* kc, void* vc, hipStream_t st);
+// ... or (bf16) the ring rows alone as [B,P,Hkv,D], P = R rounded up to 128, zero rows in front
+void chunk_ring(const LayerDims& dmc, int P, int R, int pos0, const void* k_ring, const void* v_ring, void* k_front,
+                void* v_front, hipStream_t st);
 
-// [B,T,H,head] <-> [B,Tp,H,head_padded] with zeros at t >= T and past `head_bytes` of every head row (both sizes
-// multiples of 16 bytes)
-void pad_rows(const void* src, void* dst, int B, int T, int Tp, int H, size_t head_bytes, size_t head_bytes_padded,
-              hipStream_t st);
-void unpad_rows(const void* src, void* dst, int B, int T, int Tp, int H, size_t head_bytes, size_t head_bytes_padded,
-                hipStream_t st);
-
-// rows 128 * (T / 128) .. of up to four [B,T,H,128] bf16 tensors <-> their [B,128,H,128] tail buffers (RaggedTails):
-// gather fills the buffers (zero from row T on), scatter copies the rows below T back.  n tensors, H[i] heads each.
-void gather_tails(int n, const void* const* src, void* const* tail, const int* H, int B, int T, hipStream_t st);
-void scatter_tails(int n, const void* const* tail, void* const* dst, const int* H, int B, int T, hipStream_t st);
+// rows 128 * (T / 128) .. of a [B,T,H,D] bf16 tensor into its [B,128,H,D] tail buffer, zero from row T on
+void gather_tail(const void* src, void* tail, int B, int T, int H, int D, hipStream_t st);
+// gain rows [Hq,64] of the two branches side by side, [Hq,128]; a NULL gain is all ones
+void pack_gains64(const float* gs, const float* gr, float* out, int Hq, hipStream_t st);
 
 // launches the matrix-core probe loop; returns the FLOPs it issues
 double probe_mfma(float* sink, int iters, int blocks, hipStream_t st);

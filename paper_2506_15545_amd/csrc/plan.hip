@@ -5,10 +5,9 @@
 
 namespace rattn {
 
-// dm: the dimensions the kernels would see, i.e. after any zero-padding of the sequence length to whole tiles and of
-// a head size of 64 to 128 (dm.D = 128, dm.Dv = 64)
+// dm: the dimensions the kernels would see, i.e. with the sequence length rounded up to whole tiles
 bool fast_fwd_supported(const LayerDims& dm, int dtype) {
-  if (dtype != 1 || dm.D != 128 || dm.T % 128 != 0) return false;
+  if (dtype != 1 || dm.T % 128 != 0) return false;
   if (!(dm.scale > 0.f)) return false;
   // Windows below 8 keys stay on the general path: their softmax rows are close to one-hot, so the backward's
   // dS = P (dP - delta) is a near-cancellation (exact for W = 1) that bf16 operands turn into rounding noise
@@ -29,8 +28,8 @@ FastFwdPlan fast_fwd_plan(const LayerDims& dm) {
   // alignment the first product covers the 64 keys in front of state 0
   p.ckeys = dm.chunk_req == 64 ? 64 : 128;
   p.nchunks = p.nstf > 0 ? (p.nstf - 1) * (128 / p.ckeys) + (p.base > 0 ? 1 : 0) : 0;
-  p.u_bytes = (size_t)dm.B * dm.Hkv * p.nchunks * 16384 * 4;
-  p.state_bytes = (size_t)dm.B * dm.Hkv * p.nstf * 16384 * 2;
+  p.u_bytes = (size_t)dm.B * dm.Hkv * p.nchunks * dm.D * dm.D * 4;
+  p.state_bytes = (size_t)dm.B * dm.Hkv * p.nstf * dm.D * dm.D * 2;
   return p;
 }
 
@@ -42,9 +41,22 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   // reverse-time chunk products: query rows t' in [128, Tp) in pieces of ckeys
   p.nrchunks = Tp > 128 ? (Tp - 128 + p.fwd.ckeys - 1) / p.fwd.ckeys : 0;
   const int nch = p.fwd.nchunks > p.nrchunks ? p.fwd.nchunks : p.nrchunks;
-  p.u_bytes = (size_t)dm.B * dm.Hkv * (nch > 0 ? nch : 0) * 16384 * 4;
-  p.rstate_bytes = (size_t)dm.B * dm.Hkv * p.nk * 16384 * 2;
+  p.u_bytes = (size_t)dm.B * dm.Hkv * (nch > 0 ? nch : 0) * dm.D * dm.D * 4;
+  p.rstate_bytes = (size_t)dm.B * dm.Hkv * p.nk * dm.D * dm.D * 2;
   p.RB = 4 * (dm.T / 128) * dm.B;  // one gain-gradient partial per wave of the dq kernel
+  // The dk/dv kernel holds one work-group per CU (two at D = 64), which visits the G query heads of its key tile in turn.  With few key
+  // tiles the heads are split over several work-groups (partial sums in fp32, added in order): the split with the fewest
+  // head visits on the busiest CU, where a work-group costs about half a visit on top of its own.
+  const long long tiles = (long long)(dm.T / 128) * dm.Hkv * dm.B, slots = dm.D == 64 ? 512 : 256;
+  p.nsplit = 1;
+  double best = 0.0;
+  for (int s = 1; s <= dm.G; ++s) {
+    const int hps = (dm.G + s - 1) / s, used = (dm.G + hps - 1) / hps;
+    if (used != s) continue;   // the same heads per work-group with fewer of them
+    const double cost = (double)((tiles * s + slots - 1) / slots) * (hps + 0.5) + (s > 1 ? 0.5 : 0.0);
+    if (s == 1 || cost < best) { best = cost; p.nsplit = s; }
+  }
+  p.dkv_part_bytes = p.nsplit > 1 ? (size_t)2 * p.nsplit * dm.B * dm.T * dm.Hkv * dm.D * 4 : 0;
   return p;
 }
 
