@@ -5,6 +5,7 @@ raw device pointers, the current HIP stream).  Every arithmetic step of the laye
 the library's kernels; there is no fallback: a missing library raises.
 """
 import ctypes
+import functools
 import os
 import torch
 
@@ -107,11 +108,12 @@ def _check(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without building a torch.cuda.Stream object (2.7 us of a 13 us decode call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_params(q, k, window, chunk=0, softmax_scale=1.0, rms_eps=1e-6, save_for_bwd=False, feature_map="softmax",
@@ -129,20 +131,58 @@ def rattn_workspace_bytes(params):
     return f.value, b.value, s.value
 
 
+# A call's parameter block and buffer sizes depend on shapes and options only: the last few dozen combinations are kept
+# (the library takes the block as const).
+@functools.lru_cache(maxsize=64)
+def _layer_plan(q_shape, Hkv, dtype, window, chunk, softmax_scale, rms_eps, save_for_bwd, feature_map, kernel_path,
+                state_policy):
+    B, T, Hq, D = q_shape
+    p = RattnParams(B, T, Hq, Hkv, D, window, chunk, _DTYPES[dtype], softmax_scale, rms_eps, 1 if save_for_bwd else 0,
+                    FEATURE_MAPS[feature_map], KERNEL_PATHS[kernel_path], STATE_POLICIES[state_policy])
+    return (ctypes.byref(p),) + rattn_workspace_bytes(p)
+
+
+@functools.lru_cache(maxsize=64)
+def _chunk_plan(q_shape, Hkv, dtype, window, pos0, chunk, softmax_scale, rms_eps, feature_map):
+    B, T, Hq, D = q_shape
+    p = RattnParams(B, T, Hq, Hkv, D, window, chunk, _DTYPES[dtype], softmax_scale, rms_eps, 0, FEATURE_MAPS[feature_map], 0, 0)
+    nbytes = ctypes.c_size_t()
+    _check(lib().rattn_prefill_chunk_workspace_bytes(ctypes.byref(p), pos0, ctypes.byref(nbytes)))
+    return ctypes.byref(p), nbytes.value
+
+
+@functools.lru_cache(maxsize=64)
+def _export_plan(k_shape, dtype, window, feature_map):
+    B, T, Hkv, D = k_shape
+    p = RattnParams(B, T, Hkv, Hkv, D, window, 0, _DTYPES[dtype], 1.0, 1e-6, 0, FEATURE_MAPS[feature_map], 0, 0)
+    nbytes = ctypes.c_size_t()
+    _check(lib().rattn_prefill_export_workspace_bytes(ctypes.byref(p), ctypes.byref(nbytes)))
+    return ctypes.byref(p), nbytes.value
+
+
+@functools.lru_cache(maxsize=64)
+def _decode_plan(q_shape, Hkv, window, dtype, softmax_scale, rms_eps, feature_map):
+    N, Hq, D = q_shape
+    return ctypes.byref(RattnDecodeParams(N, Hq, Hkv, D, window, _DTYPES[dtype], softmax_scale, rms_eps, FEATURE_MAPS[feature_map]))
+
+
 def _check_layer(q, k, v):
     for name, t in (("q", q), ("k", k), ("v", v)):
         if not (t.is_cuda and t.is_contiguous() and t.dim() == 4):
             raise ValueError(f"{name} must be a contiguous 4-d device tensor [B,T,H,D]")
-    if k.shape != v.shape or k.shape[0] != q.shape[0] or k.shape[1] != q.shape[1] or k.shape[3] != q.shape[3]:
+    qs, ks = q.shape, k.shape
+    if ks != v.shape or ks[0] != qs[0] or ks[1] != qs[1] or ks[3] != qs[3]:
         raise ValueError("q/k/v shapes do not match")
-    if q.dtype not in _DTYPES or k.dtype != q.dtype or v.dtype != q.dtype:
+    dt = q.dtype
+    if dt not in _DTYPES or k.dtype != dt or v.dtype != dt:
         raise ValueError("q, k, v must share dtype float32 or bfloat16")
 
 
 def _gain(g, Hq, D, dev):
     if g is None:
         return None
-    g = g.to(device=dev, dtype=torch.float32).contiguous()
+    if g.dtype is not torch.float32 or g.device != dev or not g.is_contiguous():
+        g = g.to(device=dev, dtype=torch.float32).contiguous()
     if g.shape != (Hq, D):
         raise ValueError("gains must be [Hq, D]")
     return g
@@ -159,8 +199,8 @@ def rattn_fwd(q, k, v, window, gamma_swa=None, gamma_rla=None, chunk=0, softmax_
 
     out / saved / workspace may be passed in to reuse buffers (uint8 tensors for the latter two)."""
     _check_layer(q, k, v)
-    p = make_params(q, k, window, chunk, softmax_scale, rms_eps, save_for_bwd, feature_map, kernel_path, state_policy)
-    fwd_b, _, saved_b = rattn_workspace_bytes(p)
+    p, fwd_b, _, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, window, chunk, softmax_scale, rms_eps, bool(save_for_bwd),
+                                       feature_map, kernel_path, state_policy)
     dev = q.device
     o = torch.empty_like(q) if out is None else out
     ws = _bytes(fwd_b, dev) if workspace is None else workspace
@@ -169,7 +209,7 @@ def rattn_fwd(q, k, v, window, gamma_swa=None, gamma_rla=None, chunk=0, softmax_
         sv = _bytes(saved_b, dev) if saved is None else saved
     gs = _gain(gamma_swa, q.shape[2], q.shape[3], dev)
     gr = _gain(gamma_rla, q.shape[2], q.shape[3], dev)
-    _check(lib().rattn_fwd(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(gs), _ptr(gr), _ptr(o), _ptr(sv),
+    _check(lib().rattn_fwd(p, _ptr(q), _ptr(k), _ptr(v), _ptr(gs), _ptr(gr), _ptr(o), _ptr(sv),
                            _ptr(ws), ws.numel(), _stream()))
     return (o, sv) if save_for_bwd else o
 
@@ -202,8 +242,8 @@ def rattn_bwd(q, k, v, saved, dO, window, gamma_swa=None, gamma_rla=None, chunk=
     _check_layer(q, k, v)
     if dO.shape != q.shape or dO.dtype != q.dtype or not dO.is_contiguous():
         raise ValueError("dO must match q")
-    p = make_params(q, k, window, chunk, softmax_scale, rms_eps, True, feature_map, kernel_path, state_policy)
-    _, bwd_b, saved_b = rattn_workspace_bytes(p)
+    p, _, bwd_b, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, window, chunk, softmax_scale, rms_eps, True, feature_map,
+                                       kernel_path, state_policy)
     if saved is None or saved.numel() < saved_b:
         raise ValueError("saved buffer missing or too small")
     dev = q.device
@@ -218,7 +258,7 @@ def rattn_bwd(q, k, v, saved, dO, window, gamma_swa=None, gamma_rla=None, chunk=
         dgr = torch.empty_like(dgs)
     gs = _gain(gamma_swa, q.shape[2], q.shape[3], dev)
     gr = _gain(gamma_rla, q.shape[2], q.shape[3], dev)
-    _check(lib().rattn_bwd(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(gs), _ptr(gr), _ptr(saved), _ptr(dO),
+    _check(lib().rattn_bwd(p, _ptr(q), _ptr(k), _ptr(v), _ptr(gs), _ptr(gr), _ptr(saved), _ptr(dO),
                            _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dgs), _ptr(dgr), _ptr(ws), ws.numel(), _stream()))
     return dq, dk, dv, dgs, dgr
 
@@ -226,24 +266,26 @@ def rattn_bwd(q, k, v, saved, dO, window, gamma_swa=None, gamma_rla=None, chunk=
 def rattn_decode_step(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa=None, gamma_rla=None,
                       softmax_scale=1.0, rms_eps=1e-6, out=None, feature_map="softmax"):
     """One decode step; k_ring, v_ring, state are updated in place; returns o [N,Hq,D]."""
-    N, Hq, D = q.shape
-    Hkv, W = k_ring.shape[1], k_ring.shape[2]
+    qs, ks, rs = q.shape, k_new.shape, k_ring.shape
+    N, Hq, D = qs
+    Hkv, W = rs[1], rs[2]
     for name, t in (("q", q), ("k_new", k_new), ("v_new", v_new), ("k_ring", k_ring), ("v_ring", v_ring),
                     ("state", state), ("pos", pos)):
         if not (t.is_cuda and t.is_contiguous()):
             raise ValueError(f"{name} must be a contiguous device tensor")
-    if k_new.shape != (N, Hkv, D) or v_new.shape != (N, Hkv, D) or k_ring.shape != (N, Hkv, W, D) \
-            or v_ring.shape != k_ring.shape or state.shape != (N, Hkv, D, D) or pos.shape != (N,):
+    if ks != (N, Hkv, D) or v_new.shape != ks or rs != (N, Hkv, W, D) or v_ring.shape != rs \
+            or state.shape != (N, Hkv, D, D) or pos.shape != (N,):
         raise ValueError("decode tensor shapes do not match")
     if state.dtype != torch.float32 or pos.dtype != torch.int32:
         raise ValueError("state must be float32 and pos int32")
-    if q.dtype not in _DTYPES or any(t.dtype != q.dtype for t in (k_new, v_new, k_ring, v_ring)):
+    dt = q.dtype
+    if dt not in _DTYPES or k_new.dtype != dt or v_new.dtype != dt or k_ring.dtype != dt or v_ring.dtype != dt:
         raise ValueError("q, k_new, v_new and the rings must share dtype float32 or bfloat16")
-    p = RattnDecodeParams(N, Hq, Hkv, D, W, _DTYPES[q.dtype], softmax_scale, rms_eps, FEATURE_MAPS[feature_map])
+    p = _decode_plan(qs, Hkv, W, dt, softmax_scale, rms_eps, feature_map)
     o = torch.empty_like(q) if out is None else out
     gs = _gain(gamma_swa, Hq, D, q.device)
     gr = _gain(gamma_rla, Hq, D, q.device)
-    _check(lib().rattn_decode_step(ctypes.byref(p), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(pos), _ptr(k_ring),
+    _check(lib().rattn_decode_step(p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(pos), _ptr(k_ring),
                                    _ptr(v_ring), _ptr(state), _ptr(gs), _ptr(gr), _ptr(o), _stream()))
     return o
 
@@ -258,18 +300,16 @@ def rattn_prefill_export(k, v, window, k_ring=None, v_ring=None, state=None, fea
             raise ValueError(f"{name} must be a contiguous device tensor")
     if v.shape != k.shape or v.dtype != k.dtype or k.dtype not in _DTYPES:
         raise ValueError("k and v must share shape and dtype float32 or bfloat16")
-    p = RattnParams(B, T, Hkv, Hkv, D, window, 0, _DTYPES[k.dtype], 1.0, 1e-6, 0, FEATURE_MAPS[feature_map], 0, 0)
+    p, nbytes = _export_plan(k.shape, k.dtype, window, feature_map)
     if k_ring is None:
         k_ring = torch.zeros(B, Hkv, window, D, dtype=k.dtype, device=k.device)
     if v_ring is None:
         v_ring = torch.zeros(B, Hkv, window, D, dtype=k.dtype, device=k.device)
     if state is None:
         state = torch.empty(B, Hkv, D, D, dtype=torch.float32, device=k.device)
-    nbytes = ctypes.c_size_t()
-    _check(lib().rattn_prefill_export_workspace_bytes(ctypes.byref(p), ctypes.byref(nbytes)))
-    ws = torch.empty(max(nbytes.value, 16), dtype=torch.uint8, device=k.device)
-    _check(lib().rattn_prefill_export(ctypes.byref(p), _ptr(k), _ptr(v), _ptr(k_ring), _ptr(v_ring), _ptr(state),
-                                      _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()))
+    ws = _bytes(nbytes, k.device)
+    _check(lib().rattn_prefill_export(p, _ptr(k), _ptr(v), _ptr(k_ring), _ptr(v_ring), _ptr(state), _ptr(ws), ws.numel(),
+                                      _stream()))
     return k_ring, v_ring, state
 
 
@@ -289,19 +329,17 @@ def rattn_prefill_chunk(q, k, v, window, pos0, k_ring, v_ring, state, gamma_swa=
         raise ValueError("k_ring, v_ring must be [B,Hkv,window,D] in the dtype of q")
     if tuple(state.shape) != (B, Hkv, D, D) or state.dtype != torch.float32:
         raise ValueError("state must be fp32 [B,Hkv,D,D]")
-    p = make_params(q, k, window, chunk, softmax_scale, rms_eps, False, feature_map)
-    nbytes = ctypes.c_size_t()
-    _check(lib().rattn_prefill_chunk_workspace_bytes(ctypes.byref(p), int(pos0), ctypes.byref(nbytes)))
+    pos0 = int(pos0)
+    p, nbytes = _chunk_plan(q.shape, Hkv, q.dtype, window, pos0, chunk, softmax_scale, rms_eps, feature_map)
     if workspace is None:
-        workspace = torch.empty(max(nbytes.value, 16), dtype=torch.uint8, device=q.device)
+        workspace = _bytes(nbytes, q.device)
     elif not (workspace.is_cuda and workspace.is_contiguous() and workspace.dtype == torch.uint8):
         raise ValueError("workspace must be a contiguous uint8 device tensor")
     o = torch.empty_like(q) if out is None else out
     gs = _gain(gamma_swa, Hq, D, q.device)   # fp32 [Hq,D] on the device, kept alive until the call has been enqueued
     gr = _gain(gamma_rla, Hq, D, q.device)
-    _check(lib().rattn_prefill_chunk(ctypes.byref(p), int(pos0), _ptr(q), _ptr(k), _ptr(v), _ptr(gs),
-                                     _ptr(gr), _ptr(k_ring), _ptr(v_ring), _ptr(state), _ptr(o), _ptr(workspace),
-                                     ctypes.c_size_t(workspace.numel()), _stream()))
+    _check(lib().rattn_prefill_chunk(p, pos0, _ptr(q), _ptr(k), _ptr(v), _ptr(gs), _ptr(gr), _ptr(k_ring), _ptr(v_ring),
+                                     _ptr(state), _ptr(o), _ptr(workspace), workspace.numel(), _stream()))
     return o
 
 
