@@ -43,7 +43,8 @@ __device__ __forceinline__ float exp_neg(float x) {
 }
 
 // Partial states of key segments for bf16 on the bf16 matrix cores without losing the fp32 features: phi(k) is
-// split into three bf16 terms (8 + 8 + 8 bits), v is bf16 already, and the three products share one fp32 accumulator.
+// split into three bf16 terms (8 + 8 + 8 bits), v is bf16 already, and the three products share one fp32 accumulator.  The
+// other two maps return bf16 values, which one term holds (and an infinite key stays one: inf - inf would not).
 // One-dimensional grid: block i < nseg * B * Hkv is segment i % nseg of (b, kv head) i / nseg; the others copy the rings.  Key s is row
 // key0 + s of the two-part sequence (SeqRows).
 // Tiles of 64 keys: four threads map a key row (held in registers, requested one tile ahead) into the three LDS tiles of
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
                                                                    int key0, int Tp, int nseg, int seg_len, int nstate,
                                                                    RingCopy rc) {
   typedef TileGeom<D> TG;
-  constexpr int KT = TG::KT, NB = TG::NB / 4, NX = D / 4, NV = D == 128 ? 4 : 1;
+  constexpr int KT = TG::KT, NB = TG::NB / 4, NX = D / 4, NV = D == 128 ? 4 : 1, NPART = PHI == PHI_SOFTMAX ? 3 : 1;
   __shared__ __align__(16) unsigned char smem[5 * KT];  // phi hi, mid, lo; V x 2
   if ((int)blockIdx.x >= nstate) {
     copy_rings(rc, blockIdx.x - nstate, gridDim.x - nstate);
@@ -113,14 +114,14 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
 #pragma unroll
       for (int i = 0; i < NX; ++i) x[i] = fmaxf(x[i], 0.f);
     }
-    if (s0 + row >= hi) inv = 0.f;
+    const bool none = s0 + row >= hi;  // no key: zero features, whatever the row read in its place holds
 #pragma unroll
     for (int c = 0; c < NX / 8; ++c) {
       float r[8], t[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = x[8 * c + e] * inv;
+      for (int e = 0; e < 8; ++e) r[e] = none ? 0.f : x[8 * c + e] * inv;
 #pragma unroll
-      for (int part = 0; part < 3; ++part) {
+      for (int part = 0; part < NPART; ++part) {
         const bf16x8_t pk = pack_bf16x8(r);
         *reinterpret_cast<bf16x8_t*>(smem + part * KT + row * TG::ROWB + (((NX / 8 * quarter + c) ^ swz<D>(row)) << 4)) = pk;
         unpack_bf16x8(pk, t);
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
 #pragma unroll
       for (int d = 0; d < NV; ++d) vop[d] = lds_tr2(vt + voff[d][0] + k0, vt + voff[d][1] + k0);
 #pragma unroll
-      for (int part = 2; part >= 0; --part) {
+      for (int part = NPART - 1; part >= 0; --part) {
         const unsigned char* pt = smem + part * KT + k0;
         const bf16x8_t a = lds_tr2(pt + aoff[0], pt + aoff[1]);
 #pragma unroll

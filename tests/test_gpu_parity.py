@@ -164,6 +164,29 @@ def test_bwd_bf16_shapes(B, T, Hq, Hkv, D, W):
     run_bwd_case(B, T, Hq, Hkv, D, W, "bf16", seed=400 + T, kernel_path="general")
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W", [(1, 512, 80, 16, 128, 96),   # 64 key tiles, 5 heads: 2 + 2 + 1 per work-group
+                                              (1, 512, 160, 32, 64, 96)])  # 128 key tiles of two work-groups per CU
+def test_dkv_heads_split_unevenly(B, T, Hq, Hkv, D, W):
+    """Query heads of a group over several work-groups whose partial sums are added (the smaller parity cases give every
+    head a work-group of its own, the benchmark layers split nothing).  The same fp32 sums in another order, so the
+    shapes are compared with the general kernels at the bound of two bf16 paths against each other."""
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 470 + D, with_dO=True)
+    q, k, v, dO = (dev(x[n]) for n in ("q", "k", "v", "dO"))
+    g = {}
+    rb.rattn_profile_enable(True)
+    for path in ("auto", "general"):
+        _, saved = rb.rattn_fwd(q, k, v, W, softmax_scale=1.0 / math.sqrt(D), save_for_bwd=True, kernel_path=path)
+        g[path] = rb.rattn_bwd(q, k, v, saved, dO, W, softmax_scale=1.0 / math.sqrt(D), kernel_path=path)[:3]
+        torch.cuda.synchronize()
+    names = [n for n, _ in rb.rattn_profile_records()]
+    rb.rattn_profile_enable(False)
+    assert "dkv_reduce_kernel" in names
+    for name, a, b in zip(("dq", "dk", "dv"), g["auto"], g["general"]):
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        print(f"{name}: relative 2-norm of the difference {rel:.2e}", flush=True)
+        assert rel <= 1e-2, name   # bf16 operands: 2^-9 per factor and term
+
+
 # ------------------------------------------------------------------------------ decode
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,W,T", [("f32", 64, 4, 2, 8, 30), ("f32", 128, 3, 1, 5, 12),
                                                  ("bf16", 128, 8, 2, 16, 40), ("f32", 64, 6, 1, 50, 20)])
@@ -261,6 +284,43 @@ def test_prefill_export_matches_oracle(dtype, B, T, Hkv, D, W):
     assert torch.equal(S, S2)       # fixed summation order
 
 
+@pytest.mark.parametrize("fmap", ["softmax", "relu", "identity"])
+@pytest.mark.parametrize("B,T,Hkv,D,W", [(1, 33, 1, 128, 32), (2, 96, 1, 64, 32), (1, 97, 2, 128, 32), (1, 650, 64, 64, 9),
+                                         (2, 714, 64, 128, 73)])
+def test_prefill_export_segment_edges(B, T, Hkv, D, W, fmap):
+    """One key in the state, exactly one 64-key tile, one key more, several tiles per segment with a last segment of one
+    key (650 - 9 = 10 * 64 + 1), for every map.  Bound: as in the test above."""
+    x = synth.make_random_layer(B, T, Hkv, Hkv, D, "bf16", 830 + T)
+    kr_ref, vr_ref, S_ref = orc.prefill_export(np64(x["k"]), np64(x["v"]), W, feature_map=fmap)
+    kr, vr, S = rb.rattn_prefill_export(dev(x["k"]), dev(x["v"]), W, feature_map=fmap)
+    assert np.array_equal(np64(kr), kr_ref) and np.array_equal(np64(vr), vr_ref)
+    assert float(np.max(np.abs(np64(S) - S_ref))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
+
+
+@pytest.mark.parametrize("fmap", ["relu", "identity"])
+def test_prefill_export_infinite_key(fmap):
+    """An infinite key feature is an infinite row of the state (not a NaN), and an infinite last key is not read twice."""
+    x = synth.make_random_layer(1, 40, 1, 1, 128, "bf16", 845)
+    k, v = dev(x["k"]), dev(x["v"])
+    v.abs_().clamp_(min=0.5)
+    k[0, 31, 0, 5] = float("inf")
+    S = rb.rattn_prefill_export(k, v, 8, feature_map=fmap)[2]
+    assert bool((S[0, 0, 5] == float("inf")).all())
+    S[0, 0, 5] = 0
+    assert bool(S.isfinite().all())
+
+
+def test_numbers_given_as_tensors_are_read_at_each_call():
+    x = synth.make_random_layer(1, 40, 2, 1, 64, "f32", 846)
+    q, k, v = dev(x["q"]), dev(x["k"]), dev(x["v"])
+    scale = torch.tensor(0.125)
+    a = rb.rattn_fwd(q, k, v, 8, softmax_scale=scale)
+    scale.mul_(2)
+    b = rb.rattn_fwd(q, k, v, 8, softmax_scale=scale)
+    assert torch.equal(a, rb.rattn_fwd(q, k, v, 8, softmax_scale=0.125))
+    assert torch.equal(b, rb.rattn_fwd(q, k, v, 8, softmax_scale=np.array(0.25))) and not torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,T,W", [("f32", 40, 16), ("bf16", 256, 64), ("bf16", 300, 512)])
 def test_prefill_then_decode_reproduces_forward_row(dtype, T, W):
     """fwd over T+1 tokens, last row  ==  export(first T tokens) followed by one decode step at pos = T."""
@@ -320,6 +380,15 @@ def test_chunked_prefill_reproduces_forward(dtype, D, Hq, Hkv, W, chunks):
         pos0 += n
     assert np.array_equal(np64(kr), kr_ref) and np.array_equal(np64(vr), vr_ref)
     assert float(np.max(np.abs(np64(S) - S_ref))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,W,chunks", [
+    (64, 4, 2, 128, [128, 256, 128]), (64, 3, 1, 129, [200, 1, 131, 127]), (128, 4, 2, 127, [129, 128, 1, 77]),
+    (128, 2, 2, 200, [1, 127, 128, 129]), (64, 2, 1, 8, [300, 120, 121]), (128, 2, 1, 64, [191, 65, 64])])
+def test_chunked_prefill_positions_around_tiles(D, Hq, Hkv, W, chunks):
+    """Rings that end in front of, at and past a 128-row tile, rows in front of the ring, chunks that cross a tile, states
+    carried in at both alignments, on either side of the rule ring + chunk >= 128."""
+    test_chunked_prefill_reproduces_forward("bf16", D, Hq, Hkv, W, chunks)
 
 
 def test_chunked_prefill_uses_matrix_core_kernels():
