@@ -7,6 +7,8 @@ the library's kernels; there is no fallback: a missing library raises.
 import ctypes
 import functools
 import os
+from operator import index
+
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -132,7 +134,8 @@ def rattn_workspace_bytes(params):
 
 
 # A call's parameter block and buffer sizes depend on shapes and options only: the last few dozen combinations are kept
-# (the library takes the block as const).
+# (the library takes the block as const).  Callers hand the numbers over as plain Python ones: a tensor or an array that
+# stands for a number would be found by its identity.
 @functools.lru_cache(maxsize=64)
 def _layer_plan(q_shape, Hkv, dtype, window, chunk, softmax_scale, rms_eps, save_for_bwd, feature_map, kernel_path,
                 state_policy):
@@ -199,8 +202,8 @@ def rattn_fwd(q, k, v, window, gamma_swa=None, gamma_rla=None, chunk=0, softmax_
 
     out / saved / workspace may be passed in to reuse buffers (uint8 tensors for the latter two)."""
     _check_layer(q, k, v)
-    p, fwd_b, _, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, window, chunk, softmax_scale, rms_eps, bool(save_for_bwd),
-                                       feature_map, kernel_path, state_policy)
+    p, fwd_b, _, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, index(window), index(chunk), float(softmax_scale),
+                                       float(rms_eps), bool(save_for_bwd), feature_map, kernel_path, state_policy)
     dev = q.device
     o = torch.empty_like(q) if out is None else out
     ws = _bytes(fwd_b, dev) if workspace is None else workspace
@@ -242,8 +245,8 @@ def rattn_bwd(q, k, v, saved, dO, window, gamma_swa=None, gamma_rla=None, chunk=
     _check_layer(q, k, v)
     if dO.shape != q.shape or dO.dtype != q.dtype or not dO.is_contiguous():
         raise ValueError("dO must match q")
-    p, _, bwd_b, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, window, chunk, softmax_scale, rms_eps, True, feature_map,
-                                       kernel_path, state_policy)
+    p, _, bwd_b, saved_b = _layer_plan(q.shape, k.shape[2], q.dtype, index(window), index(chunk), float(softmax_scale),
+                                       float(rms_eps), True, feature_map, kernel_path, state_policy)
     if saved is None or saved.numel() < saved_b:
         raise ValueError("saved buffer missing or too small")
     dev = q.device
@@ -281,7 +284,7 @@ def rattn_decode_step(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa=Non
     dt = q.dtype
     if dt not in _DTYPES or k_new.dtype != dt or v_new.dtype != dt or k_ring.dtype != dt or v_ring.dtype != dt:
         raise ValueError("q, k_new, v_new and the rings must share dtype float32 or bfloat16")
-    p = _decode_plan(qs, Hkv, W, dt, softmax_scale, rms_eps, feature_map)
+    p = _decode_plan(qs, Hkv, W, dt, float(softmax_scale), float(rms_eps), feature_map)
     o = torch.empty_like(q) if out is None else out
     gs = _gain(gamma_swa, Hq, D, q.device)
     gr = _gain(gamma_rla, Hq, D, q.device)
@@ -300,7 +303,7 @@ def rattn_prefill_export(k, v, window, k_ring=None, v_ring=None, state=None, fea
             raise ValueError(f"{name} must be a contiguous device tensor")
     if v.shape != k.shape or v.dtype != k.dtype or k.dtype not in _DTYPES:
         raise ValueError("k and v must share shape and dtype float32 or bfloat16")
-    p, nbytes = _export_plan(k.shape, k.dtype, window, feature_map)
+    p, nbytes = _export_plan(k.shape, k.dtype, index(window), feature_map)
     if k_ring is None:
         k_ring = torch.zeros(B, Hkv, window, D, dtype=k.dtype, device=k.device)
     if v_ring is None:
@@ -330,7 +333,8 @@ def rattn_prefill_chunk(q, k, v, window, pos0, k_ring, v_ring, state, gamma_swa=
     if tuple(state.shape) != (B, Hkv, D, D) or state.dtype != torch.float32:
         raise ValueError("state must be fp32 [B,Hkv,D,D]")
     pos0 = int(pos0)
-    p, nbytes = _chunk_plan(q.shape, Hkv, q.dtype, window, pos0, chunk, softmax_scale, rms_eps, feature_map)
+    p, nbytes = _chunk_plan(q.shape, Hkv, q.dtype, index(window), pos0, index(chunk), float(softmax_scale),
+                            float(rms_eps), feature_map)
     if workspace is None:
         workspace = _bytes(nbytes, q.device)
     elif not (workspace.is_cuda and workspace.is_contiguous() and workspace.dtype == torch.uint8):
