@@ -303,7 +303,9 @@ __device__ __forceinline__ void rms_bwd_rows(const FastBwdArgs& a, int hq, size_
 
 // GAINS: RMS gains other than one and/or gain gradients (see rms_bwd_rows); FM: feature map (FM_* in mfma.hpp)
 // grid (ntile * Hq * B), 256 threads: 128 queries of one head, wave w owns 32.
-template <int D, bool GAINS, int FM>
+// RAGGED: Tc is no multiple of 128, so the last tile has rows that do not exist (a whole-tile call compiles without the
+// clamps and the second form of the tile loads: with them the kernel spills scalar registers, 0.264 against 0.256 ms).
+template <int D, bool GAINS, int FM, bool RAGGED>
 __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdArgs a) {
   typedef TileGeom<D> TG;
   constexpr int KT = TG::KT, ND = D / 32, NB = TG::NB / 4;  // blocks of a 64-row tile per wave
@@ -325,15 +327,17 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
   const size_t qstride = (size_t)Hq * D, kstride = (size_t)Hkv * D;
   const size_t qtile_off = ((size_t)(b * T + t0) * Hq + hq) * D;   // in the saved / workspace tensors (padded length)
   // the caller's tensors: this query tile of q, dO, dq; 64-key tiles of k, v
-  const TileRows q_tile = split_rows(a.q, b, t0, Hq, hq, D);
-  const int qlive = min(q_tile.n, 128);  // rows of the tile that exist
-  const uint16_t* dO_tile = t0 < a.Tfull ? a.dO + ((size_t)((size_t)b * a.Tc + t0) * Hq + hq) * D
+  // (in one part each: the backward has no rows in front)
+  const TileRows q_tile = {a.q.back + ((size_t)((size_t)b * a.Tc + t0) * Hq + hq) * D, RAGGED ? a.Tc - t0 : 128};
+  const int qlive = RAGGED ? min(q_tile.n, 128) : 128;  // rows of the tile that exist
+  const uint16_t* dO_tile = !RAGGED || t0 < a.Tfull ? a.dO + ((size_t)((size_t)b * a.Tc + t0) * Hq + hq) * D
                                          : a.dO_tail + ((size_t)b * 128 * Hq + hq) * D;
   uint16_t* dq_tile = a.dq + (q_tile.p - a.q.back);
-  auto k_rows = [&](int row) { return split_rows(a.k, b, row, Hkv, g, D); };
-  auto v_rows = [&](int row) { return split_rows(a.v, b, row, Hkv, g, D); };
+  const ptrdiff_t kv_off = ((ptrdiff_t)((size_t)b * a.Tc) * Hkv + g) * D;
+  auto k_rows = [&](int row) { return TileRows{a.k.back + kv_off + row * (ptrdiff_t)kstride, a.Tc - row}; };
+  auto v_rows = [&](int row) { return TileRows{a.v.back + kv_off + row * (ptrdiff_t)kstride, a.Tc - row}; };
   auto load_tile = [&](const TileRows& src, unsigned char* tile) {
-    tile_load_async<D, NB>(src.p, kstride, tile, w * NB, lane, src.n);
+    tile_load_async<D, NB>(src.p, kstride, tile, w * NB, lane, RAGGED ? src.n : ALL_ROWS);
   };
   const int myq = t0 + 32 * w + r32;
   const size_t stat_off = (size_t)(b * Hq + hq) * T + myq;
@@ -460,8 +464,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
     const int kt0 = kt_lo + 64 * (ntiles - 1);
     load_tile(k_rows(kt0), smem);
     load_tile(v_rows(kt0), smem + 2 * KT);
-    tile_load_async<D, NB>(q_tile.p, qstride, smem + KT, w * NB, lane, q_tile.n);
-    tile_load_async<D, NB>(q_tile.p + (size_t)64 * qstride, qstride, smem + 3 * KT, w * NB, lane, q_tile.n - 64);
+    tile_load_async<D, NB>(q_tile.p, qstride, smem + KT, w * NB, lane, RAGGED ? q_tile.n : ALL_ROWS);
+    tile_load_async<D, NB>(q_tile.p + (size_t)64 * qstride, qstride, smem + 3 * KT, w * NB, lane, RAGGED ? q_tile.n - 64 : ALL_ROWS);
     wait_vmem();
     __syncthreads();
   }
@@ -488,7 +492,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
   const DmaLane<D> dma_lane = make_dma_lane<D>(lane, kstride);
   // all key tiles of the sweep but the one in hand (the diagonal one, loaded above) lie below t0 + 64: every row of theirs
   // exists unless the query tile itself starts past the last whole 64-row tile
-  const bool whole = t0 + 64 <= a.Tc;
+  const bool whole = !RAGGED || t0 + 64 <= a.Tc;
   const size_t sweep_off = ((size_t)((size_t)b * a.Tc + kt_lo) * Hkv + g) * D;
   const uint16_t *k_sweep = a.k.back + sweep_off, *v_sweep = a.v.back + sweep_off;
   const int Wm = W - gap;  // the true window: element masks and sub-tile skipping
@@ -1255,10 +1259,13 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
   {
     ProfScope ps("bwd_dq_kernel", st);
     const dim3 grid(a.ntile * dm.Hq * dm.B);
-#define RATTN_DQ_LAUNCH(D_, FM_)                                                   \
-  do {                                                                             \
-    if (gains) bwd_dq_kernel<D_, true, FM_><<<grid, 256, 0, st>>>(a);              \
-    else bwd_dq_kernel<D_, false, FM_><<<grid, 256, 0, st>>>(a);                   \
+    const bool ragged = Tc != dm.T;
+#define RATTN_DQ_LAUNCH(D_, FM_)                                                         \
+  do {                                                                                   \
+    if (gains && ragged) bwd_dq_kernel<D_, true, FM_, true><<<grid, 256, 0, st>>>(a);    \
+    else if (gains) bwd_dq_kernel<D_, true, FM_, false><<<grid, 256, 0, st>>>(a);        \
+    else if (ragged) bwd_dq_kernel<D_, false, FM_, true><<<grid, 256, 0, st>>>(a);       \
+    else bwd_dq_kernel<D_, false, FM_, false><<<grid, 256, 0, st>>>(a);                  \
   } while (0)
     if (dm.D == 64) {
       if (relu) RATTN_DQ_LAUNCH(64, FM_RELU); else RATTN_DQ_LAUNCH(64, FM_SOFTMAX);

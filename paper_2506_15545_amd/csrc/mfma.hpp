@@ -70,16 +70,17 @@ __device__ __forceinline__ void dma16s(const void* sbase, unsigned voff, unsigne
 // blk0 + i, lane l lands at tile + blk*1024 + l*16, i.e. row RPB*blk + l/CH, physical chunk l%CH; it fetches the logical
 // chunk that the swizzle maps there.  Rows from `nrows` on are read as row nrows - 1 (nrows may be <= 0: a row of the
 // same sequence further up).
+constexpr int ALL_ROWS = 1 << 30;
 template <int D, int NBLK>
 __device__ __forceinline__ void tile_load_async(const uint16_t* gbase, size_t row_stride, unsigned char* tile,
-                                                int blk0, int lane, int nrows = 1 << 30) {
+                                                int blk0, int lane, int nrows = ALL_ROWS) {
   typedef TileGeom<D> G;
 #pragma unroll
   for (int i = 0; i < NBLK; ++i) {
     const int blk = blk0 + i;
     const int r = blk * G::RPB + lane / G::CH;
     const int c = (lane % G::CH) ^ swz<D>(r);
-    const uint16_t* g = gbase + (ptrdiff_t)min(r, nrows - 1) * (ptrdiff_t)row_stride + c * 8;
+    const uint16_t* g = gbase + (ptrdiff_t)(nrows == ALL_ROWS ? r : min(r, nrows - 1)) * (ptrdiff_t)row_stride + c * 8;
     dma16(g, (unsigned)(size_t)RATTN_LDS(tile + blk * 1024));
   }
 }
