@@ -504,8 +504,7 @@ def main():
         other["layer3b_t4096_w512_relu"] = run_layer(cfg, True, feature_map="relu")
         # (identity map: forward only - calls that keep `saved` for a backward pass run on the general kernels)
         other["layer3b_t4096_w512_identity_fwd_only"] = run_layer(cfg, False, feature_map="identity")
-        # shapes that reach the matrix-core kernels through zero-padded copies: a ragged length (4000 -> 4096 rows)
-        # and head size 64 (rows widened to 128 features; FLOPs counted at head size 64)
+        # a ragged length (the last 128-row tile is partial) and head size 64
         other["layer3b_t4000_w512_ragged"] = run_layer(dataclasses.replace(cfg, name="layer3b_t4000_w512", T=4000), True)
         other["layer3b_t4096_w512_d64"] = run_layer(dataclasses.replace(cfg, name="layer3b_t4096_w512_d64", D=64,
                                                                         scale=0.125), True)

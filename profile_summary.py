@@ -46,7 +46,6 @@ def kernel_sources_digest():
     return h.hexdigest()[:16]
 
 
-ALIASES = {"decode_kernel_2pass": "decode_kernel"}   # the name bench.py reports the decode launch under
 WORKLOAD_KERNELS = {"decode_b128_w512": ("decode_kernel",)}
 
 
@@ -56,7 +55,7 @@ def short_name(full):
     name = m.group(1) if m else full[:48]
     if "elementwise" in full:      # torch kernels: only the out-of-place add is the calibration pass
         name = "calibration_elementwise" if "add" in full else "torch_elementwise_other"
-    return ALIASES.get(name, name)
+    return name
 
 
 def find(d, suffix):
