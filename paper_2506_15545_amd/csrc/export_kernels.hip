@@ -35,11 +35,13 @@ __device__ __forceinline__ void copy_rings(const RingCopy& a, int block, int nbl
 __global__ __launch_bounds__(256) void export_ring_kernel(RingCopy a) { copy_rings(a, blockIdx.x, gridDim.x); }
 
 // exp(x) for x <= 0, to about one ulp: the rounding of x * log2(e) is carried as a second term (a relative error of
-// |x| 2^-24 otherwise)
+// |x| 2^-24 otherwise).  Below -104 the result is zero in fp32 anyway, and is set: the second term of an x whose product
+// overflows (-inf, features at the type's lowest value) is no number.  (NaN stays NaN.)
 __device__ __forceinline__ float exp_neg(float x) {
   const float hi = x * LOG2E;
   const float lo = __builtin_fmaf(x, LOG2E, -hi) + x * 1.925963033500e-8f;   // log2(e) - (float)log2(e)
-  return fast_exp2(hi) * __builtin_fmaf(lo, LN2, 1.f);
+  const float y = fast_exp2(hi) * __builtin_fmaf(lo, LN2, 1.f);
+  return x < -104.f ? 0.f : y;
 }
 
 // Partial states of key segments for bf16 on the bf16 matrix cores without losing the fp32 features: phi(k) is

@@ -310,6 +310,26 @@ def test_prefill_export_infinite_key(fmap):
     assert bool(S.isfinite().all())
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("low", [-math.inf, torch.finfo(torch.bfloat16).min, -2.4e38, -200.0, -90.0])
+def test_prefill_export_key_features_far_below_the_row_maximum(low, D):
+    """Softmax map: a feature of -inf, at the type's lowest value or merely far below the row's maximum has weight zero (or
+    next to it); the state and the decode step on top of it are the oracle's.  Also as the state update of a chunk."""
+    T, W = 70, 8
+    x = synth.make_random_layer(1, T, 1, 1, D, "bf16", 847)
+    k, v = x["k"], x["v"]
+    k[0, 3, 0, 5] = k[0, 61, 0, D - 1] = low
+    k[0, 30, 0, 1:] = low                       # all but one feature
+    S_ref = orc.prefill_export(np64(k), np64(v), W)[2]
+    kr, vr, S = rb.rattn_prefill_export(dev(k), dev(v), W)
+    bound = 2e-5 * max(1.0, float(np.abs(S_ref).max()))   # as in test_prefill_export_matches_oracle
+    assert float(np.max(np.abs(np64(S) - S_ref))) <= bound
+    kr, vr = torch.zeros_like(kr), torch.zeros_like(vr)
+    S.fill_(float("nan"))
+    rb.rattn_prefill_chunk(dev(x["q"]), dev(k), dev(v), W, 0, kr, vr, S, softmax_scale=0.1)
+    assert float(np.max(np.abs(np64(S) - S_ref))) <= bound
+
+
 def test_numbers_given_as_tensors_are_read_at_each_call():
     x = synth.make_random_layer(1, 40, 2, 1, 64, "f32", 846)
     q, k, v = dev(x["q"]), dev(x["k"]), dev(x["v"])
