@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
   }
   // ---- softmax branch: queries s .. s + W - 1
   {
-    const int hi = min(s_hi + W - 1, T - 1), nt = (hi - s0) / 16 + 1;
+    const int hi = s_hi < T - W ? s_hi + W - 1 : T - 1, nt = (hi - s0) / 16 + 1;  // (any W up to INT_MAX: no sum beyond T)
     for (int u = w; u < G * nt; u += GW) {
       const int h = g * G + u / nt, q0 = s0 + 16 * (u % nt);
       auto off = [&](int t) { return ((size_t)(b * T + min(t, hi)) * Hq + h) * D; };

@@ -187,6 +187,20 @@ def test_dkv_heads_split_unevenly(B, T, Hq, Hkv, D, W):
         assert rel <= 1e-2, name   # bf16 operands: 2^-9 per factor and term
 
 
+@pytest.mark.parametrize("dtype,T,D", [("f32", 70, 64), ("f32", 200, 128), ("bf16", 100, 64), ("bf16", 300, 128)])
+def test_window_near_the_integer_limit(dtype, T, D):
+    """`no window' as the largest integer: every result as with a window of T."""
+    x = synth.make_random_layer(1, T, 4, 2, D, dtype, 53, with_dO=True)
+    q, k, v, dO = (dev(x[n]) for n in ("q", "k", "v", "dO"))
+    res = []
+    for W in (T, 2 ** 31 - 1, 2 ** 31 - 8):
+        o, saved = rb.rattn_fwd(q, k, v, W, softmax_scale=0.125, save_for_bwd=True)
+        res.append((o,) + tuple(rb.rattn_bwd(q, k, v, saved, dO, W, softmax_scale=0.125)))
+    for r in res[1:]:
+        for a, b in zip(r, res[0]):
+            assert torch.equal(a, b)
+
+
 # ------------------------------------------------------------------------------ decode
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,W,T", [("f32", 64, 4, 2, 8, 30), ("f32", 128, 3, 1, 5, 12),
                                                  ("bf16", 128, 8, 2, 16, 40), ("f32", 64, 6, 1, 50, 20)])
