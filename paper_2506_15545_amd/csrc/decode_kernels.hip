@@ -73,10 +73,23 @@ template <int D> struct RingSet<bf16_t, D> {
     }
   }
   static __device__ __forceinline__ float pexp(float x, float m) { return fast_exp2(x - m); }
-  // acc[e] += V^T P^T for feature EV*r16 + e of each lane's piece; two rows are interleaved per dword with v_perm_b32
+  // acc[e] += V^T P^T for feature EV*r16 + e of each lane's piece; two rows are interleaved per dword with v_perm_b32.  The
+  // fp32 probabilities pass through the bf16 tiles as three terms of 8 bits whose products share one accumulator, which is
+  // as good as fp32 products with the bf16 values (one term: 1.12 - 1.16 times the error of the output against fp64,
+  // which is mostly the output's own rounding).  The extra products hide behind the rings: 24 x 8 KV heads, W = 2048, 39.9 us
+  // either way; one sequence, where they are part of the chain, 11.2 us against 10.8.
   __device__ __forceinline__ void accumulate(const f32x4_t (&p)[2], f32x4_t (&acc)[EV]) const {
-    const float pf[8] = {p[0][0], p[0][1], p[0][2], p[0][3], p[1][0], p[1][1], p[1][2], p[1][3]};
-    const bf16x8_t pop = pack_bf16x8(pf);
+    constexpr int TERMS = 3;
+    float r[8] = {p[0][0], p[0][1], p[0][2], p[0][3], p[1][0], p[1][1], p[1][2], p[1][3]};
+    bf16x8_t pop[TERMS];
+#pragma unroll
+    for (int term = 0; term < TERMS; ++term) {
+      float t[8];
+      pop[term] = pack_bf16x8(r);
+      unpack_bf16x8(pop[term], t);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] -= t[i];  // exact
+    }
 #pragma unroll
     for (int e = 0; e < EV; ++e) {
       const int j = e >> 1;
@@ -84,7 +97,9 @@ template <int D> struct RingSet<bf16_t, D> {
       u32x4_t a;
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[i] = __builtin_amdgcn_perm(v[2 * i + 1][j], v[2 * i][j], sel);
-      acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), pop, acc[e], 0, 0, 0);
+#pragma unroll
+      for (int term = TERMS - 1; term >= 0; --term)
+        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), pop[term], acc[e], 0, 0, 0);
     }
   }
   // feature held by element (e, i) of a lane's accumulators
@@ -143,14 +158,14 @@ constexpr size_t decode_lds_bytes(int D, int esize, int hb, int nw) {
 constexpr int decode_occ(bool multi) { return multi ? 2 : 4; }
 
 // grid (Hkv, N), NW waves: one (sequence, kv head).  Every wave runs its own online softmax over its share of the ring
-// (K and V of a set are requested together, the next set's K behind the first product and its V behind the second), so
+// (K and V of a set are requested together; in fp32 the next set's K already behind the first product), so
 // W is not limited by LDS, and takes its share of the state rows; the waves' partial results meet in LDS once.  The
 // new token is not read back from the ring: its slot is masked there and it enters the merge as a partial of its own.
 // Bound: HBM.  NW is chosen so that the chip is full of waves (pick_decode).  Measured, rings and states cold in the
 // caches: 128 sequences x 8 KV heads, 4 query heads each, W = 512: 82 us = 4.9 TB/s, where a plain kernel that streams
 // the rings and reads-modifies-writes the states in the same places takes 78 us; 24 x 8, 5 heads, W = 2048, half of the
 // rings partly filled: 39 us (271 us with the scores of all W keys in LDS and vector arithmetic for more than four heads);
-// one sequence, 4 KV heads, W = 512: 11 us (18 us with four waves per KV head).
+// one sequence, 4 KV heads, W = 512: 11.2 us (18 us with four waves per KV head).
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
 template <typename IO, int D, int NW, bool MULTI>
 __global__ __launch_bounds__(NW * 64, decode_occ(MULTI)) void decode_kernel(
@@ -255,13 +270,15 @@ __global__ __launch_bounds__(NW * 64, decode_occ(MULTI)) void decode_kernel(
       for (int e = 0; e < EV; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       float m = -1.0e30f, l = 0.f;
       const int qoff = min(r16, nh - 1) * QS;  // columns >= nh are never read back
-      for (int it = w; it < nset; it += NW) {
+      for (int it = w; it < nset;) {
         const int base = set_base(it);
-        const bool more = it + NW < nset;
-        const int next = more ? set_base(it + NW) : 0;
+        it += NW;
+        const int next = it < nset ? set_base(it) : 0;
         f32x4_t s[NT];
         set.scores(qs + opaque(qoff), q4, s);
-        if (more) set.load_k(rows(kr, next), r16, q4);
+        // fp32: the next set's K arrives behind the softmax and the second product; bf16: its registers hold the operands of
+        // the second product there
+        if (sizeof(IO) == 4 && it < nset) set.load_k(rows(kr, next), r16, q4);
 #pragma unroll
         for (int c = 0; c < NT; ++c) s[c] *= sc;
         if (base + Set::KEYS > nvalid || (unsigned)(slot - base) < (unsigned)Set::KEYS) {  // wave-uniform
@@ -288,7 +305,9 @@ __global__ __launch_bounds__(NW * 64, decode_occ(MULTI)) void decode_kernel(
 #pragma unroll
         for (int e = 0; e < EV; ++e) acc[e] *= alpha;
         set.accumulate(s, acc);
-        if (more) set.load_v(rows(vr, next), r16, q4);
+        if (it >= nset) break;  // (not a condition on the loads: the old rows would stay alive across the products)
+        if (sizeof(IO) == 2) set.load_k(rows(kr, next), r16, q4);
+        set.load_v(rows(vr, next), r16, q4);
       }
       l = rows_sum(l);
       if (r16 < nh) {
