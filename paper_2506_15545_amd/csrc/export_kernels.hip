@@ -151,6 +151,34 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
     }
     __syncthreads();
   }
+  // A sum that is no number may come from a zero feature of the padding, or from terms of phi of different signs, times an
+  // infinite or NaN value: such a tile is formed again, key by key in fp32, which has neither.
+  float z = 0.f;
+#pragma unroll
+  for (int d = 0; d < NV; ++d)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[d][i], 0.f, z);
+  if (__any(z != 0.f)) {  // wave-uniform
+#pragma unroll
+    for (int d = 0; d < NV; ++d) acc[d] = f32x16_t{0};
+    for (int s = lo; s < hi; ++s) {
+      const uint16_t* kp = split_rows(k, b, key0 + s, Hkv, g, D).p;
+      const uint16_t* vp = split_rows(v, b, key0 + s, Hkv, g, D).p;
+      float x[D / 64], f[D / 64], val[NV];
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) x[e] = __uint_as_float((uint32_t)kp[lane + 64 * e] << 16);
+      feature_row<D / 64>(x, f, PHI);
+#pragma unroll
+      for (int d = 0; d < NV; ++d) val[d] = __uint_as_float((uint32_t)vp[32 * (dt0 + d) + r32] << 16);
+      const float mine = ft < 2 ? f[0] : f[D / 64 - 1];  // this wave's 32 features
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float fi = __shfl(mine, (32 * ft + 8 * (i >> 2) + 4 * h + (i & 3)) & 63);
+#pragma unroll
+        for (int d = 0; d < NV; ++d) acc[d][i] = __builtin_fmaf(fi, val[d], acc[d][i]);
+      }
+    }
+  }
   float* out = partial + ((size_t)bg * nseg + seg) * (D * D);
 #pragma unroll
   for (int d = 0; d < NV; ++d)

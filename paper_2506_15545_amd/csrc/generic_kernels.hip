@@ -134,6 +134,40 @@ template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[4 * hf + e] = mm4(a.x[i][hf][e], p[i], acc[4 * hf + e]);
 }
+// Ahead of a col_product whose tile has columns that do not see every row: `see[i]` says whether column r16 sees row
+// 4*q4 + i, and p[i] = 0 where it does not.  0 times an infinite or NaN feature is not 0, so such features are taken out of
+// the product and added here to the columns that see their row: a column keeps its bits whatever the rows hold that it
+// does not see.
+template <int D>
+__device__ __forceinline__ void hide_unseen(ColForm<D>& a, f32x4_t p, const bool (&see)[4], int r16, int q4, f32x4_t (&acc)[D / 16]) {
+  f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = fmaf(a.x[i][hf][e], 0.f, z[e]);
+  if (!__any((z[0] + z[1]) + (z[2] + z[3]) != 0.f)) return;  // wave-uniform
+#pragma unroll
+  for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+#pragma unroll 1
+        for (int r4 = 0; r4 < 4; ++r4) {  // row 4*r4 + k
+          const float pk = __shfl(p[k], 16 * r4 + r16);
+          const bool seen = __shfl((int)see[k], 16 * r4 + r16) != 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float x = __shfl(a.x[k][hf][e], 16 * r4 + 4 * q4 + i);
+            if (seen && x * 0.f != 0.f) acc[4 * hf + e][i] += pk * x;
+          }
+        }
+        a.x[k][hf][e] = a.x[k][hf][e] * 0.f == 0.f ? a.x[k][hf][e] : 0.f;
+      }
+    }
+}
 // acc[d] += sum over the features f of slice j of  M[f][d] b[f],  M row-major [D][D] fp32
 template <int D> __device__ __forceinline__ void state_product(const float* M, int j, f32x4_t b, int r16, int q4, f32x4_t (&acc)[D / 16]) {
   ColForm<D> a;
@@ -238,14 +272,21 @@ __global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict_
   auto row = [&](int u, int k) {  // token k of step u (heads outermost)
     return ((size_t)(b * T + min(lo + 64 * (u % nt) + k, hi - 1) + off) * H + g * GA + u / nt) * D;
   };
+  // b of token k of step u; tokens past the end are zero, not what the row read in their place holds
+  auto load_b = [&](int u, int k, f32x4_t (&x)[NH]) {
+    const bool live = lo + 64 * (u % nt) + k < hi;
+#pragma unroll
+    for (int hd = 0; hd < NH; ++hd) {
+      x[hd] = load4(bsrc + row(u, k) + 64 * hd + 4 * r16);
+      if (!live) x[hd] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  };
   ColForm<D> fa;
   fa.load([&](int i) { return a + row(0, 16 * w + 4 * q4 + i); }, r16);
   for (int u = 0; u < nstep; ++u) {
     f32x4_t fb[8][NH];  // the first 32 tokens' b rows, requested ahead of the map
 #pragma unroll
-    for (int tg = 0; tg < 8; ++tg)
-#pragma unroll
-      for (int hd = 0; hd < NH; ++hd) fb[tg][hd] = load4(bsrc + row(u, 4 * tg + q4) + 64 * hd + 4 * r16);
+    for (int tg = 0; tg < 8; ++tg) load_b(u, 4 * tg + q4, fb[tg]);
     fa.feature(phi);
     if (u) __syncthreads();
 #pragma unroll
@@ -261,9 +302,7 @@ __global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict_
     for (int half = 0; half < 2; ++half) {
       if (half) {
 #pragma unroll
-        for (int tg = 0; tg < 8; ++tg)
-#pragma unroll
-          for (int hd = 0; hd < NH; ++hd) fb[tg][hd] = load4(bsrc + row(u, 32 + 4 * tg + q4) + 64 * hd + 4 * r16);
+        for (int tg = 0; tg < 8; ++tg) load_b(u, 32 + 4 * tg + q4, fb[tg]);
       }
 #pragma unroll
       for (int tg = 0; tg < 8; ++tg)
@@ -352,10 +391,11 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
       f32x4_t s = row_product<D>(kf, qv);
       if (n + GW < nt) kf.load(krow(next + r16), q4);
       float mx = -INFINITY;
+      bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const unsigned dist = (unsigned)(t - (s0 + 4 * q4 + i));  // in the window <=> 0 <= query - key < W
-        s[i] = dist < (unsigned)W ? s[i] * dm.scale : -INFINITY;
+        see[i] = (unsigned)(t - (s0 + 4 * q4 + i)) < (unsigned)W;  // in the window <=> 0 <= query - key < W
+        s[i] = see[i] ? s[i] * dm.scale : -INFINITY;
         mx = fmaxf(mx, s[i]);
       }
       const float m_new = fmaxf(m, rows_max(mx)), alpha = expf(m - m_new);
@@ -365,6 +405,7 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
       for (int i = 0; i < 4; ++i) { s[i] = expf(s[i] - m); l += s[i]; }
 #pragma unroll
       for (int e = 0; e < D / 16; ++e) acc[e] *= alpha;
+      if (s0 + 15 > t0 || t_hi - s0 >= W) hide_unseen<D>(vf, s, see, r16, q4, acc);
       col_product<D>(vf, s, acc);
       if (n + GW < nt) vf.load([&](int i) { return vrow(next + 4 * q4 + i); }, r16);
     }
@@ -392,8 +433,10 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
       vf.load([&](int i) { return vrow(s0 + 4 * q4 + i); }, r16);
       kf.feature(dm.phi);
       f32x4_t c = row_product<D>(kf, qv);
+      bool see[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) c[i] = s0 + 4 * q4 + i <= t - W ? c[i] : 0.f;
+      for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
+      if (s0 + 15 > t0 - W) hide_unseen<D>(vf, c, see, r16, q4, acc);
       col_product<D>(vf, c, acc);
     }
   }
@@ -539,8 +582,10 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
       kf.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
       kf.feature(dm.phi);
       f32x4_t c = row_product<D>(vf, dxr);
+      bool see[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) c[i] = s0 + 4 * q4 + i <= t - W ? c[i] : 0.f;
+      for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
+      if (s0 + 15 > t0 - W) hide_unseen<D>(kf, c, see, r16, q4, acc);
       col_product<D>(kf, c, acc);
     }
     feature_backward<D>(q + qoff, acc, q4, dm.phi);
@@ -560,12 +605,13 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
       kc.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
       const f32x4_t s = row_product<D>(kf, qv), dp = row_product<D>(vf, dxs);
       f32x4_t da;
+      bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const unsigned dist = (unsigned)(t - (s0 + 4 * q4 + i));
-        const float p = dist < (unsigned)W ? expf(s[i] * dm.scale - lse) : 0.f;
-        da[i] = p * (dp[i] - delta) * dm.scale;
+        see[i] = (unsigned)(t - (s0 + 4 * q4 + i)) < (unsigned)W;
+        da[i] = see[i] ? expf(s[i] * dm.scale - lse) * (dp[i] - delta) * dm.scale : 0.f;
       }
+      if (s0 + 15 > t0 || t_hi - s0 >= W) hide_unseen<D>(kc, da, see, r16, q4, acc);
       col_product<D>(kc, da, acc);
     }
   }
@@ -622,16 +668,23 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
     for (int u = w; u < G * nt; u += GW) {
       const int h = g * G + u / nt, tp0 = s0 + 16 * (u % nt);
       auto off = [&](int tp) { return ((size_t)(b * T + min(tp, hi) + W) * Hq + h) * D; };
+      const bool all = tp0 >= s_hi && tp0 + 15 <= hi;  // every query of the tile sees every key
+      bool see[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { const int tp = tp0 + 4 * q4 + i; see[i] = tp >= s && tp <= hi; }
+      auto add = [&](ColForm<D>& a, f32x4_t c, f32x4_t (&acc)[D / 16]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = see[i] ? c[i] : 0.f;
+        if (!all) hide_unseen<D>(a, c, see, r16, q4, acc);
+        col_product<D>(a, c, acc);
+      };
       {
         RowForm<D> qf;
         qf.load(q + off(tp0 + r16), q4);
         ColForm<D> dc;
         dc.load([&](int i) { return dxr + off(tp0 + 4 * q4 + i); }, r16);
         qf.feature(dm.phi);
-        f32x4_t c = row_product<D>(qf, kv);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { const int tp = tp0 + 4 * q4 + i; c[i] = tp >= s && tp <= hi ? c[i] : 0.f; }
-        col_product<D>(dc, c, dva);
+        add(dc, row_product<D>(qf, kv), dva);
       }
       {
         RowForm<D> dr;
@@ -639,10 +692,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
         ColForm<D> qc;
         qc.load([&](int i) { return q + off(tp0 + 4 * q4 + i); }, r16);
         qc.feature(dm.phi);
-        f32x4_t c = row_product<D>(dr, vv);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { const int tp = tp0 + 4 * q4 + i; c[i] = tp >= s && tp <= hi ? c[i] : 0.f; }
-        col_product<D>(qc, c, dka);
+        add(qc, row_product<D>(dr, vv), dka);
       }
     }
     feature_backward<D>(k + koff, dka, q4, dm.phi);
@@ -670,19 +720,25 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
         dx.load(dxs + off(q0 + r16), q4);
         da = row_product<D>(dx, vv);
       }
+      bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = q0 + 4 * q4 + i;
-        const unsigned dist = (unsigned)(t - s);
         const size_t st = sbase + min(t, hi);
-        p[i] = dist < (unsigned)W && t <= hi ? expf(p[i] * dm.scale - lse[st]) : 0.f;
-        da[i] = p[i] * (da[i] - delta[st]) * dm.scale;
+        see[i] = (unsigned)(t - s) < (unsigned)W && t <= hi;
+        p[i] = see[i] ? expf(p[i] * dm.scale - lse[st]) : 0.f;
+        da[i] = see[i] ? p[i] * (da[i] - delta[st]) * dm.scale : 0.f;
       }
+      const bool all = q0 >= s_hi && q0 + 15 <= hi && q0 + 15 - s0 < W;  // every query of the tile sees every key
+      auto add = [&](ColForm<D>& a, f32x4_t x, f32x4_t (&acc)[D / 16]) {
+        if (!all) hide_unseen<D>(a, x, see, r16, q4, acc);
+        col_product<D>(a, x, acc);
+      };
       ColForm<D> c;
       c.load([&](int i) { return dxs + off(q0 + 4 * q4 + i); }, r16);
-      col_product<D>(c, p, dva);
+      add(c, p, dva);
       c.load([&](int i) { return q + off(q0 + 4 * q4 + i); }, r16);
-      col_product<D>(c, da, dka);
+      add(c, da, dka);
     }
   }
   const int row = threadIdx.x >> 4, c = threadIdx.x & 15;

@@ -301,6 +301,63 @@ def test_decode_bf16_probabilities_keep_fp32(N, Hq, Hkv, D, W):
     assert r["beyond_storage"] <= 1e-4
 
 
+# ------------------------------------------------------------------------------ rows that hold no numbers
+@pytest.mark.parametrize("dtype,B,T,Hq,Hkv,D,W,chunk", [("f32", 1, 37, 2, 1, 64, 8, 0), ("f32", 2, 100, 2, 2, 128, 40, 16),
+                                                        ("bf16", 1, 100, 4, 2, 64, 20, 0), ("f32", 1, 50, 1, 1, 128, 50, 0)])
+def test_general_kernels_rows_reach_only_what_sees_them(dtype, B, T, Hq, Hkv, D, W, chunk):
+    """NaN or infinite rows of k, v or dO leave every row that does not see them as it was, bit for bit: outputs and dq of
+    earlier queries, dk and dv of later keys; and an infinite value that has left the window is in the linear branch only."""
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, dtype, 871 + T, with_dO=True)
+    kw = dict(chunk=chunk, softmax_scale=1.0 / math.sqrt(D))
+
+    def layer(**changed):
+        q, k, v, dO = (dev(changed.get(n, x[n])) for n in ("q", "k", "v", "dO"))
+        o, saved = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw)
+        return (o,) + rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, **kw)[:3]
+
+    base = layer()
+    assert all(bool(t.isfinite().all()) for t in base)
+    for s in (T - 1, T // 2):
+        for n, bad in (("v", math.nan), ("v", math.inf), ("k", math.inf)):
+            y = x[n].clone()
+            y[:, s] = bad
+            o, dq, _, _ = layer(**{n: y})
+            print(f"{n}[{s}] = {bad}", flush=True)
+            assert torch.equal(o[:, :s], base[0][:, :s]) and torch.equal(dq[:, :s], base[1][:, :s])
+            assert not bool(o[:, s].isfinite().all())
+    for t in (0, T // 2):
+        y = x["dO"].clone()
+        y[:, t] = math.nan
+        o, dq, dk, dv = layer(dO=y)
+        assert torch.equal(dk[:, t + 1:], base[2][:, t + 1:]) and torch.equal(dv[:, t + 1:], base[3][:, t + 1:])
+        assert torch.equal(dq[:, :t], base[1][:, :t]) and torch.equal(dq[:, t + 1:], base[1][:, t + 1:])
+        assert bool(dk[:, :t + 1].isnan().any()) and bool(dv[:, :t + 1].isnan().any())
+    y = x["v"].clone()
+    y[:, 0, :, 0] = math.inf
+    assert bool(layer(v=y)[0][:, W:, :, 1:].isfinite().all())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("s", [36, 20])   # the last key that the state takes, and one in between
+def test_prefill_export_infinite_value(dtype, D, s):
+    """An infinite value is an infinite column of the state, and the other columns are as if it were not there."""
+    T, W = 45, 8
+    x = synth.make_random_layer(1, T, 1, 1, D, dtype, 872)
+    x["v"][0, s, 0, 7] = math.inf
+    finite = x["v"].clone()
+    finite[0, s, 0, 7] = 0
+    S_ref = orc.prefill_export(np64(x["k"]), np64(finite), W)[2]
+    rest = [d for d in range(D) if d != 7]
+    q, k, v = dev(x["q"]), dev(x["k"]), dev(x["v"])
+    kr, vr, S = rb.rattn_prefill_export(k, v, W)
+    S_chunk = torch.full_like(S, math.nan)
+    rb.rattn_prefill_chunk(q, k, v, W, 0, torch.zeros_like(kr), torch.zeros_like(vr), S_chunk, softmax_scale=0.1)
+    for got in (S, S_chunk):
+        assert bool((got[..., 7] == math.inf).all())
+        assert float(np.max(np.abs(np64(got)[..., rest] - S_ref[..., rest]))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
+
+
 # ------------------------------------------------------------------------------ prefill -> decode hand-over
 @pytest.mark.parametrize("dtype,B,T,Hkv,D,W", [("f32", 2, 5, 2, 64, 8), ("f32", 1, 8, 1, 64, 8), ("f32", 2, 77, 2, 128, 10),
                                                  ("bf16", 2, 384, 2, 128, 128), ("bf16", 1, 1000, 3, 64, 200),
