@@ -500,6 +500,23 @@ def test_chunked_prefill_positions_around_tiles(D, Hq, Hkv, W, chunks):
     test_chunked_prefill_reproduces_forward("bf16", D, Hq, Hkv, W, chunks)
 
 
+@pytest.mark.parametrize("D,W,fmap,T,pos0", [(64, 100, "softmax", 333, 900), (64, 512, "relu", 512, 1024),
+                                             (128, 256, "identity", 512, 512), (128, 100, "identity", 200, 60)])
+def test_chunked_prefill_in_fp32(D, W, fmap, T, pos0):
+    """Head size 64 and the identity map: the chunk's outputs are the exact result rounded once to bf16; beyond that
+    rounding fp32 sums over W + D terms leave at most 1e-4 (bf16 operands leave 5e-3 and more)."""
+    x = synth.make_random_layer(1, pos0 + T, 4, 2, D, "bf16", 4300 + T)
+    scale = 1.0 / math.sqrt(D)
+    ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, scale=scale, feature_map=fmap)["o"][:, pos0:]
+    q, k, v = dev(x["q"]), dev(x["k"]), dev(x["v"])
+    kr, vr, S = rb.rattn_prefill_export(k[:, :pos0].contiguous(), v[:, :pos0].contiguous(), W, feature_map=fmap)
+    o = rb.rattn_prefill_chunk(q[:, pos0:].contiguous(), k[:, pos0:].contiguous(), v[:, pos0:].contiguous(), W, pos0, kr, vr,
+                               S, softmax_scale=scale, feature_map=fmap)
+    r = pm.out_err_bf16(np64(o), ref)
+    print(f"chunk D={D} W={W} {fmap}: beyond storage rounding {r['beyond_storage']:.2e}", flush=True)
+    assert r["beyond_storage"] <= 1e-4
+
+
 def test_chunked_prefill_uses_matrix_core_kernels():
     B, Hq, Hkv, D, W = 1, 2, 1, 128, 128
     x = synth.make_random_layer(B, 384, Hq, Hkv, D, "bf16", 4200)
