@@ -75,8 +75,7 @@ typedef struct {
                             independent implementation used by tests).  It changes what `saved` holds:
                             rattn_fwd and rattn_bwd of one step must be given the same value           */
   int32_t state_policy;  /* rattn_state_policy: what rattn_fwd keeps of the linear-branch chunk states for
-                            rattn_bwd (bf16 matrix-core kernels; the general kernels always keep their fp32 states).
-                            Same value in both calls: it changes what `saved` holds                           */
+                            rattn_bwd.  Same value in both calls: it changes what `saved` holds                */
 } rattn_params;
 
 typedef enum { RATTN_PATH_AUTO = 0, RATTN_PATH_GENERAL = 1 } rattn_kernel_path;
@@ -86,7 +85,9 @@ typedef enum { RATTN_PATH_AUTO = 0, RATTN_PATH_GENERAL = 1 } rattn_kernel_path;
  * the chunk size C.  Here the same trade is selectable: KEEP stores every chunk state (one per 128 keys, bf16) in
  * `saved` so that backward reads them (m = 1); KEEP_EVERY_2ND / _4TH store states 0, m, 2m, ... and backward forms only
  * the chunk products that lead to the states in between, continuing from the stored ones (m = 2, 4); REBUILD stores
- * none and backward builds all of them again from k and v.  The chunk size of the state-building kernels is the `chunk`
+ * none and backward builds all of them again from k and v.  The general kernels keep all their fp32 states (KEEP, with
+ * chunks of at least D Hkv / (2 Hq) keys: a chunk's states then take no more room in `saved` than its branch outputs) or
+ * none.  The chunk size of the state-building kernels is the `chunk`
  * parameter: 64 selects 64-key chunk products (two per state), anything else 128-key products. */
 typedef enum {
   RATTN_STATES_KEEP = 0,

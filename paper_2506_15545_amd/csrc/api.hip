@@ -153,10 +153,12 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   L->sv_rr = off; off += align_up(nrow_f * 4);
   L->sv_states = off;
   const size_t nstate = (size_t)dm.B * dm.Hkv * dm.nst * dm.D * dm.D;   // general kernels
-  L->state_stride = !L->fast_fwd || p->state_policy == RATTN_STATES_KEEP ? 1
-                    : p->state_policy == RATTN_STATES_REBUILD ? 0 : p->state_policy;
+  if (L->fast_fwd)
+    L->state_stride = p->state_policy == RATTN_STATES_KEEP ? 1 : p->state_policy == RATTN_STATES_REBUILD ? 0 : p->state_policy;
+  else  // general kernels: all or none; all only where a chunk's states take no more room than its branch outputs
+    L->state_stride = p->state_policy == RATTN_STATES_KEEP && dm.D <= 2ll * dm.G * dm.C ? 1 : 0;
   if (!L->fast_fwd) {
-    off += align_up(nstate * 4);
+    off += L->state_stride ? align_up(nstate * 4) : 0;
   } else if (L->state_stride > 0) {
     const int nstf = rattn::fast_fwd_plan(dmf).nstf;
     off += align_up((size_t)dmf.B * dmf.Hkv * ((nstf + L->state_stride - 1) / L->state_stride) * dmf.D * dmf.D * 2);
@@ -164,10 +166,10 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   L->saved_bytes = off;
 
   L->gf_states = 0;
-  L->gen_fwd_bytes = align_up(nstate * 4);
+  L->gen_fwd_bytes = align_up(nstate * 4);   // the same for both kinds of call (states that are kept are built in `saved`)
 
   off = 0;
-  L->gb_rstates = off; off += align_up(nstate * 4);
+  L->gb_rstates = off; off += align_up(nstate * 4);   // states that were not kept are rebuilt here first
   L->gb_dxs = off; off += align_up(nq * 4);
   L->gb_dxr = off; off += align_up(nq * 4);
   L->gb_delta = off; off += align_up(nrow * 4);

@@ -790,11 +790,16 @@ void launch_bwd(const LayerDims& dm, const void* q, const void* k, const void* v
                 const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs, float* dgr,
                 const GenericBwdWs& ws, hipStream_t st) {
   const int tiles = (dm.T + 15) / 16;
+  const float* states = (const float*)sv.states;
+  if (!states) {  // not kept by the forward: built again, where the reverse states go once dq has read them
+    build_states<IO, IO, D, false>(dm, k, v, ws.rstates, dm.Hkv, 1, 0, nullptr, st);
+    states = ws.rstates;
+  }
   {
     ProfScope ps("gen_bwd_dq_kernel", st);
     gen_bwd_dq_kernel<IO, D><<<dim3(tiles, dm.Hq, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, (const IO*)dO, gs, gr,
-                                                                       sv, (const float*)sv.states, (IO*)dq, ws.dxs, ws.dxr,
-                                                                       ws.delta, dgs || dgr ? ws.dgpart : nullptr, dm);
+                                                                       sv, states, (IO*)dq, ws.dxs, ws.dxr, ws.delta,
+                                                                       dgs || dgr ? ws.dgpart : nullptr, dm);
   }
   if (dgs || dgr) dgamma_reduce(ws.dgpart, dgs, dgr, tiles * dm.B, dm.Hq * D, st);
   build_states<IO, float, D, true>(dm, q, ws.dxr, ws.rstates, dm.Hq, dm.G, dm.W, nullptr, st);

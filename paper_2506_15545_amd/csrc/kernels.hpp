@@ -31,7 +31,7 @@ struct LayerDims {
 // the state has very low rank - the first rows past the window - rounding x^r to bf16 leaves an error that the
 // state multiplies back up) and the
 // row statistics (fp32, [B,Hq,T]): log-sum-exp of the softmax branch and the two RMS reciprocals, and the
-// linear-branch chunk states (MFMA path: bf16, transposed; general path: fp32), so that backward does not rebuild them
+// linear-branch chunk states (MFMA path: bf16, transposed; general path: fp32), where backward is not to rebuild them
 struct SavedPtrs {
   void* xs;
   void* xr;
@@ -46,7 +46,7 @@ struct SavedPtrs {
 };
 
 struct GenericBwdWs {
-  float* rstates;  // [B,Hkv,nst,D,D]
+  float* rstates;  // [B,Hkv,nst,D,D]; the forward states first, where `saved` does not hold them
   float* dxs;      // [B,T,Hq,D]
   float* dxr;      // [B,T,Hq,D]
   float* delta;    // [B,Hq,T]
@@ -58,7 +58,7 @@ struct GenericBwdWs {
 void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
                  const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st, int q0 = 0,
                  const float* state0 = nullptr);
-// sv.states: the chunk states as the forward left them
+// sv.states: the chunk states as the forward left them, or NULL: rebuilt from k and v
 void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
                  const float* gr, const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs,
                  float* dgr, const GenericBwdWs& ws, hipStream_t st);

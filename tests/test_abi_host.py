@@ -228,3 +228,23 @@ def test_ragged_lengths_cost_tail_buffers_not_copies():
     # less than one tile: general kernels (fp32 branch outputs in `saved`)
     _, _, s_small = rb.rattn_workspace_bytes(params(T=100, **base))
     assert s_small >= 2 * B * 100 * Hq * 128 * 4
+
+
+@pytest.mark.parametrize("dtype,D,fmap", [(rb.RATTN_F32, 64, 0), (rb.RATTN_F32, 128, 1), (rb.RATTN_BF16, 128, 2)])
+def test_general_kernels_keep_their_states_in_saved_only_as_asked(dtype, D, fmap):
+    """`saved` of the general kernels: the fp32 branch outputs and row statistics, plus every chunk state under KEEP at
+    chunks of at least D Hkv / (2 Hq) keys; no state under the other policies or at smaller chunks.  The backward
+    workspace is the same either way."""
+    B, T, Hq, Hkv, W = 2, 640, 4, 2, 96
+    base = dict(B=B, T=T, Hq=Hq, Hkv=Hkv, D=D, window=W, dtype=dtype, feature_map=fmap)
+    up = lambda n: (n + 255) // 256 * 256
+    without = 2 * up(B * T * Hq * D * 4) + 3 * up(B * Hq * T * 4)
+    states = lambda chunk: up(B * Hkv * -(-(T - W) // chunk) * D * D * 4)
+    fwd, bwd, saved = rb.rattn_workspace_bytes(params(**base))
+    assert fwd >= states(64) and saved == without + states(64)
+    for policy in (1, 2, 4):
+        assert rb.rattn_workspace_bytes(params(state_policy=policy, **base)) == (fwd, bwd, without)
+    smallest = D * Hkv // (2 * Hq)
+    assert rb.rattn_workspace_bytes(params(chunk=smallest, **base))[2] == without + states(smallest)
+    for chunk in (smallest - 1, 1):
+        assert rb.rattn_workspace_bytes(params(chunk=chunk, **base))[2] == without

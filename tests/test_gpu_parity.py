@@ -543,3 +543,26 @@ def test_chunked_prefill_uses_matrix_core_kernels():
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
     assert "fwd_fused_kernel" in names and "chunk_fixup_kernel" in names
+
+
+@pytest.mark.parametrize("dtype,D,fmap", [("f32", 64, "softmax"), ("f32", 128, "relu"), ("bf16", 128, "identity")])
+@pytest.mark.parametrize("policy,chunk", [("rebuild", 0), ("every2", 64), ("rebuild", 32), ("keep", 1)])
+def test_general_kernels_rebuild_the_states_they_do_not_keep(policy, chunk, dtype, D, fmap):
+    """States that the forward does not keep are built again by the backward, from the same sums: no bit changes against a
+    call that keeps them."""
+    T, W = 200, 40
+    x = synth.make_random_layer(2, T, 4, 2, D, dtype, 4700 + D, with_dO=True)
+    q, k, v, dO = dev(x["q"]), dev(x["k"]), dev(x["v"]), dev(x["dO"])
+    kw = dict(softmax_scale=0.1, feature_map=fmap, chunk=chunk)
+    o, saved = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, state_policy=policy, **kw)
+    got = rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, state_policy=policy, **kw)[:3]
+    kw["chunk"] = chunk if chunk != 1 else 32       # (one key per chunk: compared with the kept states of another chunk size)
+    o0, saved0 = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw)
+    assert saved.numel() < saved0.numel()
+    want = rb.rattn_bwd(q, k, v, saved0, dO, W, want_dgamma=False, **kw)[:3]
+    for n, a, b in zip(("o", "dq", "dk", "dv"), (o,) + tuple(got), (o0,) + tuple(want)):
+        if chunk != 1:
+            assert torch.equal(a, b), n
+        else:   # the sums of up to T + D terms in another order; bf16: one rounding apart
+            d = (a.float() - b.float()).abs().max() / b.float().square().mean().sqrt()
+            assert float(d) <= (2e-2 if dtype == "bf16" else 1e-4), n
