@@ -186,6 +186,14 @@ template <int D> __device__ __forceinline__ void state_product_t(const float* M,
     }
 }
 
+// Probability of a pair from its logit as the forward formed it: with the product rounded before the difference, a query
+// that sees one key gets exactly 1
+__device__ __forceinline__ float prob(float s, float scale, float lse) {
+#pragma clang fp contract(off)
+  const float a = s * scale;
+  return expf(a - lse);
+}
+
 template <int D> __device__ __forceinline__ void zero(f32x4_t (&acc)[D / 16]) {
 #pragma unroll
   for (int e = 0; e < D / 16; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -502,7 +510,11 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
 //   RMS norms (Sec. 3.2): for y = g*x*r, r = (mean x^2+eps)^-1/2:  dx = r*(g*dy) - x*r^3*mean(g*dy*x),
 //                   dgamma += dy*x*r,  delta = <dx_s, x_s>;  dx_s, dx_r, delta are stored for the dk/dv kernel, the sums
 //                   over the 16 rows of the gain gradients go to dgpart[2][RB][Hq][D] (NULL: not wanted)
-//   softmax branch: p = exp(scale q.k - lse), dp = <dx_s, v_s>, da = p(dp - delta), dq += scale*da*k_s
+//   softmax branch: p = exp(scale q.k - lse), dp = <dx_s, v_s>, da = p(dp - delta), dq += scale*da*k_s.
+//                   Windows of up to 64 keys take delta = sum p dp over the very p and dp that form da: their rows are often
+//                   close to one-hot, where p (dp - delta) cancels (to exactly 0 for a single key) and the rounding of
+//                   <dx_s, x_s> would be what is left (W = 1: error of dq 2.4e-7 -> 2e-6 .. 8e-5, growing with the logits).
+//                   Such a range is at most five tiles, so each wave keeps the p and dp of its one or two.
 //   linear branch : dphi(q) = S_[j] dx_r + sum_{intra} <dx_r, v_s> phi(k_s);  dq += phi(q)*(dphi - <dphi,phi(q)>)
 //                   (softmax map; ReLU passes dphi where q > 0, identity passes it unchanged)
 template <typename IO, int D>
@@ -514,7 +526,9 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
                                                             float* __restrict__ dxr_out, float* __restrict__ delta_out,
                                                             float* __restrict__ dgpart, LayerDims dm) {
   constexpr int PL = plane_floats<D>();
+  constexpr int SHORT_W = 64;
   __shared__ __align__(16) float part[GW * PL];
+  __shared__ float dsum[GW][16];
   const int h = blockIdx.y, b = blockIdx.z, g = h / dm.G;
   const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
   const int T = dm.T, W = dm.W, C = dm.C, Hq = dm.Hq, Hkv = dm.Hkv;
@@ -561,7 +575,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
         store4(dxs_out + qoff + 16 * j + 4 * q4, dxs.x[j]);
         store4(dxr_out + qoff + 16 * j + 4 * q4, dxr.x[j]);
       }
-      if (q4 == 0) delta_out[so] = delta;
+      if (q4 == 0 && W > SHORT_W) delta_out[so] = delta;
     }
   }
   f32x4_t acc[D / 16];
@@ -596,23 +610,63 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
     qv.load(q + qoff, q4);
     const float lse = sv.lse[so];
     const int lo = max(0, t0 - W + 1), nt = (t_hi - lo) / 16 + 1;
-    for (int n = w; n < nt; n += GW) {
-      const int s0 = lo + 16 * n;
+    auto sees = [&](int s) { return (unsigned)(t - s) < (unsigned)W; };
+    // p and dp of the 16 keys from s0 on, 0 where the query does not see the key
+    auto scores = [&](int s0, f32x4_t& p, f32x4_t& dp) {
       RowForm<D> kf, vf;
-      ColForm<D> kc;
       kf.load(krow(s0 + r16), q4);
       vf.load(vrow(s0 + r16), q4);
-      kc.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
-      const f32x4_t s = row_product<D>(kf, qv), dp = row_product<D>(vf, dxs);
+      p = row_product<D>(kf, qv);
+      dp = row_product<D>(vf, dxs);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool see = sees(s0 + 4 * q4 + i);
+        p[i] = see ? prob(p[i], dm.scale, lse) : 0.f;
+        dp[i] = see ? dp[i] : 0.f;
+      }
+    };
+    auto add = [&](int s0, ColForm<D>& kc, f32x4_t p, f32x4_t dp) {
       f32x4_t da;
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        see[i] = (unsigned)(t - (s0 + 4 * q4 + i)) < (unsigned)W;
-        da[i] = see[i] ? expf(s[i] * dm.scale - lse) * (dp[i] - delta) * dm.scale : 0.f;
+        see[i] = sees(s0 + 4 * q4 + i);
+        da[i] = see[i] ? p[i] * (dp[i] - delta) * dm.scale : 0.f;
       }
       if (s0 + 15 > t0 || t_hi - s0 >= W) hide_unseen<D>(kc, da, see, r16, q4, acc);
       col_product<D>(kc, da, acc);
+    };
+    auto keys = [&](int s0, ColForm<D>& kc) { kc.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16); };
+    if (W <= SHORT_W) {
+      f32x4_t p[2], dp[2];
+      float dl = 0.f;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (w + GW * u < nt) {
+          scores(lo + 16 * (w + GW * u), p[u], dp[u]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dl += p[u][i] * dp[u][i];
+        }
+      dl = rows_sum(dl);
+      if (q4 == 0) dsum[w][r16] = dl;
+      __syncthreads();
+      delta = (dsum[0][r16] + dsum[1][r16]) + (dsum[2][r16] + dsum[3][r16]);
+      if (w == GW - 1 && live && q4 == 0) delta_out[so] = delta;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (w + GW * u < nt) {
+          ColForm<D> kc;
+          keys(lo + 16 * (w + GW * u), kc);
+          add(lo + 16 * (w + GW * u), kc, p[u], dp[u]);
+        }
+    } else {
+      for (int n = w; n < nt; n += GW) {
+        ColForm<D> kc;
+        keys(lo + 16 * n, kc);
+        f32x4_t p, dp;
+        scores(lo + 16 * n, p, dp);
+        add(lo + 16 * n, kc, p, dp);
+      }
     }
   }
   put_partial<D>(part + w * PL, acc, r16, q4);
@@ -726,7 +780,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
         const int t = q0 + 4 * q4 + i;
         const size_t st = sbase + min(t, hi);
         see[i] = (unsigned)(t - s) < (unsigned)W && t <= hi;
-        p[i] = see[i] ? expf(p[i] * dm.scale - lse[st]) : 0.f;
+        p[i] = see[i] ? prob(p[i], dm.scale, lse[st]) : 0.f;
         da[i] = see[i] ? p[i] * (da[i] - delta[st]) * dm.scale : 0.f;
       }
       const bool all = q0 >= s_hi && q0 + 15 <= hi && q0 + 15 - s0 < W;  // every query of the tile sees every key

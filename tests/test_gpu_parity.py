@@ -566,3 +566,27 @@ def test_general_kernels_rebuild_the_states_they_do_not_keep(policy, chunk, dtyp
         else:   # the sums of up to T + D terms in another order; bf16: one rounding apart
             d = (a.float() - b.float()).abs().max() / b.float().square().mean().sqrt()
             assert float(d) <= (2e-2 if dtype == "bf16" else 1e-4), n
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,W", [(97, 1), (97, 2), (50, 17), (97, 50), (81, 64), (64, 64)])
+def test_general_backward_of_rows_that_see_one_key(T, W, dtype, D):
+    """A softmax over one key is constant: with large logits (std 8 sqrt(D)) nothing of its rounding may reach dq or dk.
+    Exactly zero for the first query, which has no linear branch either, and for the last key of a window of one."""
+    x = synth.make_random_layer(2, T, 4, 2, D, dtype, 4800 + T, with_dO=True)
+    q, k, v, dO = dev(x["q"]), dev(x["k"]), dev(x["v"]), dev(x["dO"])
+    kw = dict(softmax_scale=8.0, kernel_path="general")
+    o, saved = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw)
+    dq, dk, dv, _, _ = rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, **kw)
+    assert bool((dq[:, 0] == 0).all())
+    if W == 1:
+        assert bool((dk[:, T - 1] == 0).all())
+    if dtype == "f32":
+        # W = 1: only the linear branch is left, sums of at most T + D terms; otherwise the error of the logits, of size
+        # 2^-24 * 8 * 4.5 D at most, in every probability
+        ref = orc.bwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), np64(x["dO"]), W, scale=8.0)
+        for n, g in (("dq", dq), ("dk", dk)):
+            err = float(np.linalg.norm(np64(g) - ref[n]) / np.linalg.norm(ref[n]))
+            print(f"T={T} W={W} D={D} {n}: {err:.2e}", flush=True)
+            assert err <= (1e-6 if W == 1 else 3e-4), n
