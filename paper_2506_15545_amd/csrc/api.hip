@@ -183,21 +183,6 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
     if (ragged) L->fast_bwd_bytes += align_up((size_t)dm.B * 128 * dm.Hq * dm.D * 2);
     L->fb_gains = L->fast_bwd_bytes;
     if (dm.D == 64) L->fast_bwd_bytes += align_up((size_t)dm.Hq * 128 * 4);
-    // The sizes rattn_workspace_bytes reports for ragged lengths and for a head size of 64 stay those of the kernels that
-    // ran such tensors through copies padded to whole tiles and 128 features: programs keep buffers of these sizes.
-    if (ragged || dm.D == 64) {
-      rattn::LayerDims w = dmf;
-      w.D = 128;
-      Layout unused;
-      size_t fwd, bwd;
-      fast_scratch(w, &unused, &fwd, &bwd);
-      const size_t rows = dm.D == 64 ? (size_t)dmf.B * dmf.T : (size_t)dmf.B * 128;
-      const size_t cq = align_up(rows * dm.Hq * 256), ckv = align_up(rows * dm.Hkv * 256), gain = align_up((size_t)dm.Hq * 512);
-      fwd += 2 * cq + 2 * ckv + 2 * gain;
-      bwd += 3 * cq + 4 * ckv + 4 * gain;
-      if (fwd > L->fast_fwd_bytes) L->fast_fwd_bytes = fwd;
-      if (bwd > L->fast_bwd_bytes) L->fast_bwd_bytes = bwd;
-    }
   }
   L->fwd_bytes = L->fast_fwd ? L->fast_fwd_bytes : L->gen_fwd_bytes;
   L->bwd_bytes = L->fast_fwd ? L->fast_bwd_bytes : L->gen_bwd_bytes;

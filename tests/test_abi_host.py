@@ -207,26 +207,23 @@ def test_matrix_core_chunk_size_defaults_to_128_keys():
 
 
 def test_ragged_lengths_cost_tail_buffers_not_copies():
-    """A bf16, D = 128 length that is no multiple of 128 runs in place on the matrix-core kernels: on top of the
-    scratch of the length rounded up, the workspace holds one 128-row buffer per tensor that passes through the
-    kernels (forward q, k, v, o; backward q, k, v, dO, dq, dk, dv) and `saved` is that of the rounded-up length.
-    A head size of 64 pays whole widened copies instead; lengths below one tile stay on the general kernels."""
+    """A bf16 length that is no multiple of 128 runs in place on the matrix-core kernels: on top of the scratch of the
+    length rounded up, the backward workspace holds one 128-row buffer per sequence for the tail of dO, the forward
+    nothing, and `saved` is that of the rounded-up length.  A head size of 64 needs the products, states and row tensors
+    of 64 features, no copies either.  Lengths below one tile stay on the general kernels."""
     B, Hq, Hkv = 2, 6, 2
-    base = dict(B=B, Hq=Hq, Hkv=Hkv, D=128, window=256, dtype=rb.RATTN_BF16)
-    f_al, b_al, s_al = rb.rattn_workspace_bytes(params(T=2048, **base))
-    f_rg, b_rg, s_rg = rb.rattn_workspace_bytes(params(T=2000, **base))
-    tail_q, tail_kv = B * 128 * Hq * 128 * 2, B * 128 * Hkv * 128 * 2
-    gains = 2 * Hq * 128 * 4                        # two widened gain rows per head (used at D = 64 only)
-    assert s_rg == s_al
-    assert f_rg == f_al + 2 * tail_q + 2 * tail_kv + gains
-    assert b_rg == b_al + 3 * tail_q + 4 * tail_kv + 2 * gains
-    # D = 64: whole tensors, widened to 128 features, forward and backward
-    f64, b64, _ = rb.rattn_workspace_bytes(params(T=2048, **dict(base, D=64)))
-    full_q, full_kv = B * 2048 * Hq * 128 * 2, B * 2048 * Hkv * 128 * 2
-    assert f64 == f_al + 2 * full_q + 2 * full_kv + gains
-    assert b64 == b_al + 3 * full_q + 4 * full_kv + 2 * gains
+    base = dict(B=B, Hq=Hq, Hkv=Hkv, window=256, dtype=rb.RATTN_BF16)
+    size = {}
+    for D in (128, 64):
+        f_al, b_al, s_al = size[D] = rb.rattn_workspace_bytes(params(T=2048, D=D, **base))
+        f_rg, b_rg, s_rg = rb.rattn_workspace_bytes(params(T=2000, D=D, **base))
+        assert s_rg == s_al and f_rg == f_al
+        assert b_rg == b_al + B * 128 * Hq * D * 2
+        nst = 2048 // 128 - 2
+        assert f_al == B * Hkv * ((nst - 1) * D * D * 4 + nst * D * D * 2)
+    assert size[64][1] < size[128][1] and size[64][2] < size[128][2]
     # less than one tile: general kernels (fp32 branch outputs in `saved`)
-    _, _, s_small = rb.rattn_workspace_bytes(params(T=100, **base))
+    _, _, s_small = rb.rattn_workspace_bytes(params(T=100, D=128, **base))
     assert s_small >= 2 * B * 100 * Hq * 128 * 4
 
 

@@ -1,7 +1,7 @@
 """The allocation-free forward entry point (rattn_fwd_static: scratch inside the library's device image) against
 rattn_fwd with a caller-provided workspace, through the C ABI: two calls in a row, the second on a smaller input
-(it reuses the front of the buffer the first call left dirty), then a ragged length that runs through padded
-copies in the scratch, and the size limit."""
+(it reuses the front of the buffer the first call left dirty), then a ragged length, head size 64, and the size
+limit."""
 import ctypes
 import math
 import pytest
@@ -32,7 +32,8 @@ def test_static_entry_matches_workspace_entry_on_two_calls_in_a_row():
     cases = [
         (2, 2048, 8, 2, 128, 256, 31),    # matrix-core path, 14 chunk states per KV head
         (1, 640, 4, 2, 128, 192, 32),     # smaller: reuses the front of the dirty buffer; states at the 64 alignment
-        (1, 1100, 2, 1, 128, 300, 33),    # ragged length: the tail buffers of q, k, v, o live in the scratch too
+        (1, 1100, 2, 1, 128, 300, 33),    # ragged length
+        (2, 4096, 24, 8, 64, 512, 35),    # head size 64: 11 MB of products and states (widened copies would not fit)
         (1, 100, 4, 2, 64, 32, 34),       # general kernels (less than one tile): fp32 chunk states in the scratch
     ]
     for (B, T, Hq, Hkv, D, W, seed) in cases:
