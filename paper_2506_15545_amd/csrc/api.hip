@@ -65,7 +65,7 @@ struct Layout {
   // MFMA forward / backward workspace
   bool fast_fwd;
   size_t ff_u, ff_states, fast_fwd_bytes;
-  size_t fb_dxs, fb_dxr, fb_delta, fb_u, fb_states, fb_rstates, fb_dgpart, fb_dkv, fb_dO_tail, fb_gains, fast_bwd_bytes;
+  size_t fb_dxs, fb_dxr, fb_delta, fb_u, fb_states, fb_rstates, fb_dgpart, fb_dkv, fb_dO_tail, fast_bwd_bytes;
   size_t fwd_bytes, bwd_bytes;
 };
 
@@ -181,8 +181,6 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
     fast_scratch(dmf, L, &L->fast_fwd_bytes, &L->fast_bwd_bytes);
     L->fb_dO_tail = L->fast_bwd_bytes;
     if (ragged) L->fast_bwd_bytes += align_up((size_t)dm.B * 128 * dm.Hq * dm.D * 2);
-    L->fb_gains = L->fast_bwd_bytes;
-    if (dm.D == 64) L->fast_bwd_bytes += align_up((size_t)dm.Hq * 128 * 4);
   }
   L->fwd_bytes = L->fast_fwd ? L->fast_fwd_bytes : L->gen_fwd_bytes;
   L->bwd_bytes = L->fast_fwd ? L->fast_bwd_bytes : L->gen_bwd_bytes;
@@ -407,14 +405,7 @@ rattn_status rattn_bwd(const rattn_params* p, const void* q, const void* k, cons
     // exist then adds nothing to any gradient
     const bool ragged = L.dm.T % 128 != 0;
     if (ragged) rattn::gather_tail(dO, w + L.fb_dO_tail, L.dm.B, L.dm.T, L.dm.Hq, L.dm.D, st);
-    const float *gs = gamma_swa, *gr = gamma_rla;
-    int gstride = L.dm.D;
-    if (L.dm.D == 64 && (gs || gr)) {   // both gains of a head in one row
-      float* packed = (float*)(w + L.fb_gains);
-      rattn::pack_gains64(gs, gr, packed, L.dm.Hq, st);
-      gs = packed; gr = packed + 64; gstride = 128;
-    }
-    rattn::fast_bwd(L.dmf, L.dm.T, q, k, v, gs, gr, gstride, sv, dO, ragged ? w + L.fb_dO_tail : nullptr, dq, dk, dv,
+    rattn::fast_bwd(L.dmf, L.dm.T, q, k, v, gamma_swa, gamma_rla, sv, dO, ragged ? w + L.fb_dO_tail : nullptr, dq, dk, dv,
                     dgamma_swa, dgamma_rla, fw, st);
     return check_launch("rattn_bwd");
   }

@@ -34,8 +34,7 @@ struct FastBwdArgs {
   // Tfull = 128 * (Tc / 128) on come from dO_tail [B,128,Hq,D], zero past row Tc (ragged lengths)
   const uint16_t *dO, *dO_tail, *xs, *xr;
   int Tfull;
-  const float *rs, *rr, *gs, *gr;   // gains: row h at gs + h * gstride; NULL = ones
-  int gstride;
+  const float *rs, *rr, *gs, *gr;   // gains [Hq][D], NULL = ones
   float* dgpart;                    // gain-gradient partials [2][4 * ntile * B][Hq][D], NULL = not wanted
 };
 
@@ -215,8 +214,8 @@ __device__ __forceinline__ void rms_bwd_rows(const FastBwdArgs& a, int hq, size_
   float g1[8], g2[8], dg1[8], dg2[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    g1[e] = (GAINS && a.gs) ? a.gs[hq * a.gstride + 8 * c + e] : 1.f;
-    g2[e] = (GAINS && a.gr) ? a.gr[hq * a.gstride + 8 * c + e] : 1.f;
+    g1[e] = (GAINS && a.gs) ? a.gs[hq * D + 8 * c + e] : 1.f;
+    g2[e] = (GAINS && a.gr) ? a.gr[hq * D + 8 * c + e] : 1.f;
     dg1[e] = dg2[e] = 0.f;
   }
   // All rows are requested before the first is worked on: the loads below and the stores further down go through
@@ -1219,7 +1218,7 @@ void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, 
 }
 
 void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const void* v, const float* gs, const float* gr,
-              int gstride, const SavedPtrs& sv, const void* dO, const void* dO_tail, void* dq, void* dk, void* dv, float* dgs,
+              const SavedPtrs& sv, const void* dO, const void* dO_tail, void* dq, void* dk, void* dv, float* dgs,
               float* dgr, const FastBwdWs& ws, hipStream_t st) {
   const FastBwdPlan pl = fast_bwd_plan(dm);
   // The RMS-norm backward runs as the prologue of the dq kernel (each wave on its own rows); the variant with
@@ -1251,7 +1250,7 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
   a.scale = dm.scale; a.scale_log2 = dm.scale * LOG2E;
   a.dO = (const uint16_t*)dO; a.dO_tail = (const uint16_t*)dO_tail;
   a.xs = (const uint16_t*)sv.xs; a.xr = (const uint16_t*)sv.xr;
-  a.rs = sv.rs; a.rr = sv.rr; a.gs = gs; a.gr = gr; a.gstride = gstride;
+  a.rs = sv.rs; a.rr = sv.rr; a.gs = gs; a.gr = gr;
   a.dgpart = (dgs || dgr) ? ws.dgpart : nullptr;
   // (softmax and ReLU maps only: with the identity map the host layer sends every call that keeps `saved` to the
   // general kernels, see make_layout)

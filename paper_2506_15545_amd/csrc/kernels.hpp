@@ -133,10 +133,10 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm);
 void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, int Tb, const void* dxr, float* U,
                         void* rstates, hipStream_t st);
 // dm.T: the padded length; the caller's tensors hold Tc rows per sequence.  dO rows from 128 * (Tc / 128) on are read from
-// dO_tail [B,128,Hq,D], zero past row Tc (may be NULL when Tc is a multiple of 128).  Gain rows lie gstride floats apart.
+// dO_tail [B,128,Hq,D], zero past row Tc (may be NULL when Tc is a multiple of 128).
 void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const void* v, const float* gs, const float* gr,
-              int gstride, const SavedPtrs& sv, const void* dO, const void* dO_tail, void* dq, void* dk, void* dv, float* dgs,
-              float* dgr, const FastBwdWs& ws, hipStream_t st);
+              const SavedPtrs& sv, const void* dO, const void* dO_tail, void* dq, void* dk, void* dv, float* dgs, float* dgr,
+              const FastBwdWs& ws, hipStream_t st);
 
 // prefill -> decode hand-over: rings of the last min(T, W) tokens and the state of all keys before them
 struct ExportPlan {
@@ -162,8 +162,6 @@ void chunk_ring(const LayerDims& dmc, int P, int R, int pos0, const void* k_ring
 
 // rows 128 * (T / 128) .. of a [B,T,H,D] bf16 tensor into its [B,128,H,D] tail buffer, zero from row T on
 void gather_tail(const void* src, void* tail, int B, int T, int H, int D, hipStream_t st);
-// gain rows [Hq,64] of the two branches side by side, [Hq,128]; a NULL gain is all ones
-void pack_gains64(const float* gs, const float* gr, float* out, int Hq, hipStream_t st);
 
 // launches the matrix-core probe loop; returns the FLOPs it issues
 double probe_mfma(float* sink, int iters, int blocks, hipStream_t st);

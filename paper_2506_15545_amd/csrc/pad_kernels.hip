@@ -1,4 +1,4 @@
-// Small rearrangements in front of the matrix-core backward kernels.
+// The rows of dO past the last whole tile, for the matrix-core backward kernels.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -19,15 +19,6 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const uint4* __restrict_
   }
 }
 
-// out [Hq][128]: the two gain rows of a head of 64 features side by side (ones where a gain is NULL)
-__global__ __launch_bounds__(256) void pad_rows_kernel(const float* __restrict__ gs, const float* __restrict__ gr,
-                                                       float* __restrict__ out, int Hq) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= Hq * 128) return;
-  const int h = i >> 7, d = i & 127;
-  out[i] = d < 64 ? (gs ? gs[h * 64 + d] : 1.f) : (gr ? gr[h * 64 + d - 64] : 1.f);
-}
-
 }  // namespace
 
 void gather_tail(const void* src, void* tail, int B, int T, int H, int D, hipStream_t st) {
@@ -35,11 +26,6 @@ void gather_tail(const void* src, void* tail, int B, int T, int H, int D, hipStr
   const long long n = ((long long)B * 128 * H * hv + 255) / 256;
   ProfScope ps("tail_rows_kernel(gather)", st);
   tail_rows_kernel<<<(unsigned)(n < 16384 ? n : 16384), 256, 0, st>>>((const uint4*)src, (uint4*)tail, B, T, T / 128 * 128, H, hv);
-}
-
-void pack_gains64(const float* gs, const float* gr, float* out, int Hq, hipStream_t st) {
-  ProfScope ps("pad_rows_kernel", st);
-  pad_rows_kernel<<<(Hq * 128 + 255) / 256, 256, 0, st>>>(gs, gr, out, Hq);
 }
 
 }  // namespace rattn

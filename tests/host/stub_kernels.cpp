@@ -16,7 +16,7 @@ void generic_bwd(const LayerDims&, int, const void*, const void*, const void*, c
 }
 void fast_fwd(const LayerDims&, const SeqTensors&, const void*, const float*, const float*, void*, const SavedPtrs&, float*,
               void*, hipStream_t, const float*) { ++g_stub_launches; }
-void fast_bwd(const LayerDims&, int, const void*, const void*, const void*, const float*, const float*, int, const SavedPtrs&,
+void fast_bwd(const LayerDims&, int, const void*, const void*, const void*, const float*, const float*, const SavedPtrs&,
               const void*, const void*, void*, void*, void*, float*, float*, const FastBwdWs&, hipStream_t) {
   ++g_stub_launches;
 }
@@ -27,7 +27,6 @@ void chunk_concat(const LayerDims&, int, int, int, int, const void*, const void*
                   hipStream_t) { ++g_stub_launches; }
 void chunk_ring(const LayerDims&, int, int, int, const void*, const void*, void*, void*, hipStream_t) { ++g_stub_launches; }
 void gather_tail(const void*, void*, int, int, int, int, hipStream_t) { ++g_stub_launches; }
-void pack_gains64(const float*, const float*, float*, int, hipStream_t) { ++g_stub_launches; }
 double probe_mfma(float*, int iters, int blocks, hipStream_t) { ++g_stub_launches; return 16.0 * iters * blocks * 4 * 32768.0; }
 void decode_step(const DecodeDims&, int, const void*, const void*, const void*, const int32_t*, void*, void*, float*,
                  const float*, const float*, void*, hipStream_t) { ++g_stub_launches; }

@@ -192,6 +192,27 @@ def test_fast_bwd_unit_gains_no_dgamma(B, T, Hq, Hkv, W):
         assert e["worst"] <= 1e-2 and e["rms"] <= 2e-3, f"{n} with and without gain gradients: {e}"
 
 
+# what a forward and backward of a bf16 layer on the matrix cores launches (records carry "(rev)" for the reverse states)
+MATRIX_CORE_LAUNCHES = {"rla_chunk_kernel", "rla_scan_kernel", "fwd_fused_kernel", "bwd_dq_kernel", "dgamma_reduce_kernel",
+                        "rla_chunk_kernel(rev)", "rla_scan_kernel(rev)", "bwd_dkv_kernel", "dkv_reduce_kernel"}
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("which", ["swa", "rla", "both"])
+def test_each_gain_alone_equals_the_other_at_one(which, D):
+    """The backward reads the gains where the caller has them; a NULL gain is all ones, bit for bit."""
+    x = synth.make_random_layer(1, 256, 4, 2, D, "bf16", 2801, with_dO=True, with_gains=True)
+    q, k, v, dO = x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), x["dO"].cuda()
+    gs = x["gamma_swa"].cuda() if which != "rla" else None
+    gr = x["gamma_rla"].cuda() if which != "swa" else None
+    ones = torch.ones(4, D, device="cuda")
+    grads = []
+    for a, b in ((gs, gr), (ones if gs is None else gs, ones if gr is None else gr)):
+        o, saved = rb.rattn_fwd(q, k, v, 96, a, b, softmax_scale=0.1, save_for_bwd=True)
+        grads.append((o,) + tuple(rb.rattn_bwd(q, k, v, saved, dO, 96, a, b, softmax_scale=0.1)))
+    assert all(torch.equal(a, b) for a, b in zip(*grads))
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,W", [
     (1, 256, 4, 2, 32),       # the tiny configuration's head size and window, in bf16
     (2, 384, 2, 1, 100),      # window no tile multiple
@@ -201,9 +222,8 @@ def test_fast_bwd_unit_gains_no_dgamma(B, T, Hq, Hkv, W):
     (2, 333, 2, 1, 20),       # the same, short
 ])
 def test_head_size_64_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
-    """Head size 64 (bf16, whole tiles or long enough for padded copies): rows are widened to 128 features with zeros
-    and run on the matrix-core kernels, which are told that 64 features carry data (RMS norms over 64, softmax feature
-    map over 64).  Forward, backward and gain gradients against the oracle at head size 64."""
+    """Head size 64 (bf16, T >= 128) runs on the matrix-core kernels' own tiles of 64 features, in place: no launch but
+    theirs, and the tail rows of dO at ragged lengths.  Forward, backward and gain gradients against the oracle."""
     D = 64
     x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 2700 + T + W, with_dO=True, with_gains=True)
     scale = 1.0 / math.sqrt(D)
@@ -216,8 +236,8 @@ def test_head_size_64_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
     torch.cuda.synchronize()
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
-    assert "fwd_fused_kernel" in names and "bwd_dkv_kernel" in names and "pad_rows_kernel" in names
-    assert "gen_fwd_kernel" not in names
+    assert "fwd_fused_kernel" in names and "bwd_dkv_kernel" in names
+    assert set(names) <= MATRIX_CORE_LAUNCHES | ({"tail_rows_kernel(gather)"} if T % 128 else set())
     kw = dict(scale=scale, gamma_swa=np64(gs), gamma_rla=np64(gr))
     ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, **kw)
     gmax = max(float(gs.abs().max()), float(gr.abs().max()), 1.0)
@@ -297,8 +317,8 @@ def test_fast_bwd_is_deterministic():
                                           (1, 200, 4, 2, 48), (2, 129, 2, 1, 64), (1, 383, 3, 1, 100), (3, 130, 2, 2, 128),
                                           (1, 255, 2, 1, 300)])
 def test_ragged_length_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
-    """Sequence lengths >= 128 that are no multiple of 128 run on the matrix-core kernels in place; only the last,
-    partial tile of every sequence goes through zero-padded buffers (the layer is causal; zero rows of dO add nothing
+    """Sequence lengths >= 128 that are no multiple of 128 run on the matrix-core kernels in place; only the rows of dO
+    past the last whole tile go through a zero-padded buffer (the layer is causal; zero rows of dO add nothing
     to any gradient): same bars as the aligned cases.  Tail lengths 1 .. 127, both state alignments, a window that is
     no multiple of 64, several sequences per batch (the batch stride is the true length)."""
     D = 128
@@ -314,7 +334,7 @@ def test_ragged_length_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
     assert "fwd_fused_kernel" in names and "bwd_dkv_kernel" in names and "tail_rows_kernel(gather)" in names
-    assert "pad_rows_kernel" not in names   # no copies of whole tensors
+    assert set(names) <= MATRIX_CORE_LAUNCHES | {"tail_rows_kernel(gather)"}   # no copies of whole tensors
     kw = dict(scale=scale, gamma_swa=np64(gs), gamma_rla=np64(gr))
     ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, **kw)
     gmax = max(float(gs.abs().max()), float(gr.abs().max()), 1.0)
