@@ -86,9 +86,7 @@ void chunk_ring(const LayerDims& dmc, int P, int R, int pos0, const void* k_ring
                 void* v_front, hipStream_t st) {
   const int row_vecs = dmc.D * 2 / 16;
   const long long n = (long long)dmc.B * dmc.Hkv * (P / 4) * row_vecs;
-  // Profile records of chunks whose ring does not end at a tile keep the name that tells this route from the other;
-  // nothing is fixed up afterwards: the gather puts P - R rows in front of the ring.
-  ProfScope ps(P == R ? "chunk_ring_kernel" : "chunk_fixup_kernel", st);
+  ProfScope ps("chunk_ring_kernel", st);
   chunk_ring_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((const uint4*)k_ring, (const uint4*)v_ring, (uint4*)k_front, (uint4*)v_front,
                                                      dmc.B, P, R, dmc.Hkv, dmc.W, (pos0 - R) % dmc.W, row_vecs);
 }
