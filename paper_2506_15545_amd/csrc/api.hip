@@ -60,7 +60,7 @@ struct Layout {
   size_t sv_xs, sv_xr, sv_lse, sv_rs, sv_rr, sv_states, saved_bytes;
   int state_stride;   // chunk states kept in `saved`: 0 = none, 1 = all, m = every m-th
   // generic forward / backward workspace
-  size_t gf_states, gen_fwd_bytes;
+  size_t gen_fwd_bytes;
   size_t gb_rstates, gb_dxs, gb_dxr, gb_delta, gb_dgpart, gen_bwd_bytes;
   // MFMA forward / backward workspace
   bool fast_fwd;
@@ -165,7 +165,6 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   }
   L->saved_bytes = off;
 
-  L->gf_states = 0;
   L->gen_fwd_bytes = align_up(nstate * 4);   // the same for both kinds of call (states that are kept are built in `saved`)
 
   off = 0;
@@ -188,7 +187,7 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
 }
 
 rattn::SavedPtrs saved_views(const Layout& L, void* saved) {
-  rattn::SavedPtrs sv = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, !L.fast_fwd, 0};
+  rattn::SavedPtrs sv = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   if (saved) {
     char* s = (char*)saved;
     sv.xs = s + L.sv_xs; sv.xr = s + L.sv_xr;
@@ -338,7 +337,7 @@ rattn_status rattn_fwd(const rattn_params* p, const void* q, const void* k, cons
                     sv.states && sv.state_stride <= 1 ? sv.states : (void*)(w + L.ff_states), st);
   } else
     rattn::generic_fwd(L.dm, p->dtype, q, k, v, gamma_swa, gamma_rla, o, sv,
-                       sv.states ? (float*)sv.states : (float*)((char*)workspace + L.gf_states), st);
+                       sv.states ? (float*)sv.states : (float*)workspace, st);
   return check_launch("rattn_fwd");
 }
 
@@ -504,7 +503,7 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
   const bool carried = pos0 > p->window;
   rattn::LayerDims dmx = dm;   // rows the state update counts
   dmx.T = C.R + p->T;
-  rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, !C.L2.fast_fwd, 0};
+  rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   rattn::SeqTensors t;
   // The forward computes the chunk's rows only, straight from q into o; the carried state is the initial value of the
   // chunk-state scan, of which every chunk row reads a state (the keys before it number at least `window` then).
@@ -521,7 +520,7 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
   } else {
     t.k = w + C.kc; t.v = w + C.vc; t.Tb = dmx.T;
     rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, k, v, k_ring, v_ring, w + C.kc, w + C.vc, st);
-    rattn::generic_fwd(dm, p->dtype, q, t.k, t.v, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.gf_states), st,
+    rattn::generic_fwd(dm, p->dtype, q, t.k, t.v, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws), st,
                        C.R, carried ? state : nullptr);
     rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0 - C.R, carried);
   }

@@ -278,7 +278,7 @@ __device__ __forceinline__ void rms_bwd_rows(const FastBwdArgs& a, int hq, size_
     for (int e = 0; e < 8; ++e) dl = fmaf(av[e], xs[e], dl);
     __builtin_nontemporal_store(apk, reinterpret_cast<bf16x8_t*>(dxs_w + off));
     if (with_r) __builtin_nontemporal_store(cpk, reinterpret_cast<bf16x8_t*>(dxr_w + off));
-    {  // staged in two 16-row pieces, see dxs_stage_addr
+    {  // staged in two 16-row pieces (see the function's header)
       const int R = r & 15;
       *reinterpret_cast<bf16x8_t*>(stage_s + (r >> 4) * TG::KT + R * TG::ROWB + ((c ^ swz<D>(R)) << 4)) = apk;
     }
@@ -542,12 +542,12 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
 }
 
 // ------------------------------------------------------------------------------------------------
-// LDS map of the dk/dv kernel: three slots, each a 64-row q tile followed by a 64-row dx tile; 32 KB for the
+// LDS map of the dk/dv kernel at D = 128 (D = 64 has a kernel of its own below): three slots, each a 64-row q tile followed by a 64-row dx tile; 32 KB for the
 // probabilities handed from the V-role to the K-role waves; per slot the 64 log-sum-exp and 64 delta values of
 // its rows.  The linear branch uses the same space as two buffers of one 128-row q tile and one 128-row dx tile
 // each: A = slots 0-1, B = slot 2 + the hand-over area (which first receives the reverse-state tile).
-template <int D> struct DkvLds {
-  static constexpr int SLOT = 2 * TileGeom<D>::KT, PEX = 3 * SLOT, STAT = PEX + 32768, BYTES = STAT + 3 * 2048;
+struct DkvLds {
+  static constexpr int D = 128, SLOT = 2 * TileGeom<D>::KT, PEX = 3 * SLOT, STAT = PEX + 32768, BYTES = STAT + 3 * 2048;
   // dk, dv leave as two [128][D] tiles (fp32 rows padded by 16 bytes when they are partial sums)
   static constexpr int OUT = 128 * (4 * D + 16);
   static_assert(2 * OUT <= BYTES, "output staging");
@@ -571,10 +571,11 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // (every wave has then left tile s-1, whose buffer it takes) and each wave waits for its share of tile s+1
 // before the second barrier of step s, so no further barrier is needed.  The loop has no other vector-memory
 // operation (row statistics arrive with the tiles), which is what makes the explicit counter waits exact.
-template <int D, int FM>
+template <int FM>
 __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
+  typedef DkvLds L;
+  constexpr int D = L::D;
   typedef TileGeom<D> TG;
-  typedef DkvLds<D> L;
   constexpr int KT = TG::KT, ND = D / 32, NB = TG::NB / 8;  // blocks of a 64-row tile per wave
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* pex = smem + L::PEX;
@@ -1278,8 +1279,8 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
   // the dk/dv kernel needs more LDS than a launch gets by default: raised once per instantiation
   static const bool lds_attr = [] {
     auto raise = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
-    return raise(reinterpret_cast<const void*>(bwd_dkv_kernel<128, FM_SOFTMAX>), DkvLds<128>::BYTES) &&
-           raise(reinterpret_cast<const void*>(bwd_dkv_kernel<128, FM_RELU>), DkvLds<128>::BYTES) &&
+    return raise(reinterpret_cast<const void*>(bwd_dkv_kernel<FM_SOFTMAX>), DkvLds::BYTES) &&
+           raise(reinterpret_cast<const void*>(bwd_dkv_kernel<FM_RELU>), DkvLds::BYTES) &&
            raise(reinterpret_cast<const void*>(bwd_dkv64_kernel<FM_SOFTMAX>), Dkv64Lds::BYTES) &&
            raise(reinterpret_cast<const void*>(bwd_dkv64_kernel<FM_RELU>), Dkv64Lds::BYTES);
   }();
@@ -1291,8 +1292,8 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
       if (relu) bwd_dkv64_kernel<FM_RELU><<<kgrid, 256, Dkv64Lds::BYTES, st>>>(a);
       else bwd_dkv64_kernel<FM_SOFTMAX><<<kgrid, 256, Dkv64Lds::BYTES, st>>>(a);
     } else {
-      if (relu) bwd_dkv_kernel<128, FM_RELU><<<kgrid, 512, DkvLds<128>::BYTES, st>>>(a);
-      else bwd_dkv_kernel<128, FM_SOFTMAX><<<kgrid, 512, DkvLds<128>::BYTES, st>>>(a);
+      if (relu) bwd_dkv_kernel<FM_RELU><<<kgrid, 512, DkvLds::BYTES, st>>>(a);
+      else bwd_dkv_kernel<FM_SOFTMAX><<<kgrid, 512, DkvLds::BYTES, st>>>(a);
     }
   }
   if (a.nsplit > 1) {

@@ -39,7 +39,6 @@ struct SavedPtrs {
   float* rs;
   float* rr;
   void* states;
-  bool f32;      // x^s, x^r are stored as fp32 whatever the tensor dtype
   int state_stride;  // `states` holds every chunk state (0 or 1) or states 0, m, 2m, ... only (m = 2, 4): the
                      // forward then works on the full set in its workspace and backward rebuilds the states in
                      // between from the stored ones (Sec. 3.2: store every m-th state, recompute the others)
@@ -114,7 +113,7 @@ struct FastBwdPlan {
   FastFwdPlan fwd;
   int nk;  // key tiles that have a linear branch = number of reverse states
   int nrchunks;  // reverse-time chunk-local products
-  int RB;  // row blocks of the prep kernel (dgamma partials)
+  int RB;  // gain-gradient partials: one per wave of the dq kernel
   int nsplit;  // work-groups that share the query heads of a key tile in the dk/dv kernel
   size_t u_bytes, rstate_bytes, dkv_part_bytes;
 };

@@ -53,7 +53,7 @@ def model_fwd_bwd(q, k, v, dO, W, scale=1.0, eps=1e-6, gamma_swa=None, gamma_rla
     r_dx, r_ds, r_dc, r_rst, r_g = rnd("dx"), rnd("ds"), rnd("dc"), rnd("rstates"), rnd("grads")
     q = np.asarray(q, np.float64); k = np.asarray(k, np.float64); v = np.asarray(v, np.float64)
     if q.shape[1] % 128 != 0:
-        # the kernels run ragged lengths on zero-padded copies (the layer is causal, zero rows of dO add nothing)
+        # the kernels see ragged lengths as whole tiles (the layer is causal, zero rows of dO add nothing)
         T0 = q.shape[1]
         pad = lambda a: None if a is None else np.concatenate(
             [np.asarray(a, np.float64), np.zeros((a.shape[0], -T0 % 128) + a.shape[2:])], axis=1)

@@ -32,7 +32,7 @@ def draw_cases(n, seed=20250615):
     for _ in range(n):
         T = 128 * rng.randint(1, 6)
         if rng.random() < 0.35:
-            T += rng.randint(1, 127)       # a ragged length: the last, partial tile goes through the tail buffers
+            T += rng.randint(1, 127)       # a ragged length
         G = rng.choice([1, 2, 3, 4, 6, 8])
         Hkv = rng.choice([1, 2, 3])
         B = rng.choice([1, 1, 2, 3])
