@@ -390,6 +390,29 @@ __global__ __launch_bounds__(NW * 64, decode_occ(MULTI)) void decode_kernel(
           c[e] += part_r[(r * HBmax + hh) * D + lane + 64 * e];
         }
       }
+      // The window branch read the slot, while it changed from the evicted row to the new one, at a probability of 0, and
+      // 0 times an infinite or NaN value is not 0.  A feature that came out without a number is formed again, key by key
+      // without the slot.  (Dropping the row inside the branch costs every call: 24 x 8 KV heads, W = 2048, 41.0 -> 42.1 us.)
+      float z = 0.f;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) z += a[e] * 0.f;
+      if (evict && __any(z != 0.f)) {
+        float again[EPL];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) again[e] = Set::pexp(lnew[hh], M) * io_traits<IO>::ld(vnr + lane + 64 * e);
+        for (int s = 0; s < W; ++s) {
+          if (s == slot) continue;
+          float dot = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e)
+            dot += io_traits<IO>::ld(qs + hh * QS + lane + 64 * e) * io_traits<IO>::ld(kr + (size_t)s * D + lane + 64 * e);
+          const float prob = Set::pexp(wave_sum(dot) * sc, M);
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) again[e] += prob * io_traits<IO>::ld(vr + (size_t)s * D + lane + 64 * e);
+        }
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) a[e] = a[e] * 0.f == 0.f ? a[e] : again[e];
+      }
       const float inv = 1.f / den;
       float s1 = 0.f, s2 = 0.f;
 #pragma unroll

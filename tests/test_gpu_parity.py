@@ -590,3 +590,39 @@ def test_general_backward_of_rows_that_see_one_key(T, W, dtype, D):
             err = float(np.linalg.norm(np64(g) - ref[n]) / np.linalg.norm(ref[n]))
             print(f"T={T} W={W} D={D} {n}: {err:.2e}", flush=True)
             assert err <= (1e-6 if W == 1 else 3e-4), n
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G,W,pos", [(2, 32, 32), (1, 50, 117), (5, 300, 911), (17, 16, 35)])
+def test_decode_infinite_value_in_the_changing_slot(G, W, pos, D, dtype):
+    """The slot that the new token takes holds the token that leaves the window, which is in the state and no longer in the
+    softmax branch.  An infinite value feature of it makes
+    that feature of the state infinite, so the norm of the linear branch takes all its other features to 0: there the
+    output is the softmax branch alone, which is the one without the infinity, bit for bit.  So with the branches exchanged
+    for the new token's value."""
+    x = synth.make_random_layer(1, W, G, 1, D, dtype, 4900 + W)
+    q = dev(synth.make_random_layer(1, 1, G, 1, D, dtype, 4901)["q"])[0]
+    k, v = dev(x["k"]), dev(x["v"])
+    kn, vn = k[:, 0].clone(), v[:, 1].clone()
+    gr0 = torch.zeros(G, D, device=q.device)
+    out = []
+    for value, gr in ((math.inf, None), (None, gr0)):
+        kr, vr = (t.transpose(1, 2).clone() for t in (k, v))
+        if value is not None:
+            vr[0, 0, pos % W, 3] = value
+        S = torch.ones(1, 1, D, D, device=q.device)
+        out.append(rb.rattn_decode_step(q, kn, vn, torch.tensor([pos], dtype=torch.int32, device=q.device), kr, vr, S, None, gr,
+                                        softmax_scale=0.1))
+    others = torch.arange(D, device=q.device) != 3
+    assert torch.equal(out[0][..., others], out[1][..., others])
+    out = []
+    for value, gs in ((math.inf, None), (None, gr0)):
+        kr, vr = (t.transpose(1, 2).clone() for t in (k, v))
+        vx = vn.clone()
+        if value is not None:
+            vx[0, 0, 3] = value
+        S = torch.ones(1, 1, D, D, device=q.device)
+        out.append(rb.rattn_decode_step(q, kn, vx, torch.tensor([pos], dtype=torch.int32, device=q.device), kr, vr, S, gs, None,
+                                        softmax_scale=0.1))
+    assert torch.equal(out[0][..., others], out[1][..., others])
