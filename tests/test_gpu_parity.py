@@ -626,3 +626,20 @@ def test_decode_infinite_value_in_the_changing_slot(G, W, pos, D, dtype):
         out.append(rb.rattn_decode_step(q, kn, vx, torch.tensor([pos], dtype=torch.int32, device=q.device), kr, vr, S, gs, None,
                                         softmax_scale=0.1))
     assert torch.equal(out[0][..., others], out[1][..., others])
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,D,W,pos", [(8, 8, 2, 128, 1000, 3000), (4, 8, 2, 128, 256, 900), (8, 4, 2, 64, 300, 3000)])
+def test_decode_fp32_logits_do_not_round_in_long_chains(N, Hq, Hkv, D, W, pos):
+    """fp32, logits of standard deviation 4.  A sum of D products over a tree of chains of 8 rounds by about
+    2^-25 sqrt(8 D / 2 + D log2(D / 8)) against products of size 1 (chains) and sums (tree), which the scale turns into
+    4 / sqrt(D) times as much in a logit and in its probability: 3.4e-7; in two chains of D / 2 it is 6.8e-7 (D = 128).  The
+    rest of the step adds about 1.5e-7, independent of it."""
+    g = torch.Generator().manual_seed(51)
+    r = lambda *s: torch.randn(*s, generator=g)
+    q, k, v, kr, vr = r(N, Hq, D), r(N, Hkv, D), r(N, Hkv, D), r(N, Hkv, W, D), r(N, Hkv, W, D)
+    S, p = r(N, Hkv, D, D) * math.sqrt((pos - W) * math.e) / D, torch.full((N,), pos, dtype=torch.int32)
+    ref = orc.decode_step(np64(q), np64(k), np64(v), p.numpy(), np64(kr), np64(vr), np64(S), W, scale=4 / math.sqrt(D))[0]
+    o = rb.rattn_decode_step(dev(q), dev(k), dev(v), dev(p), dev(kr), dev(vr), dev(S), softmax_scale=4 / math.sqrt(D))
+    err = float(np.linalg.norm(np64(o) - ref) / np.linalg.norm(ref))
+    print(f"decode fp32 D={D} W={W}: {err:.2e}", flush=True)
+    assert err <= 4e-7
