@@ -19,6 +19,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
+#include <type_traits>
 
 namespace rattn {
 
@@ -36,43 +37,22 @@ struct FastFwdArgs {
   float scale_log2, eps;
 };
 
-// One 32-key sub-tile of the softmax branch for this wave's 32 queries (lane = query):
-// S^T = K Q^T, running-max update, P^T = 2^(c S^T - m), O^T += V^T P^T.
-// `m` is the reference maximum in scaled log2 units.  It is only raised (and O, l rescaled) when some
-// row's maximum exceeds it by more than RESCALE_TH, so P stays below 2^RESCALE_TH and almost every
-// sub-tile takes the short path: 16 fma, 8 max3, 16 exp, 16 add, 8 cvt per lane.  The exponent
-// arguments x = c*s - m are formed first and the maximum is taken over them (they are already needed,
-// and being fma results they need no NaN quieting).  `masked` is wave-uniform: only the window-edge and
-// diagonal sub-tiles pay for the per-element mask.  CUR (LDS buffer) and KS (sub-tile) are compile-time
-// so every LDS address is a per-lane register plus an immediate.
+// The sweep over the 32-key sub-tiles j (upper keys first) for this wave's 32 queries (lane = query) is software-pipelined.
+// Step j is one instruction stream of
+//   1. S^T(j+1) = K Q^T (matrix cores)   ||  row maximum of S^T(j);  row sum and bf16 packing of P^T(j-1)
+//   2. O^T += V^T P^T(j-1)               ||  P^T(j) = 2^(c S^T(j) - m)
+// `m` is the reference maximum in scaled log2 units.  It is only raised (and O, l rescaled) when some row's maximum exceeds
+// it by more than RESCALE_TH, so P stays below 2^RESCALE_TH; the exponentials do not wait for that decision, they are
+// formed again in the rare step that takes it.  Vector work is dealt out evenly between the matrix instructions and operand
+// reads run FWD_AHEAD instructions in front of their use, across the border of 1 and 2; scheduling fences keep the order of
+// the source.  What bounds the loop: a SIMD starts one vector or matrix instruction every 4.4 cycles (an exponential takes
+// two such slots, an LDS read about half of one), which at 16 matrix instructions of 32 cycles per step is as much time as
+// the matrix pipe needs, so neither may wait for the other.  Left to the scheduler, every V operand was read right in front
+// of its use and the exponentials and sums stood apart from the matrix instructions.  32768 tokens, W = 4096: 1.67 -> 1.52
+// ms; 3B-shaped layer: 0.211 -> 0.204 ms (its clock falls as the pipes fill: 2.1 of 2.4 GHz).
 constexpr float RESCALE_TH = 8.f;
 constexpr float M_INIT = -1.0e30f;  // finite "minus infinity" for the running maximum
-
-// The sweep is software-pipelined per wave over its sequence of 32-key sub-tiles j (upper keys first):
-// step j issues, in one instruction stream, the S^T chain of sub-tile j+1 (matrix cores), the softmax of
-// sub-tile j (vector ALU) and the O^T update of sub-tile j-1 (matrix cores), so the two kinds of work
-// overlap inside every wave instead of relying on another wave being in the opposite phase.
-
-// A: S^T = K Q^T for sub-tile KS of the K tile in buffer KB
-template <int D, int KB, int KS>
-__device__ __forceinline__ void qk_chain(const unsigned char* smem, const LaneOff<D>& lo, const bf16x8_t (&qop)[D / 16],
-                                         f32x16_t& s) {
-  const unsigned char* kt = smem + KB * TileGeom<D>::KT;
-  s = f32x16_t{0};
-#pragma unroll
-  for (int dk = 0; dk < D / 16; ++dk) s = mfma32(lds_row<D>(kt, lo, 32 * KS, dk), qop[dk], s);
-}
-
-// C: O^T += V^T P^T for sub-tile KS of the V tile in buffer VB
-template <int D, int VB, int KS>
-__device__ __forceinline__ void pv_chain(const unsigned char* smem, const LaneOff<D>& lo, const bf16x8_t (&pop)[2],
-                                         f32x16_t (&oacc)[D / 32]) {
-  const unsigned char* vt = smem + (2 + VB) * TileGeom<D>::KT;
-#pragma unroll
-  for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) oacc[dt] = mfma32(lds_trp<D>(vt, lo, 32 * KS + 16 * mf, dt), pop[mf], oacc[dt]);
-}
+constexpr int FWD_AHEAD = 4;
 
 struct SweepGeom {
   int kt_lo, ntiles, qa, W, kmin;
@@ -85,88 +65,123 @@ struct SweepGeom {
   }
 };
 
-// Step j with R = j % 4 (fixes which LDS buffers / halves sub-tiles j+1 and j-1 live in).  Every wave runs
-// every step of the work-group's key range: sub-tiles outside a wave's own window are fully masked (their
-// probabilities are exactly 0), which costs a few percent of the matrix work and keeps one straight
-// code path.  Two scheduling regions, each pairing a matrix-core chain with vector work:
-//   1. S^T(j+1) = K Q^T          ||  exponent arguments x = c*S^T(j) - m and their row maximum
-//   2. O^T += V^T P^T(j-1)       ||  P^T(j) = 2^x, row sums, bf16 packing
-// The reference maximum m is raised only when some row exceeds it by RESCALE_TH (rare); the rescale of
-// O is applied after region 2, i.e. after the update that was still expressed against the old m.
-template <int D, int R, bool DO_C>
+template <int D> struct SweepState {
+  f32x16_t oacc[D / 32];   // O^T against the reference maximum m
+  f32x16_t s;              // S^T of the next sub-tile to be worked on
+  float p[16];             // P^T of the last one
+  float m, l;
+};
+
+// operand i of S^T = K Q^T for sub-tile half KS of the K tile in buffer KB; of O^T += V^T P^T for the V tile in buffer VB
+template <int D, int KB, int KS>
+__device__ __forceinline__ bf16x8_t k_operand(const unsigned char* smem, const LaneOff<D>& lo, int i) {
+  return lds_row<D>(smem + KB * TileGeom<D>::KT, lo, 32 * KS, i);
+}
+template <int D, int VB, int KS>
+__device__ __forceinline__ bf16x8_t v_operand(const unsigned char* smem, const LaneOff<D>& lo, int i) {
+  return lds_trp<D>(smem + (2 + VB) * TileGeom<D>::KT, lo, 32 * KS + 16 * (i / (D / 32)), i % (D / 32));
+}
+template <int D, int KB, int KS>
+__device__ __forceinline__ void qk_chain(const unsigned char* smem, const LaneOff<D>& lo, const bf16x8_t (&qop)[D / 16],
+                                         f32x16_t& s) {
+  s = f32x16_t{0};
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) s = mfma32(k_operand<D, KB, KS>(smem, lo, i), qop[i], s);
+}
+__device__ __forceinline__ void sum_and_pack(const float (&p)[16], float& l, bf16x8_t (&pop)[2]) {
+  float ps = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) ps += p[i];
+  l += ps;
+  pop[0] = pack_bf16x8(&p[0]);
+  pop[1] = pack_bf16x8(&p[8]);
+}
+template <int D, int VB, int KS>
+__device__ __forceinline__ void pv_chain(const unsigned char* smem, const LaneOff<D>& lo, const bf16x8_t (&pop)[2],
+                                         f32x16_t (&oacc)[D / 32]) {
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) oacc[i % (D / 32)] = mfma32(v_operand<D, VB, KS>(smem, lo, i), pop[i / (D / 32)], oacc[i % (D / 32)]);
+}
+
+// Step j with R = j % 4 (fixes which LDS buffers / halves sub-tiles j+1 and j-1 live in, so that every LDS address is a
+// per-lane register plus an immediate).  Every wave runs every step of the work-group's key range: sub-tiles outside a
+// wave's own window are fully masked (their probabilities are exactly 0), which costs a few percent of the matrix work and
+// keeps one straight code path.  PREV: there is a sub-tile j-1.  request(i), i = 0 .. 2 D/16 - 1: tile loads to be dealt
+// out between the matrix instructions.
+template <int D, int R, bool PREV, typename F>
 __device__ __forceinline__ void sweep_step(const unsigned char* smem, const LaneOff<D>& lo, const SweepGeom& gm, int j,
-                                           int myq, float scale_log2, const bf16x8_t (&qop)[D / 16], f32x16_t (&oacc)[D / 32],
-                                           float& m, float& l, f32x16_t& s_cur, bf16x8_t (&p_prev)[2], bool& pend,
-                                           float& alpha_pend, int lane) {
+                                           int myq, float scale_log2, const bf16x8_t (&qop)[D / 16], SweepState<D>& st,
+                                           int lane, F&& request) {
   constexpr int KS = R & 1;                           // sub-tile half of both j+1 and j-1
   constexpr int KB = (R == 1 || R == 2) ? 1 : 0;      // K buffer of sub-tile j+1
   constexpr int VB = (R == 0 || R == 3) ? 1 : 0;      // V buffer of sub-tile j-1
-  const int h = lane >> 5;
-  if (pend) {  // the rescale of O the previous step left behind (rare; wave-uniform)
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) oacc[dt] *= alpha_pend;
-    pend = false;
-  }
+  constexpr int N = D / 16, PER = 16 / N;             // matrix instructions of each half of the step
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
   if (!gm.full(j)) {  // wave-uniform: window edge, diagonal, or a sub-tile this wave does not see at all
-    const int ka = gm.ka(j);
     // in the window <=> 0 <= query - key < W: one unsigned compare per element against a per-lane base
-    const unsigned dist0 = (unsigned)(myq - ka - 4 * h), width = (unsigned)min(gm.W, myq - gm.kmin + 1);
+    unsigned dist0 = (unsigned)(myq - gm.ka(j) - 4 * (lane >> 5)), width = (unsigned)min(gm.W, myq - gm.kmin + 1);
+    asm volatile("" : "+v"(dist0));   // (nothing of this rare form is kept in registers across the steps)
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      s_cur[i] = (dist0 - (unsigned)(8 * (i >> 2) + (i & 3)) < width) ? s_cur[i] : -INFINITY;
+      st.s[i] = (dist0 - (unsigned)(8 * (i >> 2) + (i & 3)) < width) ? st.s[i] : -INFINITY;
   }
-  // ---- region 1
+  bf16x8_t op[FWD_AHEAD];
+#pragma unroll
+  for (int i = 0; i < FWD_AHEAD; ++i) op[i] = k_operand<D, KB, KS>(smem, lo, i);
+  // ---- 1
   f32x16_t s_next;
-  qk_chain<D, KB, KS>(smem, lo, qop, s_next);
-  float x[16];
+  float mx = -INFINITY, ps = 0.f;
+  bf16x8_t pop[2] = {};
+  fence();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) x[i] = __builtin_fmaf(s_cur[i], scale_log2, -m);
-  float mx = fmaxf(fmaxf(x[0], x[1]), x[2]);
+  for (int i = 0; i < N; ++i) {
+    s_next = mfma32(op[i % FWD_AHEAD], qop[i], i == 0 ? f32x16_t{0} : s_next);
+    if (i + FWD_AHEAD < N) op[i % FWD_AHEAD] = k_operand<D, KB, KS>(smem, lo, i + FWD_AHEAD);
+    else if (PREV) op[i % FWD_AHEAD] = v_operand<D, VB, KS>(smem, lo, i + FWD_AHEAD - N);
 #pragma unroll
-  for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, x[i]), x[i + 1]);
-  mx = half_max(fmaxf(mx, x[15]));
-  __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
-    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // 3 VALU
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // 1 LDS read
-  }
-  const bool trig = __builtin_amdgcn_ballot_w64(mx > RESCALE_TH) != 0;
-  if (trig) {
-    float sm = fmaxf(s_cur[0], s_cur[1]);
-#pragma unroll
-    for (int i = 2; i < 16; ++i) sm = fmaxf(sm, s_cur[i]);
-    const float m_new = fmaxf(m, half_max(sm) * scale_log2);
-    const float alpha = fast_exp2(m - m_new);
-    m = m_new;
-    l *= alpha;
-    // O is rescaled at the start of the next step: this step's O update below is still expressed against the
-    // old m, and keeping the rescale out of this place leaves the update and the exponentials in one block
-    // of straight-line code, where they overlap
-    pend = true;
-    alpha_pend = alpha;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = __builtin_fmaf(s_cur[i], scale_log2, -m);
-  }
-  // ---- region 2
-  if (DO_C) pv_chain<D, VB, KS>(smem, lo, p_prev, oacc);
-  float ps = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) { x[i] = fast_exp2(x[i]); ps += x[i]; }
-  l += ps;
-  p_prev[0] = pack_bf16x8(&x[0]);
-  p_prev[1] = pack_bf16x8(&x[8]);
-  if (DO_C) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-    for (int i = 0; i < D / 16; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // 1 MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // 6 VALU
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // 2 LDS reads
+    for (int e = PER * i; e < PER * i + PER; e += 2) {
+      if (PREV) { ps += st.p[e]; ps += st.p[e + 1]; }
+      asm volatile("v_max3_f32 %0, %0, %2, %3" : "+v"(mx), "+v"(ps) : "v"(st.s[e]), "v"(st.s[e + 1]));
     }
+    if (PREV && i == N / 2 - 1) pop[0] = pack_bf16x8(&st.p[0]);
+    if (PREV && i == N - 1) pop[1] = pack_bf16x8(&st.p[8]);
+    request(i);
+    fence();
   }
-  s_cur = s_next;
+  st.l += ps;
+  // ---- 2
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (PREV) {
+      st.oacc[i % (D / 32)] = mfma32(op[i % FWD_AHEAD], pop[i / (D / 32)], st.oacc[i % (D / 32)]);
+      if (i + FWD_AHEAD < N) op[i % FWD_AHEAD] = v_operand<D, VB, KS>(smem, lo, i + FWD_AHEAD);
+    }
+#pragma unroll
+    for (int e = PER * i; e < PER * i + PER; ++e) {
+      st.p[e] = fast_exp2(__builtin_fmaf(st.s[e], scale_log2, -st.m));
+      asm volatile("" : "+v"(st.p[e]));   // stays between the matrix instructions
+    }
+    if (i == N / 2 - 1) mx = half_max(mx) * scale_log2;
+    request(N + i);
+    fence();
+  }
+  if (__builtin_amdgcn_ballot_w64(mx - st.m > RESCALE_TH) != 0) {
+    const float m_new = fmaxf(st.m, mx);
+    const float alpha = fast_exp2(st.m - m_new);
+    st.m = m_new;
+    st.l *= alpha;   // (l and O hold the sub-tiles up to j - 1)
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) st.oacc[dt] *= alpha;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) st.p[i] = fast_exp2(__builtin_fmaf(st.s[i], scale_log2, -m_new));
+  }
+  st.s = s_next;
+}
+
+// keeps what is computed from x in a rare form of the code out of the registers of the code around it
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 // Waves per SIMD: the 32 x D accumulators of both branches and the q operand take most of 256 registers at D = 128, half
@@ -219,12 +234,12 @@ __global__ __launch_bounds__(256, fwd_occ(D)) void fwd_fused_kernel(FastFwdArgs 
   auto load_k = [&](int n) {
     const int it = ntiles - 1 - n;
     if (whole) tile_load_async_s<D, NB>(a.k.back + sweep_off + (size_t)(64 * it) * kstride, kstride, smem + (n & 1) * KT, w * NB, dl);
-    else tile_load_async_s<D, NB>(k_rows(kt_lo + 64 * it), kstride, smem + (n & 1) * KT, w * NB, dl, lane);
+    else tile_load_async_s<D, NB>(k_rows(kt_lo + 64 * it), kstride, smem + (n & 1) * KT, w * NB, dl, opaque(lane));
   };
   auto load_v = [&](int n) {
     const int it = ntiles - 1 - n;
     if (whole) tile_load_async_s<D, NB>(a.v.back + sweep_off + (size_t)(64 * it) * kstride, kstride, smem + (2 + (n & 1)) * KT, w * NB, dl);
-    else tile_load_async_s<D, NB>(v_rows(kt_lo + 64 * it), kstride, smem + (2 + (n & 1)) * KT, w * NB, dl, lane);
+    else tile_load_async_s<D, NB>(v_rows(kt_lo + 64 * it), kstride, smem + (2 + (n & 1)) * KT, w * NB, dl, opaque(lane));
   };
   load_k(0);
   load_v(0);
@@ -237,42 +252,64 @@ __global__ __launch_bounds__(256, fwd_occ(D)) void fwd_fused_kernel(FastFwdArgs 
   }
   wait_vmem();
   __syncthreads();
-  f32x16_t oacc[ND];
+  SweepState<D> sw;
+  f32x16_t (&oacc)[ND] = sw.oacc;
 #pragma unroll
   for (int dt = 0; dt < ND; ++dt) oacc[dt] = f32x16_t{0};
-  float m = M_INIT, l = 0.f;
+  sw.m = M_INIT; sw.l = 0.f;
   SweepGeom gm;
   gm.kt_lo = kt_lo; gm.ntiles = ntiles; gm.qa = t0 + 32 * w; gm.W = W - (GAP ? a.gap : 0);
   gm.kmin = a.kmin;
-  f32x16_t s_cur;
-  bf16x8_t p_prev[2];
-  bool pend = false;
-  float alpha_pend = 1.f;
-  qk_chain<D, 0, 1>(smem, lo, qop, s_cur);
+  qk_chain<D, 0, 1>(smem, lo, qop, sw.s);
   // step 0 has no earlier sub-tile to fold in; the step after the last one only folds
-  sweep_step<D, 0, false>(smem, lo, gm, 0, myq, a.scale_log2, qop, oacc, m, l, s_cur, p_prev, pend, alpha_pend, lane);
+  const auto nothing = [](int) {};
+  sweep_step<D, 0, false>(smem, lo, gm, 0, myq, a.scale_log2, qop, sw, lane, nothing);
+  // Behind the barrier in front of step 2n + 1 the buffers of K tile n and V tile n - 1 are free: K tile n + 2 and V tile
+  // n + 1 are requested load by load in the course of that step and have the next one to arrive.  (A wave that makes its
+  // loads in one go stands still while the address unit works them off: 8 loads, 46 cycles each.)
+  const ptrdiff_t tile_bytes = (ptrdiff_t)(128 * kstride), load_bytes = (ptrdiff_t)(2 * TileGeom<D>::RPB * kstride);
+  const unsigned char* k_next = reinterpret_cast<const unsigned char*>(a.k.back + sweep_off) + (ntiles - 3) * tile_bytes + w * NB * load_bytes;
+  const unsigned char* v_next = reinterpret_cast<const unsigned char*>(a.v.back + sweep_off) + (ntiles - 2) * tile_bytes + w * NB * load_bytes;
+  const unsigned lds_wave = (unsigned)(size_t)RATTN_LDS(smem) + w * NB * 1024;
+  auto odd_step = [&](int n, auto par) {   // step 2n + 1, par = n & 1
+    constexpr int P = decltype(par)::value, EVERY = D / 16 / NB;
+    const bool more_k = n + 2 < ntiles, more_v = n + 1 < ntiles, go_k = whole && more_k, go_v = whole && more_v;
+    if (!whole) {
+      if (more_k) load_k(n + 2);
+      if (more_v) load_v(n + 1);
+    }
+    sweep_step<D, 2 * P + 1, true>(smem, lo, gm, 2 * n + 1, myq, a.scale_log2, qop, sw, lane, [&](int i) {
+      if (i % EVERY) return;
+      const int part = i / EVERY % NB;
+      if (i / EVERY < NB) {
+        if (go_k) dma16s(k_next + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + P * KT + part * 1024);
+      } else {
+        if (go_v) dma16s(v_next + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + (3 - P) * KT + part * 1024);
+      }
+    });
+    k_next -= tile_bytes;
+    v_next -= tile_bytes;
+  };
   for (int n = 0; n < ntiles; n += 2) {
-    if (n > 0) sweep_step<D, 0, true>(smem, lo, gm, 2 * n, myq, a.scale_log2, qop, oacc, m, l, s_cur, p_prev, pend, alpha_pend, lane);
+    if (n > 0) sweep_step<D, 0, true>(smem, lo, gm, 2 * n, myq, a.scale_log2, qop, sw, lane, nothing);
     wait_vmem();
     __syncthreads();
-    if (n + 2 < ntiles) load_k(n + 2);
-    if (n + 1 < ntiles) load_v(n + 1);
-    sweep_step<D, 1, true>(smem, lo, gm, 2 * n + 1, myq, a.scale_log2, qop, oacc, m, l, s_cur, p_prev, pend, alpha_pend, lane);
+    odd_step(n, std::integral_constant<int, 0>{});
     if (n + 1 < ntiles) {
-      sweep_step<D, 2, true>(smem, lo, gm, 2 * n + 2, myq, a.scale_log2, qop, oacc, m, l, s_cur, p_prev, pend, alpha_pend, lane);
+      sweep_step<D, 2, true>(smem, lo, gm, 2 * n + 2, myq, a.scale_log2, qop, sw, lane, nothing);
       wait_vmem();
       __syncthreads();
-      if (n + 3 < ntiles) load_k(n + 3);
-      if (n + 2 < ntiles) load_v(n + 2);
-      sweep_step<D, 3, true>(smem, lo, gm, 2 * n + 3, myq, a.scale_log2, qop, oacc, m, l, s_cur, p_prev, pend, alpha_pend, lane);
+      odd_step(n + 1, std::integral_constant<int, 1>{});
     }
   }
-  if (pend) {
-#pragma unroll
-    for (int dt = 0; dt < ND; ++dt) oacc[dt] *= alpha_pend;
+  {
+    bf16x8_t pop[2];
+    sum_and_pack(sw.p, sw.l, pop);
+    if (ntiles & 1) pv_chain<D, 0, 0>(smem, lo, pop, oacc);
+    else pv_chain<D, 1, 0>(smem, lo, pop, oacc);
   }
-  if (ntiles & 1) pv_chain<D, 0, 0>(smem, lo, p_prev, oacc);
-  else pv_chain<D, 1, 0>(smem, lo, p_prev, oacc);
+  const float m = sw.m;
+  float l = sw.l;
   __syncthreads();
   // the two lowest key tiles are still resident: tile `it` sits in buffer (ntiles-1-it) & 1
 

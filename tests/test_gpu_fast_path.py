@@ -302,6 +302,21 @@ def test_state_policy_and_chunk_size_variants(policy, chunk, B, T, Hq, Hkv, W):
     assert saved0.numel() - saved.numel() == (nst - kept) * B * Hkv * 128 * 128 * 2
 
 
+@pytest.mark.parametrize("T,W,D,rise", [(640, 640, 128, 6.0), (700, 700, 64, 6.0), (256, 256, 128, 0.2), (1100, 300, 128, 2.0),
+                                        (129, 129, 64, 20.0), (450, 131, 128, 8.0)])
+def test_running_maximum_raised_in_late_steps(T, W, D, rise):
+    """Logits that grow by `rise` per 32 keys towards older keys: the sweep, which starts at the diagonal, has to raise its
+    reference maximum (and form that sub-tile's probabilities again) in most steps, in few, or never after the first;
+    odd and even numbers of key tiles, whole and ragged lengths."""
+    x = synth.make_random_layer(1, T, 4, 2, D, "bf16", 2500 + T + D)
+    scale = 1.0 / math.sqrt(D)
+    x["q"][..., 0] = 8.0
+    x["k"][..., 0] = (torch.arange(T - 1, -1, -1) * (rise / 32 / (8.0 * scale)))[None, :, None].to(torch.bfloat16)
+    o = rb.rattn_fwd(x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), W, softmax_scale=scale)
+    ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, scale=scale)["o"]
+    pm.assert_out_bf16(np64(o), ref)
+
+
 def test_fast_bwd_is_deterministic():
     x = synth.make_random_layer(1, 512, 4, 2, 128, "bf16", 6, with_dO=True)
     q, k, v, dO = x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), x["dO"].cuda()
