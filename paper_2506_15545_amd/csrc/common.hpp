@@ -86,6 +86,31 @@ __device__ __forceinline__ void feature_row(const float (&x)[EPL], float (&f)[EP
     for (int e = 0; e < EPL; ++e) f[e] = phi == PHI_RELU ? fmaxf(x[e], 0.f) : x[e];
   }
 }
+// Tile `i` of a DgammaSum, by 256 threads: 32 consecutive (head, feature) entries of one of the two gains.  Thread
+// (rg = tid / 8, c = tid % 8) adds every 32nd partial starting at rg for entries 4c .. 4c+3 (independent 16-byte loads),
+// then the 32 sums are added in order.
+__device__ __forceinline__ void dgamma_reduce_tile(const DgammaSum& dg, int i) {
+  __shared__ float4 part[32][8];
+  const int half = dg.HD / 32, which = i / half, rg = threadIdx.x >> 3, c = threadIdx.x & 7;
+  float* out = which == 0 ? dg.dgs : which == 1 ? dg.dgr : nullptr;
+  if (!out) return;   // (block-uniform)
+  const int e = (i % half) * 32 + 4 * c;
+  const float* src = dg.part + (size_t)which * dg.RB * dg.HD + e;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+  for (int r = rg; r < dg.RB; r += 32) {
+    const float4 x = *reinterpret_cast<const float4*>(src + (size_t)r * dg.HD);
+    s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+  }
+  part[rg][c] = s;
+  __syncthreads();
+  if (rg == 0) {
+    float4 t = part[0][c];
+#pragma unroll
+    for (int j = 1; j < 32; ++j) { const float4 x = part[j][c]; t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
+    *reinterpret_cast<float4*>(out + e) = t;
+  }
+}
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 

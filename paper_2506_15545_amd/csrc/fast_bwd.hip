@@ -39,33 +39,7 @@ struct FastBwdArgs {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Sums the per-wave gain-gradient partials of the dq kernel's prologue, in a fixed order.  grid (HD / 32, 2),
-// 256 threads: the work-group owns 32 consecutive (head, feature) entries of one of the two gains; thread
-// (rg = tid / 8, c = tid % 8) adds every 32nd partial starting at rg for entries 4c .. 4c+3 (independent 16-byte
-// loads), then the 32 sums are added in order.
-__global__ __launch_bounds__(256) void dgamma_reduce_kernel(const float* __restrict__ dgpart, float* __restrict__ dgs,
-                                                            float* __restrict__ dgr, int RB, int HD) {
-  __shared__ float4 part[32][8];
-  const int which = blockIdx.y, rg = threadIdx.x >> 3, c = threadIdx.x & 7;
-  float* out = which ? dgr : dgs;
-  if (!out) return;
-  const int i = blockIdx.x * 32 + 4 * c;
-  const float* src = dgpart + (size_t)which * RB * HD + i;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-  for (int r = rg; r < RB; r += 32) {
-    const float4 x = *reinterpret_cast<const float4*>(src + (size_t)r * HD);
-    s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
-  }
-  part[rg][c] = s;
-  __syncthreads();
-  if (rg == 0) {
-    float4 t = part[0][c];
-#pragma unroll
-    for (int j = 1; j < 32; ++j) { const float4 x = part[j][c]; t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w; }
-    *reinterpret_cast<float4*>(out + i) = t;
-  }
-}
+__global__ __launch_bounds__(256) void dgamma_reduce_kernel(DgammaSum dg) { dgamma_reduce_tile(dg, blockIdx.x); }
 
 // the D/8 8-byte pieces of row `src` that a lane holds in accumulator layout (piece 4 ft + i4 = features
 // 32ft + 8*i4 + 4h .. +3; the row's other half sits in lane ^ 32): fetched ahead of their use, unpacked by phi_row_clayout
@@ -1213,9 +1187,9 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(const float* __restrict
 
 }  // namespace
 
-void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st) {
+void dgamma_reduce(const DgammaSum& dg, hipStream_t st) {
   ProfScope ps("dgamma_reduce_kernel", st);
-  dgamma_reduce_kernel<<<dim3(HD / 32, 2), 256, 0, st>>>(dgpart, dgs, dgr, RB, HD);
+  dgamma_reduce_kernel<<<dg.tiles(), 256, 0, st>>>(dg);
 }
 
 void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const void* v, const float* gs, const float* gr,
@@ -1274,8 +1248,7 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
     }
 #undef RATTN_DQ_LAUNCH
   }
-  if (dgs || dgr) dgamma_reduce(ws.dgpart, dgs, dgr, pl.RB, dm.Hq * dm.D, st);
-  rla_reverse_states(dm, pl, q, Tc, ws.dxr, ws.U, ws.rstates, st);
+  rla_reverse_states(dm, pl, q, Tc, ws.dxr, ws.U, ws.rstates, st, DgammaSum{a.dgpart, dgs, dgr, pl.RB, dm.Hq * dm.D});
   // the dk/dv kernel needs more LDS than a launch gets by default: raised once per instantiation
   static const bool lds_attr = [] {
     auto raise = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };

@@ -855,7 +855,7 @@ void launch_bwd(const LayerDims& dm, const void* q, const void* k, const void* v
                                                                        sv, states, (IO*)dq, ws.dxs, ws.dxr, ws.delta,
                                                                        dgs || dgr ? ws.dgpart : nullptr, dm);
   }
-  if (dgs || dgr) dgamma_reduce(ws.dgpart, dgs, dgr, tiles * dm.B, dm.Hq * D, st);
+  if (dgs || dgr) dgamma_reduce(DgammaSum{ws.dgpart, dgs, dgr, tiles * dm.B, dm.Hq * D}, st);
   build_states<IO, float, D, true>(dm, q, ws.dxr, ws.rstates, dm.Hq, dm.G, dm.W, nullptr, st);
   ProfScope ps("gen_bwd_dkv_kernel", st);
   gen_bwd_dkv_kernel<IO, D><<<dim3(tiles, dm.Hkv, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr,

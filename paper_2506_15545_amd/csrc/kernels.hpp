@@ -67,9 +67,15 @@ void generic_bwd(const LayerDims& dm, int dtype, const void* q, const void* k, c
 void generic_chunk_products(const LayerDims& dm, int T, const void* k, const void* v, float* out, int Tp, int nseg,
                             int seg_len, hipStream_t st);
 
-// gain gradients [Hq*D] from RB partials each, summed in a fixed order: dgpart[2][RB][HD], HD a multiple of 32; either
-// output may be NULL
-void dgamma_reduce(const float* dgpart, float* dgs, float* dgr, int RB, int HD, hipStream_t st);
+// gain gradients [HD] from RB partials each, summed in a fixed order: part[2][RB][HD], HD a multiple of 32; either output
+// may be NULL (part NULL: nothing to sum)
+struct DgammaSum {
+  const float* part;
+  float *dgs, *dgr;
+  int RB, HD;
+  int tiles() const { return HD / 32 * 2; }   // work-groups
+};
+void dgamma_reduce(const DgammaSum& dg, hipStream_t st);
 
 // Keys and values of the matrix-core kernels.  They work in 128-row tiles over a padded length (LayerDims::T); a sequence
 // has P rows in `*_front` tensors [B,P,Hkv,D] (chunked prefill: the ring in time order behind zero rows that fill the
@@ -113,6 +119,7 @@ struct FastBwdPlan {
   FastFwdPlan fwd;
   int nk;  // key tiles that have a linear branch = number of reverse states
   int nrchunks;  // reverse-time chunk-local products
+  int rsplit;    // work-groups that share the query heads of such a product (each leaves one of its own)
   int RB;  // gain-gradient partials: one per wave of the dq kernel
   int nsplit;  // work-groups that share the query heads of a key tile in the dk/dv kernel
   size_t u_bytes, rstate_bytes, dkv_part_bytes;
@@ -127,10 +134,10 @@ struct FastBwdWs {
 };
 FastBwdPlan fast_bwd_plan(const LayerDims& dm);
 // reverse-time states R_i = sum over t' >= 128(i+1) and over the group's heads of phi(q_{t'+W})^T dxr_{t'+W},
-// i in [0, nk), nk = ceil((T-W)/128); stored transposed [d][f] bf16.  U needs (nk-1) chunks.
-// q [B,Tb,Hq,D], dxr [B,T,Hq,D] (padded length, zero in rows >= Tb).
+// i in [0, nk), nk = ceil((T-W)/128); stored transposed [d][f] bf16.  U: see FastBwdPlan.
+// q [B,Tb,Hq,D], dxr [B,T,Hq,D] (padded length, zero in rows >= Tb).  `dg`: gain gradients summed on the way.
 void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, int Tb, const void* dxr, float* U,
-                        void* rstates, hipStream_t st);
+                        void* rstates, hipStream_t st, const DgammaSum& dg);
 // dm.T: the padded length; the caller's tensors hold Tc rows per sequence.  dO rows from 128 * (Tc / 128) on are read from
 // dO_tail [B,128,Hq,D], zero past row Tc (may be NULL when Tc is a multiple of 128).
 void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const void* v, const float* gs, const float* gr,

@@ -40,7 +40,12 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   p.nk = Tp > 0 ? (Tp + 127) / 128 : 0;
   // reverse-time chunk products: query rows t' in [128, Tp) in pieces of ckeys
   p.nrchunks = Tp > 128 ? (Tp - 128 + p.fwd.ckeys - 1) / p.fwd.ckeys : 0;
-  const int nch = p.fwd.nchunks > p.nrchunks ? p.fwd.nchunks : p.nrchunks;
+  // A work-group visits the query heads of its product in turn; where there are few products the heads are split over two
+  // or four work-groups, as long as those fit on the chip together (two per CU).  2 x 1000 tokens, 4 KV heads of 4 query
+  // heads: 24 -> 96 work-groups, 19 -> 8.5 us.
+  p.rsplit = 1;
+  while (p.rsplit < 4 && 2 * p.rsplit <= dm.G && (long long)p.nrchunks * dm.Hkv * dm.B * 2 * p.rsplit <= 512) p.rsplit *= 2;
+  const int nrev = p.nrchunks * p.rsplit, nch = p.fwd.nchunks > nrev ? p.fwd.nchunks : nrev;
   p.u_bytes = (size_t)dm.B * dm.Hkv * (nch > 0 ? nch : 0) * dm.D * dm.D * 4;
   p.rstate_bytes = (size_t)dm.B * dm.Hkv * p.nk * dm.D * dm.D * 2;
   p.RB = 4 * (dm.T / 128) * dm.B;  // one gain-gradient partial per wave of the dq kernel

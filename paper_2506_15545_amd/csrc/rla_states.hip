@@ -14,7 +14,8 @@ struct ChunkArgs {
   SeqRows a;           // rows that go through phi  (k, or q for the reverse states)
   SeqRows b;           // rows multiplied in        (v, or dx_r)
   float* U;            // [B,Hkv,nchunks,D,D] fp32, U^T = B^T phi(A)
-  int H, GA;           // heads in a/b, heads summed per kv head
+  int H, GA, GS;       // heads in a/b, heads summed per kv head, work-groups that share them: product c of work-group s is
+                       // number c GS + s, a sum over heads s ceil(GA / GS) .. of the group
   int tok_off;         // token index = t' + tok_off
   int skip_m, skip_head, skip_per;  // skip_m > 1: product c leads from state i = (c - skip_head) / skip_per to i + 1 and is
                                     // left out when that state is a stored one ((i + 1) % skip_m == 0) or c < skip_head
@@ -22,7 +23,7 @@ struct ChunkArgs {
                                                    // rest_lo + ckeys (c-1); every chunk is clipped at tok_end
 };
 
-// grid (nchunks, Hkv, B), 256 threads.  D = 128: wave w owns rows d in [32w, 32w+32) of U^T; D = 64: one of its four
+// grid (nchunks GS, Hkv, B), 256 threads.  D = 128: wave w owns rows d in [32w, 32w+32) of U^T; D = 64: one of its four
 // 32 x 32 tiles.
 template <int D, int FM>
 __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
@@ -30,7 +31,8 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
   __shared__ __align__(16) unsigned char smem[4 * KT];
   unsigned char* At = smem;
   unsigned char* Bt = smem + 2 * KT;
-  const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z, nchunks = gridDim.x, Hkv = gridDim.y;
+  const int c = blockIdx.x / p.GS, g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
+  const int per = (p.GA + p.GS - 1) / p.GS, ga0 = (int)(blockIdx.x % p.GS) * per, ga1 = min(ga0 + per, p.GA);
   if (p.skip_m > 1 && (c < p.skip_head || ((c - p.skip_head) / p.skip_per + 1) % p.skip_m == 0)) return;  // block-uniform
   const int lane = lane_id(), w = wave_id();
   const int r32 = lane & 31, h = lane >> 5;
@@ -50,9 +52,9 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
   f32x16_t acc[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) acc[f] = f32x16_t{0};
-  for (int ga = 0; ga < p.GA; ++ga) {
+  for (int ga = ga0; ga < ga1; ++ga) {
     const int row = lo + p.tok_off, hd = g * p.GA + ga;   // chunks start at multiples of 64 rows
-    if (ga > 0) __syncthreads();
+    if (ga > ga0) __syncthreads();
 #pragma unroll
     for (int half = 0; half < 2; ++half)
       if (64 * half < ntok) {
@@ -73,7 +75,7 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
       for (int f = 0; f < NF; ++f) acc[f] = mfma32(aop, lds_tr2(At + aoff[f][0] + k0, At + aoff[f][1] + k0), acc[f]);
     }
   }
-  float* out = p.U + ((size_t)(b * Hkv + g) * nchunks + c) * (D * D);
+  float* out = p.U + ((size_t)(b * Hkv + g) * gridDim.x + blockIdx.x) * (D * D);
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -87,7 +89,8 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
 // PER chunk products (1, or 2 when the products cover 64 keys each).
 //   forward: state[0] = sum of the `head` products in front of it; state[i+1] = state[i] + the next `per` products
 //   reverse: state[n-1] = 0; state[i] = state[i+1] + products per*i .. per*i + per - 1 (those that exist)
-// grid (D*D/1024, Hkv, B), 256 threads, 4 elements per thread.
+// grid (D*D/1024, Hkv, B), 256 threads, 4 elements per thread.  Blocks with z >= B (reverse scan, `dg.part` given) sum gain
+// gradients instead: a launch of its own for those took 4.7 us between kernels that do not need them.
 // init (forward only, may be NULL): a state that precedes chunk 0, fp32 [B,Hkv,f,d] (not transposed).
 // Forward scan with m > 1: `subset` (may be NULL) also receives states 0, m, 2m, ... ([B,Hkv,ceil(nst/m),128,128]);
 // `restart` (may be NULL) holds such a subset, and the running sum is replaced by the stored state at every multiple
@@ -96,8 +99,12 @@ template <int D, bool REV, int PER>
 __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__ U, uint16_t* __restrict__ states,
                                                        int nchunks, int nst, int head,
                                                        const float* __restrict__ init, uint16_t* __restrict__ subset,
-                                                       const uint16_t* __restrict__ restart, int m) {
+                                                       const uint16_t* __restrict__ restart, int m, int B, DgammaSum dg) {
   const int g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
+  if (REV && b >= B) {
+    dgamma_reduce_tile(dg, ((b - B) * gridDim.y + g) * gridDim.x + blockIdx.x);
+    return;
+  }
   const int e4 = (blockIdx.x * 256 + threadIdx.x) * 4;
   constexpr int N = D * D;
   const float* Ub = U + (size_t)(b * Hkv + g) * nchunks * N + e4;
@@ -125,8 +132,9 @@ __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__
   };
   auto add = [&](const float4& u) { acc.x += u.x; acc.y += u.y; acc.z += u.z; acc.w += u.w; };
   // States are walked in groups of GRP: the group's products are all requested before the first is added, so the
-  // loads of a group are in flight together (the additions keep their fixed order).
-  constexpr int GRP = 4;
+  // loads of a group are in flight together (the additions keep their fixed order).  Groups of 4 | 8 | 16 products: 8 heads,
+  // 224 states 67 | 54 | 47 us, 4 heads, 20 states 6.4 | 5.8 | 6.0 us, 32 heads, 28 states 15.0 | 14.9 | 15.5 us.
+  constexpr int GRP = PER < 8 ? 8 / PER : 1;
   if (!REV) {
     if (!restart)
       for (int c = 0; c < head; ++c) add(ld(c));
@@ -170,16 +178,21 @@ template <int D> void launch_chunk_kernel(int phi, dim3 grid, const ChunkArgs& p
   }
 }
 
+// per: products that a state spans
 template <int D, bool REV>
-void launch_scan_kernel(const LayerDims& dm, int ckeys, const float* U, void* states, int nchunks, int nst, int head,
-                        const float* init, void* subset, const void* restart, int m, hipStream_t st) {
-  const dim3 grid(D * D / 1024, dm.Hkv, dm.B);
-  if (ckeys == 64)
-    rla_scan_kernel<D, REV, 2><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset,
-                                                     (const uint16_t*)restart, m);
-  else
-    rla_scan_kernel<D, REV, 1><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset,
-                                                     (const uint16_t*)restart, m);
+void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* states, int nchunks, int nst, int head,
+                        const float* init, void* subset, const void* restart, int m, hipStream_t st,
+                        const DgammaSum& dg = DgammaSum{}) {
+  const int slice = D * D / 1024 * dm.Hkv, extra = dg.part ? (dg.tiles() + slice - 1) / slice : 0;
+  const dim3 grid(D * D / 1024, dm.Hkv, dm.B + extra);
+#define RATTN_SCAN(PER_)                                                                                                \
+  rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset, \
+                                                      (const uint16_t*)restart, m, dm.B, dg)
+  if (REV && per == 8) RATTN_SCAN(REV ? 8 : 2);
+  else if (REV && per == 4) RATTN_SCAN(REV ? 4 : 2);
+  else if (per == 2) RATTN_SCAN(2);
+  else RATTN_SCAN(1);
+#undef RATTN_SCAN
 }
 
 }  // namespace
@@ -194,7 +207,7 @@ void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTen
     p.a = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};
     p.b = {(const uint16_t*)t.v_front, (const uint16_t*)t.v, t.P, t.Tb};
     p.U = U;
-    p.H = dm.Hkv; p.GA = 1; p.tok_off = 0;
+    p.H = dm.Hkv; p.GA = p.GS = 1; p.tok_off = 0;
     p.ckeys = pl.ckeys;
     p.first_lo = 0; p.first_n = head ? 64 : pl.ckeys; p.rest_lo = p.first_n; p.tok_end = 1 << 30;
     p.skip_m = restart ? m : 0; p.skip_head = head; p.skip_per = 128 / pl.ckeys;
@@ -203,30 +216,34 @@ void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTen
     if (dm.D == 64) launch_chunk_kernel<64>(dm.phi, grid, p, st); else launch_chunk_kernel<128>(dm.phi, grid, p, st);
   }
   ProfScope ps("rla_scan_kernel", st);
-  if (dm.D == 64) launch_scan_kernel<64, false>(dm, pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
-  else launch_scan_kernel<128, false>(dm, pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
+  if (dm.D == 64) launch_scan_kernel<64, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
+  else launch_scan_kernel<128, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
 }
 
 void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, int Tb, const void* dxr, float* U,
-                        void* rstates, hipStream_t st) {
-  if (pl.nk <= 0) return;
+                        void* rstates, hipStream_t st, const DgammaSum& dg) {
+  if (pl.nk <= 0) {
+    if (dg.part) dgamma_reduce(dg, st);
+    return;
+  }
   const int W = pl.fwd.W, Tp = dm.T - W, ck = pl.fwd.ckeys;
   if (pl.nrchunks > 0) {
     ChunkArgs p;
     p.a = {nullptr, (const uint16_t*)q, 0, Tb};
     p.b = {nullptr, (const uint16_t*)dxr, 0, dm.T};   // a workspace tensor of the padded length
     p.U = U;
-    p.H = dm.Hq; p.GA = dm.G; p.tok_off = W;
+    p.H = dm.Hq; p.GA = dm.G; p.GS = pl.rsplit; p.tok_off = W;
     p.ckeys = ck;
     p.first_lo = 128; p.first_n = ck; p.rest_lo = 128 + ck; p.tok_end = Tp;
     p.skip_m = 0; p.skip_head = 0; p.skip_per = 1;
     ProfScope ps("rla_chunk_kernel(rev)", st);
-    const dim3 grid(pl.nrchunks, dm.Hkv, dm.B);
+    const dim3 grid(pl.nrchunks * pl.rsplit, dm.Hkv, dm.B);
     if (dm.D == 64) launch_chunk_kernel<64>(dm.phi, grid, p, st); else launch_chunk_kernel<128>(dm.phi, grid, p, st);
   }
   ProfScope ps("rla_scan_kernel(rev)", st);
-  if (dm.D == 64) launch_scan_kernel<64, true>(dm, ck, U, rstates, pl.nrchunks, pl.nk, 0, nullptr, nullptr, nullptr, 1, st);
-  else launch_scan_kernel<128, true>(dm, ck, U, rstates, pl.nrchunks, pl.nk, 0, nullptr, nullptr, nullptr, 1, st);
+  const int per = 128 / ck * pl.rsplit, n = pl.nrchunks * pl.rsplit;
+  if (dm.D == 64) launch_scan_kernel<64, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, dg);
+  else launch_scan_kernel<128, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, dg);
 }
 
 }  // namespace rattn

@@ -317,6 +317,26 @@ def test_running_maximum_raised_in_late_steps(T, W, D, rise):
     pm.assert_out_bf16(np64(o), ref)
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W,chunk", [(1, 640, 3, 1, 128, 128, 0),     # three heads over two work-groups
+                                                  (1, 700, 5, 1, 64, 100, 64),     # five over four (one gets none), 64 keys
+                                                  (2, 512, 16, 2, 128, 65, 64), (1, 1024, 8, 2, 128, 64, 128),
+                                                  (8, 1280, 32, 16, 64, 192, 0)])  # too many products: not split
+def test_reverse_states_of_split_heads(B, T, Hq, Hkv, D, W, chunk):
+    """Reverse states whose query heads are shared by several work-groups, and gain gradients summed in the same launch:
+    the same fp32 sums in another order, compared with the general kernels at the bound of two bf16 paths."""
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 2600 + T + Hq, with_dO=True, with_gains=True)
+    q, k, v, dO, gs, gr = (x[n].cuda() for n in ("q", "k", "v", "dO", "gamma_swa", "gamma_rla"))
+    got = {}
+    for path in ("auto", "general"):
+        kw = dict(softmax_scale=1.0 / math.sqrt(D), kernel_path=path, chunk=chunk)
+        _, saved = rb.rattn_fwd(q, k, v, W, gs, gr, save_for_bwd=True, **kw)
+        got[path] = rb.rattn_bwd(q, k, v, saved, dO, W, gs, gr, **kw)
+    for n, a, b in zip(("dq", "dk", "dv", "dgs", "dgr"), got["auto"], got["general"]):
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        print(f"{n}: relative 2-norm of the difference {rel:.2e}", flush=True)
+        assert rel <= 1e-2, n   # bf16 operands: 2^-9 per factor and term
+
+
 def test_fast_bwd_is_deterministic():
     x = synth.make_random_layer(1, 512, 4, 2, 128, "bf16", 6, with_dO=True)
     q, k, v, dO = x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), x["dO"].cuda()
