@@ -23,7 +23,8 @@ namespace {
 struct FastBwdArgs {
   SeqRows q, k, v;                  // the caller's tensors: Tc rows per sequence, rows past them read as the last one
   const uint16_t *dxs, *dxr;        // workspace and saved tensors are laid out for the padded length T
-  const float *lse, *delta;
+  const float* lse;                 // as the forward saved it
+  float *delta, *lse2;              // <dx_s, x_s> * scale and lse * log2(e), left by the dq kernel for the dk/dv kernel
   const uint16_t *states, *rstates;
   uint16_t *dq, *dk, *dv;
   float *dk_part, *dv_part;         // fp32 [nsplit][B,Tc,Hkv,D] when the query heads of a group are split (nsplit > 1)
@@ -148,7 +149,7 @@ __device__ __forceinline__ void dq_subtile(const unsigned char* kt, const unsign
   }
   float ds[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) ds[i] = p[i] * (dp[i] - dl) * scale;
+  for (int i = 0; i < 16; ++i) ds[i] = p[i] * __builtin_fmaf(dp[i], scale, -dl);
   bf16x8_t dsop[2] = {pack_bf16x8(&ds[0]), pack_bf16x8(&ds[8])};
 #pragma unroll
   for (int mf = 0; mf < 2; ++mf) {
@@ -184,7 +185,6 @@ __device__ __forceinline__ void rms_bwd_rows(const FastBwdArgs& a, int hq, size_
   const bool with_r = stage_r != nullptr;
   uint16_t* dxs_w = const_cast<uint16_t*>(a.dxs);
   uint16_t* dxr_w = const_cast<uint16_t*>(a.dxr);
-  float* delta_w = const_cast<float*>(a.delta);
   float g1[8], g2[8], dg1[8], dg2[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -258,7 +258,7 @@ __device__ __forceinline__ void rms_bwd_rows(const FastBwdArgs& a, int hq, size_
     }
     if (stage_r) *reinterpret_cast<bf16x8_t*>(stage_r + r * TG::ROWB + ((c ^ swz<D>(r)) << 4)) = cpk;
     dl = row_sum(dl);
-    if (c == 0) { delta_w[stat0 + r] = dl; dl_stage[r] = dl; }
+    if (c == 0) { a.delta[stat0 + r] = dl * a.scale; dl_stage[r] = dl * a.scale; }
   }
   if (GAINS && dgp_s) {
 #pragma unroll
@@ -431,6 +431,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
   // layouts it needs, instead of two more round trips to global memory for row pieces.
   if (!has_lin) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the staged rows are in registers
   const float lse2 = a.lse[stat_off] * LOG2E;
+  if (h == 0) a.lse2[stat_off] = lse2;
   const int kt_lo = max(0, t0 - W);
   const int ntiles = (t0 + 128 - kt_lo) / 64;
   {
@@ -605,7 +606,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
   }
   const unsigned lds_q = (unsigned)(size_t)RATTN_LDS(smem) + w8 * (NB * 1024);
   const unsigned lds_st = (unsigned)(size_t)RATTN_LDS(smem + L::STAT) + (krole ? 1024 : 0);
-  const float* stat_base = (krole ? a.delta : a.lse) + (size_t)(b * Hq + h0) * T + s0;  // 64 rows, 16 bytes per lane
+  const float* stat_base = (krole ? a.delta : a.lse2) + (size_t)(b * Hq + h0) * T + s0;  // 64 rows, 16 bytes per lane
   const size_t tile_g = ((size_t)(b * T + s0) * Hq + h0) * D;     // workspace tensors (padded length)
   const uint16_t* q_base = a.q.back + ((ptrdiff_t)((size_t)b * a.Tc + s0) * Hq + h0) * D;
   int is_h = 0, is_n = 0, is_buf = 0;  // head, tile and slot of the next tile to request
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
                 s[i] = (dist0 + (unsigned)(8 * (i >> 2) + (i & 3)) < (unsigned)Wm) ? s[i] : -INFINITY;
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -stat[i] * LOG2E));
+            for (int i = 0; i < 16; ++i) s[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -stat[i]));
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) px[i4 * 64] = f32x4_t{s[4 * i4], s[4 * i4 + 1], s[4 * i4 + 2], s[4 * i4 + 3]};
           }
@@ -832,7 +833,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
             for (int i4 = 0; i4 < 4; ++i4) {
               const f32x4_t pv = px[i4 * 64];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) x[4 * i4 + e] = pv[e] * (s[4 * i4 + e] - stat[4 * i4 + e]) * a.scale;
+              for (int e = 0; e < 4; ++e) x[4 * i4 + e] = pv[e] * __builtin_fmaf(s[4 * i4 + e], a.scale, -stat[4 * i4 + e]);
             }
           }
           const bf16x8_t xo[2] = {pack_bf16x8(&x[0]), pack_bf16x8(&x[8])};
@@ -1044,7 +1045,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv64_kernel(FastBwdArgs a) {
   }
   const unsigned lds_q = (unsigned)(size_t)RATTN_LDS(smem) + w * (NB * 1024);
   const unsigned lds_st = (unsigned)(size_t)RATTN_LDS(smem + L::STAT) + w * 1024;
-  const float* stat_base = (w == 0 ? a.lse : a.delta) + (size_t)(b * Hq + h0) * T + s0;
+  const float* stat_base = (w == 0 ? a.lse2 : a.delta) + (size_t)(b * Hq + h0) * T + s0;
   const size_t tile_g = ((size_t)(b * T + s0) * Hq + h0) * D;
   const uint16_t* q_base = a.q.back + ((ptrdiff_t)((size_t)b * a.Tc + s0) * Hq + h0) * D;
   int is_h = 0, is_n = 0, is_buf = 0;  // head, tile and slot of the next tile to request
@@ -1106,8 +1107,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dkv64_kernel(FastBwdArgs a) {
       float p[16], ds[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        p[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -ls[i] * LOG2E));
-        ds[i] = p[i] * (dp[i] - dl[i]) * a.scale;
+        p[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -ls[i]));
+        ds[i] = p[i] * __builtin_fmaf(dp[i], a.scale, -dl[i]);
       }
 #pragma unroll
       for (int mf = 0; mf < 2; ++mf) {
@@ -1204,7 +1205,7 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
   a.k = {nullptr, (const uint16_t*)k, 0, Tc};
   a.v = {nullptr, (const uint16_t*)v, 0, Tc};
   a.dxs = (const uint16_t*)ws.dxs; a.dxr = (const uint16_t*)ws.dxr;
-  a.lse = sv.lse; a.delta = ws.delta;
+  a.lse = sv.lse; a.delta = ws.delta; a.lse2 = ws.delta + (size_t)dm.B * dm.Hq * dm.T;
   // chunk states of the forward pass: kept in `saved`, or (state policy "rebuild") built again here from k and v
   // (or, with a state stride, every m-th kept and the ones in between built again from those)
   const bool all_kept = sv.states && sv.state_stride <= 1;

@@ -126,7 +126,7 @@ struct FastBwdPlan {
 };
 struct FastBwdWs {
   void *dxs, *dxr;       // bf16 [B,T,Hq,D]
-  float* delta;          // [B,Hq,T]
+  float* delta;          // [2][B,Hq,T]: <dx_s, x_s> * scale, then the log-sum-exp in log2 units
   float* U;              // chunk scratch
   void *states, *rstates;
   float* dgpart;         // [2,RB,Hq,D]
