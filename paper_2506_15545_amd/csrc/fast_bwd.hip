@@ -24,7 +24,10 @@ struct FastBwdArgs {
   SeqRows q, k, v;                  // the caller's tensors: Tc rows per sequence, rows past them read as the last one
   const uint16_t *dxs, *dxr;        // workspace and saved tensors are laid out for the padded length T
   const float* lse;                 // as the forward saved it
-  float *delta, *lse2;              // <dx_s, x_s> * scale and lse * log2(e), left by the dq kernel for the dk/dv kernel
+  // <dx_s, x_s> * scale and lse * log2(e), left by the dq kernel for the dk/dv kernel.  Its loop is bound by the SIMDs' issue
+  // rate (a vector instruction per 4.4 cycles); scaled per (query, key) pair there, a step of the 3B-shaped layer takes
+  // 880 us against 869, at head size 64 464 against 451.
+  float *delta, *lse2;
   const uint16_t *states, *rstates;
   uint16_t *dq, *dk, *dv;
   float *dk_part, *dv_part;         // fp32 [nsplit][B,Tc,Hkv,D] when the query heads of a group are split (nsplit > 1)

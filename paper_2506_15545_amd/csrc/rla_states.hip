@@ -182,8 +182,14 @@ template <int D> void launch_chunk_kernel(int phi, dim3 grid, const ChunkArgs& p
 template <int D, bool REV>
 void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* states, int nchunks, int nst, int head,
                         const float* init, void* subset, const void* restart, int m, hipStream_t st,
-                        const DgammaSum& dg = DgammaSum{}) {
-  const int slice = D * D / 1024 * dm.Hkv, extra = dg.part ? (dg.tiles() + slice - 1) / slice : 0;
+                        DgammaSum dg = DgammaSum{}) {
+  const int slice = D * D / 1024 * dm.Hkv;
+  int extra = dg.part ? (dg.tiles() + slice - 1) / slice : 0;
+  if (dm.B + extra > 65535) {   // a grid has no more layers than that
+    dgamma_reduce(dg, st);
+    dg.part = nullptr;
+    extra = 0;
+  }
   const dim3 grid(D * D / 1024, dm.Hkv, dm.B + extra);
 #define RATTN_SCAN(PER_)                                                                                                \
   rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset, \
