@@ -787,6 +787,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
         f32x4_t* px = reinterpret_cast<f32x4_t*>(pex + (w * 2 + qs) * 4096 + lane * 16);  // [i4][lane] x 16 bytes
         f32x16_t s = {0};
         float stat[16];
+        bf16x8_t early[ND] = {};
         if (need) {
           const unsigned char* rows = KR ? dxt : qtile;
 #pragma unroll
@@ -814,6 +815,12 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
             for (int i = 0; i < 16; ++i) s[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -stat[i]));
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) px[i4 * 64] = f32x4_t{s[4 * i4], s[4 * i4 + 1], s[4 * i4 + 2], s[4 * i4 + 3]};
+          } else {
+            // The K-role gets here first: what does not need P is done while it would wait for the V-role.
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = __builtin_fmaf(s[i], a.scale, -stat[i]);
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) early[dt] = lds_trp<D>(qtile, lo, 32 * qs, dt);
           }
         }
         if (qs == 1) {  // this wave's share of tile step+1 has landed (tile step+2 may still be in flight)
@@ -836,7 +843,7 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
             for (int i4 = 0; i4 < 4; ++i4) {
               const f32x4_t pv = px[i4 * 64];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) x[4 * i4 + e] = pv[e] * __builtin_fmaf(s[4 * i4 + e], a.scale, -stat[4 * i4 + e]);
+              for (int e = 0; e < 4; ++e) x[4 * i4 + e] = pv[e] * s[4 * i4 + e];
             }
           }
           const bf16x8_t xo[2] = {pack_bf16x8(&x[0]), pack_bf16x8(&x[8])};
@@ -844,7 +851,8 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
 #pragma unroll
           for (int mf = 0; mf < 2; ++mf)
 #pragma unroll
-            for (int dt = 0; dt < ND; ++dt) acc[dt] = mfma32(lds_trp<D>(cols, lo, 32 * qs + 16 * mf, dt), xo[mf], acc[dt]);
+            for (int dt = 0; dt < ND; ++dt)
+              acc[dt] = mfma32(KR && mf == 0 ? early[dt] : lds_trp<D>(cols, lo, 32 * qs + 16 * mf, dt), xo[mf], acc[dt]);
         }
       }
     }
