@@ -816,7 +816,8 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) px[i4 * 64] = f32x4_t{s[4 * i4], s[4 * i4 + 1], s[4 * i4 + 2], s[4 * i4 + 3]};
           } else {
-            // The K-role gets here first: what does not need P is done while it would wait for the V-role.
+            // The K-role gets here first: what does not need P is done while it would wait for the V-role (3B-shaped layer:
+            // 907 -> 904.5 us a training step; the V-role's operands read ahead of the barrier too: 909).
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = __builtin_fmaf(s[i], a.scale, -stat[i]);
 #pragma unroll

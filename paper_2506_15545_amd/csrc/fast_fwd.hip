@@ -273,18 +273,26 @@ __global__ __launch_bounds__(256, fwd_occ(D)) void fwd_fused_kernel(FastFwdArgs 
   const unsigned lds_wave = (unsigned)(size_t)RATTN_LDS(smem) + w * NB * 1024;
   auto odd_step = [&](int n, auto par) {   // step 2n + 1, par = n & 1
     constexpr int P = decltype(par)::value, EVERY = D / 16 / NB;
-    const bool more_k = n + 2 < ntiles, more_v = n + 1 < ntiles, go_k = whole && more_k, go_v = whole && more_v;
+    const unsigned char *k_tile = k_next, *v_tile = v_next;
+    bool go_k = n + 2 < ntiles, go_v = n + 1 < ntiles;
+    // Otherwise each tile has a base of its own, in the tensor it lies in; requested in one go instead, a chunk of 4 x 2048
+    // tokens behind rings of 512 takes 159.6 us against 156.5, one of 700 tokens 54.7 against 52.7.
     if (!whole) {
-      if (more_k) load_k(n + 2);
-      if (more_v) load_v(n + 1);
+      const int row = kt_lo + 64 * (ntiles - 3 - n);
+      if (go_k) k_tile = reinterpret_cast<const unsigned char*>(k_rows(row).p) + w * NB * load_bytes;  // (below the queries: whole)
+      if (go_v) {
+        const TileRows r = v_rows(row + 64);
+        v_tile = reinterpret_cast<const unsigned char*>(r.p) + w * NB * load_bytes;
+        if (r.n < 64) { load_v(n + 1); go_v = false; }
+      }
     }
     sweep_step<D, 2 * P + 1, true>(smem, lo, gm, 2 * n + 1, myq, a.scale_log2, qop, sw, lane, [&](int i) {
       if (i % EVERY) return;
       const int part = i / EVERY % NB;
       if (i / EVERY < NB) {
-        if (go_k) dma16s(k_next + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + P * KT + part * 1024);
+        if (go_k) dma16s(k_tile + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + P * KT + part * 1024);
       } else {
-        if (go_v) dma16s(v_next + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + (3 - P) * KT + part * 1024);
+        if (go_v) dma16s(v_tile + part * load_bytes, dl.off[part % TileGeom<D>::NV], lds_wave + (3 - P) * KT + part * 1024);
       }
     });
     k_next -= tile_bytes;
