@@ -141,7 +141,8 @@ __device__ __forceinline__ void sweep_step(const unsigned char* smem, const Lane
 #pragma unroll
     for (int e = PER * i; e < PER * i + PER; e += 2) {
       if (PREV) { ps += st.p[e]; ps += st.p[e + 1]; }
-      asm volatile("v_max3_f32 %0, %0, %2, %3" : "+v"(mx), "+v"(ps) : "v"(st.s[e]), "v"(st.s[e + 1]));
+      mx = max3(mx, st.s[e], st.s[e + 1]);
+      asm volatile("" : "+v"(mx), "+v"(ps));   // stays between the matrix instructions
     }
     if (PREV && i == N / 2 - 1) pop[0] = pack_bf16x8(&st.p[0]);
     if (PREV && i == N - 1) pop[1] = pack_bf16x8(&st.p[8]);

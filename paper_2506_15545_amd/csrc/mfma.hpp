@@ -190,6 +190,12 @@ __device__ __forceinline__ float half_max(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// largest of three, NaN operands ignored: one v_max3_f32 (fmaxf puts a quieting instruction in front of every operand that
+// comes from a matrix instruction).  Not inline assembly: the compiler keeps the distance that a vector instruction needs from
+// the matrix instruction whose result it reads for its own instructions only.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  return __builtin_elementwise_maximumnum(a, __builtin_elementwise_maximumnum(b, c));
+}
 // 2^x on the transcendental unit (v_exp_f32): 2^-inf = 0, no denormal fix-up code
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
