@@ -6,7 +6,8 @@
 
 namespace rattn {
 
-// per-kernel event timing (see rattn_profile_* in rattn.h); no-ops while profiling is off
+// per-kernel event timing (see rattn_profile_* in rattn.h); no-ops while profiling is off.  Scopes do not nest: an inner
+// one leaves the outer one's record without its second event.
 void prof_begin(const char* name, hipStream_t st);
 void prof_end(hipStream_t st);
 struct ProfScope {

@@ -178,19 +178,18 @@ template <int D> void launch_chunk_kernel(int phi, dim3 grid, const ChunkArgs& p
   }
 }
 
+// layers (in z) of the reverse scan's grid that sum gain gradients
+int dgamma_layers(const LayerDims& dm, const DgammaSum& dg) {
+  const int slice = dm.D * dm.D / 1024 * dm.Hkv;
+  return dg.part ? (dg.tiles() + slice - 1) / slice : 0;
+}
+
 // per: products that a state spans
 template <int D, bool REV>
 void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* states, int nchunks, int nst, int head,
                         const float* init, void* subset, const void* restart, int m, hipStream_t st,
-                        DgammaSum dg = DgammaSum{}) {
-  const int slice = D * D / 1024 * dm.Hkv;
-  int extra = dg.part ? (dg.tiles() + slice - 1) / slice : 0;
-  if (dm.B + extra > 65535) {   // a grid has no more layers than that
-    dgamma_reduce(dg, st);
-    dg.part = nullptr;
-    extra = 0;
-  }
-  const dim3 grid(D * D / 1024, dm.Hkv, dm.B + extra);
+                        const DgammaSum& dg = DgammaSum{}) {
+  const dim3 grid(D * D / 1024, dm.Hkv, dm.B + dgamma_layers(dm, dg));
 #define RATTN_SCAN(PER_)                                                                                                \
   rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset, \
                                                       (const uint16_t*)restart, m, dm.B, dg)
@@ -246,10 +245,15 @@ void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* 
     const dim3 grid(pl.nrchunks * pl.rsplit, dm.Hkv, dm.B);
     if (dm.D == 64) launch_chunk_kernel<64>(dm.phi, grid, p, st); else launch_chunk_kernel<128>(dm.phi, grid, p, st);
   }
+  DgammaSum in_scan = dg;
+  if (dm.B + dgamma_layers(dm, dg) > 65535) {   // a grid has no more layers than that
+    dgamma_reduce(dg, st);
+    in_scan.part = nullptr;
+  }
   ProfScope ps("rla_scan_kernel(rev)", st);
   const int per = 128 / ck * pl.rsplit, n = pl.nrchunks * pl.rsplit;
-  if (dm.D == 64) launch_scan_kernel<64, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, dg);
-  else launch_scan_kernel<128, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, dg);
+  if (dm.D == 64) launch_scan_kernel<64, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, in_scan);
+  else launch_scan_kernel<128, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, in_scan);
 }
 
 }  // namespace rattn

@@ -337,6 +337,37 @@ def test_reverse_states_of_split_heads(B, T, Hq, Hkv, D, W, chunk):
         assert rel <= 1e-2, n   # bf16 operands: 2^-9 per factor and term
 
 
+def test_gain_gradients_of_the_largest_batch():
+    """B = 65535: the reverse scan's grid has no layer left for the gain gradients, which then take a launch of their own.
+    Every profile record of the call is complete (both events, a duration) and names one launch; the gradients are those of
+    the two halves of the batch: dq, dk, dv bit for bit, the gain gradients as sums of at most 8192 fp32 terms in 32 strands."""
+    B, T, D, W, half = 65535, 128, 64, 64, 32768
+    gen = torch.Generator(device="cuda").manual_seed(2700)
+    q, k, v, dO = (torch.randn(B, T, 1, D, device="cuda", dtype=torch.bfloat16, generator=gen) for _ in range(4))
+    gs, gr = (1.0 + 0.1 * torch.randn(1, D, device="cuda", generator=gen) for _ in range(2))
+
+    def grads(lo, hi):
+        x = [t[lo:hi] for t in (q, k, v, dO)]
+        _, saved = rb.rattn_fwd(*x[:3], W, gs, gr, softmax_scale=0.125, save_for_bwd=True)
+        return rb.rattn_bwd(*x[:3], saved, x[3], W, gs, gr, softmax_scale=0.125)
+
+    grads(0, 8)
+    rb.rattn_profile_enable(True)
+    whole = grads(0, B)
+    torch.cuda.synchronize()
+    records = rb.rattn_profile_records()
+    rb.rattn_profile_enable(False)
+    names = [n for n, _ in records]
+    assert all(ms >= 0.0 for _, ms in records), records
+    assert names.count("dgamma_reduce_kernel") == 1 and names.count("rla_scan_kernel(rev)") == 1, names
+    parts = grads(0, half), grads(half, B)
+    for n, a, b, c in zip(("dq", "dk", "dv"), whole, *parts):
+        assert torch.equal(a[:half], b) and torch.equal(a[half:], c), n
+    for n, a, b, c in zip(("dgs", "dgr"), whole[3:], parts[0][3:], parts[1][3:]):
+        want = b.double() + c.double()
+        assert float((a.double() - want).norm() / want.norm()) <= 8192 * 2.0 ** -24, n
+
+
 def test_fast_bwd_is_deterministic():
     x = synth.make_random_layer(1, 512, 4, 2, 128, "bf16", 6, with_dO=True)
     q, k, v, dO = x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), x["dO"].cuda()
