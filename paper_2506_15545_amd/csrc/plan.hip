@@ -45,6 +45,8 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   // heads: 24 -> 96 work-groups, 19 -> 8.5 us.
   p.rsplit = 1;
   while (p.rsplit < 4 && 2 * p.rsplit <= dm.G && (long long)p.nrchunks * dm.Hkv * dm.B * 2 * p.rsplit <= 512) p.rsplit *= 2;
+  const int heads = (dm.G + p.rsplit - 1) / p.rsplit;
+  p.rsplit = (dm.G + heads - 1) / heads;   // 5, 6 or 9 heads: the fourth work-group would have none
   const int nrev = p.nrchunks * p.rsplit, nch = p.fwd.nchunks > nrev ? p.fwd.nchunks : nrev;
   p.u_bytes = (size_t)dm.B * dm.Hkv * (nch > 0 ? nch : 0) * dm.D * dm.D * 4;
   p.rstate_bytes = (size_t)dm.B * dm.Hkv * p.nk * dm.D * dm.D * 2;

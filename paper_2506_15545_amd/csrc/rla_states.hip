@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
 }
 
 // Exclusive scan over chunks, every state element independently, fp32 accumulation, bf16 output.  A state spans
-// PER chunk products (1, or 2 when the products cover 64 keys each).
+// PER chunk products (1, or 2 when the products cover 64 keys each; reverse: times the work-groups that share the heads).
 //   forward: state[0] = sum of the `head` products in front of it; state[i+1] = state[i] + the next `per` products
 //   reverse: state[n-1] = 0; state[i] = state[i+1] + products per*i .. per*i + per - 1 (those that exist)
 // grid (D*D/1024, Hkv, B), 256 threads, 4 elements per thread.  Blocks with z >= B (reverse scan, `dg.part` given) sum gain
@@ -194,7 +194,9 @@ void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* stat
   rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset, \
                                                       (const uint16_t*)restart, m, dm.B, dg)
   if (REV && per == 8) RATTN_SCAN(REV ? 8 : 2);
+  else if (REV && per == 6) RATTN_SCAN(REV ? 6 : 2);
   else if (REV && per == 4) RATTN_SCAN(REV ? 4 : 2);
+  else if (REV && per == 3) RATTN_SCAN(REV ? 3 : 2);
   else if (per == 2) RATTN_SCAN(2);
   else RATTN_SCAN(1);
 #undef RATTN_SCAN
