@@ -42,9 +42,20 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   p.nrchunks = Tp > 128 ? (Tp - 128 + p.fwd.ckeys - 1) / p.fwd.ckeys : 0;
   // A work-group visits the query heads of its product in turn; where there are few products the heads are split over two
   // or four work-groups, as long as those fit on the chip together (two per CU).  2 x 1000 tokens, 4 KV heads of 4 query
-  // heads: 24 -> 96 work-groups, 19 -> 8.5 us.
+  // heads: 24 -> 96 work-groups, 19 -> 8.5 us.  Every further product is written, and read again in the scan's one chain of
+  // additions per element.  So a doubling must take at least as many keys (heads x keys of a product) off the longest
+  // work-group as it adds products, and eight times the products that it adds to a chain.  Backward at D = 128, one | two |
+  // four work-groups: 64 products of 4 heads in chains of 8 96.6 | 90.2 | 89.7 us, of 16 97.1 | 91.2 | 92.4; 96 products of
+  // 4 heads 102.6 | 97.7 | 99.3; 128 of 2 heads 82.5 | 81.1, of 3 98.6 | 98.8, of 8 in chains of 8 228.7 | 216.6 | 215.0, of
+  // 32 224.8 | 215.4 | 217.1; 192 of 2 heads 88.7 | 89.6, of 3 124.9 | 127.0; 256 of 4 heads 228.6 | 226.5 | 243.7.
+  const long long chains = (long long)dm.Hkv * dm.B;
+  auto longest = [&](int s) { return (long long)((dm.G + s - 1) / s) * p.fwd.ckeys; };   // keys
   p.rsplit = 1;
-  while (p.rsplit < 4 && 2 * p.rsplit <= dm.G && (long long)p.nrchunks * dm.Hkv * dm.B * 2 * p.rsplit <= 512) p.rsplit *= 2;
+  for (int s = 1; s < 4 && 2 * s <= dm.G && chains * p.nrchunks * 2 * s <= 512; s *= 2) {
+    const long long added = (long long)p.nrchunks * s, fewer = longest(s) - longest(2 * s);
+    if (chains * added > fewer || 8 * added > fewer) break;
+    p.rsplit = 2 * s;
+  }
   const int heads = (dm.G + p.rsplit - 1) / p.rsplit;
   p.rsplit = (dm.G + heads - 1) / heads;   // 5, 6 or 9 heads: the fourth work-group would have none
   const int nrev = p.nrchunks * p.rsplit, nch = p.fwd.nchunks > nrev ? p.fwd.nchunks : nrev;

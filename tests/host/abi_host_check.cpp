@@ -93,20 +93,24 @@ int main() {
       CHECK(rattn_prefill_chunk_workspace_bytes(&q, 2147483647, &c) != RATTN_OK);
     }
   }
-  // ---- reverse products of shared heads: every work-group has heads to visit, and the chunk scratch holds just theirs
+  // ---- reverse products of shared heads: every work-group has heads to visit, the chunk scratch holds just theirs, and a
+  // split takes at least as many keys off the longest work-group as it adds products to write and read again
   for (int G = 1; G <= 24; ++G)
     for (int D : {64, 128})
       for (int ckeys : {64, 128})
-        for (int nr : {1, 3, 8, 28}) {
-          rattn::LayerDims dm = {};
-          dm.B = 1; dm.Hkv = 2; dm.Hq = 2 * G; dm.G = G; dm.D = D; dm.W = 128; dm.T = 256 + 128 * nr; dm.scale = 1.f;
-          dm.chunk_req = ckeys;
-          const rattn::FastBwdPlan pl = rattn::fast_bwd_plan(dm);
-          const int heads = (G + pl.rsplit - 1) / pl.rsplit;
-          CHECK(pl.rsplit >= 1 && pl.rsplit <= 4 && (pl.rsplit - 1) * heads < G);
-          const size_t products = (size_t)(pl.nrchunks * pl.rsplit > pl.fwd.nchunks ? pl.nrchunks * pl.rsplit : pl.fwd.nchunks);
-          CHECK(pl.u_bytes == products * dm.Hkv * D * D * 4);
-        }
+        for (int B : {1, 8})
+          for (int nr : {1, 3, 8, 16, 28}) {
+            rattn::LayerDims dm = {};
+            dm.B = B; dm.Hkv = 2; dm.Hq = 2 * G; dm.G = G; dm.D = D; dm.W = 128; dm.T = 256 + 128 * nr; dm.scale = 1.f;
+            dm.chunk_req = ckeys;
+            const rattn::FastBwdPlan pl = rattn::fast_bwd_plan(dm);
+            const int heads = (G + pl.rsplit - 1) / pl.rsplit, fewer = (G - heads) * ckeys;
+            CHECK(pl.rsplit >= 1 && pl.rsplit <= 4 && (pl.rsplit - 1) * heads < G);
+            CHECK(B * dm.Hkv * pl.nrchunks * (pl.rsplit - 1) <= fewer && 8 * pl.nrchunks * (pl.rsplit - 1) <= fewer);
+            if (B == 1 && nr == 1 && G > 1) CHECK(pl.rsplit > 1);   // few products are split
+            const size_t products = (size_t)(pl.nrchunks * pl.rsplit > pl.fwd.nchunks ? pl.nrchunks * pl.rsplit : pl.fwd.nchunks);
+            CHECK(pl.u_bytes == products * B * dm.Hkv * D * D * 4);
+          }
   // the allocation-free entry refuses what does not fit its buffer before touching any device
   { rattn_params q = params(4, 8192, 24, 8, 128, 512, 1);
     CHECK(rattn_fwd_static(&q, fake, fake, fake, NULL, NULL, fake, NULL, NULL) == RATTN_ERR_WORKSPACE); }

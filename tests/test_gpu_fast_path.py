@@ -318,7 +318,8 @@ def test_running_maximum_raised_in_late_steps(T, W, D, rise):
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,D,W,chunk", [(1, 640, 3, 1, 128, 128, 0),     # three heads over two work-groups
-                                                  (1, 700, 5, 1, 64, 100, 64),     # five over three, 64-key products: six a state
+                                                  (1, 500, 5, 1, 64, 100, 64),     # five over three, 64-key products: six a state
+                                                  (1, 700, 5, 1, 64, 100, 64),     # five over two
                                                   (1, 896, 6, 1, 128, 128, 0),     # six over three: three products a state
                                                   (2, 512, 16, 2, 128, 65, 64), (1, 1024, 8, 2, 128, 64, 128),
                                                   (8, 1280, 32, 16, 64, 192, 0)])  # too many products: not split
