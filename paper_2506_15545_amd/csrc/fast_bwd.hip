@@ -24,9 +24,10 @@ struct FastBwdArgs {
   SeqRows q, k, v;                  // the caller's tensors: Tc rows per sequence, rows past them read as the last one
   const uint16_t *dxs, *dxr;        // workspace and saved tensors are laid out for the padded length T
   const float* lse;                 // as the forward saved it
-  // <dx_s, x_s> * scale and lse * log2(e), left by the dq kernel for the dk/dv kernel.  Its loop is bound by the SIMDs' issue
-  // rate (a vector instruction per 4.4 cycles); scaled per (query, key) pair there, a step of the 3B-shaped layer takes
-  // 880 us against 869, at head size 64 464 against 451.
+  // <dx_s, x_s> * scale and lse * log2(e), left by the dq kernel for the dk/dv kernels: fewer vector instructions per
+  // (query, key) pair.  Scaled per pair there instead, everything else alike, in turn on one box: a step of the 3B-shaped
+  // layer takes 895 us against 881 (runs of one side differ by 2 %), at head size 64 474 against 462, 12B-shaped 1210
+  // against 1203.
   float *delta, *lse2;
   const uint16_t *states, *rstates;
   uint16_t *dq, *dk, *dv;
@@ -163,12 +164,12 @@ __device__ __forceinline__ void dq_subtile(const unsigned char* kt, const unsign
 
 // Backward of the two RMS norms (Sec. 3.2) for 32 consecutive query rows of one head, by one wave: D/8 lanes per row,
 // 8 features each, four (D = 128) or eight rows per pass (row-contiguous 16-byte accesses).  With y = g * x * r, r = rsqrt(mean x^2 +
-// eps):  dx = r g dy - x r^3 mean(g dy x),  dg += dy x r.  Stores d xs, d xr (bf16) and delta = rowsum(d xs * xs)
-// to global memory for the later kernels and also into LDS: d xs in two 16-row pieces at `stage_s` and
+// eps):  dx = r g dy - x r^3 mean(g dy x),  dg += dy x r.  Stores d xs, d xr (bf16) and delta * scale, delta =
+// rowsum(d xs * xs), to global memory for the later kernels and also into LDS: d xs in two 16-row pieces at `stage_s` and
 // `stage_s` + one 64-row tile (rows 0..15 of each, swizzled row layout; the caller passes a 16-row-aligned address: these are
 // exactly the LDS rows into which the same wave later loads its share of two 64-key tiles, so no other wave's
 // tile load can land on rows that are still being read) and, if `stage_r` is given, d xr into rows 0..31 of that
-// tile, delta into dl_stage[0..31]; the wave
+// tile, delta * scale into dl_stage[0..31]; the wave
 // takes them from there as MFMA operands / row statistics without waiting for (or re-reading) the global stores.
 // dO, x_s, x_r are read once and d xs, d xr are not read again by this kernel: their accesses are marked
 // non-temporal so that they do not push the K/V tiles, which neighbouring work-groups share, out of the L2.
@@ -521,7 +522,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void bwd_dq_kernel(FastBwdAr
 
 // ------------------------------------------------------------------------------------------------
 // LDS map of the dk/dv kernel at D = 128 (D = 64 has a kernel of its own below): three slots, each a 64-row q tile followed by a 64-row dx tile; 32 KB for the
-// probabilities handed from the V-role to the K-role waves; per slot the 64 log-sum-exp and 64 delta values of
+// probabilities handed from the V-role to the K-role waves; per slot the 64 lse2 and 64 delta values (as the dq kernel leaves them) of
 // its rows.  The linear branch uses the same space as two buffers of one 128-row q tile and one 128-row dx tile
 // each: A = slots 0-1, B = slot 2 + the hand-over area (which first receives the reverse-state tile).
 struct DkvLds {
@@ -816,8 +817,9 @@ __global__ __launch_bounds__(512) void bwd_dkv_kernel(FastBwdArgs a) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) px[i4 * 64] = f32x4_t{s[4 * i4], s[4 * i4 + 1], s[4 * i4 + 2], s[4 * i4 + 3]};
           } else {
-            // The K-role gets here first: what does not need P is done while it would wait for the V-role (3B-shaped layer:
-            // 907 -> 904.5 us a training step; the V-role's operands read ahead of the barrier too: 909).
+            // The K-role gets here first: what does not need P is done while it would wait for the V-role.  Behind the barrier
+            // instead, in turn on two boxes, a step of the 3B-shaped layer takes 881.1 us against 881.8 and 884.1 against
+            // 881.6, 12B-shaped 1204.8 against 1205.1 and 1214.0 against 1211.8: 0.3 % at most.
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = __builtin_fmaf(s[i], a.scale, -stat[i]);
 #pragma unroll

@@ -45,11 +45,12 @@ struct FastFwdArgs {
 // it by more than RESCALE_TH, so P stays below 2^RESCALE_TH; the exponentials do not wait for that decision, they are
 // formed again in the rare step that takes it.  Vector work is dealt out evenly between the matrix instructions and operand
 // reads run FWD_AHEAD instructions in front of their use, across the border of 1 and 2; scheduling fences keep the order of
-// the source.  What bounds the loop: a SIMD starts one vector or matrix instruction every 4.4 cycles (an exponential takes
-// two such slots, an LDS read about half of one), which at 16 matrix instructions of 32 cycles per step is as much time as
-// the matrix pipe needs, so neither may wait for the other.  Left to the scheduler, every V operand was read right in front
-// of its use and the exponentials and sums stood apart from the matrix instructions.  32768 tokens, W = 4096: 1.67 -> 1.52
-// ms; 3B-shaped layer: 0.211 -> 0.204 ms (its clock falls as the pipes fill: 2.1 of 2.4 GHz).
+// the source.  Left to the scheduler, every V operand was read right in front of its use and the exponentials and sums stood
+// apart from the matrix instructions.  The kernel on one box, by events, the scheduler's order -> this one with the tile loads
+// dealt out: 32768 tokens, W = 4096 1.65 -> 1.54 ms, 3B-shaped layer 0.210 -> 0.201, a chunk of 4 x 2048 tokens behind rings
+// of 512 0.114 -> 0.107.  By the counters (32768 tokens) the matrix pipe is busy for 61 % of the kernel (52 before) at 6.7
+// vector and matrix instructions, 1.5 LDS reads and 2.5 scalar instructions (3.6) per matrix instruction: the two waves of a
+// SIMD still leave a third of the pipe to their waits, and the clock falls as it fills (1.66 -> 1.57 GHz over the kernel).
 constexpr float RESCALE_TH = 8.f;
 constexpr float M_INIT = -1.0e30f;  // finite "minus infinity" for the running maximum
 constexpr int FWD_AHEAD = 4;

@@ -193,8 +193,16 @@ def test_fast_bwd_unit_gains_no_dgamma(B, T, Hq, Hkv, W):
 
 
 # what a forward and backward of a bf16 layer on the matrix cores launches (records carry "(rev)" for the reverse states)
-MATRIX_CORE_LAUNCHES = {"rla_chunk_kernel", "rla_scan_kernel", "fwd_fused_kernel", "bwd_dq_kernel", "dgamma_reduce_kernel",
+MATRIX_CORE_LAUNCHES = {"rla_chunk_kernel", "rla_scan_kernel", "fwd_fused_kernel", "bwd_dq_kernel",
                         "rla_chunk_kernel(rev)", "rla_scan_kernel(rev)", "bwd_dkv_kernel", "dkv_reduce_kernel"}
+
+
+def layer_launches(T, W):
+    """The same for gain gradients too: the scan of the reverse states sums them, and they have a launch of their own exactly
+    where no key lies beyond the window (rounded up to 64 keys) of a query row of the padded length."""
+    Tpad = (T + 127) // 128 * 128
+    causal = (min(W, Tpad) + 63) // 64 * 64 >= Tpad
+    return MATRIX_CORE_LAUNCHES | ({"tail_rows_kernel(gather)"} if T % 128 else set()) | ({"dgamma_reduce_kernel"} if causal else set())
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -237,7 +245,8 @@ def test_head_size_64_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
     assert "fwd_fused_kernel" in names and "bwd_dkv_kernel" in names
-    assert set(names) <= MATRIX_CORE_LAUNCHES | ({"tail_rows_kernel(gather)"} if T % 128 else set())
+    assert set(names) <= layer_launches(T, W)
+    assert ("dgamma_reduce_kernel" in names) != ("rla_scan_kernel(rev)" in names)
     kw = dict(scale=scale, gamma_swa=np64(gs), gamma_rla=np64(gr))
     ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, **kw)
     gmax = max(float(gs.abs().max()), float(gr.abs().max()), 1.0)
@@ -323,16 +332,25 @@ def test_running_maximum_raised_in_late_steps(T, W, D, rise):
                                                   (1, 896, 6, 1, 128, 128, 0),     # six over three: three products a state
                                                   (2, 512, 16, 2, 128, 65, 64), (1, 1024, 8, 2, 128, 64, 128),
                                                   (8, 1280, 32, 16, 64, 192, 0)])  # too many products: not split
-def test_reverse_states_of_split_heads(B, T, Hq, Hkv, D, W, chunk):
-    """Reverse states whose query heads are shared by several work-groups, and gain gradients summed in the same launch:
-    the same fp32 sums in another order, compared with the general kernels at the bound of two bf16 paths."""
+@pytest.mark.parametrize("phi", ["softmax", "relu"])
+def test_reverse_states_of_split_heads(B, T, Hq, Hkv, D, W, chunk, phi):
+    """Reverse states whose query heads are shared by several work-groups (the plan's own test says how many: the host check),
+    and gain gradients summed in the launch of their scan: the same fp32 sums in another order, compared with the general
+    kernels at the bound of two bf16 paths.  No launch of its own sums the gain gradients."""
     x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 2600 + T + Hq, with_dO=True, with_gains=True)
     q, k, v, dO, gs, gr = (x[n].cuda() for n in ("q", "k", "v", "dO", "gamma_swa", "gamma_rla"))
     got = {}
     for path in ("auto", "general"):
-        kw = dict(softmax_scale=1.0 / math.sqrt(D), kernel_path=path, chunk=chunk)
+        kw = dict(softmax_scale=1.0 / math.sqrt(D), kernel_path=path, chunk=chunk, feature_map=phi)
         _, saved = rb.rattn_fwd(q, k, v, W, gs, gr, save_for_bwd=True, **kw)
+        rb.rattn_profile_enable(True)
         got[path] = rb.rattn_bwd(q, k, v, saved, dO, W, gs, gr, **kw)
+        torch.cuda.synchronize()
+        names = [n for n, _ in rb.rattn_profile_records()]
+        rb.rattn_profile_enable(False)
+        if path == "auto":
+            assert names.count("rla_chunk_kernel(rev)") == names.count("rla_scan_kernel(rev)") == 1
+            assert "dgamma_reduce_kernel" not in names
     for n, a, b in zip(("dq", "dk", "dv", "dgs", "dgr"), got["auto"], got["general"]):
         rel = float((a.double() - b.double()).norm() / b.double().norm())
         print(f"{n}: relative 2-norm of the difference {rel:.2e}", flush=True)
@@ -402,7 +420,7 @@ def test_ragged_length_runs_on_the_matrix_cores(B, T, Hq, Hkv, W):
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
     assert "fwd_fused_kernel" in names and "bwd_dkv_kernel" in names and "tail_rows_kernel(gather)" in names
-    assert set(names) <= MATRIX_CORE_LAUNCHES | {"tail_rows_kernel(gather)"}   # no copies of whole tensors
+    assert set(names) <= layer_launches(T, W)   # no copies of whole tensors
     kw = dict(scale=scale, gamma_swa=np64(gs), gamma_rla=np64(gr))
     ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, **kw)
     gmax = max(float(gs.abs().max()), float(gr.abs().max()), 1.0)
