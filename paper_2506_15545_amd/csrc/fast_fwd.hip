@@ -50,7 +50,7 @@ struct FastFwdArgs {
 // dealt out: 32768 tokens, W = 4096 1.65 -> 1.54 ms, 3B-shaped layer 0.210 -> 0.201, a chunk of 4 x 2048 tokens behind rings
 // of 512 0.114 -> 0.107.  By the counters (32768 tokens) the matrix pipe is busy for 61 % of the kernel (52 before) at 6.7
 // vector and matrix instructions, 1.5 LDS reads and 2.5 scalar instructions (3.6) per matrix instruction: the two waves of a
-// SIMD still leave a third of the pipe to their waits, and the clock falls as it fills (1.66 -> 1.57 GHz over the kernel).
+// SIMD still leave two fifths of the pipe to their waits, and the clock falls as it fills (1.66 -> 1.57 GHz over the kernel).
 constexpr float RESCALE_TH = 8.f;
 constexpr float M_INIT = -1.0e30f;  // finite "minus infinity" for the running maximum
 constexpr int FWD_AHEAD = 4;
