@@ -118,9 +118,9 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   rattn::LayerDims& dm = L->dm;
   dm.B = p->B; dm.T = p->T; dm.Hq = p->Hq; dm.Hkv = p->Hkv; dm.D = p->D;
   dm.W = p->window; dm.G = p->Hq / p->Hkv;
-  dm.C = p->chunk > 0 ? p->chunk : 64;
-  dm.chunk_req = p->chunk;
   const int Tp = p->T > p->window ? p->T - p->window : 0;
+  dm.C = p->chunk > 0 ? p->chunk : rattn::generic_chunk(dm, Tp);
+  dm.chunk_req = p->chunk;
   dm.nst = Tp > 0 ? (Tp - 1) / dm.C + 1 : 0;
   dm.scale = p->softmax_scale; dm.eps = p->rms_eps; dm.phi = p->feature_map;
   L->esize = p->dtype == RATTN_F32 ? 4 : 2;

@@ -18,8 +18,13 @@
 //
 // Bound: launch latency and the dependent chain of a wave on small tensors, the fp32 matrix rate (157 TFLOP/s; a tile
 // takes 32 cycles, so operands out of L1 keep up) on large ones.  Measured, fp32, one sequence of T = 256, 2 heads,
-// D = 64, W = 32, forward + backward: 51 us in the kernels (forward 6 + 3 + 9, dq 10, reverse states 6 + 3, dk/dv 14),
-// 427 us with one wave per row and vector arithmetic, states walked in token order and built twice.
+// D = 64, W = 32, forward + backward: 42 us in three launches of eight waves per work-group; with states of 64 keys
+// and four waves 51 us in seven launches, with one wave per row and vector arithmetic 427 us.
+//
+// The other side's 16-row tiles are dealt out to the waves; a wave requests its next tile behind the products of this one
+// (D = 64; at D = 128 the backward kernels have no registers for that), and where both forms of the same rows are needed
+// the column form comes out of the row form through LDS instead of a second trip to memory: backward of 2 x 512 tokens, 2 x 2
+// heads, W = 128 61.0 -> 49.4 us at D = 64, 110.2 -> 91.0 at D = 128 (with eight waves, the same states).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -28,7 +33,7 @@ namespace rattn {
 
 namespace {
 
-constexpr int GW = 4;  // waves per work-group
+constexpr int GWC = 4;  // waves per work-group of the chunk products
 
 __device__ __forceinline__ f32x4_t mm4(float a, float b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -115,6 +120,16 @@ template <int D> struct ColForm {
     }
   }
 };
+
+// The column form of 16 rows held in row form, through the wave's own plane of LDS (a wave's LDS accesses are done in the
+// order they are issued, so no barrier is needed)
+template <int D> __device__ __forceinline__ void to_columns(const RowForm<D>& a, ColForm<D>& c, float* plane, int r16, int q4) {
+#pragma unroll
+  for (int j = 0; j < D / 16; ++j) *reinterpret_cast<f32x4_t*>(plane + r16 * (D + 4) + 16 * j + 4 * q4) = a.x[j];
+  __builtin_amdgcn_wave_barrier();
+  c.load([&](int i) { return plane + (4 * q4 + i) * (D + 4); }, r16);
+  __builtin_amdgcn_wave_barrier();
+}
 
 // <rows of a, columns b> over the features: element i = row 4*q4 + i of a against column r16
 template <int D> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
@@ -273,7 +288,7 @@ __global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict_
   const int c = first + blockIdx.x, g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   const int lane = lane_id(), w = wave_id(), r16 = lane & 15, q4 = lane >> 4;
   const int lo = c * C, hi = min(lo + C, Tp);
-  f32x4_t acc[NH][4 * NH];  // [feature tile GW*ft + w][value 4*hd + e]
+  f32x4_t acc[NH][4 * NH];  // [feature tile GWC*ft + w][value 4*hd + e]
 #pragma unroll
   for (int ft = 0; ft < NH; ++ft) zero<D>(acc[ft]);
   const int nt = (hi - lo + 63) / 64, nstep = GA * nt;
@@ -316,7 +331,7 @@ __global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict_
       for (int tg = 0; tg < 8; ++tg)
 #pragma unroll
         for (int ft = 0; ft < NH; ++ft) {
-          const float av = pf[(32 * half + 4 * tg + q4) * PS + 16 * (GW * ft + w) + r16];
+          const float av = pf[(32 * half + 4 * tg + q4) * PS + 16 * (GWC * ft + w) + r16];
 #pragma unroll
           for (int hd = 0; hd < NH; ++hd)
 #pragma unroll
@@ -331,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void gen_chunk_kernel(const AT* __restrict_
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int hd = 0; hd < NH; ++hd)
-        store4(U + (size_t)(16 * (GW * ft + w) + 4 * q4 + i) * D + 64 * hd + 4 * r16,
+        store4(U + (size_t)(16 * (GWC * ft + w) + 4 * q4 + i) * D + 64 * hd + 4 * r16,
                f32x4_t{acc[ft][4 * hd][i], acc[ft][4 * hd + 1][i], acc[ft][4 * hd + 2][i], acc[ft][4 * hd + 3][i]});
 }
 
@@ -361,10 +376,10 @@ __global__ __launch_bounds__(64) void gen_scan_kernel(float* __restrict__ U, con
 }
 
 // ------------------------------------------------------------------------------------------------
-// Forward.  grid (ceil((T - q0) / 16), Hq, B): 16 query rows of one head.  Only rows q0 .. T-1 have queries; q, o and the
-// saved tensors hold just those Tq = T - q0 rows per sequence.
-template <typename IO, int D>
-__global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+// Forward.  grid (ceil((T - q0) / 16), Hq, B), GW waves: 16 query rows of one head.  Only rows q0 .. T-1 have queries; q, o and the
+// saved tensors hold just those Tq = T - q0 rows per sequence.  states NULL: there are none (all keys in the first chunk).
+template <typename IO, int D, int GW>
+__global__ __launch_bounds__(64 * GW, 2) void gen_fwd_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
                                                          const IO* __restrict__ v, const float* __restrict__ gs,
                                                          const float* __restrict__ gr, const float* __restrict__ states,
                                                          IO* __restrict__ o, float* __restrict__ xs_out,
@@ -426,32 +441,40 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
   f32x4_t acc[D / 16];
   zero<D>(acc);
   if (has_lin) {
-    qv.feature(dm.phi);
     const int j = max(0, t0 - W) / C;
-    const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-#pragma unroll
-    for (int jj = 0; jj < D / 16; ++jj)
-      if (jj % GW == w) state_product<D>(S, jj, qv.x[jj], r16, q4, acc);
     const int lo = j * C, nt = (t_hi - W - lo) / 16 + 1;
+    RowForm<D> kf;
+    ColForm<D> vf;
+    auto request = [&](int n) {
+      kf.load(krow(lo + 16 * n + r16), q4);
+      vf.load([&](int i) { return vrow(lo + 16 * n + 4 * q4 + i); }, r16);
+    };
+    if (w < nt) request(w);
+    qv.feature(dm.phi);
+    if (states) {
+      const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
+#pragma unroll
+      for (int jj = 0; jj < D / 16; ++jj)
+        if (jj % GW == w) state_product<D>(S, jj, qv.x[jj], r16, q4, acc);
+    }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
-      RowForm<D> kf;
-      ColForm<D> vf;
-      kf.load(krow(s0 + r16), q4);
-      vf.load([&](int i) { return vrow(s0 + 4 * q4 + i); }, r16);
       kf.feature(dm.phi);
       f32x4_t c = row_product<D>(kf, qv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
       if (s0 + 15 > t0 - W) hide_unseen<D>(vf, c, see, r16, q4, acc);
+      if (n + GW < nt) kf.load(krow(s0 + 16 * GW + r16), q4);
       col_product<D>(vf, c, acc);
+      if (n + GW < nt) vf.load([&](int i) { return vrow(s0 + 16 * GW + 4 * q4 + i); }, r16);
     }
   }
   __syncthreads();
-  // ---- the waves' partial results and the combination: 16 threads per query row, features 64hf + 4c ..
+  // ---- the waves' partial results and the combination: 16 threads per query row, features 64hf + 4c .. (further waves
+  // repeat a row and store nothing)
   {
-    const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
+    const int row = (threadIdx.x >> 4) & 15, c = threadIdx.x & 15;
     float M = ml[0][row][0];
 #pragma unroll
     for (int r = 1; r < GW; ++r) M = fmaxf(M, ml[r][row][0]);
@@ -484,7 +507,7 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
     }
     const float r_s = rsqrtf(sum16(ss) / D + dm.eps), r_r = rsqrtf(sum16(sr) / D + dm.eps);
     const int tq = 16 * blockIdx.x + row;
-    if (tq < Tq) {
+    if (tq < Tq && threadIdx.x < 256) {
       const size_t off = ((size_t)(b * Tq + tq) * Hq + h) * D;
 #pragma unroll
       for (int hf = 0; hf < D / 64; ++hf) {
@@ -517,8 +540,8 @@ __global__ __launch_bounds__(256, 2) void gen_fwd_kernel(const IO* __restrict__ 
 //                   Such a range is at most five tiles, so each wave keeps the p and dp of its one or two.
 //   linear branch : dphi(q) = S_[j] dx_r + sum_{intra} <dx_r, v_s> phi(k_s);  dq += phi(q)*(dphi - <dphi,phi(q)>)
 //                   (softmax map; ReLU passes dphi where q > 0, identity passes it unchanged)
-template <typename IO, int D>
-__global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+template <typename IO, int D, int GW>
+__global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dq_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
                                                             const IO* __restrict__ v, const IO* __restrict__ dO,
                                                             const float* __restrict__ gs, const float* __restrict__ gr,
                                                             SavedPtrs sv, const float* __restrict__ states,
@@ -541,13 +564,14 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
   RowForm<D> dxs, dxr;
   float delta;
   {
-    RowForm<D> dy, x;
+    RowForm<D> dy, x, xr;   // requested together: the stores below could alias any of them
     dy.load(dO + qoff, q4);
+    xr.load((const float*)sv.xr + qoff, q4);
+    x.load((const float*)sv.xs + qoff, q4);
     const float r_s = sv.rs[so], r_r = sv.rr[so];
     float* dg = dgpart && w == 0 ? dgpart + ((size_t)(b * gridDim.x + blockIdx.x) * Hq + h) * D : nullptr;
     const size_t dg_which = (size_t)gridDim.x * gridDim.z * Hq * D;
-    auto branch = [&](const float* xp, const float* gain, float r, RowForm<D>& dx, float* dgp) {
-      x.load(xp + qoff, q4);
+    auto branch = [&](const RowForm<D>& x, const float* gain, float r, RowForm<D>& dx, float* dgp) {
       float mean = 0.f;
 #pragma unroll
       for (int j = 0; j < D / 16; ++j) {
@@ -566,8 +590,8 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
 #pragma unroll
       for (int j = 0; j < D / 16; ++j) dx.x[j] = r * dx.x[j] - x.x[j] * (r * r * r * mean);
     };
-    branch((const float*)sv.xr, gr, r_r, dxr, dg ? dg + dg_which : nullptr);
-    branch((const float*)sv.xs, gs, r_s, dxs, dg);
+    branch(xr, gr, r_r, dxr, dg ? dg + dg_which : nullptr);
+    branch(x, gs, r_s, dxs, dg);
     delta = dxs.dot(x);
     if (w == GW - 1 && live) {
 #pragma unroll
@@ -583,24 +607,29 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
   // ---- linear branch
   if (t_hi >= W) {
     const int j = max(0, t0 - W) / C;
-    const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-#pragma unroll
-    for (int jj = 0; jj < D / 16; ++jj)
-      if (jj % GW == w) state_product_t<D>(S, jj, dxr.x[jj], r16, q4, acc);
     const int lo = j * C, nt = (t_hi - W - lo) / 16 + 1;
+    RowForm<D> vf;
+    ColForm<D> kf;
+    auto request_v = [&](int n) { vf.load(vrow(lo + 16 * n + r16), q4); };
+    auto request_k = [&](int n) { kf.load([&](int i) { return krow(lo + 16 * n + 4 * q4 + i); }, r16); };
+    if (w < nt) { request_v(w); request_k(w); }
+    if (states) {
+      const float* S = states + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
+#pragma unroll
+      for (int jj = 0; jj < D / 16; ++jj)
+        if (jj % GW == w) state_product_t<D>(S, jj, dxr.x[jj], r16, q4, acc);
+    }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
-      RowForm<D> vf;
-      ColForm<D> kf;
-      vf.load(vrow(s0 + r16), q4);
-      kf.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16);
-      kf.feature(dm.phi);
       f32x4_t c = row_product<D>(vf, dxr);
+      if (n + GW < nt) request_v(n + GW);
+      kf.feature(dm.phi);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
       if (s0 + 15 > t0 - W) hide_unseen<D>(kf, c, see, r16, q4, acc);
       col_product<D>(kf, c, acc);
+      if (n + GW < nt) request_k(n + GW);
     }
     feature_backward<D>(q + qoff, acc, q4, dm.phi);
   }
@@ -611,11 +640,14 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
     const float lse = sv.lse[so];
     const int lo = max(0, t0 - W + 1), nt = (t_hi - lo) / 16 + 1;
     auto sees = [&](int s) { return (unsigned)(t - s) < (unsigned)W; };
-    // p and dp of the 16 keys from s0 on, 0 where the query does not see the key
+    float* plane = part + w * PL;
+    RowForm<D> kf, vf;
+    auto request = [&](int n) {
+      kf.load(krow(lo + 16 * n + r16), q4);
+      vf.load(vrow(lo + 16 * n + r16), q4);
+    };
+    // p and dp of the 16 keys from s0 on (in kf, vf), 0 where the query does not see the key
     auto scores = [&](int s0, f32x4_t& p, f32x4_t& dp) {
-      RowForm<D> kf, vf;
-      kf.load(krow(s0 + r16), q4);
-      vf.load(vrow(s0 + r16), q4);
       p = row_product<D>(kf, qv);
       dp = row_product<D>(vf, dxs);
 #pragma unroll
@@ -636,13 +668,16 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
       if (s0 + 15 > t0 || t_hi - s0 >= W) hide_unseen<D>(kc, da, see, r16, q4, acc);
       col_product<D>(kc, da, acc);
     };
-    auto keys = [&](int s0, ColForm<D>& kc) { kc.load([&](int i) { return krow(s0 + 4 * q4 + i); }, r16); };
+    constexpr bool AHEAD = D == 64;  // the next tile's rows requested behind this one's products (D = 128: no registers left)
+    if (AHEAD && w < nt) request(w);
     if (W <= SHORT_W) {
-      f32x4_t p[2], dp[2];
+      constexpr int NU = (5 + GW - 1) / GW;
+      f32x4_t p[NU], dp[NU];
       float dl = 0.f;
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < NU; ++u)
         if (w + GW * u < nt) {
+          if (!AHEAD || u) request(w + GW * u);
           scores(lo + 16 * (w + GW * u), p[u], dp[u]);
 #pragma unroll
           for (int i = 0; i < 4; ++i) dl += p[u][i] * dp[u][i];
@@ -651,20 +686,24 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
       if (q4 == 0) dsum[w][r16] = dl;
       __syncthreads();
       delta = (dsum[0][r16] + dsum[1][r16]) + (dsum[2][r16] + dsum[3][r16]);
+      if (GW == 8) delta += dsum[4][r16];  // (the fifth tile; the other waves have none)
       if (w == GW - 1 && live && q4 == 0) delta_out[so] = delta;
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int u = NU - 1; u >= 0; --u)
         if (w + GW * u < nt) {
+          if (u < NU - 1) kf.load(krow(lo + 16 * (w + GW * u) + r16), q4);  // (the last one's rows are still there)
           ColForm<D> kc;
-          keys(lo + 16 * (w + GW * u), kc);
+          to_columns<D>(kf, kc, plane, r16, q4);
           add(lo + 16 * (w + GW * u), kc, p[u], dp[u]);
         }
     } else {
       for (int n = w; n < nt; n += GW) {
-        ColForm<D> kc;
-        keys(lo + 16 * n, kc);
         f32x4_t p, dp;
+        ColForm<D> kc;
+        if (!AHEAD) request(n);
         scores(lo + 16 * n, p, dp);
+        to_columns<D>(kf, kc, plane, r16, q4);
+        if (AHEAD && n + GW < nt) request(n + GW);
         add(lo + 16 * n, kc, p, dp);
       }
     }
@@ -672,7 +711,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
   put_partial<D>(part + w * PL, acc, r16, q4);
   __syncthreads();
   const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
-  if (t0 + row < T) {
+  if (row < 16 && t0 + row < T) {
 #pragma unroll
     for (int hf = 0; hf < D / 64; ++hf) {
       f32x4_t s = {0.f, 0.f, 0.f, 0.f};
@@ -687,8 +726,8 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dq_kernel(const IO* __restrict
 // Backward, dk and dv.  grid (ceil(T / 16), Hkv, B): 16 key rows of one KV head; the G query heads of the group are
 // visited in turn, so no atomics are needed.  `rstates` are the reverse-time chunk states R_[j] = sum over query chunks
 // after j of phi(q)^T dx_r (summed over the group's heads); j is the chunk of the tile's last key.
-template <typename IO, int D>
-__global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
+template <typename IO, int D, int GW>
+__global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dkv_kernel(const IO* __restrict__ q, const IO* __restrict__ k,
                                                              const IO* __restrict__ v, const float* __restrict__ dxs,
                                                              const float* __restrict__ dxr, const float* __restrict__ delta,
                                                              const float* __restrict__ lse, const float* __restrict__ rstates,
@@ -707,21 +746,31 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
   f32x4_t dka[D / 16], dva[D / 16];
   zero<D>(dka);
   zero<D>(dva);
+  constexpr bool AHEAD = D == 64;  // (D = 128: no registers for the next tile's rows)
+  float* plane = part + w * PL;
+  RowForm<D> qf, dr;  // the rows of a query tile: q and d x_r or d x_s; their column forms go through the wave's plane
   // ---- linear branch: queries t = t' + W, t' >= s
   if (s0 < Tp) {
-    kv.feature(dm.phi);
     const int j = min(s_hi, Tp - 1) / C;
-    const float* R = rstates + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
-#pragma unroll
-    for (int jj = 0; jj < D / 16; ++jj)
-      if (jj % GW == w) {
-        state_product<D>(R, jj, kv.x[jj], r16, q4, dva);
-        state_product_t<D>(R, jj, vv.x[jj], r16, q4, dka);
-      }
     const int hi = min((j + 1) * C, Tp) - 1, nt = (hi - s0) / 16 + 1;
+    auto off = [&](int u) {  // of this lane's row of step u (heads outermost)
+      return ((size_t)(b * T + min(s0 + 16 * (u % nt) + r16, hi) + W) * Hq + g * G + u / nt) * D;
+    };
+    auto request_q = [&](int u) { qf.load(q + off(u), q4); };
+    auto request_d = [&](int u) { dr.load(dxr + off(u), q4); };
+    if (AHEAD && w < G * nt) { request_d(w); request_q(w); }
+    kv.feature(dm.phi);
+    if (rstates) {
+      const float* R = rstates + ((size_t)(b * Hkv + g) * dm.nst + j) * D * D;
+#pragma unroll
+      for (int jj = 0; jj < D / 16; ++jj)
+        if (jj % GW == w) {
+          state_product<D>(R, jj, kv.x[jj], r16, q4, dva);
+          state_product_t<D>(R, jj, vv.x[jj], r16, q4, dka);
+        }
+    }
     for (int u = w; u < G * nt; u += GW) {
-      const int h = g * G + u / nt, tp0 = s0 + 16 * (u % nt);
-      auto off = [&](int tp) { return ((size_t)(b * T + min(tp, hi) + W) * Hq + h) * D; };
+      const int tp0 = s0 + 16 * (u % nt);
       const bool all = tp0 >= s_hi && tp0 + 15 <= hi;  // every query of the tile sees every key
       bool see[4];
 #pragma unroll
@@ -732,67 +781,66 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
         if (!all) hide_unseen<D>(a, c, see, r16, q4, acc);
         col_product<D>(a, c, acc);
       };
-      {
-        RowForm<D> qf;
-        qf.load(q + off(tp0 + r16), q4);
-        ColForm<D> dc;
-        dc.load([&](int i) { return dxr + off(tp0 + 4 * q4 + i); }, r16);
-        qf.feature(dm.phi);
-        add(dc, row_product<D>(qf, kv), dva);
-      }
-      {
-        RowForm<D> dr;
-        dr.load(dxr + off(tp0 + r16), q4);
-        ColForm<D> qc;
-        qc.load([&](int i) { return q + off(tp0 + 4 * q4 + i); }, r16);
-        qc.feature(dm.phi);
-        add(qc, row_product<D>(dr, vv), dka);
-      }
+      ColForm<D> col;
+      if (!AHEAD) { request_d(u); request_q(u); }
+      const f32x4_t e = row_product<D>(dr, vv);
+      to_columns<D>(dr, col, plane, r16, q4);
+      if (AHEAD && u + GW < G * nt) request_d(u + GW);
+      qf.feature(dm.phi);
+      add(col, row_product<D>(qf, kv), dva);
+      to_columns<D>(qf, col, plane, r16, q4);
+      if (AHEAD && u + GW < G * nt) request_q(u + GW);
+      add(col, e, dka);
     }
+    kv.load(k + koff, q4);  // (as it is again, for the softmax branch)
     feature_backward<D>(k + koff, dka, q4, dm.phi);
     if (s >= Tp) {  // (a key without residual queries in a tile that has some: its column is zero up to here)
 #pragma unroll
       for (int e = 0; e < D / 16; ++e) dka[e] = dva[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    kv.load(k + koff, q4);
   }
   // ---- softmax branch: queries s .. s + W - 1
   {
     const int hi = s_hi < T - W ? s_hi + W - 1 : T - 1, nt = (hi - s0) / 16 + 1;  // (any W up to INT_MAX: no sum beyond T)
+    float lse_t[4], delta_t[4];
+    auto off = [&](int u) { return ((size_t)(b * T + min(s0 + 16 * (u % nt) + r16, hi)) * Hq + g * G + u / nt) * D; };
+    auto request_q = [&](int u) { qf.load(q + off(u), q4); };
+    auto request_d = [&](int u) {
+      dr.load(dxs + off(u), q4);
+      const int q0 = s0 + 16 * (u % nt);
+      const size_t sbase = (size_t)(b * Hq + g * G + u / nt) * T;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = min(q0 + 4 * q4 + i, hi);
+        lse_t[i] = lse[sbase + t];
+        delta_t[i] = delta[sbase + t];
+      }
+    };
+    if (AHEAD && w < G * nt) { request_q(w); request_d(w); }
     for (int u = w; u < G * nt; u += GW) {
-      const int h = g * G + u / nt, q0 = s0 + 16 * (u % nt);
-      auto off = [&](int t) { return ((size_t)(b * T + min(t, hi)) * Hq + h) * D; };
-      const size_t sbase = (size_t)(b * Hq + h) * T;
-      f32x4_t p, da;
-      {
-        RowForm<D> qf;
-        qf.load(q + off(q0 + r16), q4);
-        p = row_product<D>(qf, kv);
-      }
-      {
-        RowForm<D> dx;
-        dx.load(dxs + off(q0 + r16), q4);
-        da = row_product<D>(dx, vv);
-      }
+      const int q0 = s0 + 16 * (u % nt);
+      if (!AHEAD) { request_q(u); request_d(u); }
+      f32x4_t p = row_product<D>(qf, kv), da = row_product<D>(dr, vv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = q0 + 4 * q4 + i;
-        const size_t st = sbase + min(t, hi);
         see[i] = (unsigned)(t - s) < (unsigned)W && t <= hi;
-        p[i] = see[i] ? prob(p[i], dm.scale, lse[st]) : 0.f;
-        da[i] = see[i] ? p[i] * (da[i] - delta[st]) * dm.scale : 0.f;
+        p[i] = see[i] ? prob(p[i], dm.scale, lse_t[i]) : 0.f;
+        da[i] = see[i] ? p[i] * (da[i] - delta_t[i]) * dm.scale : 0.f;
       }
       const bool all = q0 >= s_hi && q0 + 15 <= hi && q0 + 15 - s0 < W;  // every query of the tile sees every key
       auto add = [&](ColForm<D>& a, f32x4_t x, f32x4_t (&acc)[D / 16]) {
         if (!all) hide_unseen<D>(a, x, see, r16, q4, acc);
         col_product<D>(a, x, acc);
       };
-      ColForm<D> c;
-      c.load([&](int i) { return dxs + off(q0 + 4 * q4 + i); }, r16);
-      add(c, p, dva);
-      c.load([&](int i) { return q + off(q0 + 4 * q4 + i); }, r16);
-      add(c, da, dka);
+      ColForm<D> col;
+      to_columns<D>(dr, col, plane, r16, q4);
+      if (AHEAD && u + GW < G * nt) request_d(u + GW);
+      add(col, p, dva);
+      to_columns<D>(qf, col, plane, r16, q4);
+      if (AHEAD && u + GW < G * nt) request_q(u + GW);
+      add(col, da, dka);
     }
   }
   const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
@@ -802,7 +850,7 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
     put_partial<D>(part + w * PL, which ? dva : dka, r16, q4);
     __syncthreads();
     IO* dst = which ? dv : dk;
-    if (s0 + row < T) {
+    if (row < 16 && s0 + row < T) {
 #pragma unroll
       for (int hf = 0; hf < D / 64; ++hf) {
         f32x4_t x = {0.f, 0.f, 0.f, 0.f};
@@ -816,27 +864,38 @@ __global__ __launch_bounds__(256, 2) void gen_bwd_dkv_kernel(const IO* __restric
 
 // ------------------------------------------------------------------------------------------------
 // host launchers
+// The states that the consumers read: none of their own where all keys lie in the first chunk, whose state is `init`
 template <typename AT, typename BT, int D, bool REV>
-void build_states(const LayerDims& dm, const void* a, const void* bsrc, float* states, int H, int GA, int off,
-                  const float* init, hipStream_t st) {
-  if (dm.nst <= 0) return;
-  const int first = REV ? 1 : 0;
-  if (dm.nst > 1) {
+const float* build_states(const LayerDims& dm, const void* a, const void* bsrc, float* states, int H, int GA, int off,
+                          const float* init, hipStream_t st) {
+  if (dm.nst <= 1) return init;
+  {
     ProfScope ps(REV ? "gen_chunk_kernel(rev)" : "gen_chunk_kernel", st);
     gen_chunk_kernel<AT, BT, D><<<dim3(dm.nst - 1, dm.Hkv, dm.B), 256, 0, st>>>(
-        (const AT*)a, (const BT*)bsrc, states, dm.T, H, GA, off, dm.T - dm.W, dm.C, dm.nst, first, dm.phi);
+        (const AT*)a, (const BT*)bsrc, states, dm.T, H, GA, off, dm.T - dm.W, dm.C, dm.nst, REV ? 1 : 0, dm.phi);
   }
   ProfScope ps(REV ? "gen_scan_kernel(rev)" : "gen_scan_kernel", st);
   gen_scan_kernel<REV><<<dim3(D * D / 256, dm.B * dm.Hkv), 64, 0, st>>>(states, init, dm.nst, D * D / 4);
+  return states;
 }
+
+// Eight waves share the other side's tiles where every work-group has a CU to itself.  Forward + backward in us, four | eight
+// waves: T = 256, 2 heads, W = 32, one chunk 49.0 | 42.0 at D = 64, 85.6 | 72.6 at D = 128; T = 512, 2 x 2 x 2 heads, W = 128,
+// chunks of 64 69.3 | 69.3, 134.0 | 125.2 (256 work-groups; with few tiles up to 2 us of it are lost: T = 128, W = 16 46.8 |
+// 49.4).
+bool wide_groups(const LayerDims& dm, int rows, int heads) { return (long long)((rows + 15) / 16) * heads * dm.B <= 256; }
 
 template <typename IO, int D>
 void launch_fwd(const LayerDims& dm, const void* q, const void* k, const void* v, const float* gs, const float* gr, void* o,
                 const SavedPtrs& sv, float* states, hipStream_t st, int q0, const float* state0) {
-  build_states<IO, IO, D, false>(dm, k, v, states, dm.Hkv, 1, 0, state0, st);
+  const float* s = build_states<IO, IO, D, false>(dm, k, v, states, dm.Hkv, 1, 0, state0, st);
   ProfScope ps("gen_fwd_kernel", st);
-  gen_fwd_kernel<IO, D><<<dim3((dm.T - q0 + 15) / 16, dm.Hq, dm.B), 256, 0, st>>>(
-      (const IO*)q, (const IO*)k, (const IO*)v, gs, gr, states, (IO*)o, (float*)sv.xs, (float*)sv.xr, sv.lse, sv.rs, sv.rr, dm, q0);
+  const dim3 grid((dm.T - q0 + 15) / 16, dm.Hq, dm.B);
+#define RATTN_GEN_FWD(GW_)                                                                                              \
+  gen_fwd_kernel<IO, D, GW_><<<grid, 64 * GW_, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, gs, gr, s, (IO*)o,    \
+                                                        (float*)sv.xs, (float*)sv.xr, sv.lse, sv.rs, sv.rr, dm, q0)
+  if (wide_groups(dm, dm.T - q0, dm.Hq)) RATTN_GEN_FWD(8); else RATTN_GEN_FWD(4);
+#undef RATTN_GEN_FWD
 }
 
 template <typename IO, int D>
@@ -844,22 +903,26 @@ void launch_bwd(const LayerDims& dm, const void* q, const void* k, const void* v
                 const SavedPtrs& sv, const void* dO, void* dq, void* dk, void* dv, float* dgs, float* dgr,
                 const GenericBwdWs& ws, hipStream_t st) {
   const int tiles = (dm.T + 15) / 16;
-  const float* states = (const float*)sv.states;
-  if (!states) {  // not kept by the forward: built again, where the reverse states go once dq has read them
-    build_states<IO, IO, D, false>(dm, k, v, ws.rstates, dm.Hkv, 1, 0, nullptr, st);
-    states = ws.rstates;
-  }
+  // not kept by the forward: built again, where the reverse states go once dq has read them
+  const float* states = sv.states && dm.nst > 1 ? (const float*)sv.states
+                                                : build_states<IO, IO, D, false>(dm, k, v, ws.rstates, dm.Hkv, 1, 0, nullptr, st);
   {
     ProfScope ps("gen_bwd_dq_kernel", st);
-    gen_bwd_dq_kernel<IO, D><<<dim3(tiles, dm.Hq, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, (const IO*)dO, gs, gr,
-                                                                       sv, states, (IO*)dq, ws.dxs, ws.dxr, ws.delta,
-                                                                       dgs || dgr ? ws.dgpart : nullptr, dm);
+#define RATTN_GEN_DQ(GW_)                                                                                                 \
+  gen_bwd_dq_kernel<IO, D, GW_><<<dim3(tiles, dm.Hq, dm.B), 64 * GW_, 0, st>>>(                                           \
+      (const IO*)q, (const IO*)k, (const IO*)v, (const IO*)dO, gs, gr, sv, states, (IO*)dq, ws.dxs, ws.dxr, ws.delta,     \
+      dgs || dgr ? ws.dgpart : nullptr, dm)
+    if (wide_groups(dm, dm.T, dm.Hq)) RATTN_GEN_DQ(8); else RATTN_GEN_DQ(4);
+#undef RATTN_GEN_DQ
   }
   if (dgs || dgr) dgamma_reduce(DgammaSum{ws.dgpart, dgs, dgr, tiles * dm.B, dm.Hq * D}, st);
-  build_states<IO, float, D, true>(dm, q, ws.dxr, ws.rstates, dm.Hq, dm.G, dm.W, nullptr, st);
+  const float* rstates = build_states<IO, float, D, true>(dm, q, ws.dxr, ws.rstates, dm.Hq, dm.G, dm.W, nullptr, st);
   ProfScope ps("gen_bwd_dkv_kernel", st);
-  gen_bwd_dkv_kernel<IO, D><<<dim3(tiles, dm.Hkv, dm.B), 256, 0, st>>>((const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr,
-                                                                       ws.delta, sv.lse, ws.rstates, (IO*)dk, (IO*)dv, dm);
+#define RATTN_GEN_DKV(GW_)                                                                                               \
+  gen_bwd_dkv_kernel<IO, D, GW_><<<dim3(tiles, dm.Hkv, dm.B), 64 * GW_, 0, st>>>(                                        \
+      (const IO*)q, (const IO*)k, (const IO*)v, ws.dxs, ws.dxr, ws.delta, sv.lse, rstates, (IO*)dk, (IO*)dv, dm)
+  if (wide_groups(dm, dm.T, dm.Hkv)) RATTN_GEN_DKV(8); else RATTN_GEN_DKV(4);
+#undef RATTN_GEN_DKV
 }
 
 }  // namespace

@@ -53,8 +53,18 @@ struct GenericBwdWs {
   float* dgpart;   // [2,RB,Hq,D], one gain-gradient partial per 16-row tile (RB = B ceil(T/16))
 };
 
+// Keys per chunk of the general kernels where the caller names none, Tp = the keys that leave some query's window.  Few
+// enough of them form one chunk: no query sees a whole chunk then, so no states are formed (two launches less in each
+// direction) and the consumers multiply out more pairs.  That is a question of idle compute units: forward + backward in
+// us, fp32, D = 64, chunks of 64 | one chunk; work-groups of 16 query rows, Tp:
+//   32, 224: 51.5 | 42.0;  50, 344: 55.2 | 55.4;  64, 384: 57.6 | 58.2;  200, 344: 66.6 | 67.2
+//   384, 176: 66.8 | 54.6;  512, 224: 69.0 | 65.4;  672, 320: 86.1 | 104.9
+//   2048, 112: 150 | 132;  3072, 176: 211 | 231;  4096, 224: 268 | 384
+// (D = 128 alike: 32, 224: 87.9 | 72.6;  512, 224: 131 | 114;  3072, 176: 443 | 452.)
+int generic_chunk(const LayerDims& dm, int Tp);
+
 // Only rows q0 .. T-1 have queries (q, o and the saved tensors hold just those); `states` receives the chunk states
-// (B*Hkv*nst*D*D floats); state0 (fp32 [B,Hkv,D,D], may be NULL): a linear-branch state that precedes key 0.
+// (B*Hkv*nst*D*D floats; nothing where nst is 1); state0 (fp32 [B,Hkv,D,D], may be NULL): a linear-branch state that precedes key 0.
 void generic_fwd(const LayerDims& dm, int dtype, const void* q, const void* k, const void* v, const float* gs,
                  const float* gr, void* o, const SavedPtrs& sv, float* states, hipStream_t st, int q0 = 0,
                  const float* state0 = nullptr);

@@ -16,6 +16,11 @@ bool fast_fwd_supported(const LayerDims& dm, int dtype) {
   return true;
 }
 
+int generic_chunk(const LayerDims& dm, int Tp) {
+  const long long groups = (long long)((dm.T + 15) / 16) * dm.Hq * dm.B;
+  return Tp > 64 && Tp <= (groups <= 256 ? 320 : groups <= 512 ? 224 : 128) ? Tp : 64;
+}
+
 FastFwdPlan fast_fwd_plan(const LayerDims& dm) {
   FastFwdPlan p;
   const int wt = dm.W >= dm.T ? dm.T : dm.W;
