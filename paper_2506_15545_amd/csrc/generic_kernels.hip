@@ -133,12 +133,14 @@ template <int D> __device__ __forceinline__ void to_columns(const RowForm<D>& a,
 
 // <rows of a, columns b> over the features: element i = row 4*q4 + i of a against column r16
 template <int D> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
-  f32x4_t t[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  f32x4_t t[4];  // short chains of products and a tree of sums: the rounding grows with the chain
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < D / 16; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[e & 1] = mm4(a.x[j][e], b.x[j][e], t[e & 1]);
-  return t[0] + t[1];
+    for (int e = 0; e < 4; ++e) t[e] = mm4(a.x[j][e], b.x[j][e], t[e]);
+  return (t[0] + t[1]) + (t[2] + t[3]);
 }
 // acc += sum over the 16 rows of row^T (x) p,  p[i] = coefficient of row 4*q4 + i for column r16
 template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a, f32x4_t p, f32x4_t (&acc)[D / 16]) {
