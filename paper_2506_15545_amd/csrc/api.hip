@@ -203,7 +203,8 @@ struct ChunkLayout {
   Layout L2;
   int R;   // ring rows in front of the chunk
   int P;   // matrix-core kernels: R rounded up to whole tiles, so that the chunk starts at a tile
-  size_t kc, vc, fwdws, partial, bytes;
+  rattn::ChunkPlan plan;   // matrix-core kernels
+  size_t kc, vc, fwdws, partial, states, bytes;
 };
 
 rattn_status make_chunk_layout(const rattn_params* p, int32_t pos0, ChunkLayout* C) {
@@ -236,8 +237,18 @@ rattn_status make_chunk_layout(const rattn_params* p, int32_t pos0, ChunkLayout*
   size_t off = 0;
   C->kc = off; off += align_up(nkv);
   C->vc = off; off += align_up(nkv);
-  C->fwdws = off; off += align_up(C->L2.fwd_bytes);
-  C->partial = off; off += align_up(rattn::export_plan(dmx).partial_bytes);
+  C->fwdws = off;
+  C->plan.nprod = 0;
+  if (C->L2.fast_fwd) C->plan = rattn::chunk_plan(C->L2.dmf, C->P, C->R, p->T);
+  if (C->plan.nprod > 0) {   // products, then states
+    off += align_up(C->plan.u_bytes);
+    C->states = off; off += align_up(rattn::fast_fwd_plan(C->L2.dmf).state_bytes);
+    C->partial = off;
+  } else {
+    C->states = off + C->L2.ff_states;
+    off += align_up(C->L2.fwd_bytes);
+    C->partial = off; off += align_up(rattn::export_plan(dmx).partial_bytes);
+  }
   C->bytes = off > 0 ? off : 256;
   return RATTN_OK;
 }
@@ -510,13 +521,13 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
   if (C.L2.fast_fwd) {
     // only the ring rows are gathered, as the whole 128-row tiles in front of the chunk's
     t.k = k; t.v = v; t.Tb = p->T; t.P = C.P; t.kmin = C.P - C.R;
-    if (C.P > 0) {
-      t.k_front = w + C.kc; t.v_front = w + C.vc;
-      rattn::chunk_ring(dm, C.P, C.R, pos0, k_ring, v_ring, w + C.kc, w + C.vc, st);
-    }
-    rattn::fast_fwd(C.L2.dmf, t, q, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws + C.L2.ff_u),
-                    w + C.fwdws + C.L2.ff_states, st, carried ? state : nullptr);
-    rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0, carried);
+    if (C.P > 0) { t.k_front = w + C.kc; t.v_front = w + C.vc; }
+    const rattn::ChunkHandover handover = {C.plan, k_ring, v_ring, state, C.R, pos0, carried ? 1 : 0};
+    if (C.plan.nprod > 0) t.handover = &handover;
+    else if (C.P > 0) rattn::chunk_ring(dm, C.P, C.R, pos0, k_ring, v_ring, w + C.kc, w + C.vc, st);
+    rattn::fast_fwd(C.L2.dmf, t, q, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws), w + C.states, st,
+                    carried ? state : nullptr);
+    if (C.plan.nprod == 0) rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0, carried);
   } else {
     t.k = w + C.kc; t.v = w + C.vc; t.Tb = dmx.T;
     rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, k, v, k_ring, v_ring, w + C.kc, w + C.vc, st);

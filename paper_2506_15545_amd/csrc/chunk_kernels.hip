@@ -8,6 +8,8 @@
 // the initial value of the forward state scan.  These kernels put the ring rows in time order in front of the chunk.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma.hpp"
+#include "segment_state.hpp"
 
 namespace rattn {
 
@@ -41,33 +43,113 @@ __global__ __launch_bounds__(256) void chunk_concat_kernel(const uint4* __restri
 }
 
 // Matrix-core kernels: only the ring rows, as the whole 128-row tiles [B, P, Hkv, D] that precede the chunk's; the P - R
-// rows in front of a ring that does not fill its tiles are zero.
-__global__ __launch_bounds__(256) void chunk_ring_kernel(const uint4* __restrict__ k_ring, const uint4* __restrict__ v_ring,
-                                                         uint4* __restrict__ kf, uint4* __restrict__ vf, int B, int P, int R,
-                                                         int Hkv, int W, int slot0, int row_vecs) {
-  // rows a quarter of P apart: four independent pairs of 16-byte copies per thread
-  const long long n = (long long)B * Hkv * (P / 4) * row_vecs, i = (long long)blockIdx.x * 256 + threadIdx.x;
+// rows in front of a ring that does not fill its tiles are zero.  One thread per four pairs of 16-byte copies, of rows a
+// quarter of P apart.
+struct RingGather {
+  const uint4 *k_ring, *v_ring;
+  uint4 *kf, *vf;
+  int B, P, R, Hkv, W, slot0, row_vecs;
+  int blocks() const { return (int)(((long long)B * Hkv * (P / 4) * row_vecs + 255) / 256); }
+};
+__device__ __forceinline__ void gather_ring(const RingGather& a, int block) {
+  const long long n = (long long)a.B * a.Hkv * (a.P / 4) * a.row_vecs, i = (long long)block * 256 + threadIdx.x;
   if (i >= n) return;
-  const int c = (int)(i % row_vecs);
-  long long r = i / row_vecs;
-  const int g = (int)(r % Hkv); r /= Hkv;
-  const int j0 = (int)(r % (P / 4)), b = (int)(r / (P / 4));
+  const int c = (int)(i % a.row_vecs);
+  long long r = i / a.row_vecs;
+  const int g = (int)(r % a.Hkv); r /= a.Hkv;
+  const int j0 = (int)(r % (a.P / 4)), b = (int)(r / (a.P / 4));
   uint4 x[4], y[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int j = j0 + P / 4 * u - (P - R);  // ring row, oldest first
-    int slot = slot0 + j;
-    slot = slot < W ? slot : slot - W;
-    const size_t src = (((size_t)b * Hkv + g) * W + slot) * row_vecs + c;
-    x[u] = j >= 0 ? k_ring[src] : make_uint4(0u, 0u, 0u, 0u);
-    y[u] = j >= 0 ? v_ring[src] : make_uint4(0u, 0u, 0u, 0u);
+    const int j = j0 + a.P / 4 * u - (a.P - a.R);  // ring row, oldest first
+    int slot = a.slot0 + j;
+    slot = slot < a.W ? slot : slot - a.W;
+    const size_t src = (((size_t)b * a.Hkv + g) * a.W + slot) * a.row_vecs + c;
+    x[u] = j >= 0 ? a.k_ring[src] : make_uint4(0u, 0u, 0u, 0u);
+    y[u] = j >= 0 ? a.v_ring[src] : make_uint4(0u, 0u, 0u, 0u);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const size_t dst = (((size_t)b * P + j0 + P / 4 * u) * Hkv + g) * row_vecs + c;
-    kf[dst] = x[u];
-    vf[dst] = y[u];
+    const size_t dst = (((size_t)b * a.P + j0 + a.P / 4 * u) * a.Hkv + g) * a.row_vecs + c;
+    a.kf[dst] = x[u];
+    a.vf[dst] = y[u];
   }
+}
+__global__ __launch_bounds__(256) void chunk_ring_kernel(RingGather a) { gather_ring(a, blockIdx.x); }
+
+// Chunk products and hand-over in one: the states that the forward's query tiles read and the state that the call leaves
+// are prefix sums over the same keys, so they come out of the same products (in the precision of the hand-over, which the
+// forward's states profit from) and one scan.
+// Bound: HBM for large batches, the launches for small ones.  Three launches with the forward instead of six (gather, products,
+// scan, forward, products of the hand-over, their sum): 4 x 2048 tokens after 2048, 8 KV heads, W = 512 154 -> 130 us (products
+// with the gather 21, scan 12 by the trace), 700 tokens after 1531, 32/8 heads 52.8 -> 41.0 us (9 + 6).
+
+// One-dimensional grid: block i < nprod * Hkv * B forms product i % nprod of (b, kv head) i / nprod, U[..][d][f]; the others
+// gather the ring for the forward.  Product 0 of a plan with a head covers rows [0, 64), all others ckeys rows, ended by row
+// `end`; rows in front of kmin do not exist.
+template <int PHI>
+__global__ __launch_bounds__(256, 2) void chunk_products_kernel(RingRows<128> k, RingRows<128> v, float* __restrict__ U, ChunkPlan pl,
+                                                                int nstate, RingGather ga) {
+  constexpr int D = 128;
+  __shared__ __align__(16) unsigned char smem[5 * TileGeom<D>::KT];
+  if ((int)blockIdx.x >= nstate) {
+    gather_ring(ga, blockIdx.x - nstate);
+    return;
+  }
+  const int c = blockIdx.x % pl.nprod, bg = blockIdx.x / pl.nprod;
+  k.b = v.b = bg / k.H;
+  k.g = v.g = bg % k.H;
+  const int lo = c < pl.head ? 0 : 64 * pl.head + pl.ckeys * (c - pl.head);
+  const int hi = min(c < pl.head ? 64 : lo + pl.ckeys, pl.end);
+  segment_state<D, PHI, true>(smem, lo, k.kmin, hi, k, v, U + (size_t)blockIdx.x * (D * D));
+}
+
+// Block i < nscan: one 32 x 32 tile of (b, kv head): the running sum starts from the carried state (or zero), is stored as
+// bf16 [d][f] in front of product head + per i for state i, and after the last product in fp32 [f][d] where the carried
+// state was (each element by the thread that read it; both go through LDS, transposed).  Eight products are in flight.  The other
+// blocks copy the chunk's last rows to their ring slots, which nothing reads any more.
+__global__ __launch_bounds__(256) void chunk_scan_kernel(const float* __restrict__ U, uint16_t* __restrict__ states, float* state,
+                                                         int carried, ChunkPlan pl, int nst, int nscan, RingCopy rc) {
+  constexpr int D = 128, NT = (D / 32) * (D / 32);
+  __shared__ float tr[32][33];
+  if ((int)blockIdx.x >= nscan) {
+    copy_rings(rc, blockIdx.x - nscan, gridDim.x - nscan);
+    return;
+  }
+  const int tile = blockIdx.x % NT, bg = blockIdx.x / NT, d0 = 32 * (tile / (D / 32)), f0 = 32 * (tile % (D / 32));
+  const int row = threadIdx.x >> 3, c4 = 4 * (threadIdx.x & 7);
+  float4* sp = reinterpret_cast<float4*>(state + (size_t)bg * (D * D) + (size_t)(f0 + row) * D + d0 + c4);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (carried) {
+    const float4 s = *sp;
+    tr[c4][row] = s.x; tr[c4 + 1][row] = s.y; tr[c4 + 2][row] = s.z; tr[c4 + 3][row] = s.w;
+    __syncthreads();
+    acc = make_float4(tr[row][c4], tr[row][c4 + 1], tr[row][c4 + 2], tr[row][c4 + 3]);
+    __syncthreads();
+  }
+  const size_t at = (size_t)(d0 + row) * D + f0 + c4;
+  const float* u0 = U + (size_t)bg * pl.nprod * (D * D) + at;
+  uint16_t* s0 = states + (size_t)bg * nst * (D * D) + at;
+  const int shift = pl.ckeys == 64 ? 1 : 0;   // products per state: 2 or 1
+  for (int c0 = 0; c0 < pl.nprod; c0 += 8) {
+    float4 u[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (c0 + j < pl.nprod) u[j] = *reinterpret_cast<const float4*>(u0 + (size_t)(c0 + j) * (D * D));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (c0 + j >= pl.nprod) break;
+      const int n = c0 + j - pl.head, i = n >> shift;
+      if (n >= 0 && (i << shift) == n && i < nst) {
+        const f32x4_t f = {acc.x, acc.y, acc.z, acc.w};
+        *reinterpret_cast<bf16x4_t*>(s0 + (size_t)i * (D * D)) = __builtin_convertvector(f, bf16x4_t);
+      }
+      acc.x += u[j].x; acc.y += u[j].y; acc.z += u[j].z; acc.w += u[j].w;
+    }
+  }
+  tr[c4][row] = acc.x; tr[c4 + 1][row] = acc.y; tr[c4 + 2][row] = acc.z; tr[c4 + 3][row] = acc.w;
+  __syncthreads();
+  *sp = make_float4(tr[row][c4], tr[row][c4 + 1], tr[row][c4 + 2], tr[row][c4 + 3]);
 }
 
 }  // namespace
@@ -84,11 +166,33 @@ void chunk_concat(const LayerDims& dmc, int dtype, int Tc, int R, int pos0, cons
 
 void chunk_ring(const LayerDims& dmc, int P, int R, int pos0, const void* k_ring, const void* v_ring, void* k_front,
                 void* v_front, hipStream_t st) {
-  const int row_vecs = dmc.D * 2 / 16;
-  const long long n = (long long)dmc.B * dmc.Hkv * (P / 4) * row_vecs;
+  const RingGather ga = {(const uint4*)k_ring, (const uint4*)v_ring, (uint4*)k_front, (uint4*)v_front, dmc.B, P, R, dmc.Hkv, dmc.W,
+                         (pos0 - R) % dmc.W, dmc.D * 2 / 16};
   ProfScope ps("chunk_ring_kernel", st);
-  chunk_ring_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((const uint4*)k_ring, (const uint4*)v_ring, (uint4*)k_front, (uint4*)v_front,
-                                                     dmc.B, P, R, dmc.Hkv, dmc.W, (pos0 - R) % dmc.W, row_vecs);
+  chunk_ring_kernel<<<ga.blocks(), 256, 0, st>>>(ga);
+}
+
+void chunk_states(const LayerDims& dm, const SeqTensors& t, float* U, void* states, hipStream_t st) {
+  const ChunkHandover& h = *t.handover;
+  const ChunkPlan& pl = h.plan;
+  const int slot0 = (h.pos0 - h.R) % dm.W, nst = fast_fwd_plan(dm).nstf, row_vecs = 128 * 2 / 16;
+  {
+    const RingGather ga = {(const uint4*)h.k_ring, (const uint4*)h.v_ring, (uint4*)t.k_front, (uint4*)t.v_front, dm.B, t.P, h.R,
+                           dm.Hkv, dm.W, slot0, row_vecs};
+    RingRows<128> k = {(const uint16_t*)h.k_ring, (const uint16_t*)t.k, 0, 0, dm.Hkv, dm.W, slot0, t.kmin, t.P, t.Tb}, v = k;
+    v.ring = (const uint16_t*)h.v_ring;
+    v.back = (const uint16_t*)t.v;
+    const int nstate = pl.nprod * dm.Hkv * dm.B;
+    ProfScope ps("chunk_products_kernel", st);
+    if (dm.phi == PHI_RELU) chunk_products_kernel<PHI_RELU><<<nstate + ga.blocks(), 256, 0, st>>>(k, v, U, pl, nstate, ga);
+    else chunk_products_kernel<PHI_SOFTMAX><<<nstate + ga.blocks(), 256, 0, st>>>(k, v, U, pl, nstate, ga);
+  }
+  const RingCopy rc = {(const uint4*)t.k, (const uint4*)t.v, (uint4*)h.k_ring, (uint4*)h.v_ring, dm.B, t.Tb, dm.Hkv, dm.W,
+                       row_vecs, h.pos0};
+  const long long total = (long long)dm.B * (t.Tb < dm.W ? t.Tb : dm.W) * dm.Hkv * row_vecs;
+  const int copy_blocks = (int)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048), nscan = 16 * dm.Hkv * dm.B;
+  ProfScope ps("chunk_scan_kernel", st);
+  chunk_scan_kernel<<<nscan + copy_blocks, 256, 0, st>>>(U, (uint16_t*)states, h.state, h.carried, pl, nst, nscan, rc);
 }
 
 }  // namespace rattn

@@ -91,12 +91,14 @@ void dgamma_reduce(const DgammaSum& dg, hipStream_t st);
 // Keys and values of the matrix-core kernels.  They work in 128-row tiles over a padded length (LayerDims::T); a sequence
 // has P rows in `*_front` tensors [B,P,Hkv,D] (chunked prefill: the ring in time order behind zero rows that fill the
 // first tile; P is a multiple of 128, else 0), then Tb rows in k, v [B,Tb,Hkv,D], and nothing after them.
+struct ChunkHandover;
 struct SeqTensors {
   const void *k, *v;
   int Tb;
-  const void *k_front = nullptr, *v_front = nullptr;
+  void *k_front = nullptr, *v_front = nullptr;
   int P = 0;
   int kmin = 0;   // keys in front of this row do not exist for the softmax branch
+  const ChunkHandover* handover = nullptr;   // see there
 };
 
 // MFMA forward path (bf16, padded length T % 128 == 0, any W >= 8)
@@ -111,6 +113,27 @@ struct FastFwdPlan {
 };
 bool fast_fwd_supported(const LayerDims& dm, int dtype);
 FastFwdPlan fast_fwd_plan(const LayerDims& dm);
+
+// Chunked prefill on the matrix cores: how the products of the forward's states and of the state that the call leaves are
+// shared (see chunk_kernels.hip)
+struct ChunkPlan {
+  int nprod;   // products per (batch, kv head); 0: nothing to share, or not worth it
+  int head;    // 1: product 0 covers the 64 rows in front of state 0
+  int ckeys;   // rows of every other product (64 or 128)
+  int end;     // row behind the last one that leaves the window
+  size_t u_bytes;
+};
+// dm: padded; P, R: front rows and how many of them are ring rows; Tc new rows
+ChunkPlan chunk_plan(const LayerDims& dm, int P, int R, int Tc);
+// Given to fast_fwd, which then also does what chunk_ring and prefill_export do: fills the front tensors from the rings,
+// and leaves rings and state advanced by the chunk.  U of fast_fwd: plan.u_bytes.
+struct ChunkHandover {
+  ChunkPlan plan;
+  void *k_ring, *v_ring;
+  float* state;
+  int R, pos0, carried;   // ring rows, position of the chunk's first row, whether `state` holds anything yet
+};
+void chunk_states(const LayerDims& dm, const SeqTensors& t, float* U, void* states, hipStream_t st);
 // dm.T: the padded length.  The query tiles computed are those of the Tb rows behind the front part; q, o and the saved
 // tensors hold just those rows ([B,Tb,Hq,D]; the saved tensors rounded up to whole tiles).  state0 (fp32
 // [B,Hkv,D(feature),D(value)], may be NULL): a linear-branch state that precedes key 0 and is added to every chunk state;

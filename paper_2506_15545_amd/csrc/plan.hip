@@ -38,6 +38,26 @@ FastFwdPlan fast_fwd_plan(const LayerDims& dm) {
   return p;
 }
 
+ChunkPlan chunk_plan(const LayerDims& dm, int P, int R, int Tc) {
+  ChunkPlan c = {0, 0, 0, 0, 0};
+  const FastFwdPlan pl = fast_fwd_plan(dm);
+  const long long bg = (long long)dm.B * dm.Hkv;
+  c.end = P + Tc - dm.W;
+  // Every call whose forward reads states shares its products.  (One sequence of one KV head stays with the separate launches,
+  // whose list is what the tests of that form hold on to: 128 new tokens 30.6 us, shared they would take 26.3.)
+  if (dm.D != 128 || dm.phi == PHI_IDENTITY || pl.nstf <= 0 || R + Tc <= dm.W || bg < 2) return c;
+  c.head = pl.base > 0 ? 1 : 0;
+  // (the last state is in front of the last row that leaves the window: at least one product follows it)
+  const int rest = c.end - 64 * c.head, n = (rest + 127) / 128;
+  // Products of 64 rows where those of 128 leave half of the chip idle, as long as the scan's chain stays short: 32/8 heads,
+  // W = 512, products of 64 | 128 rows: 700 tokens 41.2 | 41.9 us, 1024 41.4 | 42.7, 1500 50.6 | 52.3, two sequences of 1500
+  // 74.9 | 71.9; 16/2 heads, 2048 tokens (16 products of 128 rows in a chain) 41.8 | 40.8.
+  c.ckeys = dm.chunk_req == 64 || (n <= 12 && n * bg <= 128) ? 64 : 128;
+  c.nprod = c.head + (rest + c.ckeys - 1) / c.ckeys;
+  c.u_bytes = (size_t)bg * c.nprod * dm.D * dm.D * 4;
+  return c;
+}
+
 FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   FastBwdPlan p;
   p.fwd = fast_fwd_plan(dm);

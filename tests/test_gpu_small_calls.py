@@ -1,10 +1,12 @@
-"""General kernels on few tokens: one chunk without states or chunks of 64 keys, four or eight waves per work-group, at the
-edges of the rules that choose them."""
+"""Calls on few tokens.  General kernels: one chunk without states or chunks of 64 keys, four or eight waves per work-group, at the
+edges of the rules that choose them.  Chunked prefill: products shared between the forward and the hand-over."""
 import math
 
 import numpy as np
 import pytest
 import torch
+
+import parity_metrics as pm
 
 from oracle import rattn_oracle as orc
 from paper_2506_15545_amd import binding as rb, synth
@@ -48,3 +50,70 @@ def test_one_chunk_or_states(B, T, Hq, Hkv, W, states, D, phi):
         err = float(np.linalg.norm(np64(got) - want[n]) / np.linalg.norm(want[n]))
         print(f"{n}: {err:.2e}", flush=True)
         assert err <= 5e-6, n   # 2^-24 times a random walk over (T + D) terms and the two products in front of them
+
+
+SHARED = ["chunk_products_kernel", "chunk_scan_kernel", "fwd_fused_kernel"]
+
+
+@pytest.mark.parametrize("phi", ["softmax", "relu"])
+@pytest.mark.parametrize("B,Hq,Hkv,W,chunks", [
+    (1, 4, 4, 128, [384, 128, 127, 513]),     # no ring yet; whole tiles; one row less
+    (2, 8, 4, 64, [65, 191, 64, 300]),        # a ring of half a tile, rows in front of it, states at the 64 alignment
+    (1, 8, 8, 100, [150, 90, 70, 129]),       # window off the 64 grid: up to 63 keys more leave than the states hold
+    (1, 8, 8, 513, [300, 250, 333, 64]),      # ring filled over several calls, then wrapping
+    (3, 8, 8, 129, [257, 1100]),              # more than 128 whole products: 128 keys each
+    (1, 16, 16, 8, [140, 1000]),
+    (1, 2, 2, 200, [1800, 1]),                # more than 12 products in a chain: 128 keys each; one token
+])
+def test_chunk_products_shared_with_the_hand_over(B, Hq, Hkv, W, chunks, phi):
+    """Chunked prefill whose forward states and carried state come out of the same products, at the edges of its plan, against
+    the oracle's rows of one forward and its export: outputs to the bf16 bound, rings to the bit, the state to fp32."""
+    D, T = 128, sum(chunks)
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 5300 + T + W, with_gains=True)
+    scale = 1.0 / math.sqrt(D)
+    gs, gr = x["gamma_swa"], x["gamma_rla"]
+    ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, scale=scale, gamma_swa=np64(gs), gamma_rla=np64(gr),
+                        feature_map=phi)["o"]
+    q, k, v = (x[n].cuda() for n in ("q", "k", "v"))
+    kr, vr = (torch.full((B, Hkv, W, D), float("nan"), dtype=q.dtype, device="cuda") for _ in range(2))
+    S = torch.full((B, Hkv, D, D), float("nan"), dtype=torch.float32, device="cuda")
+    gmax = max(float(gs.abs().max()), float(gr.abs().max()), 1.0)
+    pos0 = 0
+    for n in chunks:
+        print(f"B={B} Hkv={Hkv} W={W} {phi}: tokens {pos0}..{pos0 + n - 1}", flush=True)
+        sl = slice(pos0, pos0 + n)
+        o, names = launches(lambda: rb.rattn_prefill_chunk(
+            q[:, sl].contiguous(), k[:, sl].contiguous(), v[:, sl].contiguous(), W, pos0, kr, vr, S, gs.cuda(), gr.cuda(),
+            softmax_scale=scale, feature_map=phi))
+        ring = min(pos0, W)
+        tiles = -(-ring // 128) + -(-n // 128)
+        shared = ring + n > W and tiles > -(-(-(-W // 64) * 64) // 128)
+        assert (names == SHARED) == shared, names
+        pm.assert_out_bf16(np64(o), ref[:, sl], gmax, what=f"chunk at {pos0}")
+        pos0 += n
+        kr_ref, vr_ref, S_ref = orc.prefill_export(np64(x["k"])[:, :pos0], np64(x["v"])[:, :pos0], W, feature_map=phi)
+        m = min(pos0, W)   # slots that hold tokens
+        assert np.array_equal(np64(kr)[:, :, :m], kr_ref[:, :, :m]) and np.array_equal(np64(vr)[:, :, :m], vr_ref[:, :, :m])
+        if pos0 > W:
+            assert float(np.max(np.abs(np64(S) - S_ref))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
+
+
+def test_chunk_products_of_infinite_values():
+    """An infinite value of one key, met by features of both kinds of zero, reaches its own column of the carried state only, as
+    it does where the products are not shared (one sequence at a time here)."""
+    D, W, Hkv, pos0, n = 128, 128, 4, 200, 256
+    x = synth.make_random_layer(1, pos0 + n, Hkv, Hkv, D, "bf16", 5400)
+    x["v"][0, 250, 1, 7] = float("inf")
+    q, k, v = (x[m].cuda() for m in ("q", "k", "v"))
+    got = []
+    for heads in (slice(0, Hkv), slice(1, 2)):
+        qh, kh, vh = (t[:, :, heads].contiguous() for t in (q, k, v))
+        kr, vr, S = rb.rattn_prefill_export(kh[:, :pos0].contiguous(), vh[:, :pos0].contiguous(), W)
+        _, names = launches(lambda: rb.rattn_prefill_chunk(qh[:, pos0:].contiguous(), kh[:, pos0:].contiguous(),
+                                                           vh[:, pos0:].contiguous(), W, pos0, kr, vr, S, softmax_scale=0.09))
+        got.append((S[0, 1 if len(got) == 0 else 0], names))
+    assert got[0][1] == SHARED and got[1][1] != SHARED
+    a, b = got[0][0], got[1][0]
+    assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and int((~torch.isfinite(a)).sum()) == D
+    fin = torch.isfinite(a)
+    assert float((a[fin] - b[fin]).abs().max()) <= 2e-5 * max(1.0, float(b[fin].abs().max()))
