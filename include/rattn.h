@@ -165,6 +165,16 @@ rattn_status rattn_decode_step(const rattn_decode_params* p, const void* q, cons
                                float* state, const float* gamma_swa, const float* gamma_rla,
                                void* o, void* stream);
 
+/* The same step with scratch memory: where few sequences have long rings, several work-groups share a (sequence, KV
+ * head) and meet in the workspace.  workspace: 16-byte aligned, rattn_decode_workspace_bytes() bytes (0 for steps that
+ * would not gain from it), contents arbitrary; NULL: rattn_decode_step.  Calls that overlap need workspaces of their
+ * own; a captured call may be replayed. */
+rattn_status rattn_decode_workspace_bytes(const rattn_decode_params* p, size_t* bytes);
+rattn_status rattn_decode_step_ws(const rattn_decode_params* p, const void* q, const void* k_new,
+                                  const void* v_new, const int32_t* pos, void* k_ring, void* v_ring,
+                                  float* state, const float* gamma_swa, const float* gamma_rla, void* o,
+                                  void* workspace, size_t workspace_bytes, void* stream);
+
 /* Prefill -> decode hand-over (Sec. 2.1: the window cache; Sec. 2.2 and Eq. 4: the lagged state).  From the keys
  * and values of a prompt of T tokens (k, v [B,T,Hkv,D] as in rattn_fwd; Hq, chunk, softmax_scale, rms_eps,
  * save_for_bwd of *p are not used but must be valid) it fills what rattn_decode_step with pos = T expects for

@@ -25,6 +25,7 @@ STATE_POLICIES = {"keep": 0, "rebuild": 1, "every2": 2, "every4": 4}
 _DTYPES = {torch.float32: RATTN_F32, torch.bfloat16: RATTN_BF16}
 
 EXPORTS = ["rattn_workspace_bytes", "rattn_fwd", "rattn_fwd_static", "rattn_bwd", "rattn_decode_step",
+           "rattn_decode_workspace_bytes", "rattn_decode_step_ws",
            "rattn_prefill_export_workspace_bytes", "rattn_prefill_export",
            "rattn_prefill_chunk_workspace_bytes", "rattn_prefill_chunk", "rattn_probe_mfma",
            "rattn_cache_bytes", "rattn_step_time_model",
@@ -75,6 +76,10 @@ def lib():
     L.rattn_bwd.argtypes = [ctypes.POINTER(RattnParams)] + [vp] * 13 + [sz, vp]
     L.rattn_decode_step.restype = ctypes.c_int
     L.rattn_decode_step.argtypes = [ctypes.POINTER(RattnDecodeParams)] + [vp] * 11
+    L.rattn_decode_workspace_bytes.restype = ctypes.c_int
+    L.rattn_decode_workspace_bytes.argtypes = [ctypes.POINTER(RattnDecodeParams), ctypes.POINTER(sz)]
+    L.rattn_decode_step_ws.restype = ctypes.c_int
+    L.rattn_decode_step_ws.argtypes = [ctypes.POINTER(RattnDecodeParams)] + [vp] * 11 + [sz, vp]
     L.rattn_prefill_export_workspace_bytes.restype = ctypes.c_int
     L.rattn_prefill_export_workspace_bytes.argtypes = [ctypes.POINTER(RattnParams), ctypes.POINTER(sz)]
     L.rattn_prefill_export.restype = ctypes.c_int
@@ -166,7 +171,10 @@ def _export_plan(k_shape, dtype, window, feature_map):
 @functools.lru_cache(maxsize=64)
 def _decode_plan(q_shape, Hkv, window, dtype, softmax_scale, rms_eps, feature_map):
     N, Hq, D = q_shape
-    return ctypes.byref(RattnDecodeParams(N, Hq, Hkv, D, window, _DTYPES[dtype], softmax_scale, rms_eps, FEATURE_MAPS[feature_map]))
+    p = RattnDecodeParams(N, Hq, Hkv, D, window, _DTYPES[dtype], softmax_scale, rms_eps, FEATURE_MAPS[feature_map])
+    nbytes = ctypes.c_size_t()
+    _check(lib().rattn_decode_workspace_bytes(ctypes.byref(p), ctypes.byref(nbytes)))
+    return ctypes.byref(p), nbytes.value
 
 
 def _check_layer(q, k, v):
@@ -284,12 +292,13 @@ def rattn_decode_step(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa=Non
     dt = q.dtype
     if dt not in _DTYPES or k_new.dtype != dt or v_new.dtype != dt or k_ring.dtype != dt or v_ring.dtype != dt:
         raise ValueError("q, k_new, v_new and the rings must share dtype float32 or bfloat16")
-    p = _decode_plan(qs, Hkv, W, dt, float(softmax_scale), float(rms_eps), feature_map)
+    p, nbytes = _decode_plan(qs, Hkv, W, dt, float(softmax_scale), float(rms_eps), feature_map)
     o = torch.empty_like(q) if out is None else out
     gs = _gain(gamma_swa, Hq, D, q.device)
     gr = _gain(gamma_rla, Hq, D, q.device)
-    _check(lib().rattn_decode_step(p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(pos), _ptr(k_ring),
-                                   _ptr(v_ring), _ptr(state), _ptr(gs), _ptr(gr), _ptr(o), _stream()))
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device) if nbytes else None
+    _check(lib().rattn_decode_step_ws(p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(pos), _ptr(k_ring), _ptr(v_ring), _ptr(state),
+                                      _ptr(gs), _ptr(gr), _ptr(o), _ptr(ws), nbytes, _stream()))
     return o
 
 

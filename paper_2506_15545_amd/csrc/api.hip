@@ -427,9 +427,8 @@ rattn_status rattn_bwd(const rattn_params* p, const void* q, const void* k, cons
   return check_launch("rattn_bwd");
 }
 
-rattn_status rattn_decode_step(const rattn_decode_params* p, const void* q, const void* k_new, const void* v_new,
-                               const int32_t* pos, void* k_ring, void* v_ring, float* state, const float* gamma_swa,
-                               const float* gamma_rla, void* o, void* stream) {
+namespace {
+rattn_status decode_dims(const rattn_decode_params* p, rattn::DecodeDims* dd) {
   if (!p) return fail(RATTN_ERR_INVALID_ARG, "params is NULL");
   if (p->N < 1 || p->Hq < 1 || p->Hkv < 1)
     return fail(RATTN_ERR_INVALID_ARG, "N, Hq, Hkv must be >= 1 (got %d, %d, %d)", p->N, p->Hq, p->Hkv);
@@ -446,17 +445,50 @@ rattn_status rattn_decode_step(const rattn_decode_params* p, const void* q, cons
   if (p->N > 65535) return fail(RATTN_ERR_UNSUPPORTED, "N must be <= 65535 (got %d)", p->N);
   if ((long long)p->N * p->Hkv * p->window * p->D >= (1ll << 40))
     return fail(RATTN_ERR_UNSUPPORTED, "ring buffers too large");
+  dd->N = p->N; dd->Hq = p->Hq; dd->Hkv = p->Hkv; dd->D = p->D; dd->W = p->window; dd->G = p->Hq / p->Hkv;
+  dd->scale = p->softmax_scale; dd->eps = p->rms_eps; dd->phi = p->feature_map;
+  return RATTN_OK;
+}
+// A number that no other call of this process has, spread over the upper 56 bits (the multiplier is odd: no two counts give
+// the same), so that what happens to lie in memory does not look like one
+unsigned long long decode_nonce() {
+  static unsigned long long count = 0;
+  return (__atomic_add_fetch(&count, 1, __ATOMIC_RELAXED) * 0x9E3779B97F4A7C15ull) << 8;
+}
+}  // namespace
+
+rattn_status rattn_decode_workspace_bytes(const rattn_decode_params* p, size_t* bytes) {
+  rattn::DecodeDims dd;
+  rattn_status s = decode_dims(p, &dd);
+  if (s != RATTN_OK) return s;
+  if (bytes) *bytes = rattn::decode_split(dd, p->dtype == RATTN_F32 ? 4 : 2).bytes;
+  return RATTN_OK;
+}
+
+rattn_status rattn_decode_step_ws(const rattn_decode_params* p, const void* q, const void* k_new, const void* v_new,
+                                  const int32_t* pos, void* k_ring, void* v_ring, float* state, const float* gamma_swa,
+                                  const float* gamma_rla, void* o, void* workspace, size_t workspace_bytes, void* stream) {
+  rattn::DecodeDims dd;
+  rattn_status s = decode_dims(p, &dd);
+  if (s != RATTN_OK) return s;
   if (!q || !k_new || !v_new || !pos || !k_ring || !v_ring || !state || !o)
     return fail(RATTN_ERR_INVALID_ARG, "q, k_new, v_new, pos, k_ring, v_ring, state, o must be non-NULL");
   if (!aligned16(q) || !aligned16(k_new) || !aligned16(v_new) || !aligned16(k_ring) || !aligned16(v_ring) ||
-      !aligned16(state) || !aligned16(o))
+      !aligned16(state) || !aligned16(o) || !aligned16(workspace))
     return fail(RATTN_ERR_INVALID_ARG, "tensor pointers must be 16-byte aligned");
-  rattn::DecodeDims dd;
-  dd.N = p->N; dd.Hq = p->Hq; dd.Hkv = p->Hkv; dd.D = p->D; dd.W = p->window; dd.G = p->Hq / p->Hkv;
-  dd.scale = p->softmax_scale; dd.eps = p->rms_eps; dd.phi = p->feature_map;
+  const size_t need = rattn::decode_split(dd, p->dtype == RATTN_F32 ? 4 : 2).bytes;
+  if (workspace && workspace_bytes < need)
+    return fail(RATTN_ERR_WORKSPACE, "decode step needs %zu workspace bytes (or none), got %zu", need, workspace_bytes);
+  if (workspace && need > 0) { dd.workspace = workspace; dd.nonce = decode_nonce(); }
   rattn::decode_step(dd, p->dtype, q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa, gamma_rla, o,
                      (hipStream_t)stream);
   return check_launch("rattn_decode_step");
+}
+
+rattn_status rattn_decode_step(const rattn_decode_params* p, const void* q, const void* k_new, const void* v_new,
+                               const int32_t* pos, void* k_ring, void* v_ring, float* state, const float* gamma_swa,
+                               const float* gamma_rla, void* o, void* stream) {
+  return rattn_decode_step_ws(p, q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa, gamma_rla, o, nullptr, 0, stream);
 }
 
 rattn_status rattn_prefill_export_workspace_bytes(const rattn_params* p, size_t* bytes) {

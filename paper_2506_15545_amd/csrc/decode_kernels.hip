@@ -161,6 +161,53 @@ constexpr size_t decode_lds_bytes(int D, int esize, int hb, int nw) {
   return (size_t)hb * (D * esize + 16) + ((size_t)(hb + 2) * D + DEC_HB + (size_t)nw * DEC_HB * 2 + (size_t)2 * nw * hb * D) * 4;
 }
 
+// Where few (sequence, kv head) pairs have long rings, several work-groups share each (decode_split, with times): a CU takes in
+// some 59 bytes a nanosecond, a hundredth of what the memory delivers.  Every work-group leaves the partial
+// results of its share of ring and state rows in the workspace; the one that arrives last adds them up in order (no matter who
+// that is), forms the output and puts the new token into its slot, from which everyone has taken the evicted one by then.
+// Nobody waits for anybody.
+// Arrivals are counted in a ticket per pair, nonce | count.  The workspace is not initialised: a ticket whose upper 56 bits are
+// not this call's nonce counts as zero, and the last arrival clears it, so that a captured launch finds none of its own
+// when it is replayed.  (A ticket that holds the nonce by accident, one in 2^56, is the one case that goes wrong.)
+struct SplitArgs {
+  float* part;                   // [pair][work-group][head][row]: window sums, state sums, maximum, sum of exponentials
+  unsigned long long* ticket;    // [pair]
+  unsigned long long nonce;      // low 8 bits zero
+  int n, rows;                   // work-groups per pair, 2 .. DEC_MAX_SPLIT, and ring rows that each takes at least
+  static constexpr __host__ __device__ int row(int D) { return 2 * D + 4; }
+};
+// Stores and loads of agent scope meet in memory, past the caches of an XCD.  So the order of a wave's own accesses is all
+// that an arrival needs: its stores are complete (vmcnt) before its work-group is counted, and the last one's loads are issued
+// after it was.  A release and an acquire of agent scope instead write back and drop the XCD's whole L2 for every
+// work-group: 12.0 -> 22.8 us at 16 work-groups for each of 4 pairs, 24 -> 83 at 4 for 256, where this way takes 18.2 and 30.4.
+__device__ __forceinline__ void put_shared(float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_shared(const float* p) { return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Called by the whole work-group after its put_shared; true in the one that arrives last, whose get_shared then see everyone's
+__device__ __forceinline__ bool arrive_last(unsigned long long* ticket, unsigned long long nonce, int n) {
+  __shared__ int last;
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  wait_vmem();  // this wave's stores are in memory
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    // A cleared ticket gets the nonce from whoever comes first, and one more arrival is counted, in one trip to memory
+    unsigned long long old = 0, now;
+    __hip_atomic_compare_exchange_strong(ticket, &old, nonce, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    now = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    // Added to something else: counted again by exchange (which fails only because another of the n arrivals came in between,
+    // n rounds at most for each of its two kinds)
+    if ((now & ~255ull) != nonce) {
+      old = now;
+      do now = (old & ~255ull) == nonce ? old + 1 : nonce + 1;
+      while (!__hip_atomic_compare_exchange_strong(ticket, &old, now, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    last = (int)(now & 255) == n;
+    if (last) __hip_atomic_store(ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return last != 0;
+}
+
 // Waves per SIMD the kernel is compiled for.  A set in flight and the accumulators take 96 registers, the sums of fp32 logits
 // of 128 features some 32 more; the loop over several groups of query heads keeps more alive.
 constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esize == 512 ? 2 : 4; }
@@ -175,11 +222,12 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // rings partly filled: 39 us (271 us with the scores of all W keys in LDS and vector arithmetic for more than four heads);
 // one sequence, 4 KV heads, W = 512: 11.2 us (18 us with four waves per KV head).
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
-template <typename IO, int D, int NW, bool MULTI>
+// SPLIT: nsplit work-groups share a (sequence, kv head), see split_combine.
+template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
 __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
     const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
     IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
-    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd) {
+    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd, SplitArgs split) {
   typedef RingSet<IO, D> Set;
   constexpr int EPL = D / 64, EV = Set::EV, NT = Set::KEYS / 16, NH = D / 64, QS = D + 16 / (int)sizeof(IO);
   const int W = dd.W, G = dd.G, Hq = dd.Hq, Hkv = dd.Hkv;
@@ -194,13 +242,17 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
   float* part_s = ml + NW * DEC_HB * 2; // [NW][HBmax][D]
   float* part_r = part_s + NW * HBmax * D;
 
-  const int g = blockIdx.x, n = blockIdx.y;
+  const int g = SPLIT ? blockIdx.x / split.n : blockIdx.x, sp = SPLIT ? blockIdx.x % split.n : 0, n = blockIdx.y;
   const int lane = lane_id(), w = wave_id();
   const int r16 = lane & 15, q4 = lane >> 4;
   const int p = pos[n];
   const int slot = p % W;
   const bool evict = p >= W;
   const int nvalid = min(p, W);  // ring rows written by earlier steps (with a full ring, row `slot` is the evicted token)
+  // A ring that is not full yet takes fewer work-groups; the others leave at once (one is no split at all)
+  const int nsplit = SPLIT ? min(split.n, (max(nvalid, 1) - 1) / split.rows + 1) : 1;
+  if (SPLIT && sp >= nsplit) return;
+  const int w0 = SPLIT ? w * nsplit + sp : w, nw = SPLIT ? NW * nsplit : NW;  // this wave among those of the (sequence, kv head)
   IO* kr = k_ring + (size_t)(n * Hkv + g) * W * D;
   IO* vr = v_ring + (size_t)(n * Hkv + g) * W * D;
   const IO* knr = k_new + (size_t)(n * Hkv + g) * D;
@@ -209,7 +261,7 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
   const int nset = (nvalid + Set::KEYS - 1) / Set::KEYS;
   // Work-groups run in lockstep over rings that lie a multiple of W*D elements apart; starting each one at a different
   // set spreads the simultaneous requests over the memory channels.
-  const int rot = (int)((blockIdx.y * gridDim.x + blockIdx.x) % (unsigned)max(nset, 1));
+  const int rot = (int)((n * Hkv + g) % (unsigned)max(nset, 1));
   auto set_base = [&](int it) { const int s = it + rot; return (s < nset ? s : s - nset) * Set::KEYS; };
   auto rows = [&](const IO* ring, int base) {
     return make_rsrc(ring + (size_t)base * D, (unsigned)(min(Set::KEYS, nvalid - base) * D * (int)sizeof(IO)));
@@ -255,22 +307,23 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
     };
     auto wanted = [&](int item) { return item < nh || (item < nitem && evict); };
     if (wanted(w)) load_item(w);
-    if (w < nset) {
-      set.load_k(rows(kr, set_base(w)), r16, q4);
-      set.load_v(rows(vr, set_base(w)), r16, q4);
+    if (w0 < nset) {
+      set.load_k(rows(kr, set_base(w0)), r16, q4);
+      set.load_v(rows(vr, set_base(w0)), r16, q4);
     }
     if (wanted(w)) stage_item(w);
     for (int item = w + NW; item < nitem; item += NW)
       if (wanted(item)) { load_item(item); stage_item(item); }
     __syncthreads();
-    // ---- the new token takes the slot of the evicted one (whose content now sits in LDS)
-    if (hb == 0 && w == NW - 1) {
+    // ---- the new token takes the slot of the evicted one (whose content now sits in LDS; SPLIT: in everyone's, see below)
+    auto put_new = [&]() {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
         kr[(size_t)slot * D + lane + 64 * e] = knr[lane + 64 * e];
         vr[(size_t)slot * D + lane + 64 * e] = vnr[lane + 64 * e];
       }
-    }
+    };
+    if (nsplit == 1 && hb == 0 && w == NW - 1) put_new();
     // ---- softmax branch
     auto window_branch = [&]() {
       f32x4_t acc[EV];
@@ -278,9 +331,9 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
       for (int e = 0; e < EV; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       float m = -1.0e30f, l = 0.f;
       const int qoff = min(r16, nh - 1) * QS;  // columns >= nh are never read back
-      for (int it = w; it < nset;) {
+      for (int it = w0; it < nset;) {
         const int base = set_base(it);
-        it += NW;
+        it += nw;
         const int next = it < nset ? set_base(it) : 0;
         f32x4_t s[NT];
         set.scores(qs + opaque(qoff), q4, s);
@@ -341,26 +394,26 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
       constexpr int NSTEP = D / 8, SPW = (NSTEP + NW - 1) / NW;
       // steps past the last one, and all stores of a state that is not updated, fall outside their resource
       const rsrc_t src = make_rsrc(S, D * D * 4), dst = make_rsrc(S, upd ? D * D * 4 : 0);
-      const int off0 = opaque(4 * ((8 * w + 2 * q4) * D + 4 * r16));
+      const int off0 = opaque(4 * ((8 * w0 + 2 * q4) * D + 4 * r16));
       f32x4_t sv[SPW][2][NH];
 #pragma unroll
       for (int j = 0; j < SPW; ++j)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int hf = 0; hf < NH; ++hf) sv[j][i][hf] = buf_load<f32x4_t>(src, off0 + 4 * (8 * NW * D * j + D * i + 64 * hf));
+          for (int hf = 0; hf < NH; ++hf) sv[j][i][hf] = buf_load<f32x4_t>(src, off0 + 4 * (8 * nw * D * j + D * i + 64 * hf));
 #pragma unroll
       for (int j = 0; j < SPW; ++j)
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const int f = min(8 * (w + NW * j), D - 8) + 2 * q4 + i;
+          const int f = min(8 * (w0 + nw * j), D - 8) + 2 * q4 + i;
           const float qv = qfh[f];
           const float kf = upd ? kfo[f] : 0.f;
 #pragma unroll
           for (int hf = 0; hf < NH; ++hf) {
             const f32x4_t s = sv[j][i][hf] + kf * vold[hf];
-            buf_store(dst, s, off0 + 4 * (8 * NW * D * j + D * i + 64 * hf));
-            if (NSTEP % NW == 0 || w + NW * j < NSTEP) {
+            buf_store(dst, s, off0 + 4 * (8 * nw * D * j + D * i + 64 * hf));
+            if ((!SPLIT && NSTEP % NW == 0) || w0 + nw * j < NSTEP) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) xr[4 * hf + e] = mfma16_f32(s[e], qv, xr[4 * hf + e]);
             }
@@ -379,15 +432,9 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
     __builtin_amdgcn_sched_barrier(0);  // (the registers of one branch at a time)
     linear_branch();
     __syncthreads();
-    // ---- the waves' partial results, the new token's, and the combination (Sec. 3.2); one wave per head
-    for (int hh = w; hh < nh; hh += NW) {
-      const int h = g * G + hb + hh;
-      float M = lnew[hh];
-#pragma unroll
-      for (int r = 0; r < NW; ++r) M = fmaxf(M, ml[(r * DEC_HB + hh) * 2]);
-      float a[EPL], c[EPL], den = Set::pexp(lnew[hh], M);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) { a[e] = den * io_traits<IO>::ld(vnr + lane + 64 * e); c[e] = 0.f; }
+    // sums over the waves of this work-group for head hh, relative to the maximum M: exponentials on top of den and both
+    // branches' accumulators on top of a, c
+    auto wave_sums = [&](int hh, float M, float& den, float (&a)[EPL], float (&c)[EPL]) {
 #pragma unroll
       for (int r = 0; r < NW; ++r) {
         const float sw = Set::pexp(ml[(r * DEC_HB + hh) * 2], M);
@@ -397,6 +444,63 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
           a[e] += sw * part_s[(r * HBmax + hh) * D + lane + 64 * e];
           c[e] += part_r[(r * HBmax + hh) * D + lane + 64 * e];
         }
+      }
+    };
+    auto wave_max_of = [&](int hh, float M) {
+#pragma unroll
+      for (int r = 0; r < NW; ++r) M = fmaxf(M, ml[(r * DEC_HB + hh) * 2]);
+      return M;
+    };
+    const size_t grp = (size_t)n * Hkv + g;
+    if (SPLIT && nsplit > 1) {
+      for (int hh = w; hh < nh; hh += NW) {
+        const float M = wave_max_of(hh, -1.0e30f);
+        float a[EPL], c[EPL], den = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) a[e] = c[e] = 0.f;
+        wave_sums(hh, M, den, a, c);
+        float* dst = split.part + ((grp * split.n + sp) * G + hh) * SplitArgs::row(D);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) { put_shared(dst + lane + 64 * e, a[e]); put_shared(dst + D + lane + 64 * e, c[e]); }
+        if (lane == 0) { put_shared(dst + 2 * D, M); put_shared(dst + 2 * D + 1, den); }
+      }
+      if (!arrive_last(split.ticket + grp, split.nonce, nsplit)) return;
+      if (w == NW - 1) put_new();  // every work-group has taken the evicted token out of the slot
+    }
+    // ---- the partial results, the new token's, and the combination (Sec. 3.2); one wave per head
+    for (int hh = w; hh < nh; hh += NW) {
+      const int h = g * G + hb + hh;
+      float a[EPL], c[EPL], den, M;
+      if (SPLIT && nsplit > 1) {
+        const float* src = split.part + (grp * split.n * G + hh) * SplitArgs::row(D);
+        const size_t step = (size_t)G * SplitArgs::row(D);
+        const float* mine = src + min(lane, nsplit - 1) * step + 2 * D;  // lane i: maximum and sum of work-group i
+        const float Mi = get_shared(mine), Li = get_shared(mine + 1);
+        float x[DEC_MAX_SPLIT][2 * EPL];
+#pragma unroll
+        for (int i = 0; i < DEC_MAX_SPLIT; ++i)
+          if (i < nsplit) {
+#pragma unroll
+            for (int e = 0; e < 2 * EPL; ++e) x[i][e] = get_shared(src + i * step + lane + 64 * e);
+          }
+        M = fmaxf(lnew[hh], wave_max(Mi));
+        const float own = Set::pexp(lnew[hh], M), sw = lane < nsplit ? Set::pexp(Mi, M) : 0.f;
+        den = own + wave_sum(sw * Li);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) { a[e] = own * io_traits<IO>::ld(vnr + lane + 64 * e); c[e] = 0.f; }
+#pragma unroll
+        for (int i = 0; i < DEC_MAX_SPLIT; ++i)
+          if (i < nsplit) {
+            const float wi = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sw), i));
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) { a[e] += wi * x[i][e]; c[e] += x[i][EPL + e]; }
+          }
+      } else {
+        M = wave_max_of(hh, lnew[hh]);
+        den = Set::pexp(lnew[hh], M);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) { a[e] = den * io_traits<IO>::ld(vnr + lane + 64 * e); c[e] = 0.f; }
+        wave_sums(hh, M, den, a, c);
       }
       // The window branch read the slot, while it changed from the evicted row to the new one, at a probability of 0, and
       // 0 times an infinite or NaN value is not 0.  A feature that came out without a number is formed again, key by key
@@ -438,31 +542,48 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
   } while (MULTI && hb < G);
 }
 
-template <typename IO, int D, int NW, bool MULTI>
-void launch_decode(const DecodeDims& dd, const void* q, const void* k_new, const void* v_new, const int32_t* pos,
-                   void* k_ring, void* v_ring, float* state, const float* gs, const float* gr, void* o, hipStream_t st) {
+struct DecodeTensors {
+  const void *q, *k_new, *v_new;
+  const int32_t* pos;
+  void *k_ring, *v_ring;
+  float* state;
+  const float *gs, *gr;
+  void* o;
+};
+
+template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
+void launch_decode(const DecodeDims& dd, const DecodeTensors& t, const SplitArgs& split, hipStream_t st) {
   const int hb = dd.G < DEC_HB ? dd.G : DEC_HB;
   const size_t bytes = decode_lds_bytes(D, sizeof(IO), hb, NW);
-  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI, SPLIT>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
   (void)attr;
-  decode_kernel<IO, D, NW, MULTI><<<dim3(dd.Hkv, dd.N), NW * 64, bytes, st>>>((const IO*)q, (const IO*)k_new, (const IO*)v_new, pos,
-                                                                      (IO*)k_ring, (IO*)v_ring, state, gs, gr, (IO*)o, dd);
+  decode_kernel<IO, D, NW, MULTI, SPLIT><<<dim3(dd.Hkv * (SPLIT ? split.n : 1), dd.N), NW * 64, bytes, st>>>(
+      (const IO*)t.q, (const IO*)t.k_new, (const IO*)t.v_new, t.pos, (IO*)t.k_ring, (IO*)t.v_ring, t.state, t.gs, t.gr,
+      (IO*)t.o, dd, split);
 }
 
 // Waves per (sequence, kv head): the fewer work-groups there are for the 256 CUs, the more of the waves a CU can hold
 // (4 SIMDs of decode_occ waves) each of them needs to keep its CU's share of the memory requests in flight.
 template <typename IO, int D, bool MULTI>
-void pick_decode(const DecodeDims& dd, const void* q, const void* k_new, const void* v_new, const int32_t* pos,
-                 void* k_ring, void* v_ring, float* state, const float* gs, const float* gr, void* o, hipStream_t st) {
+void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
+  if constexpr (!MULTI) {
+    const DecodeSplit ds = decode_split(dd, sizeof(IO));
+    if (dd.workspace && ds.n > 1) {
+      const SplitArgs split = {(float*)((char*)dd.workspace + ds.part_off), (unsigned long long*)dd.workspace, dd.nonce, ds.n, ds.rows};
+      launch_decode<IO, D, 8, false, true>(dd, t, split, st);
+      return;
+    }
+  }
+  const SplitArgs none = {nullptr, nullptr, 0, 1, 1};
   constexpr int cap = decode_occ(D, sizeof(IO), MULTI) == 4 ? 16 : 8;
   const long long groups = (long long)dd.N * dd.Hkv;
   int nw = 4;
   while (nw < cap && groups * nw < 256 * cap) nw *= 2;
-  while (nw > 4 && decode_lds_bytes(D, sizeof(IO), dd.G < DEC_HB ? dd.G : DEC_HB, nw) > 160 * 1024) nw /= 2;
-  if (nw == 4) launch_decode<IO, D, 4, MULTI>(dd, q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, st);
-  else if (nw == 8) launch_decode<IO, D, 8, MULTI>(dd, q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, st);
-  else if constexpr (cap == 16) launch_decode<IO, D, 16, false>(dd, q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, st);
+  while (nw > 4 && decode_lds_bytes(D, sizeof(IO), dd.G < DEC_HB ? dd.G : DEC_HB, nw) > 160 * 1024 - 256) nw /= 2;
+  if (nw == 4) launch_decode<IO, D, 4, MULTI, false>(dd, t, none, st);
+  else if (nw == 8) launch_decode<IO, D, 8, MULTI, false>(dd, t, none, st);
+  else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false>(dd, t, none, st);
 }
 
 }  // namespace
@@ -471,10 +592,11 @@ void decode_step(const DecodeDims& dd, int dtype, const void* q, const void* k_n
                  const int32_t* pos, void* k_ring, void* v_ring, float* state, const float* gs, const float* gr,
                  void* o, hipStream_t st) {
   ProfScope ps("decode_kernel", st);
-#define RATTN_DECODE(IO, DD)                                                                                          \
-  do {                                                                                                                \
-    if (dd.G <= DEC_HB) pick_decode<IO, DD, false>(dd, q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, st);   \
-    else pick_decode<IO, DD, true>(dd, q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, st);                   \
+  const DecodeTensors t = {q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o};
+#define RATTN_DECODE(IO, DD)                            \
+  do {                                                  \
+    if (dd.G <= DEC_HB) pick_decode<IO, DD, false>(dd, t, st);  \
+    else pick_decode<IO, DD, true>(dd, t, st);          \
   } while (0)
   if (dtype == 0) {
     if (dd.D == 64) RATTN_DECODE(float, 64); else RATTN_DECODE(float, 128);

@@ -210,7 +210,16 @@ struct DecodeDims {
   int N, Hq, Hkv, D, W, G;
   float scale, eps;
   int phi;  // as LayerDims::phi
+  void* workspace = nullptr;         // NULL, or decode_split(..).bytes
+  unsigned long long nonce = 0;      // with a workspace: a number no other call has, low 8 bits zero
 };
+// Work-groups that share a (sequence, kv head) in a decode step with a workspace (1: the step needs none)
+constexpr int DEC_MAX_SPLIT = 16;
+struct DecodeSplit {
+  int n, rows;   // work-groups, and ring rows that each takes at least (rings that are not full yet)
+  size_t part_off, bytes;   // tickets from offset 0
+};
+DecodeSplit decode_split(const DecodeDims& dd, int esize);
 void decode_step(const DecodeDims& dd, int dtype, const void* q, const void* k_new, const void* v_new,
                  const int32_t* pos, void* k_ring, void* v_ring, float* state, const float* gs, const float* gr,
                  void* o, hipStream_t st);

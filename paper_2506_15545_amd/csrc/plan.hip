@@ -103,6 +103,28 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
   return p;
 }
 
+DecodeSplit decode_split(const DecodeDims& dd, int esize) {
+  // A work-group of eight waves for every 64 KB of rings, up to 128 of them in all: more are bound by what the memory delivers.
+  // A step in us, one work-group per pair (16 waves) | 2 | 4 | 8 | 16 of eight waves, bf16, D = 128 (the ring-less part of a call
+  // takes 8, 9.5 with a workspace to allocate):
+  //   4 pairs, W = 512 12.0 | 10.7 | 9.5 | 9.5 | 10.3;  W = 2048 25.0 | 18.6 | 13.4 | 11.5 | 11.5;  W = 4096 42.8 | 29.0 | 18.6 | 13.7 | 12.7
+  //   16 pairs, W = 1024 15.9 | 13.4 | 11.0 | 11.0 | 12.4;  64, W = 512 14.3 | 13.3 | 13.4 | 15.1 | 26.5
+  //   128 pairs, W = 512 16.1 | 16.8 | 17.4;  W = 2048 38.1 | 34.1 | 34.2 | 39.4 (not taken: rings with 100 - 400 tokens
+  //   10.7 | 11.6);  192, W = 2048 35.5 | 39.2 | 39.6
+  //   32 pairs, D = 64, W = 512 7.8 | 9.9;  4 pairs, fp32, W = 512 18.5 | 15.4 | 12.6 | 11.2 | 11.8
+  DecodeSplit s = {1, dd.W, 0, 0};
+  const long long pairs = (long long)dd.N * dd.Hkv, ring = 2ll * dd.W * dd.D * esize;
+  if (dd.G > 16 || ring < 256 << 10) return s;
+  const int share = 64 << 10;
+  s.n = DEC_MAX_SPLIT;
+  while (s.n > 1 && (ring / s.n < share || pairs * s.n > 128)) s.n /= 2;
+  if (s.n < 2) return s;
+  s.rows = (int)(share * (long long)dd.W / ring);
+  s.part_off = ((size_t)pairs * 8 + 255) / 256 * 256;
+  s.bytes = s.part_off + (size_t)pairs * s.n * dd.G * (2 * dd.D + 4) * 4;
+  return s;
+}
+
 ExportPlan export_plan(const LayerDims& dm) {
   ExportPlan pl;
   pl.Tp = dm.T > dm.W ? dm.T - dm.W : 0;
