@@ -132,15 +132,17 @@ template <int D> __device__ __forceinline__ void to_columns(const RowForm<D>& a,
 }
 
 // <rows of a, columns b> over the features: element i = row 4*q4 + i of a against column r16
-template <int D> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
-  f32x4_t t[4];  // short chains of products and a tree of sums: the rounding grows with the chain
+// NC chains of products and a tree of sums: the rounding grows with the length of a chain, the additions with their number (in
+// large grids, which are bound by arithmetic, four take 2 % more than two)
+template <int D, int NC> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
+  f32x4_t t[NC];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) t[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < NC; ++e) t[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < D / 16; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = mm4(a.x[j][e], b.x[j][e], t[e]);
-  return (t[0] + t[1]) + (t[2] + t[3]);
+    for (int e = 0; e < 4; ++e) t[e % NC] = mm4(a.x[j][e], b.x[j][e], t[e % NC]);
+  return NC == 4 ? (t[0] + t[1]) + (t[2] + t[NC - 1]) : t[0] + t[1];
 }
 // acc += sum over the 16 rows of row^T (x) p,  p[i] = coefficient of row 4*q4 + i for column r16
 template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a, f32x4_t p, f32x4_t (&acc)[D / 16]) {
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_fwd_kernel(const IO* __restric
     }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n, next = s0 + 16 * GW;
-      f32x4_t s = row_product<D>(kf, qv);
+      f32x4_t s = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
       if (n + GW < nt) kf.load(krow(next + r16), q4);
       float mx = -INFINITY;
       bool see[4];
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_fwd_kernel(const IO* __restric
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
       kf.feature(dm.phi);
-      f32x4_t c = row_product<D>(kf, qv);
+      f32x4_t c = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
@@ -623,7 +625,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dq_kernel(const IO* __rest
     }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
-      f32x4_t c = row_product<D>(vf, dxr);
+      f32x4_t c = row_product<D, GW == 8 ? 4 : 2>(vf, dxr);
       if (n + GW < nt) request_v(n + GW);
       kf.feature(dm.phi);
       bool see[4];
@@ -650,8 +652,8 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dq_kernel(const IO* __rest
     };
     // p and dp of the 16 keys from s0 on (in kf, vf), 0 where the query does not see the key
     auto scores = [&](int s0, f32x4_t& p, f32x4_t& dp) {
-      p = row_product<D>(kf, qv);
-      dp = row_product<D>(vf, dxs);
+      p = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
+      dp = row_product<D, GW == 8 ? 4 : 2>(vf, dxs);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool see = sees(s0 + 4 * q4 + i);
@@ -785,11 +787,11 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dkv_kernel(const IO* __res
       };
       ColForm<D> col;
       if (!AHEAD) { request_d(u); request_q(u); }
-      const f32x4_t e = row_product<D>(dr, vv);
+      const f32x4_t e = row_product<D, GW == 8 ? 4 : 2>(dr, vv);
       to_columns<D>(dr, col, plane, r16, q4);
       if (AHEAD && u + GW < G * nt) request_d(u + GW);
       qf.feature(dm.phi);
-      add(col, row_product<D>(qf, kv), dva);
+      add(col, row_product<D, GW == 8 ? 4 : 2>(qf, kv), dva);
       to_columns<D>(qf, col, plane, r16, q4);
       if (AHEAD && u + GW < G * nt) request_q(u + GW);
       add(col, e, dka);
@@ -822,7 +824,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dkv_kernel(const IO* __res
     for (int u = w; u < G * nt; u += GW) {
       const int q0 = s0 + 16 * (u % nt);
       if (!AHEAD) { request_q(u); request_d(u); }
-      f32x4_t p = row_product<D>(qf, kv), da = row_product<D>(dr, vv);
+      f32x4_t p = row_product<D, GW == 8 ? 4 : 2>(qf, kv), da = row_product<D, GW == 8 ? 4 : 2>(dr, vv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
