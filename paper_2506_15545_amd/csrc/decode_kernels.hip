@@ -6,6 +6,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
+#include <type_traits>
 
 namespace rattn {
 
@@ -173,8 +174,13 @@ struct SplitArgs {
   float* part;                   // [pair][work-group][head][row]: window sums, state sums, maximum, sum of exponentials
   unsigned long long* ticket;    // [pair]
   unsigned long long nonce;      // low 8 bits zero
-  int n, rows;                   // work-groups per pair, 2 .. DEC_MAX_SPLIT, and ring rows that each takes at least
+  int n, rows;                   // work-groups per pair, 2 .. DEC_MAX_SPLIT, and ring rows for each before there is another
   static constexpr __host__ __device__ int row(int D) { return 2 * D + 4; }
+};
+struct NoSplit {
+  static constexpr float* part = nullptr;
+  static constexpr unsigned long long *ticket = nullptr, nonce = 0;
+  static constexpr int n = 1, rows = 1;
 };
 // Stores and loads of agent scope meet in memory, past the caches of an XCD.  So the order of a wave's own accesses is all
 // that an arrival needs: its stores are complete (vmcnt) before its work-group is counted, and the last one's loads are issued
@@ -227,7 +233,8 @@ template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
 __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
     const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
     IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
-    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd, SplitArgs split) {
+    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
+    std::conditional_t<SPLIT, SplitArgs, NoSplit> split) {
   typedef RingSet<IO, D> Set;
   constexpr int EPL = D / 64, EV = Set::EV, NT = Set::KEYS / 16, NH = D / 64, QS = D + 16 / (int)sizeof(IO);
   const int W = dd.W, G = dd.G, Hq = dd.Hq, Hkv = dd.Hkv;
@@ -249,8 +256,9 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
   const int slot = p % W;
   const bool evict = p >= W;
   const int nvalid = min(p, W);  // ring rows written by earlier steps (with a full ring, row `slot` is the evicted token)
-  // A ring that is not full yet takes fewer work-groups; the others leave at once (one is no split at all)
-  const int nsplit = SPLIT ? min(split.n, (max(nvalid, 1) - 1) / split.rows + 1) : 1;
+  // A ring that is not full yet takes fewer work-groups, a short one a single one; the others leave at once.  (56 pairs, W = 589,
+  // 177 - 281 tokens: 9.2 us with two, 8.7 with one.)
+  const int nsplit = !SPLIT || nvalid <= 3 * split.rows ? 1 : min(split.n, (nvalid - 1) / split.rows + 1);
   if (SPLIT && sp >= nsplit) return;
   const int w0 = SPLIT ? w * nsplit + sp : w, nw = SPLIT ? NW * nsplit : NW;  // this wave among those of the (sequence, kv head)
   IO* kr = k_ring + (size_t)(n * Hkv + g) * W * D;
@@ -552,7 +560,7 @@ struct DecodeTensors {
 };
 
 template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
-void launch_decode(const DecodeDims& dd, const DecodeTensors& t, const SplitArgs& split, hipStream_t st) {
+void launch_decode(const DecodeDims& dd, const DecodeTensors& t, std::conditional_t<SPLIT, SplitArgs, NoSplit> split, hipStream_t st) {
   const int hb = dd.G < DEC_HB ? dd.G : DEC_HB;
   const size_t bytes = decode_lds_bytes(D, sizeof(IO), hb, NW);
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI, SPLIT>),
@@ -575,7 +583,7 @@ void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
       return;
     }
   }
-  const SplitArgs none = {nullptr, nullptr, 0, 1, 1};
+  const NoSplit none;
   constexpr int cap = decode_occ(D, sizeof(IO), MULTI) == 4 ? 16 : 8;
   const long long groups = (long long)dd.N * dd.Hkv;
   int nw = 4;

@@ -216,7 +216,7 @@ struct DecodeDims {
 // Work-groups that share a (sequence, kv head) in a decode step with a workspace (1: the step needs none)
 constexpr int DEC_MAX_SPLIT = 16;
 struct DecodeSplit {
-  int n, rows;   // work-groups, and ring rows that each takes at least (rings that are not full yet)
+  int n, rows;   // work-groups, and ring rows for each before there is another (rings that are not full yet)
   size_t part_off, bytes;   // tickets from offset 0
 };
 DecodeSplit decode_split(const DecodeDims& dd, int esize);

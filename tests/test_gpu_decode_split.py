@@ -30,13 +30,14 @@ def workspace_bytes(N, Hq, Hkv, D, W, dtype):
 
 @pytest.mark.parametrize("N,Hq,Hkv,D,W,dtype,n,pos", [
     (1, 4, 1, 128, 512, "bf16", 4, [2000]),
-    (4, 6, 2, 128, 515, "bf16", 4, [0, 127, 128, 129]),         # one work-group, one, two: rings that are not full yet
-    (5, 6, 2, 128, 515, "bf16", 4, [383, 384, 514, 515, 516]),
+    (4, 6, 2, 128, 515, "bf16", 4, [0, 1, 384, 385]),           # one work-group, three, four: rings that are not full yet
+    (4, 6, 2, 128, 515, "bf16", 4, [512, 514, 515, 516]),
+    (3, 2, 1, 128, 1024, "bf16", 8, [512, 513, 897]),           # four, five, eight
     (2, 16, 1, 128, 4096, "bf16", 16, [4095, 9000]),            # all sixteen, sixteen heads
     (1, 5, 1, 64, 1025, "bf16", 4, [1024]),
     (3, 3, 1, 64, 1100, "f32", 8, [100, 1099, 5000]),
     (2, 16, 1, 128, 1030, "f32", 16, [700, 3333]),
-    (64, 8, 1, 128, 512, "bf16", 2, [511] * 32 + [700] * 32),   # 128 work-groups
+    (64, 8, 1, 128, 512, "bf16", 2, [400] * 32 + [700] * 32),   # 128 work-groups
     (65, 8, 1, 128, 512, "bf16", 1, [700] * 65),                # one pair more: no split
     (1, 1, 1, 128, 511, "bf16", 1, [700]),                      # rings below 256 KB
 ])
