@@ -1,7 +1,7 @@
 """ctypes binding of librattn.so: same entry-point names as include/rattn.h.
 
 Only argument marshalling happens here (shape checks, buffer allocation through torch,
-raw device pointers, the current HIP stream).  Every arithmetic step of the layer runs in
+raw device pointers, the current HIP stream; for the decode step in native code, _marshal).  Every arithmetic step of the layer runs in
 the library's kernels; there is no fallback: a missing library raises.
 """
 import ctypes
@@ -105,8 +105,18 @@ def lib():
     L.rattn_profile_count.restype = ctypes.c_int
     L.rattn_profile_get.restype = ctypes.c_int
     L.rattn_profile_get.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_float)]
+    from . import _marshal   # (built with the library)
+    addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    _marshal.bind(addr(L.rattn_decode_step_ws), addr(L.rattn_decode_workspace_bytes))
+    global _decode_native
+    _decode_native = _marshal.decode_step
     _lib = L
     return L
+
+
+def _decode_native(*args):   # until the library is loaded
+    lib()
+    return _decode_native(*args)
 
 
 def _check(status):
@@ -277,6 +287,12 @@ def rattn_bwd(q, k, v, saved, dO, window, gamma_swa=None, gamma_rla=None, chunk=
 def rattn_decode_step(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa=None, gamma_rla=None,
                       softmax_scale=1.0, rms_eps=1e-6, out=None, feature_map="softmax"):
     """One decode step; k_ring, v_ring, state are updated in place; returns o [N,Hq,D]."""
+    o = _decode_native(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa, gamma_rla, softmax_scale, rms_eps, out, feature_map)
+    if o is not None:
+        if o.__class__ is int:
+            _check(o)
+        return o
+    # arguments that need converting, or are refused
     qs, ks, rs = q.shape, k_new.shape, k_ring.shape
     N, Hq, D = qs
     Hkv, W = rs[1], rs[2]

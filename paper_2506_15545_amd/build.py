@@ -1,13 +1,17 @@
-"""Builds librattn.so (HIP, gfx950 only) in-tree with hipcc.  No torch involved."""
+"""Builds librattn.so (HIP, gfx950 only) in-tree with hipcc, no torch involved, and _marshal.so, the binding's native argument
+marshalling (host code against torch's headers)."""
+import importlib.util
 import os
 import shutil
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "librattn.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 OBJDIR = os.path.join(PKG, "_build")
 
 # packed fp32 VALU forms are switched off on purpose: some of them have produced wrong results on gfx950 boxes
@@ -27,8 +31,22 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
+def build_marshal():
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    inc = os.path.join(torch, "include")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-I", os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L", os.path.join(torch, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s\n%s" % (r.stdout, r.stderr))
+
+
 def build_library(verbose=False, jobs=8):
-    """Compile every csrc/*.hip and link paper_2506_15545_amd/librattn.so.  Always recompiles."""
+    """Compile every csrc/*.hip and link paper_2506_15545_amd/librattn.so, and build _marshal.so.  Always recompiles."""
     os.makedirs(OBJDIR, exist_ok=True)
     cc = hipcc()
 
@@ -43,7 +61,9 @@ def build_library(verbose=False, jobs=8):
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(compile_one, sources()))
+        marshal.result()
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -1,0 +1,64 @@
+"""The decode step's native argument marshalling: what is not plainly an accepted call goes to the Python path, which converts or
+refuses it as ever; both give the same."""
+import pytest
+import torch
+
+from paper_2506_15545_amd import binding as rb
+
+
+def tensors(dev, N=2, Hq=4, Hkv=2, D=64, W=16, dtype=torch.float32):
+    g = torch.Generator().manual_seed(5900)
+    r = lambda *s, dt=dtype: torch.randn(*s, generator=g).to(device=dev, dtype=dt)
+    return dict(q=r(N, Hq, D), k_new=r(N, Hkv, D), v_new=r(N, Hkv, D), pos=torch.tensor([3, 40], dtype=torch.int32, device=dev),
+                k_ring=r(N, Hkv, W, D), v_ring=r(N, Hkv, W, D), state=r(N, Hkv, D, D, dt=torch.float32))
+
+
+def native(t, gs=None, gr=None, scale=0.125, eps=1e-6, out=None, phi="softmax"):
+    rb.lib()
+    return rb._decode_native(*t.values(), gs, gr, scale, eps, out, phi)
+
+
+def test_host_tensors_are_refused_as_ever():
+    t = tensors("cpu")
+    assert native(t) is None
+    with pytest.raises(ValueError, match="q must be a contiguous device tensor"):
+        rb.rattn_decode_step(**t)
+    with pytest.raises((ValueError, AttributeError)):
+        rb.rattn_decode_step(None, **{k: v for k, v in t.items() if k != "q"})
+    with pytest.raises(TypeError):
+        rb._decode_native(t["q"])
+
+
+@pytest.mark.gpu
+def test_forms_that_python_converts_or_refuses():
+    t = tensors("cuda")
+    gain = torch.full((4, 64), 1.25, device="cuda")
+    refused = [dict(q=t["q"].transpose(1, 2)), dict(pos=t["pos"].long()), dict(state=t["state"].bfloat16()),
+               dict(k_ring=t["k_ring"][:, :, :8].contiguous()), dict(v_new=t["v_new"].bfloat16()), dict(q=t["q"].half()),
+               dict(pos=t["pos"][:1].contiguous()), dict(k_new=t["k_new"].cpu())]
+    for change in refused:
+        bad = {**t, **change}
+        assert native(bad) is None, change.keys()
+        with pytest.raises(ValueError):
+            rb.rattn_decode_step(**bad)
+    # the library's own refusals come out as its status
+    with pytest.raises(rb.RattnError):
+        rb.rattn_decode_step(**t, rms_eps=0.0)
+    with pytest.raises(ValueError):
+        rb.rattn_decode_step(**t, gamma_swa=gain[:3])
+    with pytest.raises(KeyError):
+        rb.rattn_decode_step(**t, feature_map="cosine")
+    fresh = lambda: {k: v.clone() for k, v in t.items()}
+    out = torch.empty_like(t["q"])
+    x = fresh()
+    assert native(x, gain, None, out=out) is out
+    for phi in ("softmax", "relu", "identity"):
+        want = rb.rattn_decode_step(**fresh(), gamma_swa=gain, softmax_scale=0.125, feature_map=phi)
+        for gs, scale in ((gain.double(), 0.125), (gain.bfloat16(), 0.125), (gain.t().contiguous().t(), 0.125),
+                          (gain, torch.tensor(0.125)), (gain.cpu(), 0.125)):
+            x = fresh()
+            assert native(x, gs, None, scale, phi=phi) is None
+            got = rb.rattn_decode_step(**x, gamma_swa=gs, softmax_scale=scale, feature_map=phi)
+            assert torch.equal(got, want)
+    assert torch.equal(out, rb.rattn_decode_step(**fresh(), gamma_swa=gain, softmax_scale=0.125))
+    assert not torch.equal(rb.rattn_decode_step(**fresh(), softmax_scale=1), out)
