@@ -170,6 +170,87 @@ __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__
   }
 }
 
+// Few products: products and scan in one launch.  A work-group holds all chunks of one (b, kv head) in LDS, for 32 value
+// features, and keeps the running sum in registers.  The map is formed once for every 32 value features, so that a launch is
+// saved only where there are few chunks (MAX_WALK, see rla_forward_states).  Each product is a sum of its own, added in order.
+struct WalkArgs {
+  const uint16_t *a, *b;   // rows that go through phi, rows multiplied in: [B,T,H,D]
+  uint16_t* states;
+  int H, T, B, head, nchunks, nst;   // product 0 covers 64 rows if head is 1; state i is the sum of products 0 .. head + i - 1
+};
+constexpr int MAX_WALK = 3;
+constexpr int walk_bytes(int D) { return 128 * (2 * D + 64); }   // LDS of a chunk: rows of a, 32 features of b
+// 512 threads; D/32 work-groups per (b, kv head).  Rows of 32 features of b need no swizzle (4 rows of 64 bytes are all banks).
+// Wave w < D/32 owns features 32w .. of phi.
+template <int D, int FM>
+__global__ __launch_bounds__(512) void rla_walk_kernel(WalkArgs p) {
+  typedef TileGeom<D> TG;
+  constexpr int NS = D / 32, AT = 128 * TG::ROWB, CB = walk_bytes(D), NBLK = AT / 1024 / 8;
+  extern __shared__ __align__(16) unsigned char chunks[];
+  const int pair = blockIdx.x / NS, slice = blockIdx.x % NS, g = pair % p.H, b = pair / p.H;
+  const int lane = lane_id(), w = wave_id(), r32 = lane & 31, h = lane >> 5;
+  const size_t rstride = (size_t)p.H * D;
+  const uint16_t* arow = p.a + ((size_t)b * p.T * p.H + g) * D;
+  const uint16_t* brow = p.b + ((size_t)b * p.T * p.H + g) * D + 32 * slice;
+  auto rows = [&](int c) { return c < p.head ? 64 : 128; };
+  for (int c = 0; c < p.nchunks; ++c) {
+    unsigned char* at = chunks + c * CB;
+    const int lo = c < p.head ? 0 : 64 * p.head + 128 * (c - p.head), n = rows(c);
+#pragma unroll
+    for (int i = 0; i < NBLK; ++i) {
+      const int blk = NBLK * w + i, r = blk * TG::RPB + lane / TG::CH;
+      if (blk * TG::RPB < n)
+        dma16(arow + (size_t)(lo + r) * rstride + (((lane % TG::CH) ^ swz<D>(r)) << 3), (unsigned)(size_t)RATTN_LDS(at + blk * 1024));
+    }
+    if (16 * w < n) dma16(brow + (size_t)(lo + 16 * w + lane / 4) * rstride + 8 * (lane % 4), (unsigned)(size_t)RATTN_LDS(at + AT + w * 1024));
+  }
+  int aoff[2], boff[2];
+#pragma unroll
+  for (int ab = 0; ab < 2; ++ab) {
+    aoff[ab] = tr_lane_off<D>(8 * h + 4 * ab, w % NS, lane);
+    boff[ab] = AT + (8 * h + 4 * ab + ((lane & 15) >> 2)) * 64 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+  }
+  uint16_t* out = p.states + (size_t)pair * p.nst * (D * D) + (size_t)(32 * slice + 4 * h) * D + 32 * w + r32;
+  f32x16_t run = {0};
+  auto put = [&](int i) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      out[(size_t)i * (D * D) + (size_t)(8 * (e >> 2) + (e & 3)) * D] = __builtin_bit_cast(uint16_t, (__bf16)run[e]);
+  };
+  wait_vmem();
+  __syncthreads();
+  for (int c = 0; c < p.nchunks; ++c) {
+    const int row = threadIdx.x >> 2;
+    phi_row_inplace<FM, D, 4>(row < rows(c) ? chunks + c * CB : nullptr, row, threadIdx.x & 3);
+  }
+  __syncthreads();
+  if (w >= NS) return;
+  if (p.head == 0) put(0);
+  for (int c = 0; c < p.nchunks; ++c) {
+    const unsigned char* at = chunks + c * CB;
+    f32x16_t acc = {0};
+    for (int ks = 0; ks < rows(c) / 16; ++ks)
+      acc = mfma32(lds_tr2(at + boff[0] + 1024 * ks, at + boff[1] + 1024 * ks),
+                   lds_tr2(at + aoff[0] + 16 * TG::ROWB * ks, at + aoff[1] + 16 * TG::ROWB * ks), acc);
+    run += acc;
+    if (c + 1 >= p.head) put(c + 1 - p.head);
+  }
+}
+
+template <int D, int FM> void launch_walk_kernel(const WalkArgs& p, hipStream_t st) {
+  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(rla_walk_kernel<D, FM>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, MAX_WALK * walk_bytes(D)) == hipSuccess;
+  (void)attr;
+  rla_walk_kernel<D, FM><<<D / 32 * p.H * p.B, 512, p.nchunks * walk_bytes(D), st>>>(p);
+}
+template <int D> void launch_walk(int phi, const WalkArgs& p, hipStream_t st) {
+  switch (phi) {
+    case PHI_RELU: launch_walk_kernel<D, FM_RELU>(p, st); break;
+    case PHI_IDENTITY: launch_walk_kernel<D, FM_IDENTITY>(p, st); break;
+    default: launch_walk_kernel<D, FM_SOFTMAX>(p, st); break;
+  }
+}
+
 template <int D> void launch_chunk_kernel(int phi, dim3 grid, const ChunkArgs& p, hipStream_t st) {
   switch (phi) {
     case PHI_RELU: rla_chunk_kernel<D, FM_RELU><<<grid, 256, 0, st>>>(p); break;
@@ -209,6 +290,15 @@ void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTen
   if (pl.nstf <= 0) return;
   if (m < 2) { m = 1; subset_out = nullptr; restart = nullptr; }
   const int head = pl.base > 0 ? 1 : 0;  // products in front of state 0: the 64 keys before it when it sits at key 64
+  // Forward without saving in us, two launches | one: one product, 8 pairs of batch and kv head 28.2 | 23.4, 128 pairs 74.4 | 65.1;
+  // two, 8 pairs 26.0 | 23.0, 64 pairs 37.4 | 34.1; three, 8 pairs 39.2 | 37.3 (D = 64 24.2 | 22.6), 64 pairs 49.2 | 47.8, 128 pairs
+  // 123.4 | 125.8, where the work-groups no longer have a CU each
+  if (!state0 && m == 1 && t.P == 0 && pl.ckeys == 128 && pl.nchunks <= (dm.Hkv * (long long)dm.B <= 64 ? 3 : 2)) {
+    const WalkArgs p = {(const uint16_t*)t.k, (const uint16_t*)t.v, (uint16_t*)states, dm.Hkv, t.Tb, dm.B, head, pl.nchunks, pl.nstf};
+    ProfScope ps("rla_chunk_kernel", st);
+    if (dm.D == 64) launch_walk<64>(dm.phi, p, st); else launch_walk<128>(dm.phi, p, st);
+    return;
+  }
   if (pl.nchunks > 0) {
     ChunkArgs p;
     p.a = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};

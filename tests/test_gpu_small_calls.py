@@ -117,3 +117,29 @@ def test_chunk_products_of_infinite_values():
     assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and int((~torch.isfinite(a)).sum()) == D
     fin = torch.isfinite(a)
     assert float((a[fin] - b[fin]).abs().max()) <= 2e-5 * max(1.0, float(b[fin].abs().max()))
+
+
+@pytest.mark.parametrize("phi", ["softmax", "relu"])
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W,products", [
+    (1, 256, 2, 1, 128, 100, 0), (2, 384, 4, 2, 128, 128, 1), (1, 384, 3, 3, 64, 190, 1),      # state 0 alone; one more
+    (1, 400, 4, 2, 128, 130, 2), (2, 512, 2, 1, 64, 65, 3), (1, 639, 4, 4, 128, 128, 3),      # states at the 64 alignment; three
+    (1, 641, 4, 4, 128, 128, 4), (65, 640, 1, 1, 64, 128, 3),                                 # two launches: four products, 65 pairs
+])
+def test_states_of_few_products(B, T, Hq, Hkv, D, W, products, phi):
+    """Forward states out of one launch (few products) or two: outputs and gradients against the general kernels, which form
+    them in fp32, at the bound of two bf16 paths; at least the last state is read by a query tile of every case."""
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 5500 + T + W, with_dO=True)
+    q, k, v, dO = (x[n].cuda() for n in ("q", "k", "v", "dO"))
+    print(f"B={B} T={T} Hq={Hq} Hkv={Hkv} D={D} W={W} {phi}", flush=True)
+    one = products <= (3 if B * Hkv <= 64 else 2)
+    got = {}
+    for path in ("auto", "general"):
+        kw = dict(softmax_scale=1.0 / math.sqrt(D), kernel_path=path, feature_map=phi)
+        (o, saved), names = launches(lambda: rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw))
+        got[path] = (o,) + rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, **kw)[:3]
+        if path == "auto":
+            assert names == (["rla_chunk_kernel"] if one else ["rla_chunk_kernel", "rla_scan_kernel"]) + ["fwd_fused_kernel"]
+    for n, a, b in zip(("o", "dq", "dk", "dv"), got["auto"], got["general"]):
+        rel = float((a.double() - b.double()).norm() / b.double().norm())
+        print(f"{n}: {rel:.2e}", flush=True)
+        assert rel <= 1e-2, n   # bf16 operands: 2^-9 per factor and term
