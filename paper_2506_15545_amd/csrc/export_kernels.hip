@@ -11,7 +11,15 @@ namespace rattn {
 
 namespace {
 
-__global__ __launch_bounds__(256) void export_ring_kernel(RingCopy a) { copy_rings(a, blockIdx.x, gridDim.x); }
+// Blocks behind the first ncopy clear the state (nzero 16-byte pieces): no key has left the window.
+__global__ __launch_bounds__(256) void export_ring_kernel(RingCopy a, int ncopy, float4* state, long long nzero) {
+  if ((int)blockIdx.x < ncopy) {
+    copy_rings(a, blockIdx.x, ncopy);
+    return;
+  }
+  for (long long i = (long long)(blockIdx.x - ncopy) * 256 + threadIdx.x; i < nzero; i += (long long)(gridDim.x - ncopy) * 256)
+    state[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
 
 // Partial states of key segments for bf16 (segment_state).
 // One-dimensional grid: block i < nseg * B * Hkv is segment i % nseg of (b, kv head) i / nseg; the others copy the rings.  Key s is row
@@ -65,12 +73,31 @@ __global__ __launch_bounds__(256) void export_state_reduce_kernel(const float4* 
 
 void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k_ring, void* v_ring, float* state,
                     float* partial, hipStream_t st, int tok0, bool accumulate) {
-  const ExportPlan pl = export_plan(dm);
-  const int esize = dtype == 0 ? 4 : 2;
+  ExportPlan pl = export_plan(dm);
+  const int esize = dtype == 0 ? 4 : 2, tiles = (pl.Tp + 63) / 64;
   const RingCopy rc = {(const uint4*)t.k, (const uint4*)t.v, (uint4*)k_ring, (uint4*)v_ring, dm.B, t.Tb, dm.Hkv, dm.W,
                        dm.D * esize / 16, tok0};
   const long long total = (long long)dm.B * (t.Tb < dm.W ? t.Tb : dm.W) * dm.Hkv * rc.row_vecs;
   const int copy_blocks = (int)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
+  if (pl.nseg == 0 && !accumulate) {
+    const long long nzero = (long long)dm.B * dm.Hkv * dm.D * dm.D / 4;
+    ProfScope ps("export_ring_kernel", st);
+    export_ring_kernel<<<copy_blocks + (int)((nzero + 255) / 256 < 2048 ? (nzero + 255) / 256 : 2048), 256, 0, st>>>(
+        rc, copy_blocks, (float4*)state, nzero);
+    return;
+  }
+  // Few keys: one segment, straight into the state, saves the launch that sums the segments.  Export alone in us, segments and
+  // sum | one segment (two launches one behind the other take the host 10): bf16, D = 128, 4 pairs of batch and head, 64 keys
+  // 10.6 | 7.3, 128 10.4 | 8.6, 192 10.3 | 11.4; 128 pairs, 320 keys 21.9 | 18.5, 512 25.6 | 26.7; D = 64, 320 keys 10.4 | 8.7, 512
+  // 10.7 | 12.6; fp32, D = 64, 128 keys 14.1 | 12.4, 192 13.6 | 17.1, D = 128, 64 keys 15.4 | 13.3, 128 15.7 | 22.5.
+  // (With a carried state the sum adds it.)
+  const int one = dtype == 0 ? (dm.D == 64 ? 2 : 1) : dm.D == 64 || dm.B * (long long)dm.Hkv >= 128 ? 5 : 2;
+  const bool direct = !accumulate && tiles <= one;
+  if (direct) {
+    pl.nseg = 1;
+    pl.seg_len = 64 * tiles;
+    partial = state;
+  }
   if (pl.nseg > 0 && dtype == 1) {
     ProfScope ps("export_state_mfma_kernel", st);
     const int nstate = pl.nseg * dm.Hkv * dm.B;
@@ -89,10 +116,11 @@ void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k
   } else {
     {
       ProfScope ps("export_ring_kernel", st);
-      export_ring_kernel<<<copy_blocks, 256, 0, st>>>(rc);
+      export_ring_kernel<<<copy_blocks, 256, 0, st>>>(rc, copy_blocks, nullptr, 0);
     }
     if (pl.nseg > 0) generic_chunk_products(dm, t.Tb, t.k, t.v, partial, pl.Tp, pl.nseg, pl.seg_len, st);
   }
+  if (direct) return;
   const int vecs = dm.D * dm.D / 4;
   ProfScope ps("export_state_reduce_kernel", st);
   export_state_reduce_kernel<<<dim3(vecs / 64, dm.B * dm.Hkv), 256, 0, st>>>((const float4*)partial, (float4*)state,

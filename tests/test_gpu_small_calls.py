@@ -143,3 +143,23 @@ def test_states_of_few_products(B, T, Hq, Hkv, D, W, products, phi):
         rel = float((a.double() - b.double()).norm() / b.double().norm())
         print(f"{n}: {rel:.2e}", flush=True)
         assert rel <= 1e-2, n   # bf16 operands: 2^-9 per factor and term
+
+
+@pytest.mark.parametrize("B,Hkv,D,dtype,W,out,launched", [
+    (2, 3, 128, "bf16", 100, 0, 1), (2, 3, 64, "f32", 100, 0, 1), (1, 2, 128, "bf16", 64, -20, 1),   # nothing leaves the window
+    (2, 3, 128, "bf16", 50, 1, 1), (2, 3, 128, "bf16", 50, 128, 1), (2, 3, 128, "bf16", 50, 129, 2),
+    (16, 8, 128, "bf16", 20, 320, 1), (16, 8, 128, "bf16", 20, 321, 2), (2, 3, 64, "bf16", 50, 320, 1), (2, 3, 64, "bf16", 50, 321, 2),
+    (1, 2, 64, "f32", 30, 128, 2), (1, 2, 64, "f32", 30, 129, 3), (1, 2, 128, "f32", 30, 64, 2), (1, 2, 128, "f32", 30, 65, 3)])
+@pytest.mark.parametrize("phi", ["softmax", "identity"])
+def test_export_of_few_keys(B, Hkv, D, dtype, W, out, launched, phi):
+    """Prefill export with no key, few keys and one more beyond the window: rings to the bit, the state to fp32, buffers that hold
+    noise before."""
+    T = W + out
+    x = synth.make_random_layer(B, T, Hkv, Hkv, D, dtype, 5600 + T)
+    kr, vr = (torch.zeros(B, Hkv, W, D, dtype=x["k"].dtype, device="cuda") for _ in range(2))
+    S = torch.full((B, Hkv, D, D), float("nan"), device="cuda")
+    _, names = launches(lambda: rb.rattn_prefill_export(x["k"].cuda(), x["v"].cuda(), W, kr, vr, S, feature_map=phi))
+    assert len(names) == launched, names
+    kr_ref, vr_ref, S_ref = orc.prefill_export(np64(x["k"]), np64(x["v"]), W, feature_map=phi)
+    assert np.array_equal(np64(kr), kr_ref) and np.array_equal(np64(vr), vr_ref)
+    assert float(np.max(np.abs(np64(S) - S_ref))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
