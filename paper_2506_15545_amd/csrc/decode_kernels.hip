@@ -25,9 +25,10 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, unsigned bytes) {
 // Keeps the compiler from reasoning about a per-lane value: offsets built from it stay one register plus an immediate,
 // and what is computed from it inside a loop is not hoisted out of it into registers.
 __device__ __forceinline__ int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
-template <typename V> __device__ __forceinline__ V buf_load(rsrc_t r, int off) {
-  if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-  else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+// ONCE: marked non-temporal
+template <typename V, bool ONCE = false> __device__ __forceinline__ V buf_load(rsrc_t r, int off) {
+  if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, ONCE ? 2 : 0));
+  else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, ONCE ? 2 : 0));
 }
 __device__ __forceinline__ void buf_store(rsrc_t r, f32x4_t v, int off) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, off, 0, 0);
@@ -42,9 +43,9 @@ __device__ __forceinline__ void buf_store(rsrc_t r, f32x4_t v, int off) {
 //       they pin which keys contraction slot (q4, .) stands for, and lane group q4 loads the V rows of exactly those
 //       keys, lane r16 taking the r16-th piece (EV features) of each row.
 // bf16: 32 keys, 16x16x32 tiles; fp32: 16 keys, 16x16x4 tiles (exact fp32 products and sums).
-template <typename IO, int D> struct RingSet;
+template <typename IO, int D, bool ONCE> struct RingSet;
 
-template <int D> struct RingSet<bf16_t, D> {
+template <int D, bool ONCE> struct RingSet<bf16_t, D, ONCE> {
   static constexpr int KEYS = 32, EV = D / 16;
   typedef uint32_t vrow_t __attribute__((ext_vector_type(EV / 2)));
   bf16x8_t k[2][D / 32];
@@ -55,13 +56,13 @@ template <int D> struct RingSet<bf16_t, D> {
     for (int c = 0; c < 2; ++c) {
       const int offc = c ? opaque(off + 32 * D) : off;
 #pragma unroll
-      for (int j = 0; j < D / 32; ++j) k[c][j] = buf_load<bf16x8_t>(rows, offc + 64 * j);
+      for (int j = 0; j < D / 32; ++j) k[c][j] = buf_load<bf16x8_t, ONCE>(rows, offc + 64 * j);
     }
   }
   __device__ __forceinline__ void load_v(rsrc_t rows, int r16, int q4) {
     const int off = opaque(8 * D * q4 + 2 * EV * r16), off1 = opaque(off + 32 * D);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = buf_load<vrow_t>(rows, (u < 4 ? off : off1) + 2 * D * (u & 3));
+    for (int u = 0; u < 8; ++u) v[u] = buf_load<vrow_t, ONCE>(rows, (u < 4 ? off : off1) + 2 * D * (u & 3));
   }
   // q: this lane's head in LDS
   __device__ __forceinline__ void scores(const bf16_t* q, int q4, f32x4_t (&s)[2]) const {
@@ -107,21 +108,21 @@ template <int D> struct RingSet<bf16_t, D> {
   static __device__ __forceinline__ int feature0(int e4, int i, int q4) { return EV * (4 * q4 + i) + 4 * e4; }
 };
 
-template <int D> struct RingSet<float, D> {
+template <int D, bool ONCE> struct RingSet<float, D, ONCE> {
   static constexpr int KEYS = 16, EV = D / 16;
   f32x4_t k[D / 16];
   f32x4_t v[4][D / 64];
   __device__ __forceinline__ void load_k(rsrc_t rows, int r16, int q4) {
     const int off = opaque(4 * D * r16 + 16 * q4);
 #pragma unroll
-    for (int j = 0; j < D / 16; ++j) k[j] = buf_load<f32x4_t>(rows, off + 64 * j);
+    for (int j = 0; j < D / 16; ++j) k[j] = buf_load<f32x4_t, ONCE>(rows, off + 64 * j);
   }
   __device__ __forceinline__ void load_v(rsrc_t rows, int r16, int q4) {
     const int off = opaque(16 * D * q4 + 16 * r16);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int hf = 0; hf < D / 64; ++hf) v[i][hf] = buf_load<f32x4_t>(rows, off + 4 * D * i + 256 * hf);
+      for (int hf = 0; hf < D / 64; ++hf) v[i][hf] = buf_load<f32x4_t, ONCE>(rows, off + 4 * D * i + 256 * hf);
   }
   // Short chains of products and a tree of sums: the rounding of the logits grows with the chain.  With all features in two
   // chains it was 2.1 times that of the sums of partial sums per lane before (error of o at logits of std 4: 5.5e-7, 2.7e-7).
@@ -229,13 +230,14 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // one sequence, 4 KV heads, W = 512: 11.2 us (18 us with four waves per KV head).
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
 // SPLIT: nsplit work-groups share a (sequence, kv head), see split_combine.
-template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
+// ONCE: the rings are read past the caches (see pick_decode).
+template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
 __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
     const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
     IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
     const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
     std::conditional_t<SPLIT, SplitArgs, NoSplit> split) {
-  typedef RingSet<IO, D> Set;
+  typedef RingSet<IO, D, ONCE> Set;
   constexpr int EPL = D / 64, EV = Set::EV, NT = Set::KEYS / 16, NH = D / 64, QS = D + 16 / (int)sizeof(IO);
   const int W = dd.W, G = dd.G, Hq = dd.Hq, Hkv = dd.Hkv;
   const int HBmax = min(G, DEC_HB);
@@ -559,14 +561,14 @@ struct DecodeTensors {
   void* o;
 };
 
-template <typename IO, int D, int NW, bool MULTI, bool SPLIT>
+template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE = false>
 void launch_decode(const DecodeDims& dd, const DecodeTensors& t, std::conditional_t<SPLIT, SplitArgs, NoSplit> split, hipStream_t st) {
   const int hb = dd.G < DEC_HB ? dd.G : DEC_HB;
   const size_t bytes = decode_lds_bytes(D, sizeof(IO), hb, NW);
-  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI, SPLIT>),
+  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI, SPLIT, ONCE>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
   (void)attr;
-  decode_kernel<IO, D, NW, MULTI, SPLIT><<<dim3(dd.Hkv * (SPLIT ? split.n : 1), dd.N), NW * 64, bytes, st>>>(
+  decode_kernel<IO, D, NW, MULTI, SPLIT, ONCE><<<dim3(dd.Hkv * (SPLIT ? split.n : 1), dd.N), NW * 64, bytes, st>>>(
       (const IO*)t.q, (const IO*)t.k_new, (const IO*)t.v_new, t.pos, (IO*)t.k_ring, (IO*)t.v_ring, t.state, t.gs, t.gr,
       (IO*)t.o, dd, split);
 }
@@ -589,6 +591,16 @@ void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
   int nw = 4;
   while (nw < cap && groups * nw < 256 * cap) nw *= 2;
   while (nw > 4 && decode_lds_bytes(D, sizeof(IO), dd.G < DEC_HB ? dd.G : DEC_HB, nw) > 160 * 1024 - 256) nw /= 2;
+  // Enough work-groups to be bound by the memory: rings that are read once need no place in the caches.  Rings and states cold,
+  // us, as usual | non-temporal: 1024 pairs, W = 512 84.0 | 75.4; 512, W = 512 42.7 | 39.6, W = 2048 115 | 107, D = 64 51.1 | 48.0,
+  // fp32 70.4 | 61.6; 256, W = 512 24.3 | 21.3.  With fewer the two halves of a row of K, which come with two loads, are fetched
+  // twice: 192 pairs, W = 2048 40.2 | 44.0, 128 38.4 | 41.1, 64, fp32, D = 64 10.7 | 11.2.
+  if (!MULTI && groups >= 256) {
+    if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dd, t, none, st);
+    else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dd, t, none, st);
+    else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dd, t, none, st);
+    return;
+  }
   if (nw == 4) launch_decode<IO, D, 4, MULTI, false>(dd, t, none, st);
   else if (nw == 8) launch_decode<IO, D, 8, MULTI, false>(dd, t, none, st);
   else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false>(dd, t, none, st);
