@@ -224,12 +224,12 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // W is not limited by LDS, and takes its share of the state rows; the waves' partial results meet in LDS once.  The
 // new token is not read back from the ring: its slot is masked there and it enters the merge as a partial of its own.
 // Bound: HBM.  NW is chosen so that the chip is full of waves (pick_decode).  Measured, rings and states cold in the
-// caches: 128 sequences x 8 KV heads, 4 query heads each, W = 512: 82 us = 4.9 TB/s, where a plain kernel that streams
-// the rings and reads-modifies-writes the states in the same places takes 78 us; 24 x 8, 5 heads, W = 2048, half of the
-// rings partly filled: 39 us (271 us with the scores of all W keys in LDS and vector arithmetic for more than four heads);
-// one sequence, 4 KV heads, W = 512: 11.2 us (18 us with four waves per KV head).
+// caches: 128 sequences x 8 KV heads, 4 query heads each, W = 512: 64.5 us = 6.3 TB/s (84 with the rings kept in the caches, see
+// pick_decode); 24 x 8, 5 heads, W = 2048, half of the rings partly filled: 39 us (271 us with the scores of all W keys in LDS and
+// vector arithmetic for more than four heads); one sequence, 4 KV heads, W = 512: 11.2 us by one work-group per KV head (18 us
+// with four waves of it), 9.1 shared.
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
-// SPLIT: nsplit work-groups share a (sequence, kv head), see split_combine.
+// SPLIT: nsplit work-groups share a (sequence, kv head), see SplitArgs.
 // ONCE: the rings are read past the caches (see pick_decode).
 template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
 __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
@@ -591,11 +591,15 @@ void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
   int nw = 4;
   while (nw < cap && groups * nw < 256 * cap) nw *= 2;
   while (nw > 4 && decode_lds_bytes(D, sizeof(IO), dd.G < DEC_HB ? dd.G : DEC_HB, nw) > 160 * 1024 - 256) nw /= 2;
-  // Enough work-groups to be bound by the memory: rings that are read once need no place in the caches.  Rings and states cold,
-  // us, as usual | non-temporal: 1024 pairs, W = 512 84.0 | 75.4; 512, W = 512 42.7 | 39.6, W = 2048 115 | 107, D = 64 51.1 | 48.0,
-  // fp32 70.4 | 61.6; 256, W = 512 24.3 | 21.3.  With fewer the two halves of a row of K, which come with two loads, are fetched
-  // twice: 192 pairs, W = 2048 40.2 | 44.0, 128 38.4 | 41.1, 64, fp32, D = 64 10.7 | 11.2.
-  if (!MULTI && groups >= 256) {
+  // Enough work-groups to be bound by the memory, and so much in one layer that the memory-side cache (256 MB) cannot hold two:
+  // rings that are read once need no place there.  Three layers stepped in turn, us, as usual | non-temporal: 1024 pairs, W = 512
+  // (336 MB) 84.0 | 64.5; 512, W = 512 (168 MB) 42.4 | 35.7, W = 384 (134 MB) 35.0 | 30.4; fp32, W = 256 44.7 | 36.6; D = 64,
+  // W = 900 (126 MB) 27.0 | 24.5, W = 512 (75 MB) 15.0 | 16.6; 256, W = 512 (84 MB) 18.2 | 19.3.  (A single layer that is stepped
+  // again and again has it in that cache up to some 300 MB: 168 MB 31.7 | 34.8, 268 MB 53.0 | 53.2, 403 MB 87.1 | 75.7.)
+  // With fewer work-groups the two halves of a row of K, which come with two loads, are fetched twice: 192 pairs, W = 2048
+  // 40.2 | 44.0, 128 38.4 | 41.1.
+  const long long layer_bytes = groups * (2ll * dd.W * D * sizeof(IO) + D * D * 4ll);
+  if (!MULTI && groups >= 256 && layer_bytes >= 128ll << 20) {
     if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dd, t, none, st);
     else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dd, t, none, st);
     else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dd, t, none, st);

@@ -1,4 +1,5 @@
-"""Decode steps whose (sequence, KV head) pairs are shared by several work-groups that meet in a workspace."""
+"""Decode steps whose (sequence, KV head) pairs are shared by several work-groups that meet in a workspace, and large ones whose
+rings are read past the caches."""
 import ctypes
 import math
 
@@ -132,3 +133,29 @@ def test_replayed_and_overlapping_calls():
     torch.cuda.synchronize()
     for seed, o, y in got:
         assert torch.equal(o, want[seed][0]) and torch.equal(y["state"], want[seed][1])
+
+
+@pytest.mark.parametrize("N,D,W,dtype", [
+    (32, 128, 895, "bf16"), (32, 128, 896, "bf16"),   # 256 pairs, 16 waves: the last window below 128 MB of rings and states, the first above
+    (64, 128, 383, "bf16"), (64, 128, 385, "bf16"),   # 512, eight waves
+    (128, 128, 128, "bf16"), (128, 64, 450, "bf16"),  # 1024, four waves
+    (32, 128, 448, "f32"), (64, 128, 191, "f32"), (64, 128, 193, "f32"), (128, 64, 224, "f32"),
+])
+def test_large_steps_match_small_ones(N, D, W, dtype):
+    """A batch at once and 16 sequences at a time (128 pairs: always the plain kernel): rings and states to the bit, outputs as far
+    as sums in another order go (fp32: 4 ulp of a norm; bf16: ties of its rounding)."""
+    print(f"N={N} D={D} W={W} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5900 + W)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    draw = lambda *shape: torch.randn(*shape, device="cuda", generator=gen).to(dt)
+    pos = torch.randint(0, 4 * W, (N,), dtype=torch.int32, device="cuda", generator=gen)
+    pos[:4] = torch.tensor([0, W - 1, W, 2 * W - 1], dtype=torch.int32)
+    d = dict(q=draw(N, 16, D), k_new=draw(N, 8, D), v_new=draw(N, 8, D), pos=pos, k_ring=draw(N, 8, W, D), v_ring=draw(N, 8, W, D),
+             state=draw(N, 8, D, D).float() / D)
+    few = {m: t.clone() for m, t in d.items()}
+    got = rb.rattn_decode_step(*(d[m] for m in NAMES), softmax_scale=D ** -0.5)
+    want = torch.cat([rb.rattn_decode_step(*(few[m][i:i + 16] for m in NAMES), softmax_scale=D ** -0.5) for i in range(0, N, 16)])
+    err = float((got.float() - want.float()).norm() / want.float().norm())
+    assert err <= (2e-3 if dtype == "bf16" else 5e-7), err
+    for m in ("k_ring", "v_ring", "state"):
+        assert torch.equal(d[m], few[m]), m
