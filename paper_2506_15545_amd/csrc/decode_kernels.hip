@@ -230,13 +230,13 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // with four waves of it), 9.1 shared.
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
 // SPLIT: nsplit work-groups share a (sequence, kv head), see SplitArgs.
-// ONCE: the ring is read past the caches; of the kernel: rings of once_rows rows and more (see pick_decode).
+// ONCE: the rings are read past the caches (see pick_decode).
 template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
-__device__ __forceinline__ void decode_group(
+__global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
     const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
     IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
-    const float* __restrict__ gr, IO* __restrict__ o, const DecodeDims& dd,
-    const std::conditional_t<SPLIT, SplitArgs, NoSplit>& split) {
+    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
+    std::conditional_t<SPLIT, SplitArgs, NoSplit> split) {
   typedef RingSet<IO, D, ONCE> Set;
   constexpr int EPL = D / 64, EV = Set::EV, NT = Set::KEYS / 16, NH = D / 64, QS = D + 16 / (int)sizeof(IO);
   const int W = dd.W, G = dd.G, Hq = dd.Hq, Hkv = dd.Hkv;
@@ -552,19 +552,6 @@ __device__ __forceinline__ void decode_group(
   } while (MULTI && hb < G);
 }
 
-template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
-__global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
-    const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
-    IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
-    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
-    std::conditional_t<SPLIT, SplitArgs, NoSplit> split) {
-  // (whole bodies: a branch around the loads alone merges their registers, and 64 of them spill)
-  if (ONCE && min(pos[blockIdx.y], dd.W) >= dd.once_rows)
-    decode_group<IO, D, NW, MULTI, SPLIT, ONCE>(q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, dd, split);
-  else
-    decode_group<IO, D, NW, MULTI, SPLIT, false>(q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, dd, split);
-}
-
 struct DecodeTensors {
   const void *q, *k_new, *v_new;
   const int32_t* pos;
@@ -611,15 +598,11 @@ void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
   // again and again has it in that cache up to some 300 MB: 168 MB 31.7 | 34.8, 268 MB 53.0 | 53.2, 403 MB 87.1 | 75.7.)
   // With fewer work-groups the two halves of a row of K, which come with two loads, are fetched twice: 192 pairs, W = 2048
   // 40.2 | 44.0, 128 38.4 | 41.1.
-  // Rings that are not full yet count as far as they are filled, in the kernel: 344 pairs, D = 64, W = 2933, 543 - 573 tokens
-  // (55 MB) 14.8 | 16.3.
-  const long long once_rows = ((128ll << 20) / groups - D * D * 4ll) / (2ll * D * (int)sizeof(IO));
-  if (!MULTI && groups >= 256 && dd.W >= once_rows) {
-    DecodeDims dim = dd;
-    dim.once_rows = (int)(once_rows > 0 ? once_rows : 0);
-    if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dim, t, none, st);
-    else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dim, t, none, st);
-    else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dim, t, none, st);
+  const long long layer_bytes = groups * (2ll * dd.W * D * sizeof(IO) + D * D * 4ll);
+  if (!MULTI && groups >= 256 && layer_bytes >= 128ll << 20) {
+    if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dd, t, none, st);
+    else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dd, t, none, st);
+    else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dd, t, none, st);
     return;
   }
   if (nw == 4) launch_decode<IO, D, 4, MULTI, false>(dd, t, none, st);
