@@ -172,7 +172,8 @@ __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__
 
 // Few products: products and scan in one launch.  A work-group holds all chunks of one (b, kv head) in LDS, for 32 value
 // features, and keeps the running sum in registers.  The map is formed once for every 32 value features, so that a launch is
-// saved only where there are few chunks (MAX_WALK, see rla_forward_states).  Each product is a sum of its own, added in order.
+// saved only where there are few chunks (MAX_WALK, see rla_forward_states).  Each product is a sum of its own, added in order:
+// the states are the bits that rla_chunk_kernel and rla_scan_kernel leave.
 struct WalkArgs {
   const uint16_t *a, *b;   // rows that go through phi, rows multiplied in: [B,T,H,D]
   uint16_t* states;
@@ -219,9 +220,10 @@ __global__ __launch_bounds__(512) void rla_walk_kernel(WalkArgs p) {
   };
   wait_vmem();
   __syncthreads();
-  for (int c = 0; c < p.nchunks; ++c) {
-    const int row = threadIdx.x >> 2;
-    phi_row_inplace<FM, D, 4>(row < rows(c) ? chunks + c * CB : nullptr, row, threadIdx.x & 3);
+  // two threads per row, as in rla_chunk_kernel: the features are the same bits (each half of the threads takes every other chunk)
+  for (int c = threadIdx.x >> 8; c < p.nchunks; c += 2) {
+    const int row = (threadIdx.x & 255) >> 1;
+    phi_row_inplace<FM, D, 2>(row < rows(c) ? chunks + c * CB : nullptr, row, threadIdx.x & 1);
   }
   __syncthreads();
   if (w >= NS) return;

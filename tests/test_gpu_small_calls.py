@@ -145,6 +145,21 @@ def test_states_of_few_products(B, T, Hq, Hkv, D, W, products, phi):
         assert rel <= 1e-2, n   # bf16 operands: 2^-9 per factor and term
 
 
+@pytest.mark.parametrize("phi", ["softmax", "relu"])
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W", [(2, 384, 4, 2, 128, 128), (1, 400, 4, 2, 128, 130), (2, 512, 2, 1, 64, 65), (1, 639, 4, 4, 128, 128)])
+def test_states_of_one_launch_or_two_are_the_same_bits(B, T, Hq, Hkv, D, W, phi):
+    """One, two and three products: a forward that forms all states in one launch and one whose states are kept by halves, which
+    takes two."""
+    x = synth.make_random_layer(B, T, Hq, Hkv, D, "bf16", 5500 + T + W)
+    q, k, v = (x[n].cuda() for n in ("q", "k", "v"))
+    got = {}
+    for policy in ("keep", "every2"):
+        (got[policy], _), names = launches(lambda: rb.rattn_fwd(q, k, v, W, softmax_scale=1.0 / math.sqrt(D), save_for_bwd=True,
+                                                                feature_map=phi, state_policy=policy))
+        assert ("rla_scan_kernel" in names) == (policy == "every2")
+    assert torch.equal(got["keep"], got["every2"])
+
+
 @pytest.mark.parametrize("B,Hkv,D,dtype,W,out,launched", [
     (2, 3, 128, "bf16", 100, 0, 1), (2, 3, 64, "f32", 100, 0, 1), (1, 2, 128, "bf16", 64, -20, 1),   # nothing leaves the window
     (2, 3, 128, "bf16", 50, 1, 1), (2, 3, 128, "bf16", 50, 128, 1), (2, 3, 128, "bf16", 50, 129, 2),
