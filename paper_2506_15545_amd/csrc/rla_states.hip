@@ -297,7 +297,7 @@ void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTen
   // 123.4 | 125.8, where the work-groups no longer have a CU each
   if (!state0 && m == 1 && t.P == 0 && pl.ckeys == 128 && pl.nchunks <= (dm.Hkv * (long long)dm.B <= 64 ? 3 : 2)) {
     const WalkArgs p = {(const uint16_t*)t.k, (const uint16_t*)t.v, (uint16_t*)states, dm.Hkv, t.Tb, dm.B, head, pl.nchunks, pl.nstf};
-    ProfScope ps("rla_chunk_kernel", st);
+    ProfScope ps("rla_walk_kernel", st);
     if (dm.D == 64) launch_walk<64>(dm.phi, p, st); else launch_walk<128>(dm.phi, p, st);
     return;
   }

@@ -193,7 +193,7 @@ def test_fast_bwd_unit_gains_no_dgamma(B, T, Hq, Hkv, W):
 
 
 # what a forward and backward of a bf16 layer on the matrix cores launches (records carry "(rev)" for the reverse states)
-MATRIX_CORE_LAUNCHES = {"rla_chunk_kernel", "rla_scan_kernel", "fwd_fused_kernel", "bwd_dq_kernel",
+MATRIX_CORE_LAUNCHES = {"rla_chunk_kernel", "rla_scan_kernel", "rla_walk_kernel", "fwd_fused_kernel", "bwd_dq_kernel",
                         "rla_chunk_kernel(rev)", "rla_scan_kernel(rev)", "bwd_dkv_kernel", "dkv_reduce_kernel"}
 
 
@@ -289,7 +289,8 @@ def test_state_policy_and_chunk_size_variants(policy, chunk, B, T, Hq, Hkv, W):
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
     assert "bwd_dkv_kernel" in names
-    assert ("rla_chunk_kernel" in names) == (policy != "keep")        # forward states (re)built in backward
+    # forward states (re)built in backward
+    assert bool({"rla_chunk_kernel", "rla_walk_kernel"} & set(names)) == (policy != "keep")
     ref = orc.fwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), W, scale=scale)
     pm.assert_out_bf16(np64(o), ref["o"])
     refb = orc.bwd_dense(np64(x["q"]), np64(x["k"]), np64(x["v"]), np64(x["dO"]), W, scale=scale)

@@ -138,7 +138,7 @@ def test_states_of_few_products(B, T, Hq, Hkv, D, W, products, phi):
         (o, saved), names = launches(lambda: rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw))
         got[path] = (o,) + rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, **kw)[:3]
         if path == "auto":
-            assert names == (["rla_chunk_kernel"] if one else ["rla_chunk_kernel", "rla_scan_kernel"]) + ["fwd_fused_kernel"]
+            assert names == (["rla_walk_kernel"] if one else ["rla_chunk_kernel", "rla_scan_kernel"]) + ["fwd_fused_kernel"]
     for n, a, b in zip(("o", "dq", "dk", "dv"), got["auto"], got["general"]):
         rel = float((a.double() - b.double()).norm() / b.double().norm())
         print(f"{n}: {rel:.2e}", flush=True)
@@ -156,7 +156,7 @@ def test_states_of_one_launch_or_two_are_the_same_bits(B, T, Hq, Hkv, D, W, phi)
     for policy in ("keep", "every2"):
         (got[policy], _), names = launches(lambda: rb.rattn_fwd(q, k, v, W, softmax_scale=1.0 / math.sqrt(D), save_for_bwd=True,
                                                                 feature_map=phi, state_policy=policy))
-        assert ("rla_scan_kernel" in names) == (policy == "every2")
+        assert names == (["rla_walk_kernel"] if policy == "keep" else ["rla_chunk_kernel", "rla_scan_kernel"]) + ["fwd_fused_kernel"]
     assert torch.equal(got["keep"], got["every2"])
 
 
