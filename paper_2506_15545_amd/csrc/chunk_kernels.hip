@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256, 2) void chunk_products_kernel(RingRows<128> k,
   k.g = v.g = bg % k.H;
   const int lo = c < pl.head ? 0 : 64 * pl.head + pl.ckeys * (c - pl.head);
   const int hi = min(c < pl.head ? 64 : lo + pl.ckeys, pl.end);
-  segment_state<D, PHI, true>(smem, lo, k.kmin, hi, k, v, U + (size_t)blockIdx.x * (D * D));
+  segment_state<D, PHI, true, false>(smem, lo, k.kmin, hi, k, v, U + (size_t)blockIdx.x * (D * D));
 }
 
 // Block i < nscan: one 32 x 32 tile of (b, kv head): the running sum starts from the carried state (or zero), is stored as

@@ -26,10 +26,11 @@ __global__ __launch_bounds__(256) void export_ring_kernel(RingCopy a, int ncopy,
 // key0 + s of the two-part sequence (SeqRows).
 // Bound: HBM on long prompts (12 matrix instructions per 16 keys and wave are about 1.6 times as fast as the keys
 // arrive), the launch on short ones.
-template <int D, int PHI>
+// DIRECT: one segment, in pieces, which is the state.
+template <int D, int PHI, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, SeqRows v, float* __restrict__ partial, int Hkv,
                                                                    int key0, int Tp, int nseg, int seg_len, int nstate,
-                                                                   RingCopy rc) {
+                                                                   RingCopy rc, int piece) {
   __shared__ __align__(16) unsigned char smem[5 * TileGeom<D>::KT];  // phi hi, mid, lo; V x 2
   if ((int)blockIdx.x >= nstate) {
     copy_rings(rc, blockIdx.x - nstate, gridDim.x - nstate);
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
   const int seg = blockIdx.x % nseg, bg = blockIdx.x / nseg, g = bg % Hkv, b = bg / Hkv;
   const int lo = seg * seg_len, hi = min(lo + seg_len, Tp);
   const TwoPartRows<D> krow = {k, b, key0, Hkv, g}, vrow = {v, b, key0, Hkv, g};
-  segment_state<D, PHI, false>(smem, lo, 0, hi, krow, vrow, partial + ((size_t)bg * nseg + seg) * (D * D));
+  segment_state<D, PHI, false, DIRECT>(smem, lo, 0, hi, krow, vrow, partial + ((size_t)bg * nseg + seg) * (D * D), piece);
 }
 
 // state[b,g] = (accumulate ? state[b,g] : 0) + sum over segments: four runs of segments, each in order, then the four sums
@@ -86,13 +87,21 @@ void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k
         rc, copy_blocks, (float4*)state, nzero);
     return;
   }
-  // Few keys: one segment, straight into the state, saves the launch that sums the segments.  Export alone in us, segments and
-  // sum | one segment (two launches one behind the other take the host 10): bf16, D = 128, 4 pairs of batch and head, 64 keys
-  // 10.6 | 7.3, 128 10.4 | 8.6, 192 10.3 | 11.4; 128 pairs, 320 keys 21.9 | 18.5, 512 25.6 | 26.7; D = 64, 320 keys 10.4 | 8.7, 512
-  // 10.7 | 12.6; fp32, D = 64, 128 keys 14.1 | 12.4, 192 13.6 | 17.1, D = 128, 64 keys 15.4 | 13.3, 128 15.7 | 22.5.
+  // Few keys: one segment, straight into the state, saves the launch that sums the segments; the keys of what would be a segment
+  // stay a sum of their own, added in the order in which export_state_reduce_kernel adds up to four: the state is the same bits
+  // either way.  (One chain over all keys, without those sums: 128 keys at D = 128 1.08e-7 -> 1.34e-7 of the norm off, 320 at
+  // D = 64 1.11e-7 -> 1.94e-7.)  Export alone in us, segments and sum | one segment, captured and eager (where the host
+  // takes 10 for the two launches one behind the other); pairs of batch and head, keys beyond the window:
+  //   bf16, D = 128   4, 64: 7.8 | 6.3, 10.3 | 6.9;  4, 128: 7.9 | 9.4, 10.1 | 9.7;  16, 128: 8.9 | 9.7, 10.5 | 10.0
+  //                   64, 128: 13.6 | 10.6, 13.7 | 10.9;  128, 192: 22.6 | 15.1;  128, 320: 23.6 | 20.3;  256, 320: 39 | 25
+  //   bf16, D = 64    4, 128: 5.4 | 5.0, 10.4 | 6.9;  4, 192: 5.5 | 6.5, 10.5 | 7.5;  4, 256: 5.5 | 7.9, 10.5 | 9.3
+  //                   64, 192: 7.6 | 7.1;  64, 256: 8.1 | 8.6;  128, 320: 11.8 | 10.3
+  //   fp32            D = 64: 4, 64: 10.2 | 8.2;  4, 128: 10.3 | 12.7;  128, 128: 17.8 | 19.0;  D = 128: 4, 64: 15.2 | 13.1
   // (With a carried state the sum adds it.)
-  const int one = dtype == 0 ? (dm.D == 64 ? 2 : 1) : dm.D == 64 || dm.B * (long long)dm.Hkv >= 128 ? 5 : 2;
+  const long long pairs = dm.B * (long long)dm.Hkv;
+  const int one = dtype == 0 ? 1 : pairs >= 128 ? 5 : dm.D == 64 ? 3 : pairs >= 64 ? 2 : 1;
   const bool direct = !accumulate && tiles <= one;
+  const int piece = pl.seg_len;
   if (direct) {
     pl.nseg = 1;
     pl.seg_len = 64 * tiles;
@@ -103,9 +112,11 @@ void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k
     const int nstate = pl.nseg * dm.Hkv * dm.B;
     const SeqRows ks = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};
     const SeqRows vs = {(const uint16_t*)t.v_front, (const uint16_t*)t.v, t.P, t.Tb};
-#define RATTN_EXPORT(D_, PHI_)                                                                                             \
-  export_state_mfma_kernel<D_, PHI_><<<nstate + copy_blocks, 256, 0, st>>>(ks, vs, partial, dm.Hkv, t.kmin, pl.Tp, pl.nseg, \
-                                                                           pl.seg_len, nstate, rc)
+#define RATTN_EXPORT_AS(D_, PHI_, DIRECT_)                                                                                 \
+  export_state_mfma_kernel<D_, PHI_, DIRECT_><<<nstate + copy_blocks, 256, 0, st>>>(ks, vs, partial, dm.Hkv, t.kmin, pl.Tp, \
+                                                                                    pl.nseg, pl.seg_len, nstate, rc, piece)
+#define RATTN_EXPORT(D_, PHI_) \
+  do { if (direct) RATTN_EXPORT_AS(D_, PHI_, true); else RATTN_EXPORT_AS(D_, PHI_, false); } while (0)
 #define RATTN_EXPORT_MAP(D_)                                    \
   if (dm.phi == PHI_SOFTMAX) RATTN_EXPORT(D_, PHI_SOFTMAX);     \
   else if (dm.phi == PHI_RELU) RATTN_EXPORT(D_, PHI_RELU);      \
@@ -113,6 +124,7 @@ void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k
     if (dm.D == 64) { RATTN_EXPORT_MAP(64) } else { RATTN_EXPORT_MAP(128) }
 #undef RATTN_EXPORT_MAP
 #undef RATTN_EXPORT
+#undef RATTN_EXPORT_AS
   } else {
     {
       ProfScope ps("export_ring_kernel", st);

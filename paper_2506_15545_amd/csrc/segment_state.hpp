@@ -65,8 +65,11 @@ template <int D> struct RingRows {
 // Tiles of 64 keys: four threads map a key row (held in registers, requested one tile ahead) into the three LDS tiles of
 // phi; V arrives by direct-to-LDS loads, also one tile ahead; wave w then owns features 32w .. of the partial (D = 64: one
 // of its four 32 x 32 tiles).  smem: 5 tiles of 64 rows.  out: [f][d], or [d][f] when TRANSPOSED.
-template <int D, int PHI, bool TRANSPOSED, typename KR, typename VR>
-__device__ __forceinline__ void segment_state(unsigned char* smem, int lo, int first, int hi, KR krow, VR vrow, float* out) {
+// PIECES: every `piece` keys (a multiple of 64) are a sum of their own, and those are added in order: rounding grows with the
+// length of an accumulator's chain.
+template <int D, int PHI, bool TRANSPOSED, bool PIECES, typename KR, typename VR>
+__device__ __forceinline__ void segment_state(unsigned char* smem, int lo, int first, int hi, KR krow, VR vrow, float* out,
+                                              int piece = 0) {
   typedef TileGeom<D> TG;
   constexpr int KT = TG::KT, NB = TG::NB / 4, NX = D / 4, NV = D == 128 ? 4 : 1, NPART = PHI == PHI_SOFTMAX ? 3 : 1;
   const int lane = lane_id(), w = wave_id(), r32 = lane & 31, h = lane >> 5;
@@ -92,11 +95,39 @@ __device__ __forceinline__ void segment_state(unsigned char* smem, int lo, int f
 #pragma unroll
     for (int c = 0; c < NX / 8; ++c) kreg[c] = *reinterpret_cast<const bf16x8_t*>(kp + 8 * c);
   };
-  f32x16_t acc[NV];
+  f32x16_t acc[NV], sum[NV];
 #pragma unroll
-  for (int d = 0; d < NV; ++d) acc[d] = f32x16_t{0};
+  for (int d = 0; d < NV; ++d) acc[d] = sum[d] = f32x16_t{0};
+  // A sum (of keys a .. b-1) that is no number may come from a zero feature of the padding, or from terms of phi of different
+  // signs, times an infinite or NaN value: such a tile is formed again, key by key in fp32, which has neither.
+  auto settle = [&](int a, int b) {
+    float z = 0.f;
+#pragma unroll
+    for (int d = 0; d < NV; ++d)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[d][i], 0.f, z);
+    if (!__any(z != 0.f)) return;  // wave-uniform
+#pragma unroll
+    for (int d = 0; d < NV; ++d) acc[d] = f32x16_t{0};
+    for (int s = max(a, first); s < b; ++s) {
+      const uint16_t *kp = krow(s), *vp = vrow(s);
+      float x[D / 64], f[D / 64];
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) x[e] = __uint_as_float((uint32_t)kp[lane + 64 * e] << 16);
+      feature_row<D / 64>(x, f, PHI);
+      const float mine = ft < 2 ? f[0] : f[D / 64 - 1];  // this wave's 32 features
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 8 * (i >> 2) + 4 * h + (i & 3);
+        const float fi = __shfl(mine, (32 * ft + (TRANSPOSED ? r32 : r)) & 63);
+#pragma unroll
+        for (int d = 0; d < NV; ++d)
+          acc[d][i] = __builtin_fmaf(fi, __uint_as_float((uint32_t)vp[32 * (dt0 + d) + (TRANSPOSED ? r : r32)] << 16), acc[d][i]);
+      }
+    }
+  };
   request(lo, 0);
-  int buf = 0;
+  int buf = 0, piece_lo = lo;
   for (int s0 = lo; s0 < hi; s0 += 64, buf ^= 1) {
     float x[NX];
 #pragma unroll
@@ -152,40 +183,20 @@ __device__ __forceinline__ void segment_state(unsigned char* smem, int lo, int f
       }
     }
     __syncthreads();
-  }
-  // A sum that is no number may come from a zero feature of the padding, or from terms of phi of different signs, times an
-  // infinite or NaN value: such a tile is formed again, key by key in fp32, which has neither.
-  float z = 0.f;
+    if (PIECES && (s0 + 64 >= hi || s0 + 64 - piece_lo == piece)) {
+      settle(piece_lo, min(s0 + 64, hi));
+      piece_lo = s0 + 64;
 #pragma unroll
-  for (int d = 0; d < NV; ++d)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[d][i], 0.f, z);
-  if (__any(z != 0.f)) {  // wave-uniform
-#pragma unroll
-    for (int d = 0; d < NV; ++d) acc[d] = f32x16_t{0};
-    for (int s = max(lo, first); s < hi; ++s) {
-      const uint16_t *kp = krow(s), *vp = vrow(s);
-      float x[D / 64], f[D / 64];
-#pragma unroll
-      for (int e = 0; e < D / 64; ++e) x[e] = __uint_as_float((uint32_t)kp[lane + 64 * e] << 16);
-      feature_row<D / 64>(x, f, PHI);
-      const float mine = ft < 2 ? f[0] : f[D / 64 - 1];  // this wave's 32 features
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int r = 8 * (i >> 2) + 4 * h + (i & 3);
-        const float fi = __shfl(mine, (32 * ft + (TRANSPOSED ? r32 : r)) & 63);
-#pragma unroll
-        for (int d = 0; d < NV; ++d)
-          acc[d][i] = __builtin_fmaf(fi, __uint_as_float((uint32_t)vp[32 * (dt0 + d) + (TRANSPOSED ? r : r32)] << 16), acc[d][i]);
-      }
+      for (int d = 0; d < NV; ++d) { sum[d] += acc[d]; acc[d] = f32x16_t{0}; }
     }
   }
+  if (!PIECES) settle(lo, hi);
 #pragma unroll
   for (int d = 0; d < NV; ++d)
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int r = 8 * (i >> 2) + 4 * h + (i & 3);
-      out[TRANSPOSED ? (size_t)(32 * (dt0 + d) + r) * D + 32 * ft + r32 : (size_t)(32 * ft + r) * D + 32 * (dt0 + d) + r32] = acc[d][i];
+      out[TRANSPOSED ? (size_t)(32 * (dt0 + d) + r) * D + 32 * ft + r32 : (size_t)(32 * ft + r) * D + 32 * (dt0 + d) + r32] = PIECES ? sum[d][i] : acc[d][i];
     }
 }
 
