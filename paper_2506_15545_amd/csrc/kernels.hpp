@@ -120,6 +120,7 @@ struct ChunkPlan {
   int nprod;   // products per (batch, kv head); 0: nothing to share, or not worth it
   int head;    // 1: product 0 covers the 64 rows in front of state 0
   int ckeys;   // rows of every other product (64 or 128)
+  int piece;   // rows of a product that are summed for themselves (64, or ckeys)
   int end;     // row behind the last one that leaves the window
   size_t u_bytes;
 };

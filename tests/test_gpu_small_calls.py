@@ -98,6 +98,27 @@ def test_chunk_products_shared_with_the_hand_over(B, Hq, Hkv, W, chunks, phi):
             assert float(np.max(np.abs(np64(S) - S_ref))) <= 2e-5 * max(1.0, float(np.abs(S_ref).max()))
 
 
+@pytest.mark.parametrize("B,T,Hkv,W,pos0", [(1, 2048, 2, 129, 4000), (1, 1300, 2, 300, 9000), (4, 2048, 8, 512, 2048), (1, 700, 8, 512, 1531)])
+def test_carried_state_of_shared_products_in_fp32(B, T, Hkv, W, pos0):
+    """The state after a chunk against fp64, to what sums of 64 keys each (where every CU has two such products: 128), added in runs
+    of a quarter of them, leave: measured on these inputs 1.03e-7, 8.5e-8, 1.21e-7 and 9.1e-8 of the norm.  (One chain per 128 keys
+    and one over the products: 1.26e-7, 1.20e-7, 1.37e-7, 1.04e-7.)"""
+    D = 128
+    g = torch.Generator(device="cuda").manual_seed(5450 + T)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, k, v = (r(B, T, Hkv, D).bfloat16() for _ in range(3))
+    kr, vr = (r(B, Hkv, W, D).bfloat16() for _ in range(2))
+    S = r(B, Hkv, D, D) * math.sqrt((pos0 - W) * math.e) / D
+    slots = [(pos0 + i) % W for i in range(W)]
+    rows = [torch.cat([ring[:, :, slots], x.transpose(1, 2)], 2)[:, :, :T].double() for ring, x in ((kr, k), (vr, v))]
+    want = S.double() + torch.softmax(rows[0], -1).transpose(-1, -2) @ rows[1]
+    _, names = launches(lambda: rb.rattn_prefill_chunk(q, k, v, W, pos0, kr, vr, S, softmax_scale=0.09))
+    assert names == SHARED
+    err = float((S.double() - want).norm() / want.norm())
+    print(f"{err:.3e}", flush=True)
+    assert err <= {4000: 1.03e-7, 9000: 8.5e-8, 2048: 1.21e-7, 1531: 9.1e-8}[pos0] * 1.01   # (inputs differ by 0.5 % at most)
+
+
 def test_chunk_products_of_infinite_values():
     """An infinite value of one key, met by features of both kinds of zero, reaches its own column of the carried state only, as
     it does where the products are not shared (one sequence at a time here)."""
