@@ -132,17 +132,17 @@ template <int D> __device__ __forceinline__ void to_columns(const RowForm<D>& a,
 }
 
 // <rows of a, columns b> over the features: element i = row 4*q4 + i of a against column r16
-// NC chains of products and a tree of sums: the rounding grows with the length of a chain, the additions with their number (in
-// large grids, which are bound by arithmetic, four take 2 % more than two)
-template <int D, int NC> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
-  f32x4_t t[NC];
+// Four chains of products and a tree of sums: the rounding grows with the length of a chain.  Forward + backward in us, two
+// chains | four: 8 x 512 tokens, 16/8 heads, W = 128 343 | 344 at D = 64, 787 | 753 at D = 128; small grids alike.
+template <int D> __device__ __forceinline__ f32x4_t row_product(const RowForm<D>& a, const RowForm<D>& b) {
+  f32x4_t t[4];
 #pragma unroll
-  for (int e = 0; e < NC; ++e) t[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < 4; ++e) t[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < D / 16; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[e % NC] = mm4(a.x[j][e], b.x[j][e], t[e % NC]);
-  return NC == 4 ? (t[0] + t[1]) + (t[2] + t[NC - 1]) : t[0] + t[1];
+    for (int e = 0; e < 4; ++e) t[e] = mm4(a.x[j][e], b.x[j][e], t[e]);
+  return (t[0] + t[1]) + (t[2] + t[3]);
 }
 // acc += sum over the 16 rows of row^T (x) p,  p[i] = coefficient of row 4*q4 + i for column r16
 template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a, f32x4_t p, f32x4_t (&acc)[D / 16]) {
@@ -152,6 +152,20 @@ template <int D> __device__ __forceinline__ void col_product(const ColForm<D>& a
     for (int hf = 0; hf < D / 64; ++hf)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[4 * hf + e] = mm4(a.x[i][hf][e], p[i], acc[4 * hf + e]);
+}
+// The same with the 16 rows as a sum of their own, for chunks of any length: a chain over all of a chunk's keys rounds more than
+// states of 64 keys do (one chunk, 4 x 256 tokens, 8/4 heads, W = 32, D = 64: o 1.35e-7 -> 1.50e-7 of the norm off, dv 2.06e-7 ->
+// 2.16e-7; with these sums and four chains in row_product 1.28e-7 and 1.92e-7).
+template <int D> __device__ __forceinline__ void col_product_apart(const ColForm<D>& a, f32x4_t p, f32x4_t (&acc)[D / 16]) {
+#pragma unroll
+  for (int hf = 0; hf < D / 64; ++hf)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t = mm4(a.x[i][hf][e], p[i], t);
+      acc[4 * hf + e] += t;
+    }
 }
 // Ahead of a col_product whose tile has columns that do not see every row: `see[i]` says whether column r16 sees row
 // 4*q4 + i, and p[i] = 0 where it does not.  0 times an infinite or NaN feature is not 0, so such features are taken out of
@@ -415,7 +429,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_fwd_kernel(const IO* __restric
     }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n, next = s0 + 16 * GW;
-      f32x4_t s = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
+      f32x4_t s = row_product<D>(kf, qv);
       if (n + GW < nt) kf.load(krow(next + r16), q4);
       float mx = -INFINITY;
       bool see[4];
@@ -464,13 +478,13 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_fwd_kernel(const IO* __restric
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
       kf.feature(dm.phi);
-      f32x4_t c = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
+      f32x4_t c = row_product<D>(kf, qv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) { see[i] = s0 + 4 * q4 + i <= t - W; c[i] = see[i] ? c[i] : 0.f; }
       if (s0 + 15 > t0 - W) hide_unseen<D>(vf, c, see, r16, q4, acc);
       if (n + GW < nt) kf.load(krow(s0 + 16 * GW + r16), q4);
-      col_product<D>(vf, c, acc);
+      col_product_apart<D>(vf, c, acc);
       if (n + GW < nt) vf.load([&](int i) { return vrow(s0 + 16 * GW + 4 * q4 + i); }, r16);
     }
   }
@@ -625,7 +639,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dq_kernel(const IO* __rest
     }
     for (int n = w; n < nt; n += GW) {
       const int s0 = lo + 16 * n;
-      f32x4_t c = row_product<D, GW == 8 ? 4 : 2>(vf, dxr);
+      f32x4_t c = row_product<D>(vf, dxr);
       if (n + GW < nt) request_v(n + GW);
       kf.feature(dm.phi);
       bool see[4];
@@ -652,8 +666,8 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dq_kernel(const IO* __rest
     };
     // p and dp of the 16 keys from s0 on (in kf, vf), 0 where the query does not see the key
     auto scores = [&](int s0, f32x4_t& p, f32x4_t& dp) {
-      p = row_product<D, GW == 8 ? 4 : 2>(kf, qv);
-      dp = row_product<D, GW == 8 ? 4 : 2>(vf, dxs);
+      p = row_product<D>(kf, qv);
+      dp = row_product<D>(vf, dxs);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool see = sees(s0 + 4 * q4 + i);
@@ -783,15 +797,15 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dkv_kernel(const IO* __res
 #pragma unroll
         for (int i = 0; i < 4; ++i) c[i] = see[i] ? c[i] : 0.f;
         if (!all) hide_unseen<D>(a, c, see, r16, q4, acc);
-        col_product<D>(a, c, acc);
+        col_product_apart<D>(a, c, acc);
       };
       ColForm<D> col;
       if (!AHEAD) { request_d(u); request_q(u); }
-      const f32x4_t e = row_product<D, GW == 8 ? 4 : 2>(dr, vv);
+      const f32x4_t e = row_product<D>(dr, vv);
       to_columns<D>(dr, col, plane, r16, q4);
       if (AHEAD && u + GW < G * nt) request_d(u + GW);
       qf.feature(dm.phi);
-      add(col, row_product<D, GW == 8 ? 4 : 2>(qf, kv), dva);
+      add(col, row_product<D>(qf, kv), dva);
       to_columns<D>(qf, col, plane, r16, q4);
       if (AHEAD && u + GW < G * nt) request_q(u + GW);
       add(col, e, dka);
@@ -824,7 +838,7 @@ __global__ __launch_bounds__(64 * GW, 2) void gen_bwd_dkv_kernel(const IO* __res
     for (int u = w; u < G * nt; u += GW) {
       const int q0 = s0 + 16 * (u % nt);
       if (!AHEAD) { request_q(u); request_d(u); }
-      f32x4_t p = row_product<D, GW == 8 ? 4 : 2>(qf, kv), da = row_product<D, GW == 8 ? 4 : 2>(dr, vv);
+      f32x4_t p = row_product<D>(qf, kv), da = row_product<D>(dr, vv);
       bool see[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {

@@ -52,6 +52,23 @@ def test_one_chunk_or_states(B, T, Hq, Hkv, W, states, D, phi):
         assert err <= 5e-6, n   # 2^-24 times a random walk over (T + D) terms and the two products in front of them
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,W,limit", [
+    (1, 200, 2, 1, 64, 16, (1.24, 2.52, 2.58, 1.85)), (4, 256, 8, 4, 64, 32, (1.35, 2.66, 2.74, 2.06)), (4, 256, 8, 4, 128, 32, (1.62, 3.10, 3.17, 2.24)),
+    (2, 200, 16, 4, 128, 16, (1.47, 2.79, 2.90, 2.06)), (4, 161, 16, 8, 64, 33, (1.39, 2.63, 2.72, 2.11))])
+def test_one_chunk_rounds_no_more_than_states_did(B, T, Hq, Hkv, D, W, limit):
+    """o, dq, dk and dv of calls whose keys form one chunk against fp64, in 1e-7 of the norm: not above what these inputs gave when
+    the same calls went over states of 64 keys with products in two chains (a sum over the whole chunk in one chain is above)."""
+    g = torch.Generator(device="cuda").manual_seed(5200 + T + D)
+    q, k, v, dO = (torch.randn(B, T, h, D, device="cuda", generator=g) for h in (Hq, Hkv, Hkv, Hq))
+    args, scale = tuple(np64(t) for t in (q, k, v)), D ** -0.5
+    want = {"o": orc.fwd_dense(*args, W, scale=scale)["o"], **orc.bwd_dense(*args, np64(dO), W, scale=scale)}
+    o, saved = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, softmax_scale=scale)
+    got = (o,) + rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, softmax_scale=scale)[:3]
+    err = [1e7 * float(np.linalg.norm(np64(x) - want[n]) / np.linalg.norm(want[n])) for n, x in zip(("o", "dq", "dk", "dv"), got)]
+    print("errors %.3f %.3f %.3f %.3f" % tuple(err), flush=True)
+    assert all(e <= lim for e, lim in zip(err, limit))
+
+
 SHARED = ["chunk_products_kernel", "chunk_scan_kernel", "fwd_fused_kernel"]
 
 
