@@ -308,6 +308,9 @@ def rattn_decode_step(q, k_new, v_new, pos, k_ring, v_ring, state, gamma_swa=Non
     dt = q.dtype
     if dt not in _DTYPES or k_new.dtype != dt or v_new.dtype != dt or k_ring.dtype != dt or v_ring.dtype != dt:
         raise ValueError("q, k_new, v_new and the rings must share dtype float32 or bfloat16")
+    if out is not None and not (out.is_cuda and out.device == q.device and out.dtype == dt and out.is_contiguous()
+                                and out.numel() >= q.numel()):
+        raise ValueError("out must be a contiguous tensor on the device and in the dtype of q that holds its elements")
     p, nbytes = _decode_plan(qs, Hkv, W, dt, float(softmax_scale), float(rms_eps), feature_map)
     o = torch.empty_like(q) if out is None else out
     gs = _gain(gamma_swa, Hq, D, q.device)

@@ -82,7 +82,9 @@ PyObject* step(PyObject* const* args) {
     o = fresh.data_ptr();
   } else {
     if (!THPVariable_CheckExact(args[11])) Py_RETURN_NONE;
-    o = THPVariable_Unpack(args[11]).data_ptr();
+    const at::Tensor& out = THPVariable_Unpack(args[11]);   // the step writes N Hq D elements of it, whatever its shape
+    if (!plain(out, dev, dt, out.dim()) || out.numel() < q.numel()) Py_RETURN_NONE;
+    o = out.data_ptr();
   }
   size_t bytes = 0;
   rattn_status s = g_bytes(&p, &bytes);

@@ -1,5 +1,8 @@
 """The decode step's native argument marshalling: what is not plainly an accepted call goes to the Python path, which converts or
 refuses it as ever; both give the same."""
+import contextlib
+import ctypes
+
 import pytest
 import torch
 
@@ -16,6 +19,20 @@ def tensors(dev, N=2, Hq=4, Hkv=2, D=64, W=16, dtype=torch.float32):
 def native(t, gs=None, gr=None, scale=0.125, eps=1e-6, out=None, phi="softmax"):
     rb.lib()
     return rb._decode_native(*t.values(), gs, gr, scale, eps, out, phi)
+
+
+@contextlib.contextmanager
+def step_replaced(f):
+    """The native path with `f`, a function of libpython that takes nothing and returns an int, in the step's place: nothing is
+    launched, and what f returns is the status."""
+    lib = rb.lib()
+    from paper_2506_15545_amd import _marshal
+    addr = lambda g: ctypes.cast(g, ctypes.c_void_p).value
+    try:
+        _marshal.bind(addr(f), addr(lib.rattn_decode_workspace_bytes))
+        yield
+    finally:
+        _marshal.bind(addr(lib.rattn_decode_step_ws), addr(lib.rattn_decode_workspace_bytes))
 
 
 def test_host_tensors_are_refused_as_ever():
@@ -62,3 +79,28 @@ def test_forms_that_python_converts_or_refuses():
             assert torch.equal(got, want)
     assert torch.equal(out, rb.rattn_decode_step(**fresh(), gamma_swa=gain, softmax_scale=0.125))
     assert not torch.equal(rb.rattn_decode_step(**fresh(), softmax_scale=1), out)
+
+
+@pytest.mark.gpu
+def test_out_that_cannot_take_the_result_is_refused():
+    """The step writes N Hq D elements of q's type: an `out` that does not hold them is refused ahead of any launch (nothing here
+    is launched through it), one of another shape that does is taken."""
+    t = tensors("cuda")
+    N, Hq, D = t["q"].shape
+    keep = {k: v.clone() for k, v in t.items()}
+    for out in (torch.empty(N, Hq, D), torch.empty(N - 1, Hq, D, device="cuda"), torch.empty(0, device="cuda"),
+                torch.empty(N, Hq, D, device="cuda", dtype=torch.bfloat16), torch.empty(N, D, Hq, device="cuda").transpose(1, 2),
+                torch.empty(N, Hq, 2 * D, device="cuda")[..., :D]):
+        with step_replaced(ctypes.pythonapi.Py_IsInitialized):   # (1)
+            assert native(t, out=out) is None
+        for scale in (0.125, torch.tensor(0.125)):   # the native path's refusal, the Python path's own
+            with pytest.raises(ValueError, match="out must be"):
+                rb.rattn_decode_step(**t, softmax_scale=scale, out=out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(t[k], keep[k]) for k in t)
+    want = rb.rattn_decode_step(**{k: v.clone() for k, v in t.items()}, softmax_scale=0.125)
+    for scale in (0.125, torch.tensor(0.125)):
+        out = torch.empty(N * Hq * D + 8, device="cuda")
+        x = {k: v.clone() for k, v in t.items()}
+        assert rb.rattn_decode_step(**x, softmax_scale=scale, out=out) is out
+        assert torch.equal(out[:N * Hq * D].view(N, Hq, D), want)
