@@ -38,6 +38,12 @@ bool plain(const at::Tensor& t, int dev, at::ScalarType dt, int nd) {
 }
 bool shaped(const at::Tensor& t, int64_t a, int64_t b, int64_t c) { return t.size(0) == a && t.size(1) == b && t.size(2) == c; }
 
+// The interpreter lock is free while one of these lives, as in a ctypes call
+struct NoGil {
+  PyThreadState* state = PyEval_SaveThread();
+  ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 PyObject* step(PyObject* const* args) {
   const at::Tensor* t[7];
   for (int i = 0; i < 7; ++i) {
@@ -86,14 +92,20 @@ PyObject* step(PyObject* const* args) {
     if (!plain(out, dev, dt, out.dim()) || out.numel() < q.numel()) Py_RETURN_NONE;
     o = out.data_ptr();
   }
-  size_t bytes = 0;
-  rattn_status s = g_bytes(&p, &bytes);
-  if (s != RATTN_OK) return PyLong_FromLong(s);
-  c10::DataPtr ws;   // from the caching allocator, on the current stream: back in its pool when the step is enqueued
-  if (bytes > 0) ws = c10::hip::HIPCachingAllocator::get()->allocate(bytes);
-  s = g_step(&p, q.data_ptr(), kn.data_ptr(), vn.data_ptr(), (const int32_t*)pos.data_ptr(), kr.data_ptr(), vr.data_ptr(),
-             (float*)state.data_ptr(), gain[0], gain[1], o, ws.get(), bytes,
-             (void*)c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream());
+  const void *qp = q.data_ptr(), *knp = kn.data_ptr(), *vnp = vn.data_ptr();
+  void *posp = pos.data_ptr(), *krp = kr.data_ptr(), *vrp = vr.data_ptr(), *sp = state.data_ptr();
+  rattn_status s;
+  {
+    NoGil others_run;   // the allocator may wait for the device, a launch for room in the stream's queue
+    size_t bytes = 0;
+    s = g_bytes(&p, &bytes);
+    if (s == RATTN_OK) {
+      c10::DataPtr ws;   // from the caching allocator, on the current stream: back in its pool when the step is enqueued
+      if (bytes > 0) ws = c10::hip::HIPCachingAllocator::get()->allocate(bytes);
+      s = g_step(&p, qp, knp, vnp, (const int32_t*)posp, krp, vrp, (float*)sp, gain[0], gain[1], o, ws.get(), bytes,
+                 (void*)c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream());
+    }
+  }
   if (s != RATTN_OK) return PyLong_FromLong(s);
   if (fresh.defined()) return THPVariable_Wrap(fresh);
   Py_INCREF(args[11]);

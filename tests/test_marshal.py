@@ -104,3 +104,12 @@ def test_out_that_cannot_take_the_result_is_refused():
         x = {k: v.clone() for k, v in t.items()}
         assert rb.rattn_decode_step(**x, softmax_scale=scale, out=out) is out
         assert torch.equal(out[:N * Hq * D].view(N, Hq, D), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("W", [16, 1024])   # without a workspace, with one
+def test_other_threads_run_during_the_step(W):
+    """The interpreter lock is not held while the step is enqueued, which can wait for the device."""
+    t = tensors("cuda", D=128, W=W, dtype=torch.bfloat16)
+    with step_replaced(ctypes.pythonapi.PyGILState_Check):   # 1 with the lock held
+        assert torch.is_tensor(native(t))
