@@ -7,6 +7,7 @@
 // or raises as it always did), and a status as an int when the library refuses the call.
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 #include <ATen/ATen.h>
 #include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
@@ -81,16 +82,22 @@ PyObject* step(PyObject* const* args) {
   else if (PyUnicode_CompareWithASCIIString(args[12], "relu") == 0) p.feature_map = RATTN_PHI_RELU;
   else if (PyUnicode_CompareWithASCIIString(args[12], "identity") == 0) p.feature_map = RATTN_PHI_IDENTITY;
   else Py_RETURN_NONE;
-  at::Tensor fresh;
+  // The result as an object ahead of the step: behind it nothing may fail, since a caller that is told so would step again and
+  // fold the evicted token into the state twice
+  THPObjectPtr result;
   void* o;
   if (args[11] == Py_None) {
-    fresh = at::empty_like(q);
+    at::Tensor fresh = at::empty_like(q);
     o = fresh.data_ptr();
+    result = THPVariable_Wrap(std::move(fresh));
+    if (!result) return nullptr;
   } else {
     if (!THPVariable_CheckExact(args[11])) Py_RETURN_NONE;
     const at::Tensor& out = THPVariable_Unpack(args[11]);   // the step writes N Hq D elements of it, whatever its shape
     if (!plain(out, dev, dt, out.dim()) || out.numel() < q.numel()) Py_RETURN_NONE;
     o = out.data_ptr();
+    Py_INCREF(args[11]);
+    result = args[11];
   }
   const void *qp = q.data_ptr(), *knp = kn.data_ptr(), *vnp = vn.data_ptr();
   void *posp = pos.data_ptr(), *krp = kr.data_ptr(), *vrp = vr.data_ptr(), *sp = state.data_ptr();
@@ -102,14 +109,11 @@ PyObject* step(PyObject* const* args) {
     if (s == RATTN_OK) {
       c10::DataPtr ws;   // from the caching allocator, on the current stream: back in its pool when the step is enqueued
       if (bytes > 0) ws = c10::hip::HIPCachingAllocator::get()->allocate(bytes);
-      s = g_step(&p, qp, knp, vnp, (const int32_t*)posp, krp, vrp, (float*)sp, gain[0], gain[1], o, ws.get(), bytes,
-                 (void*)c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream());
+      void* stream = (void*)c10::hip::getCurrentHIPStream((c10::DeviceIndex)dev).stream();
+      s = g_step(&p, qp, knp, vnp, (const int32_t*)posp, krp, vrp, (float*)sp, gain[0], gain[1], o, ws.get(), bytes, stream);
     }
   }
-  if (s != RATTN_OK) return PyLong_FromLong(s);
-  if (fresh.defined()) return THPVariable_Wrap(fresh);
-  Py_INCREF(args[11]);
-  return args[11];
+  return s == RATTN_OK ? result.release() : PyLong_FromLong(s);
 }
 
 PyObject* decode_step(PyObject*, PyObject* const* args, Py_ssize_t n) {

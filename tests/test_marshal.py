@@ -113,3 +113,23 @@ def test_other_threads_run_during_the_step(W):
     t = tensors("cuda", D=128, W=W, dtype=torch.bfloat16)
     with step_replaced(ctypes.pythonapi.PyGILState_Check):   # 1 with the lock held
         assert torch.is_tensor(native(t))
+
+
+@pytest.mark.gpu
+def test_a_result_that_cannot_be_made_stops_the_step():
+    """No memory for the result's object: the error comes ahead of the step (whose stand-in would return 1), not behind it."""
+    testcapi = pytest.importorskip("_testcapi")
+    t = tensors("cuda")
+    args = (*t.values(), None, None, 0.125, 1e-6, None, "softmax")
+    rb.lib()
+    f, got = rb._decode_native, None
+    with step_replaced(ctypes.pythonapi.Py_IsInitialized):
+        assert f(*args) == 1
+        testcapi.set_nomemory(0, 0)
+        try:
+            got = f(*args)
+        except MemoryError:
+            got = "refused"
+        finally:
+            testcapi.remove_mem_hooks()
+    assert got == "refused"
