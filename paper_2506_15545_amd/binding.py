@@ -105,17 +105,26 @@ def lib():
     L.rattn_profile_count.restype = ctypes.c_int
     L.rattn_profile_get.restype = ctypes.c_int
     L.rattn_profile_get.argtypes = [ctypes.c_int, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_float)]
-    from . import _marshal   # (built with the library)
-    addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-    _marshal.bind(addr(L.rattn_decode_step_ws), addr(L.rattn_decode_workspace_bytes))
-    global _decode_native
-    _decode_native = _marshal.decode_step
     _lib = L
     return L
 
 
-def _decode_native(*args):   # until the library is loaded
-    lib()
+def _load_decode_native():
+    """The decode step's native marshalling, which only that step needs; raises if it has not been built for this torch."""
+    global _decode_native
+    L = lib()
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError(f"{os.path.join(_PKG, '_marshal.so')} is not built for this torch ({e}); run "
+                           "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+    addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    _marshal.bind(addr(L.rattn_decode_step_ws), addr(L.rattn_decode_workspace_bytes))
+    _decode_native = _marshal.decode_step
+
+
+def _decode_native(*args):   # until the first step
+    _load_decode_native()
     return _decode_native(*args)
 
 

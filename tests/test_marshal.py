@@ -2,10 +2,12 @@
 refuses it as ever; both give the same."""
 import contextlib
 import ctypes
+import sys
 
 import pytest
 import torch
 
+import paper_2506_15545_amd
 from paper_2506_15545_amd import binding as rb
 
 
@@ -17,7 +19,6 @@ def tensors(dev, N=2, Hq=4, Hkv=2, D=64, W=16, dtype=torch.float32):
 
 
 def native(t, gs=None, gr=None, scale=0.125, eps=1e-6, out=None, phi="softmax"):
-    rb.lib()
     return rb._decode_native(*t.values(), gs, gr, scale, eps, out, phi)
 
 
@@ -25,6 +26,7 @@ def native(t, gs=None, gr=None, scale=0.125, eps=1e-6, out=None, phi="softmax"):
 def step_replaced(f):
     """The native path with `f`, a function of libpython that takes nothing and returns an int, in the step's place: nothing is
     launched, and what f returns is the status."""
+    rb._load_decode_native()
     lib = rb.lib()
     from paper_2506_15545_amd import _marshal
     addr = lambda g: ctypes.cast(g, ctypes.c_void_p).value
@@ -44,6 +46,17 @@ def test_host_tensors_are_refused_as_ever():
         rb.rattn_decode_step(None, **{k: v for k, v in t.items() if k != "q"})
     with pytest.raises(TypeError):
         rb._decode_native(t["q"])
+
+
+def test_only_the_decode_step_needs_the_extension(monkeypatch):
+    """Without it (or with one built for another torch) everything else loads, and a decode step says what to run."""
+    monkeypatch.setitem(sys.modules, "paper_2506_15545_amd._marshal", None)   # importing it raises ImportError
+    monkeypatch.delattr(paper_2506_15545_amd, "_marshal", raising=False)
+    monkeypatch.setattr(rb, "_lib", None)
+    monkeypatch.setattr(rb, "_decode_native", lambda *a: rb._load_decode_native())
+    assert rb.rattn_cache_bytes(4, 0, 100, 16, 1, 2, 64, 2) > 0
+    with pytest.raises(RuntimeError, match="_marshal.so is not built"):
+        rb.rattn_decode_step(**tensors("cpu"))
 
 
 @pytest.mark.gpu
@@ -121,9 +134,9 @@ def test_a_result_that_cannot_be_made_stops_the_step():
     testcapi = pytest.importorskip("_testcapi")
     t = tensors("cuda")
     args = (*t.values(), None, None, 0.125, 1e-6, None, "softmax")
-    rb.lib()
-    f, got = rb._decode_native, None
+    got = None
     with step_replaced(ctypes.pythonapi.Py_IsInitialized):
+        f = rb._decode_native
         assert f(*args) == 1
         testcapi.set_nomemory(0, 0)
         try:
