@@ -152,7 +152,9 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   L->sv_rs = off; off += align_up(nrow_f * 4);
   L->sv_rr = off; off += align_up(nrow_f * 4);
   L->sv_states = off;
-  const size_t nstate = (size_t)dm.B * dm.Hkv * dm.nst * dm.D * dm.D;   // general kernels
+  // general kernels; with all keys in the first chunk there are none.  (The forward's workspace keeps room for that one: a call
+  // without it is refused for every chunk size or for none.)
+  const size_t nstate_fwd = (size_t)dm.B * dm.Hkv * dm.nst * dm.D * dm.D, nstate = dm.nst > 1 ? nstate_fwd : 0;
   if (L->fast_fwd)
     L->state_stride = p->state_policy == RATTN_STATES_KEEP ? 1 : p->state_policy == RATTN_STATES_REBUILD ? 0 : p->state_policy;
   else  // general kernels: all or none; all only where a chunk's states take no more room than its branch outputs
@@ -165,7 +167,7 @@ rattn_status make_layout(const rattn_params* p, Layout* L) {
   }
   L->saved_bytes = off;
 
-  L->gen_fwd_bytes = align_up(nstate * 4);   // the same for both kinds of call (states that are kept are built in `saved`)
+  L->gen_fwd_bytes = align_up(nstate_fwd * 4);   // the same for both kinds of call (states that are kept are built in `saved`)
 
   off = 0;
   L->gb_rstates = off; off += align_up(nstate * 4);   // states that were not kept are rebuilt here first

@@ -245,3 +245,10 @@ def test_general_kernels_keep_their_states_in_saved_only_as_asked(dtype, D, fmap
     assert rb.rattn_workspace_bytes(params(chunk=smallest, **base))[2] == without + states(smallest)
     for chunk in (smallest - 1, 1):
         assert rb.rattn_workspace_bytes(params(chunk=chunk, **base))[2] == without
+    # all keys in one chunk, by the caller's choice or (few keys) the library's: no states are kept or rebuilt
+    assert rb.rattn_workspace_bytes(params(chunk=T - W, **base))[2] == without
+    assert rb.rattn_workspace_bytes(params(chunk=T - W - 1, **base))[2] == without + states(T - W - 1)
+    few = dict(base, T=W + 200)
+    size = {chunk: rb.rattn_workspace_bytes(params(chunk=chunk, **few)) for chunk in (0, 64)}
+    assert size[0][2] == 2 * up(B * few["T"] * Hq * D * 4) + 3 * up(B * Hq * few["T"] * 4)
+    assert size[0][1] == size[64][1] - up(B * Hkv * 4 * D * D * 4)

@@ -550,12 +550,16 @@ def test_chunked_prefill_uses_matrix_core_kernels():
 def test_general_kernels_rebuild_the_states_they_do_not_keep(policy, chunk, dtype, D, fmap):
     """States that the forward does not keep are built again by the backward, from the same sums: no bit changes against a
     call that keeps them."""
-    T, W = 200, 40
+    T, W = 200 if chunk else 400, 40   # (360 keys beyond the window: more than the default takes as one chunk, without states)
     x = synth.make_random_layer(2, T, 4, 2, D, dtype, 4700 + D, with_dO=True)
     q, k, v, dO = dev(x["q"]), dev(x["k"]), dev(x["v"]), dev(x["dO"])
     kw = dict(softmax_scale=0.1, feature_map=fmap, chunk=chunk)
     o, saved = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, state_policy=policy, **kw)
+    rb.rattn_profile_enable(True)
     got = rb.rattn_bwd(q, k, v, saved, dO, W, want_dgamma=False, state_policy=policy, **kw)[:3]
+    torch.cuda.synchronize()
+    assert "gen_chunk_kernel" in [n for n, _ in rb.rattn_profile_records()]
+    rb.rattn_profile_enable(False)
     kw["chunk"] = chunk if chunk != 1 else 32       # (one key per chunk: compared with the kept states of another chunk size)
     o0, saved0 = rb.rattn_fwd(q, k, v, W, save_for_bwd=True, **kw)
     assert saved.numel() < saved0.numel()
