@@ -550,7 +550,7 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
   dmx.T = C.R + p->T;
   rattn::SavedPtrs none = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   rattn::SeqTensors t;
-  // The forward computes the chunk's rows only, straight from q into o; the carried state is the initial value of the
+  // The forward computes the chunk's rows only, straight from q into o; a carried state is the initial value of the
   // chunk-state scan, of which every chunk row reads a state (the keys before it number at least `window` then).
   if (C.L2.fast_fwd) {
     // only the ring rows are gathered, as the whole 128-row tiles in front of the chunk's
@@ -559,9 +559,9 @@ rattn_status rattn_prefill_chunk(const rattn_params* p, int32_t pos0, const void
     const rattn::ChunkHandover handover = {C.plan, k_ring, v_ring, state, C.R, pos0, carried ? 1 : 0};
     if (C.plan.nprod > 0) t.handover = &handover;
     else if (C.P > 0) rattn::chunk_ring(dm, C.P, C.R, pos0, k_ring, v_ring, w + C.kc, w + C.vc, st);
-    rattn::fast_fwd(C.L2.dmf, t, q, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws), w + C.states, st,
-                    carried ? state : nullptr);
-    if (C.plan.nprod == 0) rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0, carried);
+    rattn::fast_fwd(C.L2.dmf, t, q, gamma_swa, gamma_rla, o, none, (float*)(w + C.fwdws), w + C.states, st);
+    // (not shared: nothing is carried either, so the state is what the export forms)
+    if (C.plan.nprod == 0) rattn::prefill_export(dmx, p->dtype, t, k_ring, v_ring, state, (float*)(w + C.partial), st, pos0);
   } else {
     t.k = w + C.kc; t.v = w + C.vc; t.Tb = dmx.T;
     rattn::chunk_concat(dm, p->dtype, p->T, C.R, pos0, k, v, k_ring, v_ring, w + C.kc, w + C.vc, st);

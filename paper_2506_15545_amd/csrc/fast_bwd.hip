@@ -1226,8 +1226,7 @@ void fast_bwd(const LayerDims& dm, int Tc, const void* q, const void* k, const v
   if (!all_kept && pl.fwd.nstf > 0) {
     SeqTensors t;
     t.k = k; t.v = v; t.Tb = Tc;
-    rla_forward_states(dm, pl.fwd, t, ws.U, ws.states, st, nullptr, nullptr, sv.state_stride > 1 ? sv.states : nullptr,
-                       sv.state_stride);
+    rla_forward_states(dm, pl.fwd, t, ws.U, ws.states, st, nullptr, sv.state_stride > 1 ? sv.states : nullptr, sv.state_stride);
   }
   a.states = (const uint16_t*)(all_kept ? sv.states : ws.states); a.rstates = (const uint16_t*)ws.rstates;
   a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv;

@@ -498,13 +498,13 @@ __global__ __launch_bounds__(256, fwd_occ(D)) void fwd_fused_kernel(FastFwdArgs 
 }  // namespace
 
 void fast_fwd(const LayerDims& dm, const SeqTensors& t, const void* q, const float* gs, const float* gr, void* o,
-              const SavedPtrs& sv, float* U, void* states, hipStream_t st, const float* state0) {
+              const SavedPtrs& sv, float* U, void* states, hipStream_t st) {
   const FastFwdPlan pl = fast_fwd_plan(dm);
   // `states` receives every chunk state; with a state stride the stored subset also goes to `saved`
   if (t.handover)
     chunk_states(dm, t, U, states, st);
   else if (pl.nstf > 0)
-    rla_forward_states(dm, pl, t, U, states, st, state0, sv.state_stride > 1 ? sv.states : nullptr, nullptr, sv.state_stride);
+    rla_forward_states(dm, pl, t, U, states, st, sv.state_stride > 1 ? sv.states : nullptr, nullptr, sv.state_stride);
   FastFwdArgs a;
   a.q = {nullptr, (const uint16_t*)q, 0, t.Tb};
   a.k = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};

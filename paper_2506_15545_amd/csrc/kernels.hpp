@@ -117,14 +117,14 @@ FastFwdPlan fast_fwd_plan(const LayerDims& dm);
 // Chunked prefill on the matrix cores: how the products of the forward's states and of the state that the call leaves are
 // shared (see chunk_kernels.hip)
 struct ChunkPlan {
-  int nprod;   // products per (batch, kv head); 0: nothing to share, or not worth it
+  int nprod;   // products per (batch, kv head); 0: nothing to share
   int head;    // 1: product 0 covers the 64 rows in front of state 0
   int ckeys;   // rows of every other product (64 or 128)
   int piece;   // rows of a product that are summed for themselves (64, or ckeys)
   int end;     // row behind the last one that leaves the window
   size_t u_bytes;
 };
-// dm: padded; P, R: front rows and how many of them are ring rows; Tc new rows
+// dm: padded, D = 128, softmax or ReLU map; P, R: front rows and how many of them are ring rows; Tc new rows
 ChunkPlan chunk_plan(const LayerDims& dm, int P, int R, int Tc);
 // Given to fast_fwd, which then also does what chunk_ring and prefill_export do: fills the front tensors from the rings,
 // and leaves rings and state advanced by the chunk.  U of fast_fwd: plan.u_bytes.
@@ -136,19 +136,16 @@ struct ChunkHandover {
 };
 void chunk_states(const LayerDims& dm, const SeqTensors& t, float* U, void* states, hipStream_t st);
 // dm.T: the padded length.  The query tiles computed are those of the Tb rows behind the front part; q, o and the saved
-// tensors hold just those rows ([B,Tb,Hq,D]; the saved tensors rounded up to whole tiles).  state0 (fp32
-// [B,Hkv,D(feature),D(value)], may be NULL): a linear-branch state that precedes key 0 and is added to every chunk state;
-// tiles whose chunk starts before key 0 do not see it, so the caller uses it only when no computed tile is of that kind.
+// tensors hold just those rows ([B,Tb,Hq,D]; the saved tensors rounded up to whole tiles).
 void fast_fwd(const LayerDims& dm, const SeqTensors& t, const void* q, const float* gs, const float* gr, void* o,
-              const SavedPtrs& sv, float* U, void* states, hipStream_t st, const float* state0 = nullptr);
+              const SavedPtrs& sv, float* U, void* states, hipStream_t st);
 
 // linear-branch chunk states for the MFMA paths (bf16 [d][f] per state, fp32 scratch U per chunk)
 // With m > 1: `subset_out` (forward) also receives states 0, m, 2m, ...; `restart` (backward) holds those states from
 // the forward pass: only the chunk products that lead to a state in between are formed, and the scan restarts from
 // every stored state.
 void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTensors& t, float* U, void* states,
-                        hipStream_t st, const float* state0 = nullptr, void* subset_out = nullptr,
-                        const void* restart = nullptr, int m = 1);
+                        hipStream_t st, void* subset_out = nullptr, const void* restart = nullptr, int m = 1);
 // MFMA backward path (same shape class as the MFMA forward)
 struct FastBwdPlan {
   FastFwdPlan fwd;

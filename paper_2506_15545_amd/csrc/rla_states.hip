@@ -91,15 +91,14 @@ __global__ __launch_bounds__(256, 2) void rla_chunk_kernel(ChunkArgs p) {
 //   reverse: state[n-1] = 0; state[i] = state[i+1] + products per*i .. per*i + per - 1 (those that exist)
 // grid (D*D/1024, Hkv, B), 256 threads, 4 elements per thread.  Blocks with z >= B (reverse scan, `dg.part` given) sum gain
 // gradients instead: a launch of its own for those took 4.7 us between kernels that do not need them.
-// init (forward only, may be NULL): a state that precedes chunk 0, fp32 [B,Hkv,f,d] (not transposed).
 // Forward scan with m > 1: `subset` (may be NULL) also receives states 0, m, 2m, ... ([B,Hkv,ceil(nst/m),128,128]);
 // `restart` (may be NULL) holds such a subset, and the running sum is replaced by the stored state at every multiple
 // of m (the products that lead to a stored state are then never used and need not exist).
 template <int D, bool REV, int PER>
 __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__ U, uint16_t* __restrict__ states,
                                                        int nchunks, int nst, int head,
-                                                       const float* __restrict__ init, uint16_t* __restrict__ subset,
-                                                       const uint16_t* __restrict__ restart, int m, int B, DgammaSum dg) {
+                                                       uint16_t* __restrict__ subset, const uint16_t* __restrict__ restart,
+                                                       int m, int B, DgammaSum dg) {
   const int g = blockIdx.y, b = blockIdx.z, Hkv = gridDim.y;
   if (REV && b >= B) {
     dgamma_reduce_tile(dg, ((b - B) * gridDim.y + g) * gridDim.x + blockIdx.x);
@@ -110,11 +109,6 @@ __global__ __launch_bounds__(256) void rla_scan_kernel(const float* __restrict__
   const float* Ub = U + (size_t)(b * Hkv + g) * nchunks * N + e4;
   uint16_t* Sb = states + (size_t)(b * Hkv + g) * nst * N + e4;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (!REV && init) {  // element (d, f .. f+3) of the transposed state = init[f .. f+3][d]
-    const float* ib = init + (size_t)(b * Hkv + g) * N + e4 / D;
-    const int f = e4 % D;
-    acc = make_float4(ib[(size_t)f * D], ib[(size_t)(f + 1) * D], ib[(size_t)(f + 2) * D], ib[(size_t)(f + 3) * D]);
-  }
   const int nsub = (!REV && m > 1) ? (nst + m - 1) / m : 0;
   const size_t sub0 = (size_t)(b * Hkv + g) * nsub * N + e4;
   auto put = [&](int i) {
@@ -270,11 +264,11 @@ int dgamma_layers(const LayerDims& dm, const DgammaSum& dg) {
 // per: products that a state spans
 template <int D, bool REV>
 void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* states, int nchunks, int nst, int head,
-                        const float* init, void* subset, const void* restart, int m, hipStream_t st,
+                        void* subset, const void* restart, int m, hipStream_t st,
                         const DgammaSum& dg = DgammaSum{}) {
   const dim3 grid(D * D / 1024, dm.Hkv, dm.B + dgamma_layers(dm, dg));
 #define RATTN_SCAN(PER_)                                                                                                \
-  rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, init, (uint16_t*)subset, \
+  rla_scan_kernel<D, REV, PER_><<<grid, 256, 0, st>>>(U, (uint16_t*)states, nchunks, nst, head, (uint16_t*)subset, \
                                                       (const uint16_t*)restart, m, dm.B, dg)
   if (REV && per == 8) RATTN_SCAN(REV ? 8 : 2);
   else if (REV && per == 6) RATTN_SCAN(REV ? 6 : 2);
@@ -288,14 +282,14 @@ void launch_scan_kernel(const LayerDims& dm, int per, const float* U, void* stat
 }  // namespace
 
 void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTensors& t, float* U, void* states,
-                        hipStream_t st, const float* state0, void* subset_out, const void* restart, int m) {
+                        hipStream_t st, void* subset_out, const void* restart, int m) {
   if (pl.nstf <= 0) return;
   if (m < 2) { m = 1; subset_out = nullptr; restart = nullptr; }
   const int head = pl.base > 0 ? 1 : 0;  // products in front of state 0: the 64 keys before it when it sits at key 64
   // Forward without saving in us, two launches | one: one product, 8 pairs of batch and kv head 28.2 | 23.4, 128 pairs 74.4 | 65.1;
   // two, 8 pairs 26.0 | 23.0, 64 pairs 37.4 | 34.1; three, 8 pairs 39.2 | 37.3 (D = 64 24.2 | 22.6), 64 pairs 49.2 | 47.8, 128 pairs
   // 123.4 | 125.8, where the work-groups no longer have a CU each
-  if (!state0 && m == 1 && t.P == 0 && pl.ckeys == 128 && pl.nchunks <= (dm.Hkv * (long long)dm.B <= 64 ? 3 : 2)) {
+  if (m == 1 && t.P == 0 && pl.ckeys == 128 && pl.nchunks <= (dm.Hkv * (long long)dm.B <= 64 ? 3 : 2)) {
     const WalkArgs p = {(const uint16_t*)t.k, (const uint16_t*)t.v, (uint16_t*)states, dm.Hkv, t.Tb, dm.B, head, pl.nchunks, pl.nstf};
     ProfScope ps("rla_walk_kernel", st);
     if (dm.D == 64) launch_walk<64>(dm.phi, p, st); else launch_walk<128>(dm.phi, p, st);
@@ -315,8 +309,8 @@ void rla_forward_states(const LayerDims& dm, const FastFwdPlan& pl, const SeqTen
     if (dm.D == 64) launch_chunk_kernel<64>(dm.phi, grid, p, st); else launch_chunk_kernel<128>(dm.phi, grid, p, st);
   }
   ProfScope ps("rla_scan_kernel", st);
-  if (dm.D == 64) launch_scan_kernel<64, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
-  else launch_scan_kernel<128, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, state0, subset_out, restart, m, st);
+  if (dm.D == 64) launch_scan_kernel<64, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, subset_out, restart, m, st);
+  else launch_scan_kernel<128, false>(dm, 128 / pl.ckeys, U, states, pl.nchunks, pl.nstf, head, subset_out, restart, m, st);
 }
 
 void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* q, int Tb, const void* dxr, float* U,
@@ -346,8 +340,8 @@ void rla_reverse_states(const LayerDims& dm, const FastBwdPlan& pl, const void* 
   }
   ProfScope ps("rla_scan_kernel(rev)", st);
   const int per = 128 / ck * pl.rsplit, n = pl.nrchunks * pl.rsplit;
-  if (dm.D == 64) launch_scan_kernel<64, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, in_scan);
-  else launch_scan_kernel<128, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, nullptr, 1, st, in_scan);
+  if (dm.D == 64) launch_scan_kernel<64, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, 1, st, in_scan);
+  else launch_scan_kernel<128, true>(dm, per, U, rstates, n, pl.nk, 0, nullptr, nullptr, 1, st, in_scan);
 }
 
 }  // namespace rattn

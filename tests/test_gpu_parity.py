@@ -528,10 +528,11 @@ def test_chunked_prefill_uses_matrix_core_kernels():
     torch.cuda.synchronize()
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
-    # the ring is gathered, the forward runs on the chunk's query tiles only and takes the carried state as the start of
-    # its state scan; nothing is copied or fixed up afterwards.  (One query tile: its state is the carried one.)
-    rest = ["rla_scan_kernel", "fwd_fused_kernel", "export_state_mfma_kernel", "export_state_reduce_kernel"]
-    assert names == ["chunk_ring_kernel"] + rest, names
+    # the ring is gathered by the launch that forms the products of both states, their scan starts from the carried state and
+    # hands rings and state over, and the forward runs on the chunk's query tiles only; nothing is copied or fixed up
+    # afterwards.  (One query tile: its state is the carried one.)
+    shared = ["chunk_products_kernel", "chunk_scan_kernel", "fwd_fused_kernel"]
+    assert names == shared, names
     # a window that is no multiple of 128: the same launches, with zero rows in front of the ring
     x = synth.make_random_layer(B, 704, Hq, Hkv, D, "bf16", 4201)      # ring 192 + chunk 320 = 512 rows
     q, k, v = dev(x["q"]), dev(x["k"]), dev(x["v"])
@@ -542,7 +543,17 @@ def test_chunked_prefill_uses_matrix_core_kernels():
     torch.cuda.synchronize()
     names = [n for n, _ in rb.rattn_profile_records()]
     rb.rattn_profile_enable(False)
-    assert names == ["chunk_ring_kernel", "rla_chunk_kernel"] + rest, names
+    assert names == shared, names
+    # a window that the ring and the chunk do not reach past by a tile: no query tile reads a state, the export forms the one that
+    # the call leaves
+    kr, vr, S = rb.rattn_prefill_export(k[:, :100].contiguous(), v[:, :100].contiguous(), 200)
+    rb.rattn_profile_enable(True)
+    rb.rattn_prefill_chunk(q[:, 100:228].contiguous(), k[:, 100:228].contiguous(), v[:, 100:228].contiguous(), 200, 100, kr, vr, S,
+                           softmax_scale=0.09)
+    torch.cuda.synchronize()
+    names = [n for n, _ in rb.rattn_profile_records()]
+    rb.rattn_profile_enable(False)
+    assert names == ["chunk_ring_kernel", "fwd_fused_kernel", "export_state_mfma_kernel"], names
 
 
 @pytest.mark.parametrize("dtype,D,fmap", [("f32", 64, "softmax"), ("f32", 128, "relu"), ("bf16", 128, "identity")])

@@ -80,6 +80,7 @@ SHARED = ["chunk_products_kernel", "chunk_scan_kernel", "fwd_fused_kernel"]
     (1, 8, 8, 513, [300, 250, 333, 64]),      # ring filled over several calls, then wrapping
     (3, 8, 8, 129, [257, 1100]),              # more than 128 whole products: 128 keys each
     (1, 16, 16, 8, [140, 1000]),
+    (1, 3, 1, 128, [384, 128, 127, 513]),     # one sequence of one KV head
     (1, 2, 2, 200, [1800, 1]),                # more than 12 products in a chain: 128 keys each; one token
 ])
 def test_chunk_products_shared_with_the_hand_over(B, Hq, Hkv, W, chunks, phi):
@@ -136,25 +137,22 @@ def test_carried_state_of_shared_products_in_fp32(B, T, Hkv, W, pos0):
     assert err <= {4000: 1.03e-7, 9000: 8.5e-8, 2048: 1.21e-7, 1531: 9.1e-8}[pos0] * 1.01   # (inputs differ by 0.5 % at most)
 
 
-def test_chunk_products_of_infinite_values():
-    """An infinite value of one key, met by features of both kinds of zero, reaches its own column of the carried state only, as
-    it does where the products are not shared (one sequence at a time here)."""
-    D, W, Hkv, pos0, n = 128, 128, 4, 200, 256
-    x = synth.make_random_layer(1, pos0 + n, Hkv, Hkv, D, "bf16", 5400)
-    x["v"][0, 250, 1, 7] = float("inf")
+@pytest.mark.parametrize("B,Hkv", [(1, 1), (1, 4), (2, 2)])
+def test_chunk_products_of_infinite_values(B, Hkv):
+    """An infinite value of one key, met by features of both kinds of zero, reaches its own column of the carried state only: the
+    oracle's state of the whole sequence, which has that column and finite values otherwise."""
+    D, W, pos0, n = 128, 128, 200, 256
+    x = synth.make_random_layer(B, pos0 + n, Hkv, Hkv, D, "bf16", 5400)
+    x["v"][0, 250, Hkv - 1, 7] = float("inf")
     q, k, v = (x[m].cuda() for m in ("q", "k", "v"))
-    got = []
-    for heads in (slice(0, Hkv), slice(1, 2)):
-        qh, kh, vh = (t[:, :, heads].contiguous() for t in (q, k, v))
-        kr, vr, S = rb.rattn_prefill_export(kh[:, :pos0].contiguous(), vh[:, :pos0].contiguous(), W)
-        _, names = launches(lambda: rb.rattn_prefill_chunk(qh[:, pos0:].contiguous(), kh[:, pos0:].contiguous(),
-                                                           vh[:, pos0:].contiguous(), W, pos0, kr, vr, S, softmax_scale=0.09))
-        got.append((S[0, 1 if len(got) == 0 else 0], names))
-    assert got[0][1] == SHARED and got[1][1] != SHARED
-    a, b = got[0][0], got[1][0]
-    assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and int((~torch.isfinite(a)).sum()) == D
-    fin = torch.isfinite(a)
-    assert float((a[fin] - b[fin]).abs().max()) <= 2e-5 * max(1.0, float(b[fin].abs().max()))
+    kr, vr, S = rb.rattn_prefill_export(k[:, :pos0].contiguous(), v[:, :pos0].contiguous(), W)
+    _, names = launches(lambda: rb.rattn_prefill_chunk(q[:, pos0:].contiguous(), k[:, pos0:].contiguous(), v[:, pos0:].contiguous(),
+                                                       W, pos0, kr, vr, S, softmax_scale=0.09))
+    assert names == SHARED
+    want = orc.prefill_export(np64(x["k"]), np64(x["v"]), W)[2]
+    got, fin = np64(S), np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), fin) and int((~fin).sum()) == D and bool((got[~fin] == np.inf).all())
+    assert float(np.abs(got[fin] - want[fin]).max()) <= 2e-5 * max(1.0, float(np.abs(want[fin]).max()))
 
 
 @pytest.mark.parametrize("phi", ["softmax", "relu"])
