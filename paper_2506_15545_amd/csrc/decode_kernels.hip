@@ -230,9 +230,9 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // with four waves of it), 9.1 shared.
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
 // SPLIT: nsplit work-groups share a (sequence, kv head), see SplitArgs.
-// ONCE: the rings are read past the caches (see pick_decode).
+// ONCE: the ring is read past the caches; of the kernel: rings of once_rows rows and more (see pick_decode).
 template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
-__global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
+__device__ __forceinline__ void decode_group(
     const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
     IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
     const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
@@ -442,17 +442,25 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
     __builtin_amdgcn_sched_barrier(0);  // (the registers of one branch at a time)
     linear_branch();
     __syncthreads();
-    // sums over the waves of this work-group for head hh, relative to the maximum M: exponentials on top of den and both
-    // branches' accumulators on top of a, c
-    auto wave_sums = [&](int hh, float M, float& den, float (&a)[EPL], float (&c)[EPL]) {
+    // sums over the waves of this work-group for head hh, relative to the maximum M, on top of `own` times a row of values (NULL:
+    // none): exponentials in den, both branches' accumulators in a, c.  (Fused by name: of two products and a sum the compiler
+    // fuses either one, and not the same one in every instantiation.)
+    auto wave_sums = [&](int hh, float M, float own, const IO* row, float& den, float (&a)[EPL], float (&c)[EPL]) {
+      den = own;
 #pragma unroll
       for (int r = 0; r < NW; ++r) {
         const float sw = Set::pexp(ml[(r * DEC_HB + hh) * 2], M);
-        den += sw * ml[(r * DEC_HB + hh) * 2 + 1];
+        den = __builtin_fmaf(sw, ml[(r * DEC_HB + hh) * 2 + 1], den);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-          a[e] += sw * part_s[(r * HBmax + hh) * D + lane + 64 * e];
-          c[e] += part_r[(r * HBmax + hh) * D + lane + 64 * e];
+          const float x = part_s[(r * HBmax + hh) * D + lane + 64 * e], y = part_r[(r * HBmax + hh) * D + lane + 64 * e];
+          if (r == 0) {
+            a[e] = row ? __builtin_fmaf(own, io_traits<IO>::ld(row + lane + 64 * e), sw * x) : sw * x;
+            c[e] = y;
+          } else {
+            a[e] = __builtin_fmaf(sw, x, a[e]);
+            c[e] += y;
+          }
         }
       }
     };
@@ -465,10 +473,8 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
     if (SPLIT && nsplit > 1) {
       for (int hh = w; hh < nh; hh += NW) {
         const float M = wave_max_of(hh, -1.0e30f);
-        float a[EPL], c[EPL], den = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) a[e] = c[e] = 0.f;
-        wave_sums(hh, M, den, a, c);
+        float a[EPL], c[EPL], den;
+        wave_sums(hh, M, 0.f, nullptr, den, a, c);
         float* dst = split.part + ((grp * split.n + sp) * G + hh) * SplitArgs::row(D);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) { put_shared(dst + lane + 64 * e, a[e]); put_shared(dst + D + lane + 64 * e, c[e]); }
@@ -507,10 +513,7 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
           }
       } else {
         M = wave_max_of(hh, lnew[hh]);
-        den = Set::pexp(lnew[hh], M);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) { a[e] = den * io_traits<IO>::ld(vnr + lane + 64 * e); c[e] = 0.f; }
-        wave_sums(hh, M, den, a, c);
+        wave_sums(hh, M, Set::pexp(lnew[hh], M), vnr, den, a, c);
       }
       // The window branch read the slot, while it changed from the evicted row to the new one, at a probability of 0, and
       // 0 times an infinite or NaN value is not 0.  A feature that came out without a number is formed again, key by key
@@ -550,6 +553,19 @@ __global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void dec
     hb += DEC_HB;
     if (MULTI && hb < G) __syncthreads();
   } while (MULTI && hb < G);
+}
+
+template <typename IO, int D, int NW, bool MULTI, bool SPLIT, bool ONCE>
+__global__ __launch_bounds__(NW * 64, decode_occ(D, sizeof(IO), MULTI)) void decode_kernel(
+    const IO* __restrict__ q, const IO* __restrict__ k_new, const IO* __restrict__ v_new, const int32_t* __restrict__ pos,
+    IO* __restrict__ k_ring, IO* __restrict__ v_ring, float* __restrict__ state, const float* __restrict__ gs,
+    const float* __restrict__ gr, IO* __restrict__ o, DecodeDims dd,
+    std::conditional_t<SPLIT, SplitArgs, NoSplit> split) {
+  // (whole bodies: a branch around the loads alone merges their registers, and 64 of them spill)
+  if (ONCE && min(pos[blockIdx.y], dd.W) >= dd.once_rows)
+    decode_group<IO, D, NW, MULTI, SPLIT, ONCE>(q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, dd, split);
+  else
+    decode_group<IO, D, NW, MULTI, SPLIT, false>(q, k_new, v_new, pos, k_ring, v_ring, state, gs, gr, o, dd, split);
 }
 
 struct DecodeTensors {
@@ -598,11 +614,17 @@ void pick_decode(const DecodeDims& dd, const DecodeTensors& t, hipStream_t st) {
   // again and again has it in that cache up to some 300 MB: 168 MB 31.7 | 34.8, 268 MB 53.0 | 53.2, 403 MB 87.1 | 75.7.)
   // With fewer work-groups the two halves of a row of K, which come with two loads, are fetched twice: 192 pairs, W = 2048
   // 40.2 | 44.0, 128 38.4 | 41.1.
-  const long long layer_bytes = groups * (2ll * dd.W * D * sizeof(IO) + D * D * 4ll);
-  if (!MULTI && groups >= 256 && layer_bytes >= 128ll << 20) {
-    if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dd, t, none, st);
-    else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dd, t, none, st);
-    else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dd, t, none, st);
+  // Rings that are not full yet count as far as they are filled, in the kernel: one that would make 128 MB if all were filled like
+  // it is read past the caches.  Two layers, through the caches | past them | chosen: 344 pairs, D = 64, W = 2933, 543 - 573 tokens
+  // (55 MB) 14.85 | 16.1 | 14.9; 256 pairs, fp32, W = 512, 100 - 300 tokens 15.8 | 17.3 | 16.1; full rings (1024 pairs, W = 512)
+  // 76.9 | 64.2 | 64.6.
+  const long long once_rows = ((128ll << 20) / groups - D * D * 4ll) / (2ll * D * (int)sizeof(IO));
+  if (!MULTI && groups >= 256 && dd.W >= once_rows) {
+    DecodeDims dim = dd;
+    dim.once_rows = (int)(once_rows > 0 ? once_rows : 0);
+    if (nw == 4) launch_decode<IO, D, 4, false, false, !MULTI>(dim, t, none, st);
+    else if (nw == 8) launch_decode<IO, D, 8, false, false, !MULTI>(dim, t, none, st);
+    else if constexpr (cap == 16) launch_decode<IO, D, 16, false, false, !MULTI>(dim, t, none, st);
     return;
   }
   if (nw == 4) launch_decode<IO, D, 4, MULTI, false>(dd, t, none, st);

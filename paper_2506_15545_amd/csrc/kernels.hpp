@@ -210,6 +210,7 @@ struct DecodeDims {
   int phi;  // as LayerDims::phi
   void* workspace = nullptr;         // NULL, or decode_split(..).bytes
   unsigned long long nonce = 0;      // with a workspace: a number no other call has, low 8 bits zero
+  int once_rows = 0;                 // set by pick_decode: filled rows from which on a ring is read past the caches
 };
 // Work-groups that share a (sequence, kv head) in a decode step with a workspace (1: the step needs none)
 constexpr int DEC_MAX_SPLIT = 16;

@@ -31,7 +31,7 @@ def workspace_bytes(N, Hq, Hkv, D, W, dtype):
 
 @pytest.mark.parametrize("N,Hq,Hkv,D,W,dtype,n,pos", [
     (1, 4, 1, 128, 512, "bf16", 4, [2000]),
-    (4, 6, 2, 128, 515, "bf16", 4, [0, 1, 384, 385]),           # one work-group, three, four: rings that are not full yet
+    (4, 6, 2, 128, 515, "bf16", 4, [0, 1, 384, 385]),           # one work-group, four: rings that are not full yet
     (4, 6, 2, 128, 515, "bf16", 4, [512, 514, 515, 516]),
     (3, 2, 1, 128, 1024, "bf16", 8, [512, 513, 897]),           # four, five, eight
     (2, 16, 1, 128, 4096, "bf16", 16, [4095, 9000]),            # all sixteen, sixteen heads
@@ -157,5 +157,28 @@ def test_large_steps_match_small_ones(N, D, W, dtype):
     want = torch.cat([rb.rattn_decode_step(*(few[m][i:i + 16] for m in NAMES), softmax_scale=D ** -0.5) for i in range(0, N, 16)])
     err = float((got.float() - want.float()).norm() / want.float().norm())
     assert err <= (2e-3 if dtype == "bf16" else 5e-7), err
+    for m in ("k_ring", "v_ring", "state"):
+        assert torch.equal(d[m], few[m]), m
+
+
+@pytest.mark.parametrize("N,D,W,dtype", [(43, 64, 2933, "bf16"), (32, 128, 1500, "bf16"), (32, 128, 600, "f32")])
+def test_large_steps_with_rings_around_the_caches_limit(N, D, W, dtype):
+    """Rings that are filled as far as 128 MB of all pairs', one row less and one more, and hardly at all, in one step: those below
+    are read through the caches, the others past them.  As above."""
+    print(f"N={N} D={D} W={W} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5950 + W)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    draw = lambda *shape: torch.randn(*shape, device="cuda", generator=gen).to(dt)
+    limit = ((128 << 20) // (8 * N) - 4 * D * D) // (2 * D * dt.itemsize)
+    assert 2 < limit < W
+    pos = torch.tensor([limit, limit - 1, limit + 1, 1, 0, 40, W - 1, W, 3 * W + 5], dtype=torch.int32, device="cuda").repeat(N)[:N]
+    d = dict(q=draw(N, 16, D), k_new=draw(N, 8, D), v_new=draw(N, 8, D), pos=pos, k_ring=draw(N, 8, W, D), v_ring=draw(N, 8, W, D),
+             state=draw(N, 8, D, D).float() / D)
+    few = {m: t.clone() for m, t in d.items()}
+    got = rb.rattn_decode_step(*(d[m] for m in NAMES), softmax_scale=D ** -0.5)
+    want = torch.cat([rb.rattn_decode_step(*(few[m][i:i + 16] for m in NAMES), softmax_scale=D ** -0.5) for i in range(0, N, 16)])
+    for n in range(N):   # (each sequence by itself: few keys in one ring, many in the next)
+        err = float((got[n].float() - want[n].float()).norm() / want[n].float().norm())
+        assert err <= (4e-3 if dtype == "bf16" else 1e-6), (int(pos[n]), err)
     for m in ("k_ring", "v_ring", "state"):
         assert torch.equal(d[m], few[m]), m
