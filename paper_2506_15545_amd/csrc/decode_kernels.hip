@@ -251,7 +251,9 @@ __device__ __forceinline__ void decode_group(
   float* part_s = ml + NW * DEC_HB * 2; // [NW][HBmax][D]
   float* part_r = part_s + NW * HBmax * D;
 
-  const int g = SPLIT ? blockIdx.x / split.n : blockIdx.x, sp = SPLIT ? blockIdx.x % split.n : 0, n = blockIdx.y;
+  // SPLIT: the pairs' first work-groups come first, so that where they are the only ones with work all XCDs have some of it.  (Those of
+  // a pair side by side: every n-th has work, on 8 / n XCDs.  64 pairs, W = 1024, 380 tokens 10.0 | 9.0 us, unshared 9.5.)
+  const int g = blockIdx.x, sp = SPLIT ? blockIdx.y / dd.N : 0, n = SPLIT ? blockIdx.y % dd.N : blockIdx.y;
   const int lane = lane_id(), w = wave_id();
   const int r16 = lane & 15, q4 = lane >> 4;
   const int p = pos[n];
@@ -442,10 +444,10 @@ __device__ __forceinline__ void decode_group(
     __builtin_amdgcn_sched_barrier(0);  // (the registers of one branch at a time)
     linear_branch();
     __syncthreads();
-    // sums over the waves of this work-group for head hh, relative to the maximum M, on top of `own` times a row of values (NULL:
-    // none): exponentials in den, both branches' accumulators in a, c.  (Fused by name: of two products and a sum the compiler
+    // sums over the waves of this work-group for head hh, relative to the maximum M, on top of `own` times the values v:
+    // exponentials in den, both branches' accumulators in a, c.  (Fused by name: of two products and a sum the compiler
     // fuses either one, and not the same one in every instantiation.)
-    auto wave_sums = [&](int hh, float M, float own, const IO* row, float& den, float (&a)[EPL], float (&c)[EPL]) {
+    auto wave_sums = [&](int hh, float M, float own, const float (&v)[EPL], float& den, float (&a)[EPL], float (&c)[EPL]) {
       den = own;
 #pragma unroll
       for (int r = 0; r < NW; ++r) {
@@ -455,7 +457,7 @@ __device__ __forceinline__ void decode_group(
         for (int e = 0; e < EPL; ++e) {
           const float x = part_s[(r * HBmax + hh) * D + lane + 64 * e], y = part_r[(r * HBmax + hh) * D + lane + 64 * e];
           if (r == 0) {
-            a[e] = row ? __builtin_fmaf(own, io_traits<IO>::ld(row + lane + 64 * e), sw * x) : sw * x;
+            a[e] = __builtin_fmaf(own, v[e], sw * x);
             c[e] = y;
           } else {
             a[e] = __builtin_fmaf(sw, x, a[e]);
@@ -474,7 +476,8 @@ __device__ __forceinline__ void decode_group(
       for (int hh = w; hh < nh; hh += NW) {
         const float M = wave_max_of(hh, -1.0e30f);
         float a[EPL], c[EPL], den;
-        wave_sums(hh, M, 0.f, nullptr, den, a, c);
+        const float none[EPL] = {};
+        wave_sums(hh, M, 0.f, none, den, a, c);
         float* dst = split.part + ((grp * split.n + sp) * G + hh) * SplitArgs::row(D);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) { put_shared(dst + lane + 64 * e, a[e]); put_shared(dst + D + lane + 64 * e, c[e]); }
@@ -487,6 +490,9 @@ __device__ __forceinline__ void decode_group(
     for (int hh = w; hh < nh; hh += NW) {
       const int h = g * G + hb + hh;
       float a[EPL], c[EPL], den, M;
+      float vn[EPL];
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) vn[e] = io_traits<IO>::ld(vnr + lane + 64 * e);
       if (SPLIT && nsplit > 1) {
         const float* src = split.part + (grp * split.n * G + hh) * SplitArgs::row(D);
         const size_t step = (size_t)G * SplitArgs::row(D);
@@ -503,7 +509,7 @@ __device__ __forceinline__ void decode_group(
         const float own = Set::pexp(lnew[hh], M), sw = lane < nsplit ? Set::pexp(Mi, M) : 0.f;
         den = own + wave_sum(sw * Li);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) { a[e] = own * io_traits<IO>::ld(vnr + lane + 64 * e); c[e] = 0.f; }
+        for (int e = 0; e < EPL; ++e) { a[e] = own * vn[e]; c[e] = 0.f; }
 #pragma unroll
         for (int i = 0; i < DEC_MAX_SPLIT; ++i)
           if (i < nsplit) {
@@ -513,7 +519,7 @@ __device__ __forceinline__ void decode_group(
           }
       } else {
         M = wave_max_of(hh, lnew[hh]);
-        wave_sums(hh, M, Set::pexp(lnew[hh], M), vnr, den, a, c);
+        wave_sums(hh, M, Set::pexp(lnew[hh], M), vn, den, a, c);
       }
       // The window branch read the slot, while it changed from the evicted row to the new one, at a probability of 0, and
       // 0 times an infinite or NaN value is not 0.  A feature that came out without a number is formed again, key by key
@@ -524,7 +530,7 @@ __device__ __forceinline__ void decode_group(
       if (evict && __any(z != 0.f)) {
         float again[EPL];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) again[e] = Set::pexp(lnew[hh], M) * io_traits<IO>::ld(vnr + lane + 64 * e);
+        for (int e = 0; e < EPL; ++e) again[e] = Set::pexp(lnew[hh], M) * vn[e];
         for (int s = 0; s < W; ++s) {
           if (s == slot) continue;
           float dot = 0.f;
@@ -584,7 +590,7 @@ void launch_decode(const DecodeDims& dd, const DecodeTensors& t, std::conditiona
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<IO, D, NW, MULTI, SPLIT, ONCE>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256) == hipSuccess;
   (void)attr;
-  decode_kernel<IO, D, NW, MULTI, SPLIT, ONCE><<<dim3(dd.Hkv * (SPLIT ? split.n : 1), dd.N), NW * 64, bytes, st>>>(
+  decode_kernel<IO, D, NW, MULTI, SPLIT, ONCE><<<dim3(dd.Hkv, dd.N * (SPLIT ? split.n : 1)), NW * 64, bytes, st>>>(
       (const IO*)t.q, (const IO*)t.k_new, (const IO*)t.v_new, t.pos, (IO*)t.k_ring, (IO*)t.v_ring, t.state, t.gs, t.gr,
       (IO*)t.o, dd, split);
 }
