@@ -227,7 +227,7 @@ constexpr int decode_occ(int D, int esize, bool multi) { return multi || D * esi
 // caches: 128 sequences x 8 KV heads, 4 query heads each, W = 512: 64.5 us = 6.3 TB/s (84 with the rings kept in the caches, see
 // pick_decode); 24 x 8, 5 heads, W = 2048, half of the rings partly filled: 39 us (271 us with the scores of all W keys in LDS and
 // vector arithmetic for more than four heads); one sequence, 4 KV heads, W = 512: 11.2 us by one work-group per KV head (18 us
-// with four waves of it), 9.1 shared.
+// with four waves of it), 8.9 shared.
 // More than 16 query heads per KV head (MULTI) are served in several passes over the rings.
 // SPLIT: nsplit work-groups share a (sequence, kv head), see SplitArgs.
 // ONCE: the ring is read past the caches; of the kernel: rings of once_rows rows and more (see pick_decode).

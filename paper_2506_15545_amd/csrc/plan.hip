@@ -108,8 +108,13 @@ FastBwdPlan fast_bwd_plan(const LayerDims& dm) {
 
 DecodeSplit decode_split(const DecodeDims& dd, int esize) {
   // A work-group of eight waves for every 64 KB of rings, up to 128 of them in all: more are bound by what the memory delivers.
-  // A step in us, one work-group per pair (16 waves) | 2 | 4 | 8 | 16 of eight waves, bf16, D = 128 (the ring-less part of a call
-  // takes 8, 9.5 with a workspace to allocate):
+  // Captured steps in us, one work-group per pair (16 waves) | as split, bf16, D = 128, full rings:
+  //   4 pairs, W = 512 11.1 | 9.0;  1024 14.5 | 9.5;  2048 23.4 | 10.8;  4096 41.0 | 12.1;  16, 512 11.2 | 9.3;  2048 23.6 | 11.7
+  //   32, 512 10.9 | 9.5;  2048 24.7 | 13.4;  64, 512 12.1 | 11.4;  1024 16.1 | 14.3;  2048 25.7 | 19.6;  4096 44.2 | 29.5
+  //   D = 64, 4 pairs, W = 1024 9.6 | 7.8;  4096 25.2 | 9.4;  fp32, 4 pairs, W = 512 17.9 | 10.6;  16 pairs, 4096 91.7 | 21.5
+  // Rings that are not full, 100 tokens 7.3 | 6.9 (4 pairs), 7.5 | 7.1 (64);  380, one work-group of eight waves, 9.4 | 8.7, 9.5 | 9.0;
+  // slower by up to 3 % remain D = 64, 4 pairs, 550 - 768 tokens 7.6 | 7.8 and fp32, 100 tokens 9.0 | 9.3.
+  // How many were compared eagerly, when the host took 8 of each step and 9.5 with a workspace (now 3.6 and 3.9); one | 2 | 4 | 8 | 16:
   //   4 pairs, W = 512 12.0 | 10.7 | 9.5 | 9.5 | 10.3;  W = 2048 25.0 | 18.6 | 13.4 | 11.5 | 11.5;  W = 4096 42.8 | 29.0 | 18.6 | 13.7 | 12.7
   //   16 pairs, W = 1024 15.9 | 13.4 | 11.0 | 11.0 | 12.4;  64, W = 512 14.3 | 13.3 | 13.4 | 15.1 | 26.5
   //   128 pairs, W = 512 16.1 | 16.8 | 17.4;  W = 2048 38.1 | 34.1 | 34.2 | 39.4 (not taken: rings with 100 - 400 tokens
