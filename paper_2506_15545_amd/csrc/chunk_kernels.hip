@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256, 2) void chunk_products_kernel(RingRows<128> k,
 // Block i < nscan: one 32 x 32 tile of (b, kv head): the running sum starts from the carried state (or zero), is stored as
 // bf16 [d][f] in front of product head + per i for state i, and after the last product in fp32 [f][d] where the carried
 // state was (each element by the thread that read it; both go through LDS, transposed).  Eight products are in flight, and are
-// summed in pairs: in one chain, of products of 128 keys in one chain each, the state was up to 1.4 times as far from fp64 as the
+// summed in pairs (a remainder in two runs): in one chain, of products of 128 keys in one chain each, the state was up to 1.4 times as far from fp64 as the
 // hand-over's own sums (1 x 1300 tokens after 9000, 2 heads, W = 300: 8.5e-8 | 1.20e-7 of the norm, so 6.1e-8).  The other blocks
 // copy the chunk's last rows to their ring slots, which nothing reads any more.
 __global__ __launch_bounds__(256) void chunk_scan_kernel(const float* __restrict__ U, uint16_t* __restrict__ states, float* state,
@@ -133,26 +133,35 @@ __global__ __launch_bounds__(256) void chunk_scan_kernel(const float* __restrict
   const float* u0 = U + (size_t)bg * pl.nprod * (D * D) + at;
   uint16_t* s0 = states + (size_t)bg * nst * (D * D) + at;
   const int shift = pl.ckeys == 64 ? 1 : 0;   // products per state: 2 or 1
-  for (int c0 = 0; c0 < pl.nprod; c0 += 8) {
+  auto put = [&](int c, f32x4_t f) {   // the state in front of product c, if there is one
+    const int n = c - pl.head, i = n >> shift;
+    if (n >= 0 && (i << shift) == n && i < nst) *reinterpret_cast<bf16x4_t*>(s0 + (size_t)i * (D * D)) = __builtin_convertvector(f, bf16x4_t);
+  };
+  auto product = [&](int c) { return *reinterpret_cast<const f32x4_t*>(u0 + (size_t)c * (D * D)); };
+  int c0 = 0;
+  for (; c0 + 8 <= pl.nprod; c0 += 8) {
     f32x4_t u[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) u[j] = *reinterpret_cast<const f32x4_t*>(u0 + (size_t)min(c0 + j, pl.nprod - 1) * (D * D));
-    if (c0 + 8 > pl.nprod) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (c0 + j >= pl.nprod) u[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    // f[j]: in front of product c0 + j.  (All of them ahead of the stores, which a wait for a load would wait for, too.)
-    const f32x4_t u01 = u[0] + u[1], u03 = u01 + (u[2] + u[3]), u45 = u[4] + u[5], u07 = u03 + (u45 + (u[6] + u[7]));
+    for (int j = 0; j < 8; ++j) u[j] = product(c0 + j);
+    const f32x4_t u01 = u[0] + u[1], u03 = u01 + (u[2] + u[3]), u45 = u[4] + u[5];
     const f32x4_t f[8] = {acc, acc + u[0], acc + u01, acc + (u01 + u[2]), acc + u03, acc + (u03 + u[4]), acc + (u03 + u45),
                           acc + (u03 + (u45 + u[6]))};
-    acc += u07;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int n = c0 + j - pl.head, i = n >> shift;
-      if (n >= 0 && (i << shift) == n && i < nst)
-        *reinterpret_cast<bf16x4_t*>(s0 + (size_t)i * (D * D)) = __builtin_convertvector(f[j], bf16x4_t);
+    for (int j = 0; j < 8; ++j) put(c0 + j, f[j]);
+    acc += u03 + (u45 + (u[6] + u[7]));
+  }
+  if (c0 < pl.nprod) {   // up to seven more, in two runs (with few products the instructions of eight are what takes the time)
+    f32x4_t u[7], a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+      if (c0 + j < pl.nprod) u[j] = product(c0 + j);
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+      if (c0 + j >= pl.nprod) break;
+      put(c0 + j, j == 0 ? acc : j <= 4 ? acc + a : acc + (a + b));
+      if (j < 4) a += u[j]; else b += u[j];
     }
+    acc += a + b;
   }
   tr[c4][row] = acc[0]; tr[c4 + 1][row] = acc[1]; tr[c4 + 2][row] = acc[2]; tr[c4 + 3][row] = acc[3];
   __syncthreads();

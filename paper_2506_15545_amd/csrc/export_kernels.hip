@@ -26,8 +26,8 @@ __global__ __launch_bounds__(256) void export_ring_kernel(RingCopy a, int ncopy,
 // key0 + s of the two-part sequence (SeqRows).
 // Bound: HBM on long prompts (12 matrix instructions per 16 keys and wave are about 1.6 times as fast as the keys
 // arrive), the launch on short ones.
-// DIRECT: one segment, in pieces, which is the state.
-template <int D, int PHI, bool DIRECT>
+// PIECES: the only segment, whose keys are summed `piece` at a time.
+template <int D, int PHI, bool PIECES>
 __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, SeqRows v, float* __restrict__ partial, int Hkv,
                                                                    int key0, int Tp, int nseg, int seg_len, int nstate,
                                                                    RingCopy rc, int piece) {
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256, 2) void export_state_mfma_kernel(SeqRows k, Se
   const int seg = blockIdx.x % nseg, bg = blockIdx.x / nseg, g = bg % Hkv, b = bg / Hkv;
   const int lo = seg * seg_len, hi = min(lo + seg_len, Tp);
   const TwoPartRows<D> krow = {k, b, key0, Hkv, g}, vrow = {v, b, key0, Hkv, g};
-  segment_state<D, PHI, false, DIRECT>(smem, lo, 0, hi, krow, vrow, partial + ((size_t)bg * nseg + seg) * (D * D), piece);
+  segment_state<D, PHI, false, PIECES>(smem, lo, 0, hi, krow, vrow, partial + ((size_t)bg * nseg + seg) * (D * D), piece);
 }
 
 // state[b,g] = (accumulate ? state[b,g] : 0) + sum over segments: four runs of segments, each in order, then the four sums
@@ -112,11 +112,11 @@ void prefill_export(const LayerDims& dm, int dtype, const SeqTensors& t, void* k
     const int nstate = pl.nseg * dm.Hkv * dm.B;
     const SeqRows ks = {(const uint16_t*)t.k_front, (const uint16_t*)t.k, t.P, t.Tb};
     const SeqRows vs = {(const uint16_t*)t.v_front, (const uint16_t*)t.v, t.P, t.Tb};
-#define RATTN_EXPORT_AS(D_, PHI_, DIRECT_)                                                                                 \
-  export_state_mfma_kernel<D_, PHI_, DIRECT_><<<nstate + copy_blocks, 256, 0, st>>>(ks, vs, partial, dm.Hkv, t.kmin, pl.Tp, \
+#define RATTN_EXPORT_AS(D_, PHI_, PIECES_)                                                                                 \
+  export_state_mfma_kernel<D_, PHI_, PIECES_><<<nstate + copy_blocks, 256, 0, st>>>(ks, vs, partial, dm.Hkv, t.kmin, pl.Tp, \
                                                                                     pl.nseg, pl.seg_len, nstate, rc, piece)
 #define RATTN_EXPORT(D_, PHI_) \
-  do { if (direct) RATTN_EXPORT_AS(D_, PHI_, true); else RATTN_EXPORT_AS(D_, PHI_, false); } while (0)
+  do { if (piece < pl.seg_len) RATTN_EXPORT_AS(D_, PHI_, true); else RATTN_EXPORT_AS(D_, PHI_, false); } while (0)
 #define RATTN_EXPORT_MAP(D_)                                    \
   if (dm.phi == PHI_SOFTMAX) RATTN_EXPORT(D_, PHI_SOFTMAX);     \
   else if (dm.phi == PHI_RELU) RATTN_EXPORT(D_, PHI_RELU);      \
